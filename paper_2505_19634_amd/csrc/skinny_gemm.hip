@@ -3,14 +3,15 @@
 // 64 GB of weights for the 32B model).  bf16 in, fp32 accumulate on the matrix cores, bf16 out.
 // HBM-bound on streaming W once: 2 * M flop per weight byte is far below the MFMA balance.
 //
-//   skinny_gemm_stream_kernel<MT, RT, WAVES>  grid (blocks of 32 * WAVES weight rows, K splits).  Each wavefront
-//       owns an MFMA row tile of 32 weight rows and walks the K range in steps of half a chunk (64 k); W and X both go
-//       from global memory straight into LDS stages, with no registers in between; Y^T[n][m] accumulates in
-//       registers over the whole K range.  WAVES = 8 (256 weight rows, one workgroup per unit): long K runs and
-//       every launch with more than 128 tokens.  WAVES = 4 (128 weight rows, two workgroups per unit): up to 128
-//       tokens on short K runs (QKV, O), where more, smaller workgroups keep every unit streaming.
+//   skinny_gemm_stream_kernel<MT, RT, WAVES, KG>  grid (blocks of weight rows, K splits).  A workgroup walks its K range
+//       in steps of half a chunk (64 k); W and X both go from global memory straight into LDS stages, with no registers
+//       in between; Y^T[n][m] accumulates in registers over the whole K range.  Three forms: 256 weight rows (eight
+//       wavefronts side by side), 128 (four) and 64 (two row wavefronts x two groups that share every stage and take half
+//       of its k each; their accumulators are added up through LDS at the end).
 //   skinny_gemm_reduce_kernel  only when K is split across workgroups (few weight rows): sums the fp32
 //       partials in a fixed order and converts.
+//   skinny_gemm_direct_kernel<RN, TT, WAVES, UB>  small matrices: a workgroup owns 16 * RN weight rows and 16 * TT tokens for
+//       the WHOLE K range, its wavefronts a share of K each; no partials, no second launch.
 #include "lotts_common.h"
 
 namespace lotts {
@@ -18,89 +19,141 @@ namespace lotts {
 typedef __bf16 g_bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 g_bf16x4 __attribute__((ext_vector_type(4)));
 typedef float g_f32x16 __attribute__((ext_vector_type(16)));
+typedef float g_f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned g_u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGemmRows = 32;               // weight rows per wavefront = M of the MFMA
-constexpr int kGemmBlockN = 4 * kGemmRows;  // weight rows of a four-wavefront workgroup; eight cover twice that
-constexpr int kGemmChunk = 128;             // K elements per chunk
+constexpr int kGemmRows = 32;    // weight rows per wavefront = M of the MFMA
+constexpr int kGemmChunk = 128;  // K elements per chunk
 constexpr int kGemmMaxM = 256;
 constexpr int kGemmMaxSplit = 32;
+constexpr int kGemmTileFloats = 32 * 32;  // one accumulator tile: 32 weight rows x 32 tokens
+constexpr int kGemmOutRow = 80;           // bytes per token row of a 32 x 32 bf16 tile on its way out through LDS (64 + pad)
 
 struct GemmParams {
     const __bf16 *X, *W;
     __bf16* Y;
-    float* part;  // [ksplit][M][N] fp32 when ksplit > 1
+    float* part;  // fp32 partials when ksplit > 1: [ksplit][block of weight rows][row wavefront][tile][quad][lane] float4
     int M, N, K, ksplit;
-    int rows;  // weight rows a wavefront owns: 32, or fewer (a multiple of 4) when that fills the chip better
+    int rows;     // weight rows a wavefront owns: 32, or fewer (a multiple of 4) when that fills the chip better
+    int nblocks, roww, rt, tt;  // launch geometry, for the reduce kernel: blocks, row wavefronts, row / token tiles per wavefront
     long long ldx, ldw, ldy;
 };
 
+enum GemmForm { kStream256, kStream128, kStream64, kDirect };
+
 struct GemmPlan {
-    int mt, stream, nblocks, ksplit, rows;  // rows: weight rows per wavefront; stream: eight wavefronts, 256 weight rows per workgroup; else four and 128
+    GemmForm form;
+    int mt, rt;            // stream forms: token tiles of 32; row tiles per wavefront (2: pairs split the token tiles)
+    int rows, roww;        // weight rows per wavefront; wavefronts side by side over the rows
+    int nblocks, ksplit;
+    int rn, tt, nby;       // direct: 16-row and 16-token tiles per workgroup, workgroups over the tokens
 };
-// K split for `nblocks` blocks of weight rows.  Few blocks: split K so that the launch fills the chip.
-// Measured on the 32B-shaped layers: a workgroup count just above the number of compute units is the
-// worst choice (a few units run two workgroups and everybody waits for them), so the count stays at
-// or below one per unit -- or, when two fit a unit and every workgroup still gets a long run of
-// chunks, at or below two per unit.
-static inline int plan_ksplit(int nblocks, int chunks, bool two_per_cu) {
-    if (nblocks >= kNumCU) return 1;
-    int ks = two_per_cu ? (2 * kNumCU) / nblocks : kNumCU / nblocks;
-    if (two_per_cu && chunks / ks < 16) ks = kNumCU / nblocks;
-    const int max_ks = chunks / 4 > 0 ? chunks / 4 : 1;  // at least 4 chunks per workgroup
+
+// Largest number of K splits that keeps the launch at or below one workgroup per compute unit (a count just above is the
+// worst choice: a few units run two and everybody waits for them), with at least 4 chunks per workgroup.
+static inline int plan_ksplit(int nblocks, int chunks) {
+    int ks = kNumCU / nblocks;
+    const int max_ks = chunks / 4 > 0 ? chunks / 4 : 1;
     if (ks > max_ks) ks = max_ks;
     if (ks > kGemmMaxSplit) ks = kGemmMaxSplit;
     return ks < 1 ? 1 : ks;
 }
 
-static inline GemmPlan plan_gemm(int M, int N, int K) {
-    GemmPlan pl;
-    pl.mt = (M + 31) / 32;
-    const int chunks = K / kGemmChunk;
-    // Eight wavefronts cover 256 weight rows per workgroup, one workgroup per unit, so an X chunk staged in LDS
-    // serves twice the rows of the four-wavefront form.  Up to 128 tokens they win when the workgroups still get long
-    // runs of chunks (gate+up, down on the 32B-shaped layers) and lose on short ones (QKV, O: the four-wavefront form
-    // splits K less, so fewer fp32 partials are written and added up); above 128 tokens two workgroups per unit do
-    // not fit (LDS stages, accumulators), and the eight-wavefront form always runs.
-    pl.rows = kGemmRows;
-    int nb_stream = (N + 8 * kGemmRows - 1) / (8 * kGemmRows);
-    int ks_stream = plan_ksplit(nb_stream, chunks, false);
-    if (pl.mt <= 2) {
-        // Up to 64 tokens the launch is HBM-bound and what counts is how many units stream: with 28 weight rows per
-        // wavefront instead of 32 the 55296 rows of the 32B shape's gate+up make 247 workgroups instead of 216, and
-        // the LM head's last round of workgroups is fuller (measured 1..2 % and 2..7 % faster; with more tokens the
-        // padded MFMA rows cost more than the idle units).  Taken when it fills the last round visibly better.
-        const int nb28 = (N + 8 * 28 - 1) / (8 * 28), ks28 = plan_ksplit(nb28, chunks, false);
-        auto fill = [](int wgs) { return (double)wgs / (double)(((wgs + kNumCU - 1) / kNumCU) * kNumCU); };
-        if (fill(nb28 * ks28) > fill(nb_stream * ks_stream) + 0.03) {
-            pl.rows = 28;
-            nb_stream = nb28;
-            ks_stream = ks28;
+// Fewest weight rows per wavefront (20 .. 32) that still give at most one workgroup per unit: up to 96 tokens the launch
+// is bound by how fast each unit takes in its share of W and X, not by the padded MFMA rows.  Measured at 40 tokens:
+// 22016 x 2048 in 230 workgroups of 96 rows 21.6 us, in 172 of 128 rows 22.2; 33280 x 3072 in 208 of 160 rows 41.7 us, in
+// 130 of 256 48.9.
+static inline int plan_rows(int N, int roww, int mt) {
+    if (mt > 3) return kGemmRows;
+    for (int rows = 20; rows < kGemmRows; rows += 4)
+        if ((N + roww * rows - 1) / (roww * rows) <= kNumCU) return rows;
+    return kGemmRows;
+}
+
+// Direct form: the tile that leaves the fewest bytes (its weight rows plus its tokens, over the whole K) to a workgroup with
+// at most one workgroup per unit.  Returns those KB, or 0 if no tile fits.
+static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
+    static const int tiles[][2] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 3}, {4, 2}, {4, 3}};
+    double best = 0.0;
+    for (const auto& t : tiles) {
+        const long long nx = (N + 16 * t[0] - 1) / (16 * t[0]), ny = (M + 16 * t[1] - 1) / (16 * t[1]);
+        if (nx * ny > kNumCU) continue;
+        const double kb = (16.0 * t[0] + (16 * t[1] < M ? 16 * t[1] : M)) * K * 2.0 / 1024.0;
+        if (best == 0.0 || kb < best) {
+            best = kb;
+            pl->rn = t[0]; pl->tt = t[1]; pl->nblocks = (int)nx; pl->nby = (int)ny;
         }
     }
-    pl.stream = (pl.mt > 4 || chunks / ks_stream >= 16) ? 1 : 0;
-    if (pl.stream) {
-        pl.nblocks = nb_stream;
-        pl.ksplit = ks_stream;
-    } else {
-        pl.rows = kGemmRows;
-        pl.nblocks = (N + kGemmBlockN - 1) / kGemmBlockN;
-        pl.ksplit = plan_ksplit(pl.nblocks, chunks, true);
+    return best;
+}
+
+// Which form, and how it is cut.  Measured on 16 matrices between 1536 x 1536 and 152064 x 5120 at 1 .. 256 tokens, calls
+// back to back over rotated weights, reduce launch included.
+//   Direct: while everything a wavefront needs is in flight at once (K <= 4096) it takes 3.4 us + 0.026 us per KB of a
+//     workgroup's W and X, against 6.4 us + 0.13 us per MB of W + 7e-6 us per token and (N + K) of the split stream forms:
+//     2560 x 2048 at 1 / 40 / 192 tokens 5.2 / 7.8 / 13.5 us against 7.9 / 9.2 / 15.0; 4096 x 4096 at 1 token 8.8 against
+//     11.5, at 40 tokens 17.5 against 13.5.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1
+//     token 19.8 us against 14.2.
+//   256-row stream form: more than 256 blocks of 128 rows; an X chunk in LDS serves the most rows.  55296 x 5120 at 64
+//     tokens 92 us, 128-row form 104.
+//   128-row form below that, 64-row form when it would have to be split more than sevenfold (N <= 4608): the fewer splits,
+//     the fewer fp32 partials, but the more often a unit reads X.  2048 x 11008 at 40 / 192 tokens in 64-row blocks x 8
+//     splits 16.8 / 24.5 us, 128 x 16 17.6 / 26.7; 5120 x 5120 at 64 / 192 tokens 128 x 6 18.4 / 25.9, 64 x 3 19.4 / 28.9.
+static inline GemmPlan plan_gemm(int M, int N, int K) {
+    GemmPlan pl = {};
+    const int chunks = K / kGemmChunk;
+    pl.mt = (M + 31) / 32;
+    // An even number of token tiles from 4 on: pairs of wavefronts own two row tiles together and half of the token tiles each.
+    pl.rt = pl.mt >= 4 && pl.mt % 2 == 0 ? 2 : 1;
+    pl.ksplit = 1;
+    if (K <= 4096) {
+        const double kb = plan_direct(M, N, K, &pl);
+        if (kb > 0.0 && 3.4 + 0.026 * kb < 6.4 + 0.13 * (2e-6 * N * K) + 7e-6 * M * (N + K)) {
+            pl.form = kDirect;
+            return pl;
+        }
     }
+    const int nb128 = (N + 127) / 128;
+    if (nb128 > kNumCU) {
+        pl.form = kStream256;
+        pl.roww = 8;
+        pl.rows = plan_rows(N, 8, pl.mt);
+        const int nb32 = (N + 255) / 256, nb28 = (N + 223) / 224;
+        // several rounds of workgroups: 28 rows instead of 32 where that fills the last round visibly better
+        auto fill = [](int wgs) { return (double)wgs / (double)(((wgs + kNumCU - 1) / kNumCU) * kNumCU); };
+        if (pl.mt <= 3 && nb32 > kNumCU && fill(nb28) > fill(nb32) + 0.03) pl.rows = 28;
+    } else if (nb128 > 36) {
+        pl.form = kStream128;
+        pl.roww = 4;
+        pl.ksplit = plan_ksplit(nb128, chunks);
+        pl.rows = pl.ksplit == 1 ? plan_rows(N, 4, pl.mt) : kGemmRows;
+    } else {
+        pl.form = kStream64;
+        pl.roww = 2;
+        pl.rows = kGemmRows;
+        pl.ksplit = plan_ksplit((N + 63) / 64, chunks);
+    }
+    pl.nblocks = (N + pl.roww * pl.rows - 1) / (pl.roww * pl.rows);
     return pl;
 }
 
-// The kernel.  WAVES wavefronts (eight: two per SIMD, one workgroup per unit; four: two workgroups per unit),
-// 32 * WAVES weight rows per workgroup: each wavefront owns one MFMA row tile of 32 weight rows and
-// all M tokens -- or, for an even number of token tiles from 4 on (97..128, 161..192, 225..256 tokens), two
-// neighbouring wavefronts own two row tiles together and half of the token tiles each: a k step then reads
-// 2 + MT / 2 fragments for MT MFMAs instead of 1 + MT, and LDS reads are what bounds the loop at these token counts
+// fp32 partials of one K split
+static inline size_t split_floats(const GemmPlan& pl) { return (size_t)pl.nblocks * pl.roww * pl.mt * kGemmTileFloats; }
+
+// The streaming kernel.  WAVES = ROWW * KG wavefronts, 32 * ROWW weight rows per workgroup: a row wavefront owns one MFMA row
+// tile of 32 weight rows and all M tokens -- or, for an even number of token tiles from 4 on (97..128, 161..192,
+// 225..256 tokens), two neighbouring ones own two row tiles together and half of the token tiles each: a k step then
+// reads 2 + MT / 2 fragments for MT MFMAs instead of 1 + MT, and LDS reads are what bounds the loop at these token counts
 // (measured 1..11 % faster on the 32B-shaped layers).
+// KG = 2: two groups of row wavefronts share every stage; group g multiplies k steps 2 g and 2 g + 1 of its four.  That puts two
+// wavefronts of a 64-row block on every row tile without more LDS or more transfers, so a matrix of few rows makes twice the
+// workgroups of the 128-row form from half the K splits.
 // Neither operand passes through registers: global-to-LDS loads (16 bytes per lane, landing at a wavefront-uniform
 // LDS base + 16 * lane) fill stages of half a chunk (64 k) --
 //   X: two stages per workgroup, one multiplied while the other is filled, one barrier per stage;
-//   W: three stages per wavefront (32 rows x 64 k, 4 KB): one multiplied, two on their way, so that a W transfer has
-//      a whole chunk of time to arrive from HBM; non-temporal; private to the wavefront, or to the pair (each
-//      fills its half of the pair's stage; the step barrier that publishes X publishes these too).
+//   W: three stages per row wavefront (32 rows x 64 k, 4 KB): one multiplied, two on their way, so that a W transfer has
+//      a whole chunk of time to arrive from HBM; non-temporal; private to the wavefront, or to those that share its rows
+//      (pair and groups: each fills its part; the step barrier that publishes X publishes these too).
 // A stage keeps rows of 128 bytes back to back (a load instruction fills 8 whole rows), so the 16-byte pieces of a
 // row are stored permuted -- piece p of row r at slot p ^ ((r >> 1) & 7) -- which spreads the 16 lanes of a
 // fragment read over all 64 banks without padding.  With no staging registers there is room for two fragment sets
@@ -111,25 +164,38 @@ static inline GemmPlan plan_gemm(int M, int N, int K) {
 // transfers that are meant to stay in flight; and without a "memory" clobber, with which the same wait comes
 // back: the barrier statements of the step loop, which have it, fence every read of a stage against the transfer
 // that refills it, and volatile statements keep their order among themselves.  M0 carries the LDS base.  Since the
-// compiler does not know of the loads, the waits are written out too: before the barrier of a step, vmcnt(4) -- the
-// step's X transfers have landed, and with them the older W stage; only the 4 W transfers issued after them (the
+// compiler does not know of the loads, the waits are written out too: before the barrier of a step, vmcnt(WI) -- the
+// step's X transfers have landed, and with them the older W stage; only the WI W transfers issued after them (the
 // next step's stage) may still be in flight -- or vmcnt(0) in the last step, after which nothing was issued.
-template <int MT, int RT, int WAVES>
-__global__ __launch_bounds__(WAVES * kWave, 8 / WAVES) void skinny_gemm_stream_kernel(const GemmParams p) {
+//
+// The way out.  Accumulator lanes hold one token and scattered weight rows, so stores straight from them write 16 bytes
+// per row of Y (32 of a row of fp32 partials), and the launch ended on them: 2560 x 2048 at 192 tokens took 18.6 us for 8
+// steps.  Partials now go out as they lie in the registers, 1 KB per store, and the reduce kernel reads them back the same
+// way; Y tiles turn through LDS into 64-byte row pieces.  With the forms above (before: 128 / 256 rows only), reduce launch
+// included, 40 / 192 tokens: 2048 x 11008 20.2 / 34.5 -> 16.8 / 24.5 us; 7168 x 5120 21.5 / 40 -> 20.0 / 29.7; 22016 x 2048
+// 25.4 / 41.5 -> 21.6 / 31.0.
+template <int MT, int RT, int WAVES, int KG>
+__global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(const GemmParams p) {
     static_assert(RT == 1 || (RT == 2 && MT % 2 == 0), "a pair of wavefronts splits the token tiles evenly");
+    constexpr int ROWW = WAVES / KG;  // wavefronts side by side over the weight rows
+    constexpr int WI = 4 / KG;        // W transfers per wavefront and stage
     constexpr int TT = MT / RT;  // token tiles per wavefront
     constexpr int XROWS = 32 * MT;
     constexpr int XINSTR = XROWS / 8;
     constexpr int XI = (XINSTR + WAVES - 1) / WAVES;
     constexpr int kStageRow = 128;
     constexpr int XSTAGE = XROWS * kStageRow, WSTAGE = 32 * kStageRow;
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * XSTAGE + WAVES * 3 * WSTAGE];
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+    constexpr int TILES = RT * TT;   // accumulator tiles per wavefront
+    constexpr int TILE_Q = kGemmTileFloats / 4;
+    constexpr int STAGES = 2 * XSTAGE + ROWW * 3 * WSTAGE, PARK = ROWW * TILES * (KG - 1) * TILE_Q * 16;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES > PARK ? STAGES : PARK];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
+    const int kgrp = KG == 1 ? 0 : wave / ROWW, wr = KG == 1 ? wave : wave % ROWW;
     const int ln = lane & 31, hh = lane >> 5;
-    // RT = 1: wavefront w owns row tile w and all tokens.  RT = 2: wavefronts 2j and 2j + 1 own row tiles 2j and
+    // RT = 1: row wavefront w owns row tile w and all tokens.  RT = 2: row wavefronts 2j and 2j + 1 own row tiles 2j and
     // 2j + 1 together, each half of the token tiles, and share the W stages of their 64 rows.
-    const int grp = RT == 1 ? wave : wave >> 1, th = RT == 1 ? 0 : wave & 1;
-    const int n0 = blockIdx.x * (p.rows * WAVES) + grp * (p.rows * RT);  // pairs always own 2 x 32 rows
+    const int grp = RT == 1 ? wr : wr >> 1, th = RT == 1 ? 0 : wr & 1;
+    const int n0 = blockIdx.x * (p.rows * ROWW) + grp * (p.rows * RT);  // pairs always own 2 x 32 rows
     const int chunks = p.K / kGemmChunk;
     const int c_lo = (int)((long long)blockIdx.y * chunks / p.ksplit);
     const int c_hi = (int)((long long)(blockIdx.y + 1) * chunks / p.ksplit);
@@ -142,7 +208,7 @@ __global__ __launch_bounds__(WAVES * kWave, 8 / WAVES) void skinny_gemm_stream_k
     // slot ^ swizzle(row).
     const int l_row = lane >> 3, l_slot = lane & 7;
     const __bf16* x_src[XI];
-    const __bf16* w_src[4];
+    const __bf16* w_src[WI];
 #pragma unroll
     for (int i = 0; i < XI; ++i) {
         const int r = (wave + i * WAVES) * 8 + l_row;
@@ -150,8 +216,8 @@ __global__ __launch_bounds__(WAVES * kWave, 8 / WAVES) void skinny_gemm_stream_k
         x_src[i] = p.X + (long long)m * p.ldx + (long long)c_lo * kGemmChunk + (l_slot ^ ((r >> 1) & 7)) * 8;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = th * 32 + i * 8 + l_row;  // of a pair, each wavefront brings in 32 of the 64 rows
+    for (int i = 0; i < WI; ++i) {
+        const int r = th * 32 + (kgrp * WI + i) * 8 + l_row;  // of a pair, each wavefront brings in 32 of the 64 rows
         int n = n0 + (RT == 1 && r >= p.rows ? p.rows - 1 : r);  // a short tile re-reads its last row
         n = n < p.N ? n : p.N - 1;  // rows past the end re-read the last row; never stored
         w_src[i] = p.W + (long long)n * p.ldw + (long long)c_lo * kGemmChunk + (l_slot ^ ((r >> 1) & 7)) * 8;
@@ -176,9 +242,9 @@ __global__ __launch_bounds__(WAVES * kWave, 8 / WAVES) void skinny_gemm_stream_k
     auto fetch_w = [&](int g) {
         unsigned char* stage = wsl + (g % 3) * (RT * WSTAGE) + th * WSTAGE;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < WI; ++i) {
             const unsigned lds_base = __builtin_amdgcn_readfirstlane(
-                (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)(stage + i * 8 * kStageRow));
+                (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)(stage + (kgrp * WI + i) * 8 * kStageRow));
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
                          :
                          : "v"(w_src[i] + (long long)g * 64), "s"(lds_base)
@@ -206,10 +272,10 @@ __global__ __launch_bounds__(WAVES * kWave, 8 / WAVES) void skinny_gemm_stream_k
                 b[t] = *reinterpret_cast<const g_bf16x8*>(xst + ((th * TT + t) * 32 + ln) * kStageRow +
                                                           (((2 * s + hh) ^ swz) * 16));
         };
-        frags(0, fa[0], fb[0]);
+        frags(kgrp * WI, fa[0], fb[0]);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            if (s + 1 < 4) frags(s + 1, fa[(s + 1) & 1], fb[(s + 1) & 1]);
+        for (int s = 0; s < WI; ++s) {
+            if (s + 1 < WI) frags(kgrp * WI + s + 1, fa[(s + 1) & 1], fb[(s + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int r = 0; r < RT; ++r)
@@ -228,62 +294,255 @@ __global__ __launch_bounds__(WAVES * kWave, 8 / WAVES) void skinny_gemm_stream_k
     for (int g = 0; g < G; ++g) {
         // issued after step g's X: the 4 W transfers of step g + 1, unless there is none
         if (g + 1 < G)
-            asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(WI) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (g + 1 < G) fetch_x(g + 1);
         if (g + 2 < G) fetch_w(g + 2);
         multiply(xs + (g & 1) * XSTAGE, wsl + (g % 3) * (RT * WSTAGE));
     }
+    // KG = 2: the groups add up.  Group g finishes the tiles j with j % KG == g; each wavefront parks the others in LDS (the
+    // stages are free: no transfer is in flight after the last step) and adds what its partner parked, groups in order.
+    if (KG > 1) {
+        __syncthreads();
+        float4* park = reinterpret_cast<float4*>(lds);
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) {
+            const int dst = j % KG;
+            if (dst != kgrp) {
+                float4* slot = park + (size_t)((wr * TILES + j) * (KG - 1) + (kgrp < dst ? kgrp : kgrp - 1)) * TILE_Q + lane;
+                const g_f32x16& a = acc[j / TT][j % TT];
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    slot[q4 * kWave] = make_float4(a[q4 * 4 + 0], a[q4 * 4 + 1], a[q4 * 4 + 2], a[q4 * 4 + 3]);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < TILES; ++j) {
+            const int dst = j % KG;
+            if (dst == kgrp) {
+                g_f32x16& a = acc[j / TT][j % TT];
+                g_f32x16 sum;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+#pragma unroll
+                for (int g = 0; g < KG; ++g) {
+                    if (g == dst) {
+                        sum += a;
+                    } else {
+                        const float4* slot = park + (size_t)((wr * TILES + j) * (KG - 1) + (g < dst ? g : g - 1)) * TILE_Q + lane;
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4) {
+                            const float4 v = slot[q4 * kWave];
+                            sum[q4 * 4 + 0] += v.x; sum[q4 * 4 + 1] += v.y; sum[q4 * 4 + 2] += v.z; sum[q4 * 4 + 3] += v.w;
+                        }
+                    }
+                }
+                a = sum;
+            }
+        }
+    }
     // register i of accumulator (r, t) of this lane: output row m = (th * TT + t) * 32 + ln,
     // column n = n0 + r * 32 + (i / 4) * 8 + hh * 4 + i % 4
+    if (p.ksplit > 1) {
+        float4* dst = reinterpret_cast<float4*>(p.part) +
+                      ((long long)(blockIdx.y * gridDim.x + blockIdx.x) * ROWW + wr) * (TILES * TILE_Q) + lane;
 #pragma unroll
-    for (int t = 0; t < TT; ++t) {
-        const int m = (th * TT + t) * 32 + ln;
-        if (m >= p.M) continue;
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
+        for (int j = 0; j < TILES; ++j) {
+            if (KG > 1 && j % KG != kgrp) continue;
+            if ((th * TT + j % TT) * 32 + ln >= p.M) continue;
+            const g_f32x16& a = acc[j / TT][j % TT];
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const int n = n0 + r * 32 + q4 * 8 + hh * 4;
-                if (RT == 1 && q4 * 8 + hh * 4 >= p.rows) continue;  // beyond a short tile (rows is a multiple of 4)
-                if (n >= p.N) continue;  // N is a multiple of 8: the 4 columns are in or out together
-                if (p.ksplit == 1) {
-                    g_bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[r][t][q4 * 4 + e];
-                    *reinterpret_cast<g_bf16x4*>(p.Y + (long long)m * p.ldy + n) = o;
-                } else {
-                    *reinterpret_cast<float4*>(p.part + ((long long)blockIdx.y * p.M + m) * p.N + n) = make_float4(
-                        acc[r][t][q4 * 4 + 0], acc[r][t][q4 * 4 + 1], acc[r][t][q4 * 4 + 2], acc[r][t][q4 * 4 + 3]);
-                }
+                if (RT == 1 && q4 * 8 >= p.rows) continue;  // beyond a short tile
+                dst[j * TILE_Q + q4 * kWave] = make_float4(a[q4 * 4 + 0], a[q4 * 4 + 1], a[q4 * 4 + 2], a[q4 * 4 + 3]);
             }
+        }
+        return;
+    }
+    // Y tiles turn through LDS, 32 tokens x 32 weight rows at a time, wavefront-private: a token's 64 bytes leave together
+    __syncthreads();  // nobody reads a stage or a parked tile any more
+    unsigned char* tr = lds + wave * (32 * kGemmOutRow);
+#pragma unroll
+    for (int j = 0; j < TILES; ++j) {
+        if (KG > 1 && j % KG != kgrp) continue;
+        const int m_base = (th * TT + j % TT) * 32;
+        if (m_base >= p.M) continue;
+        const g_f32x16& a = acc[j / TT][j % TT];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            g_bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (__bf16)a[q4 * 4 + e];
+            *reinterpret_cast<g_bf16x4*>(tr + ln * kGemmOutRow + (q4 * 8 + hh * 4) * 2) = o;
+        }
+        const int nc = (lane & 7) * 4, n = n0 + (j / TT) * 32 + nc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int ml = i * 8 + (lane >> 3);
+            const g_bf16x4 o = *reinterpret_cast<const g_bf16x4*>(tr + ml * kGemmOutRow + nc * 2);
+            if (m_base + ml < p.M && n < p.N && (RT > 1 || nc < p.rows))  // N a multiple of 8: 4 columns are in or out together
+                *reinterpret_cast<g_bf16x4*>(p.Y + (long long)(m_base + ml) * p.ldy + n) = o;
+        }
     }
 }
 
+// One workgroup per accumulator tile of 32 tokens x 32 weight rows: thread (quad, lane) adds up the tile's partials as the stream
+// kernel's lanes left them, in split order (deterministic), and the bf16 tile turns through LDS into 64-byte row pieces of Y.
 __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const GemmParams p) {
-    const long long i4 = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;  // 4 consecutive columns of one row
-    if (i4 >= (long long)p.M * p.N) return;
-    const int m = (int)(i4 / p.N), n = (int)(i4 - (long long)m * p.N);
+    __shared__ __attribute__((aligned(16))) unsigned char tr[32 * kGemmOutRow];
+    const int tiles = p.rt * p.tt;
+    const int j = blockIdx.x % tiles, wb = blockIdx.x / tiles;
+    const int wr = wb % p.roww, block = wb / p.roww;
+    const int grp = p.rt == 1 ? wr : wr >> 1, th = p.rt == 1 ? 0 : wr & 1;
+    const int m_base = (th * p.tt + j % p.tt) * 32;
+    const int n_base = block * (p.rows * p.roww) + grp * (p.rows * p.rt) + (j / p.tt) * 32;
+    if (m_base >= p.M || n_base >= p.N) return;  // uniform over the workgroup
+    const int q4 = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1), ln = lane & 31, hh = lane >> 5;
+    const bool in = m_base + ln < p.M && (p.rt > 1 || q4 * 8 < p.rows);  // what the stream kernel has stored
+    const long long stride = (long long)p.nblocks * p.roww * tiles * (kGemmTileFloats / 4);
+    const float4* src = reinterpret_cast<const float4*>(p.part) + (long long)blockIdx.x * (kGemmTileFloats / 4) + threadIdx.x;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int ks = 0; ks < p.ksplit; ++ks) {  // fixed order: deterministic
-        const float4 v = *reinterpret_cast<const float4*>(p.part + ((long long)ks * p.M + m) * p.N + n);
-        s.x += v.x;
-        s.y += v.y;
-        s.z += v.z;
-        s.w += v.w;
+    if (in) {
+        for (int k0 = 0; k0 < p.ksplit; k0 += 8) {  // eight loads in flight
+            float4 v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (k0 + e < p.ksplit) v[e] = src[(k0 + e) * stride];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (k0 + e < p.ksplit) {
+                    s.x += v[e].x;
+                    s.y += v[e].y;
+                    s.z += v[e].z;
+                    s.w += v[e].w;
+                }
+        }
     }
     g_bf16x4 o;
     o[0] = (__bf16)s.x;
     o[1] = (__bf16)s.y;
     o[2] = (__bf16)s.z;
     o[3] = (__bf16)s.w;
-    *reinterpret_cast<g_bf16x4*>(p.Y + (long long)m * p.ldy + n) = o;
+    *reinterpret_cast<g_bf16x4*>(tr + ln * kGemmOutRow + (q4 * 8 + hh * 4) * 2) = o;
+    __syncthreads();
+    const int ml = threadIdx.x >> 3, nc = (threadIdx.x & 7) * 4;
+    if (m_base + ml < p.M && n_base + nc < p.N && (p.rt > 1 || nc < p.rows))
+        *reinterpret_cast<g_bf16x4*>(p.Y + (long long)(m_base + ml) * p.ldy + n_base + nc) =
+            *reinterpret_cast<const g_bf16x4*>(tr + ml * kGemmOutRow + nc * 2);
 }
 
+// The direct form.  Small matrices are bound by fixed costs -- launch, first data, the exchange of partials -- so the whole K
+// range stays in one workgroup and both operands go straight from memory into fragment registers: with 16x16x32 MFMA a load
+// covers 64 contiguous bytes of 16 rows, and a wavefront's share of K is at most two batches of UB steps at K = 2048 (all of
+// it in flight at once).  The wavefronts' sums meet in LDS, added in wavefront order.  W is non-temporal when a single
+// workgroup column reads it (NT); with several over the tokens the later ones find it in the L2.
+template <int RN, int TT, int WAVES, int UB, bool NT>
+__global__ __launch_bounds__(WAVES * kWave) void skinny_gemm_direct_kernel(const GemmParams p) {
+    constexpr int TILES = RN * TT;
+    __shared__ __attribute__((aligned(16))) float4 red[WAVES][TILES][kWave];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
+    const int lr = lane & 15, kg = lane >> 4;
+    const int n0 = blockIdx.x * (16 * RN), m0 = blockIdx.y * (16 * TT);
+    const int S = p.K / 32;
+    const int s_lo = (int)((long long)wave * S / WAVES), s_hi = (int)((long long)(wave + 1) * S / WAVES);
+    const __bf16 *wp[RN], *xp[TT];
+#pragma unroll
+    for (int i = 0; i < RN; ++i) wp[i] = p.W + (long long)min(n0 + i * 16 + lr, p.N - 1) * p.ldw + kg * 8;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) xp[t] = p.X + (long long)min(m0 + t * 16 + lr, p.M - 1) * p.ldx + kg * 8;
+    g_f32x4 acc[RN][TT];
+#pragma unroll
+    for (int i = 0; i < RN; ++i)
+#pragma unroll
+        for (int t = 0; t < TT; ++t) acc[i][t] = g_f32x4{0.f, 0.f, 0.f, 0.f};
+    union frag { g_u32x4 u; g_bf16x8 v; };
+    struct buf { frag w[UB][RN], x[UB][TT]; };
+    auto load = [&](int s0, buf& b) {
+#pragma unroll
+        for (int j = 0; j < UB; ++j) {
+            const int s = min(s0 + j, s_hi - 1);
+#pragma unroll
+            for (int i = 0; i < RN; ++i) {
+                const g_u32x4* a = reinterpret_cast<const g_u32x4*>(wp[i] + s * 32);
+                b.w[j][i].u = NT ? __builtin_nontemporal_load(a) : *a;
+            }
+#pragma unroll
+            for (int t = 0; t < TT; ++t) b.x[j][t].u = *reinterpret_cast<const g_u32x4*>(xp[t] + s * 32);
+        }
+    };
+    auto mul = [&](int s0, buf& b) {
+#pragma unroll
+        for (int j = 0; j < UB; ++j) {
+            if (s0 + j < s_hi) {
+#pragma unroll
+                for (int i = 0; i < RN; ++i)
+#pragma unroll
+                    for (int t = 0; t < TT; ++t)
+                        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.w[j][i].v, b.x[j][t].v, acc[i][t], 0, 0, 0);
+            }
+        }
+    };
+    if (s_lo < s_hi) {  // with few chunks some wavefronts have no share
+        buf A, B;
+        load(s_lo, A);
+        for (int s = s_lo; s < s_hi; s += 2 * UB) {
+            if (s + UB < s_hi) load(s + UB, B);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(s, A);
+            if (s + 2 * UB < s_hi) load(s + 2 * UB, A);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + UB < s_hi) mul(s + UB, B);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RN; ++i)
+#pragma unroll
+        for (int t = 0; t < TT; ++t) red[wave][i * TT + t][lane] = make_float4(acc[i][t][0], acc[i][t][1], acc[i][t][2], acc[i][t][3]);
+    __syncthreads();
+    for (int e = tid; e < TILES * kWave; e += WAVES * kWave) {
+        const int tile = e / kWave, l = e % kWave;
+        float4 s = red[0][tile][l];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            const float4 v = red[w][tile][l];
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
+        const int i = tile / TT, t = tile % TT;
+        const int m = m0 + t * 16 + (l & 15), n = n0 + i * 16 + (l >> 4) * 4;
+        if (m < p.M && n < p.N) {
+            g_bf16x4 o;
+            o[0] = (__bf16)s.x; o[1] = (__bf16)s.y; o[2] = (__bf16)s.z; o[3] = (__bf16)s.w;
+            *reinterpret_cast<g_bf16x4*>(p.Y + (long long)m * p.ldy + n) = o;
+        }
+    }
+}
 static inline bool gemm_sizes_ok(int M, int N, int K) {
     return M >= 1 && M <= kGemmMaxM && N >= 8 && (N % 8) == 0 && K >= kGemmChunk && (K % kGemmChunk) == 0 &&
            (long long)M * N < (1LL << 40);
+}
+
+template <int WAVES, int KG>
+static void launch_stream(int mt, dim3 grid, hipStream_t s, const GemmParams& p) {
+    const dim3 block(WAVES * kWave);
+    switch (mt) {
+        case 1: LOTTS_LAUNCH((skinny_gemm_stream_kernel<1, 1, WAVES, KG>), grid, block, s, p); break;
+        case 2: LOTTS_LAUNCH((skinny_gemm_stream_kernel<2, 1, WAVES, KG>), grid, block, s, p); break;
+        case 3: LOTTS_LAUNCH((skinny_gemm_stream_kernel<3, 1, WAVES, KG>), grid, block, s, p); break;
+        case 4: LOTTS_LAUNCH((skinny_gemm_stream_kernel<4, 2, WAVES, KG>), grid, block, s, p); break;
+        case 5: LOTTS_LAUNCH((skinny_gemm_stream_kernel<5, 1, WAVES, KG>), grid, block, s, p); break;
+        case 6: LOTTS_LAUNCH((skinny_gemm_stream_kernel<6, 2, WAVES, KG>), grid, block, s, p); break;
+        case 7: LOTTS_LAUNCH((skinny_gemm_stream_kernel<7, 1, WAVES, KG>), grid, block, s, p); break;
+        default: LOTTS_LAUNCH((skinny_gemm_stream_kernel<8, 2, WAVES, KG>), grid, block, s, p); break;
+    }
+}
+
+template <int RN, int TT, int WAVES, int UB>
+static void launch_direct(dim3 grid, hipStream_t s, const GemmParams& p) {
+    const dim3 block(WAVES * kWave);
+    if (grid.y == 1) LOTTS_LAUNCH((skinny_gemm_direct_kernel<RN, TT, WAVES, UB, true>), grid, block, s, p);
+    else LOTTS_LAUNCH((skinny_gemm_direct_kernel<RN, TT, WAVES, UB, false>), grid, block, s, p);
 }
 
 }  // namespace lotts
@@ -291,7 +550,7 @@ static inline bool gemm_sizes_ok(int M, int N, int K) {
 extern "C" size_t skinny_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
     if (!lotts::gemm_sizes_ok(M, N, K)) return 0;
     const lotts::GemmPlan pl = lotts::plan_gemm(M, N, K);
-    const size_t bytes = pl.ksplit > 1 ? (size_t)pl.ksplit * M * N * sizeof(float) : 0;
+    const size_t bytes = pl.ksplit > 1 ? pl.ksplit * lotts::split_floats(pl) * sizeof(float) : 0;
     return bytes < 256 ? 256 : bytes;
 }
 
@@ -311,32 +570,28 @@ extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64
     p.Y = static_cast<__bf16*>(Y);
     p.part = static_cast<float*>(workspace);
     p.M = M; p.N = N; p.K = K; p.ksplit = pl.ksplit; p.rows = pl.rows;
+    p.nblocks = pl.nblocks; p.roww = pl.roww; p.rt = pl.rt; p.tt = pl.mt / pl.rt;
     p.ldx = ldx; p.ldw = ldw; p.ldy = ldy;
     hipStream_t s = (hipStream_t)stream;
-    const dim3 grid(pl.nblocks, pl.ksplit), block4(4 * kWave), block8(8 * kWave);
-    if (pl.stream) {
-        switch (pl.mt) {
-            case 1: LOTTS_LAUNCH((skinny_gemm_stream_kernel<1, 1, 8>), grid, block8, s, p); break;
-            case 2: LOTTS_LAUNCH((skinny_gemm_stream_kernel<2, 1, 8>), grid, block8, s, p); break;
-            case 3: LOTTS_LAUNCH((skinny_gemm_stream_kernel<3, 1, 8>), grid, block8, s, p); break;
-            case 4: LOTTS_LAUNCH((skinny_gemm_stream_kernel<4, 2, 8>), grid, block8, s, p); break;
-            case 5: LOTTS_LAUNCH((skinny_gemm_stream_kernel<5, 1, 8>), grid, block8, s, p); break;
-            case 6: LOTTS_LAUNCH((skinny_gemm_stream_kernel<6, 2, 8>), grid, block8, s, p); break;
-            case 7: LOTTS_LAUNCH((skinny_gemm_stream_kernel<7, 1, 8>), grid, block8, s, p); break;
-            default: LOTTS_LAUNCH((skinny_gemm_stream_kernel<8, 2, 8>), grid, block8, s, p); break;
-        }
-    } else if (pl.mt == 1) {
-        LOTTS_LAUNCH((skinny_gemm_stream_kernel<1, 1, 4>), grid, block4, s, p);
-    } else if (pl.mt == 2) {
-        LOTTS_LAUNCH((skinny_gemm_stream_kernel<2, 1, 4>), grid, block4, s, p);
-    } else if (pl.mt == 3) {
-        LOTTS_LAUNCH((skinny_gemm_stream_kernel<3, 1, 4>), grid, block4, s, p);
-    } else {
-        LOTTS_LAUNCH((skinny_gemm_stream_kernel<4, 2, 4>), grid, block4, s, p);
+    const dim3 grid(pl.nblocks, pl.form == kDirect ? pl.nby : pl.ksplit);
+    switch (pl.form) {
+        case kStream256: launch_stream<8, 1>(pl.mt, grid, s, p); break;
+        case kStream128: launch_stream<4, 1>(pl.mt, grid, s, p); break;
+        case kStream64: launch_stream<4, 2>(pl.mt, grid, s, p); break;
+        case kDirect:
+            switch (pl.rn * 10 + pl.tt) {
+                case 11: launch_direct<1, 1, 8, 8>(grid, s, p); break;
+                case 12: launch_direct<1, 2, 8, 4>(grid, s, p); break;
+                case 21: launch_direct<2, 1, 8, 8>(grid, s, p); break;
+                case 22: launch_direct<2, 2, 8, 4>(grid, s, p); break;
+                case 23: launch_direct<2, 3, 8, 4>(grid, s, p); break;
+                case 42: launch_direct<4, 2, 4, 2>(grid, s, p); break;
+                default: launch_direct<4, 3, 4, 2>(grid, s, p); break;
+            }
+            break;
     }
     int rc = check_launch();
     if (rc != LOTTS_OK || pl.ksplit == 1) return rc;
-    const long long quads = ((long long)M * N + 3) / 4;
-    LOTTS_LAUNCH(skinny_gemm_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), s, p);
+    LOTTS_LAUNCH(skinny_gemm_reduce_kernel, dim3((unsigned)(pl.nblocks * pl.roww * pl.mt)), dim3(256), s, p);
     return check_launch();
 }
