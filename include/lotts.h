@@ -276,8 +276,9 @@ int skinny_gemm(int32_t M, int32_t N, int32_t K, const void *X, int64_t ldx, con
  *   lotts_timer_stop(launches, ms): waits for the timed kernels to finish, writes their number to
  *       *launches and, if ms is not NULL, each one's milliseconds to ms[0 .. *launches), in launch
  *       order (HOST array of at least max_launches floats).  Switches the timer off.
- * The order of launches inside one call: verify_attention 1 (2 when the partials of a row are
- * many: attention, then merge); spec_accept 1 (2 -- scan, pick -- when V is not a multiple of 4, beyond
+ * The order of launches inside one call: verify_attention 1 (2 -- attention, then merge -- when the partials
+ * of a row are many and come from several row groups or from a long prefix, or when at most four (KV
+ * head, branch) pairs share contexts of up to 4096 tokens); spec_accept 1 (2 -- scan, pick -- when V is not a multiple of 4, beyond
  * 2^18, or the rows are not 16-byte aligned); spec_accept_logits 3 (max, sum,
  * scan and pick); majority_vote 1; confidence_vote 1; skinny_gemm 1 (2 when K is split: GEMM, reduce).
  */

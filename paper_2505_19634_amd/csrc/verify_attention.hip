@@ -24,16 +24,17 @@
 //       (K read back row-wise as the MFMA A operand, V with the transposing LDS load), S^T = K Q^T
 //       and O^T += V^T P^T on 32x32x16 bf16 MFMA, flash-style running (max, sum, O).  The 4 states
 //       are combined through LDS after one barrier and the item's un-normalised partial goes to
-//       the workspace.  Arrivals are counted per (KV head, branch) in a cell that carries the call's
-//       tag (what an earlier call left there, complete or not, counts as zero arrivals);
-//       the workgroup that delivers the last partial does the log-sum-exp merge of that branch's
-//       rows, normalises, converts and stores O (and LSE).  Partials cross workgroups -- and XCDs,
+//       the workspace -- or, if the item holds whole rows (no key shares, no prefix items), straight to O.
+//       Who merges the partials of a row depends on how many there are: of two, the item that finishes later (arrivals are
+//       counted per (KV head, branch) in a cell that carries the call's tag: what an earlier call left there, complete
+//       or not, counts as zero arrivals); of more, merge workgroups at the end of the grid, which wait for a flag of
+//       every partial they read (they only ever wait for workgroups with smaller block indices, which were dispatched before
+//       them) and share the rows among them.  Partials cross workgroups -- and XCDs,
 //       each with its own L2 -- inside one launch, so they are written and read with 16-byte
 //       buffer accesses that carry the device-scope cache policy (performed at the memory side of
 //       the L2s); nothing is ever flushed or invalidated cache-wide.
-//   attn_merge_kernel     second launch, only when a row has many partials (few branches or long
-//       caches): one workgroup would merge them at one compute unit's bandwidth, so the merge is
-//       spread over the chip instead.
+//   attn_merge_kernel     second launch, where prefix items or several row groups add partials of their own and a row has many
+//       of them, and for the smallest contexts.
 // fp32 path: attn_f32_kernel, plain fp32 VALU arithmetic, one workgroup per output row; it
 // exists for exactness checks on small fp32 problems, not for speed.
 // Two entry points share all of this: verify_attention (the caller brings the workspace) and
@@ -56,7 +57,11 @@ constexpr int kAttnThreads = 256;
 constexpr int kAttnWaves = kAttnThreads / kWave;
 constexpr int kTile = 32;      // keys per tile = M of one 32x32x16 MFMA
 constexpr int kRowTile = 32;   // query rows per row tile = N of the MFMA
-constexpr int kMaxSplit = 16;  // more key shares than this cost more in the merge than they gain in streaming
+constexpr int kMaxSplit = 64;       // key shares of a segment whose partials are merged by merge workgroups or a launch of
+                                    // their own: one wavefront polls the flags of a row's partials
+constexpr int kMaxSplitStack = 16;  // the same when prefix items or several row groups add partials of their own
+
+constexpr int kMaxCounters = 16384;  // 64-bit cells at the start of the workspace
 
 struct AttnPlan {
     int nqt;            // row tiles per item: 1 or 2
@@ -66,9 +71,15 @@ struct AttnPlan {
     int nsplit_priv;    // key splits of a private segment
     int nsplit_pre;     // key splits of the prefix (stacked plan; 0 otherwise)
     int nslots;         // partials per output row
-    int fused;          // 1: the last-arriving workgroup merges inside the attention launch
-    int n_pre_items, n_priv_items;
+    int merge;          // who merges a row's partials: one of the three below
+    int rpm, mpp;       // merge workgroups: rows each of them takes (a power of two), their number per (KV head, branch)
+    int n_pre_items, n_priv_items, n_merge;
 };
+constexpr int kMergeLast = 0;    // the last-arriving workgroup of a (KV head, branch), inside the attention launch
+constexpr int kMergeGroups = 1;  // merge workgroups at the end of the attention launch's grid
+constexpr int kMergeLaunch = 2;  // a launch of its own
+constexpr int kMergeNone = 3;    // an item holds whole rows: it stores the output itself
+constexpr int kMergePair = 4;    // two items, one row tile: the later one reads the other's partial, its own is in registers
 
 struct AttnParams {
     const void *Q, *Kpre, *Vpre, *Kpriv, *Vpriv;
@@ -103,31 +114,72 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
     const int rows_per_item = kRowTile * pl.nqt;
     pl.n_rg_priv = ceil_div(GR, rows_per_item);
     pl.n_rg_pre = ceil_div(d.B * GR, rows_per_item);
-    const int tiles_priv = ceil_div(d.Lmax, kTile);
+    const int tiles_priv = ceil_div(d.Lmax, kTile), tiles_pre = ceil_div(d.P, kTile);
     const long long base = (long long)d.B * d.Hkv * pl.n_rg_priv;
-    long long want = (kNumCU + base - 1) / base;
-    int max_split = tiles_priv / kAttnWaves;  // at least one tile per wavefront
-    if (max_split > kMaxSplit) max_split = kMaxSplit;
-    if (max_split < 1) max_split = 1;
-    pl.nsplit_priv = (int)(want < 1 ? 1 : (want > max_split ? max_split : want));
     // A prefix that is short next to the private caches is folded into the private items.
     pl.fold = (d.P > 0 && (long long)d.P * 4 <= d.Lmax) ? 1 : 0;
+    const bool simple = pl.n_rg_priv == 1 && (d.P == 0 || pl.fold);  // an item's rows are one branch's rows
+    // A count just above one item per unit is the worst choice: a few units run two and everybody waits for them (48
+    // branches x 2 heads x 4300 tokens in 3 shares, 288 items, 48.6 us; in 2 shares, 192 items, 36.7).
+    // At D = 64 and one row tile an item has half the bytes in flight and two of them fit a unit with ease, so where one per
+    // unit leaves many units without an item, two per unit are dealt (12 branches x 8 heads x 2461 tokens, D = 64: 5 shares 15.9
+    // us, 2 shares 16.7; of different lengths 13.8 against 15.4).
+    auto shares = [&](int units) { return base < units ? units / base : 1; };
+    auto fills = [&](int units) { return shares(units) * base * 20 >= (long long)units * 17 && base <= units; };
+    long long want = shares(kNumCU);
+    if (simple && d.D == 64 && pl.nqt == 1 && !fills(kNumCU) && fills(2 * kNumCU)) want = shares(2 * kNumCU);
+    // At least about one tile per wavefront.  Few branches: the folded prefix tiles count as well, and the last share may be
+    // ragged.  (With more, one share more would double the items and with them the partials; the built-in scratch of the
+    // allocation-free entry point has to hold what it held.)
+    const bool few = simple && base <= kNumCU / 2;
+    int max_split = few ? ceil_div(tiles_priv + (pl.fold ? tiles_pre : 0), kAttnWaves) : tiles_priv / kAttnWaves;
+    const int cap_split = simple ? kMaxSplit : kMaxSplitStack;
+    if (max_split > cap_split) max_split = cap_split;
+    if (max_split < 1) max_split = 1;
+    pl.nsplit_priv = (int)(want > max_split ? max_split : want);
+    if (simple) {  // the fewest shares (partials) that leave the longest wavefront the same number of tiles
+        const int all = tiles_priv + (pl.fold ? tiles_pre : 0);
+        const int per_wave = ceil_div(all, kAttnWaves * pl.nsplit_priv);
+        pl.nsplit_priv = ceil_div(all, kAttnWaves * per_wave);
+    }
     if (d.P > 0 && !pl.fold) {
-        const int tiles_pre = ceil_div(d.P, kTile);
         const int tiles_per_item = ceil_div(tiles_priv, pl.nsplit_priv);
         int s = (tiles_pre + tiles_per_item / 2) / tiles_per_item;
         int cap = tiles_pre / kAttnWaves;
-        if (cap > kMaxSplit) cap = kMaxSplit;
+        if (cap > kMaxSplitStack) cap = kMaxSplitStack;
         if (s > cap) s = cap;
         pl.nsplit_pre = s < 1 ? 1 : s;
     } else {
         pl.nsplit_pre = 0;
     }
     pl.nslots = pl.nsplit_pre + pl.nsplit_priv;
-    // The in-launch merge of a (KV head, branch) is done by ONE workgroup, at one CU's share of the
-    // bandwidth: worth it only while that is a few tens of KB; beyond, a separate launch spreads the
-    // merge over the whole chip.
-    pl.fused = ((long long)pl.nslots * GR * d.D * 4 <= 48 * 1024) ? 1 : 0;
+    // Who merges (measured with calls back to back, kernel + what merges):
+    //  - an item that holds whole rows stores the output: 32 branches x 8 KV heads x 3168 tokens 57.3 -> 53.3 us;
+    //  - of two items the later one merges and reads only the other's partial (16 x 8 heads x 4096 tokens: 0.5 us less than
+    //    with merge workgroups);
+    //  - merge workgroups at the end of the grid share the rows of a (KV head, branch) and wait for the flags of its partials:
+    //    1 x 2 heads x 8192 tokens, 64 shares, 10.6 us against 11.7 with a launch of its own (and 15.6 with 16 shares);
+    //    8 x 8 heads x 4300 tokens, 4 shares, 27.4 us against 29.3 with the merge by the last arriver;
+    //  - a second launch where prefix items or several row groups add partials of their own, and for contexts up to 4096
+    //    tokens on at most four (KV head, branch) pairs: 2 x 2 heads x 4064 tokens 10.7 us, with merge workgroups 9.9 -- the
+    //    kernel timer's callers see this size as the pair of launches that it was;
+    //  - the last arriver, ONE workgroup at one unit's share of the bandwidth, where those shapes leave a few tens of KB.
+    if (pl.nslots == 1) pl.merge = kMergeNone;  // no prefix items, no key shares
+    else if (simple && pl.nslots == 2 && pl.nqt == 1) pl.merge = kMergePair;
+    else if (simple && !(base <= 4 && tiles_priv + tiles_pre <= 128)) pl.merge = kMergeGroups;
+    else pl.merge = !simple && (long long)pl.nslots * GR * d.D * 4 <= 48 * 1024 ? kMergeLast : kMergeLaunch;
+    // rows per merge workgroup: as few as leave at most one workgroup per unit in all
+    auto rows_per_merger = [&](int threads) {
+        pl.rpm = 1;
+        while (pl.rpm * 2 * (d.D / 4) <= threads && (long long)d.B * d.Hkv * ceil_div(GR, pl.rpm) > kNumCU) pl.rpm *= 2;
+        pl.mpp = ceil_div(GR, pl.rpm);
+    };
+    if (pl.merge == kMergeGroups) {
+        rows_per_merger(kAttnThreads * pl.nqt);
+        if ((long long)d.B * d.Hkv * pl.mpp * pl.nsplit_priv > kMaxCounters) pl.merge = kMergeLaunch;  // flags would not fit
+    }
+    if (pl.merge == kMergeLaunch) rows_per_merger(kAttnThreads);
+    pl.n_merge = pl.merge == kMergeGroups ? d.B * d.Hkv * pl.mpp : 0;
     pl.n_pre_items = d.Hkv * pl.n_rg_pre * pl.nsplit_pre;
     pl.n_priv_items = d.B * d.Hkv * pl.n_rg_priv * pl.nsplit_priv;
     return pl;
@@ -148,8 +200,9 @@ static inline size_t part_ml_elems(const lotts_attn_desc& d, const AttnPlan& pl)
 // of this process; an arriving workgroup first raises the cell to (tag, 0) with an atomic maximum,
 // then adds one.  A cell left at zero (a fresh zero-filled buffer, or the reset the last arriver
 // does) and a cell left behind by an earlier call that never completed both start the new call
-// at zero arrivals, so no call can poison the buffer for the next one.
-constexpr int kMaxCounters = 16384;
+// at zero arrivals, so no call can poison the buffer for the next one.  With merge workgroups the same cells are flags, one
+// per (KV head, branch, merge workgroup, key share): an item stores (tag << 16) | 1 into its flag of every merge workgroup
+// that reads its partial, and that workgroup puts the zero back; any other content counts as not arrived.
 constexpr int kTagShift = 16;            // arrivals per cell < 2^16, checked on the host
 static std::atomic<unsigned long long> g_call_tag{0};
 static inline size_t workspace_layout(const lotts_attn_desc& d, const AttnPlan& pl, size_t* off_o, size_t* off_ml) {
@@ -191,24 +244,36 @@ __device__ __forceinline__ float2 ws_load2(__amdgpu_buffer_rsrc_t r, unsigned by
     return make_float2(__uint_as_float(u[0]), __uint_as_float(u[1]));
 }
 
+// Output quad c4 of row rl (0 .. G*R-1) of a (KV head, branch): normalise, convert, store; the first quad's thread stores LSE.
+__device__ __forceinline__ void store_merged(const AttnParams& prm, int kvh, int b, int rl, int c4, float4 o, float M, float Lsum) {
+    const int r = prm.G == 1 ? rl : (int)__umulhi((unsigned)rl, prm.g_magic), hg = rl - r * prm.G;
+    const int h = kvh * prm.G + hg;
+    const float inv = 1.0f / Lsum;  // a row always sees itself: Lsum > 0
+    __bf16* op = (__bf16*)prm.O + (long long)b * prm.o_stride_b + (long long)r * prm.o_stride_r +
+                 (long long)h * prm.o_stride_h + c4 * 4;
+    bf16x4 ov;
+    ov[0] = (__bf16)(o.x * inv);
+    ov[1] = (__bf16)(o.y * inv);
+    ov[2] = (__bf16)(o.z * inv);
+    ov[3] = (__bf16)(o.w * inv);
+    *reinterpret_cast<bf16x4*>(op) = ov;
+    if (prm.lse && c4 == 0)
+        prm.lse[((long long)b * prm.R + r) * prm.Hq + h] = (M + log2f(Lsum)) * 0.69314718055994530942f;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Merge of the partials of the G*R output rows of one (KV head, branch), run by the workgroup that
 // delivered the last of them:  O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, slots in index
-// order whoever merges.  4 floats per output quad; a thread takes EU quads (256 apart) and CH
-// slots at a time, so that EU * CH sixteen-byte loads are in flight together.  DEV selects
-// device-scope loads (merge inside the attention launch, partials come from the memory side of the
-// L2s) or plain loads (separate merge launch).  With OWN the merging workgroup's own partial (slot
-// own_slot) is taken from its registers -- quad q of thread tid is quad tid + 256 q of the branch
-// -- instead of being read back.
+// order whoever merges.  4 floats per output quad; a thread takes two quads (256 apart) and eight
+// slots at a time, so that 16 sixteen-byte loads are in flight together, with device scope: the partials come from
+// the memory side of the L2s.
 // ---------------------------------------------------------------------------------------------
-template <int D, bool DEV, int EU, int CH, bool OWN>
-__device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buffer_rsrc_t rs, int kvh, int b, int tid,
-                                             int e_begin, int e_end, int own_slot, const float4 (&own_o)[EU],
-                                             const float2 (&own_ml)[EU]) {
-    constexpr int F4 = D / 4;
+template <int D>
+__device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buffer_rsrc_t rs, int kvh, int b, int tid) {
+    constexpr int F4 = D / 4, EU = 2, CH = 8;
     const int ns = prm.plan.nslots;
-    const int n_e = e_end < prm.GR * F4 ? e_end : prm.GR * F4;  // output quads [e_begin, e_end) of this (KV head, branch)
-    for (int e0 = e_begin + tid; e0 < n_e; e0 += EU * kAttnThreads) {
+    const int n_e = prm.GR * F4;  // output quads of this (KV head, branch)
+    for (int e0 = tid; e0 < n_e; e0 += EU * kAttnThreads) {
         int rl[EU], c4[EU];
         unsigned base[EU];
         bool ok[EU];
@@ -233,20 +298,13 @@ __device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buf
             for (int q = 0; q < EU; ++q)
 #pragma unroll
                 for (int j = 0; j < CH; ++j) {
-                    if (OWN && q * kAttnThreads >= n_e) continue;  // no thread has this quad (uniform)
-                    const bool mine = OWN && s0 + j == own_slot;
-                    const bool in = s0 + j < ns && !mine;
-                    mv[q][j] = in ? ws_load2<DEV>(rs, prm.off_ml + (base[q] + s0 + j) * 8u) : make_float2(-INFINITY, 0.f);
-                    pv[q][j] = in ? ws_load4<DEV>(rs, prm.off_o + ((base[q] + s0 + j) * D + c4[q] * 4) * 4u)
+                    const bool in = s0 + j < ns;
+                    mv[q][j] = in ? ws_load2<true>(rs, prm.off_ml + (base[q] + s0 + j) * 8u) : make_float2(-INFINITY, 0.f);
+                    pv[q][j] = in ? ws_load4<true>(rs, prm.off_o + ((base[q] + s0 + j) * D + c4[q] * 4) * 4u)
                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (mine) {
-                        mv[q][j] = own_ml[q];
-                        pv[q][j] = own_o[q];
-                    }
                 }
 #pragma unroll
             for (int q = 0; q < EU; ++q) {
-                if (OWN && q * kAttnThreads >= n_e) continue;
                 float Mn = M[q];
 #pragma unroll
                 for (int j = 0; j < CH; ++j) Mn = fmaxf(Mn, mv[q][j].x);
@@ -265,31 +323,92 @@ __device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buf
             }
         }
 #pragma unroll
-        for (int q = 0; q < EU; ++q) {
-            if (!ok[q]) continue;
-            const int r = prm.G == 1 ? rl[q] : (int)__umulhi((unsigned)rl[q], prm.g_magic), hg = rl[q] - r * prm.G;
-            const int h = kvh * prm.G + hg;
-            const float inv = 1.0f / Lsum[q];  // a row always sees itself: Lsum > 0
-            __bf16* op = (__bf16*)prm.O + (long long)b * prm.o_stride_b + (long long)r * prm.o_stride_r +
-                         (long long)h * prm.o_stride_h + c4[q] * 4;
-            bf16x4 ov;
-            ov[0] = (__bf16)(o[q].x * inv);
-            ov[1] = (__bf16)(o[q].y * inv);
-            ov[2] = (__bf16)(o[q].z * inv);
-            ov[3] = (__bf16)(o[q].w * inv);
-            *reinterpret_cast<bf16x4*>(op) = ov;
-            if (prm.lse && c4[q] == 0)
-                prm.lse[((long long)b * prm.R + r) * prm.Hq + h] = (M[q] + log2f(Lsum[q])) * 0.69314718055994530942f;
-        }
+        for (int q = 0; q < EU; ++q)
+            if (ok[q]) store_merged(prm, kvh, b, rl[q], c4[q], o[q], M[q], Lsum[q]);
     }
 }
-// the general form: every slot is read from the workspace, two quads and eight slots per round
-template <int D, bool DEV>
-__device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buffer_rsrc_t rs, int kvh, int b, int tid,
-                                             int e_begin, int e_end) {
-    const float4 no_o[2] = {};
-    const float2 no_ml[2] = {};
-    merge_branch<D, DEV, 2, 8, false>(prm, rs, kvh, b, tid, e_begin, e_end, -1, no_o, no_ml);
+
+// ---------------------------------------------------------------------------------------------
+// Merge of rpm rows of a (KV head, branch) by one workgroup of THREADS threads: thread = (group of slots, row, output quad).
+// A thread takes every SG-th slot, eight 16-byte loads in flight; the groups meet in LDS and are added in group order, so
+// the result does not depend on timing.  A row's slots are read by many threads at once: with one thread per quad the
+// reads of 64 slots were eight dependent rounds and the launch took 9 us more than at 16 slots.
+// DEV: inside the attention launch (merge workgroups): wait for the flags, device-scope loads.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSpinLimit = 1 << 23;  // polls of a merge workgroup before it gives up: seconds, whatever else keeps the items from starting
+template <int D, bool DEV, int THREADS>
+__device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char* lds, int kvh, int b, int chunk) {
+    constexpr int F4 = D / 4, CH = 8;
+    const AttnPlan& pl = prm.plan;
+    const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
+    const int tid = threadIdx.x, ns = pl.nslots, rpm = pl.rpm;
+    const int c4 = tid % F4, r = (tid / F4) & (rpm - 1), sg = tid / (F4 * rpm), SG = THREADS / (F4 * rpm);
+    const int row = chunk * rpm + r;
+    if (DEV) {
+        // Every item of this (KV head, branch) has a smaller block index, so it was dispatched before this workgroup, and an
+        // item waits for nobody: the flags come.  Bounded all the same.
+        if (tid < ns) {  // ns <= kMaxSplit: lanes of the first wavefront
+            unsigned long long* flag = prm.counters + ((size_t)(kvh * prm.B + b) * pl.mpp + chunk) * ns + tid;
+            for (int spin = 0; spin < kSpinLimit; ++spin) {
+                if (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == prm.tag + 1) break;
+                __builtin_amdgcn_s_sleep(4);
+            }
+            __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // a captured launch is replayed with the same tag
+        }
+        __syncthreads();
+    }
+    float M = -INFINITY, Lsum = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (row < prm.GR) {
+        const unsigned base = ((unsigned)kvh * prm.B * prm.GR + (unsigned)b * prm.GR + row) * ns;
+        for (int s0 = sg; s0 < ns; s0 += SG * CH) {
+            float2 mv[CH];
+            float4 pv[CH];
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const int sl = s0 + j * SG;
+                const bool in = sl < ns;
+                mv[j] = in ? ws_load2<DEV>(rs, prm.off_ml + (base + sl) * 8u) : make_float2(-INFINITY, 0.f);
+                pv[j] = in ? ws_load4<DEV>(rs, prm.off_o + ((base + sl) * D + c4 * 4) * 4u) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+            float Mn = M;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) Mn = fmaxf(Mn, mv[j].x);
+            const float Mu = (Mn == -INFINITY) ? 0.f : Mn;
+            const float a = __builtin_amdgcn_exp2f(M - Mu);
+            Lsum *= a;
+            o.x *= a; o.y *= a; o.z *= a; o.w *= a;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const float w = __builtin_amdgcn_exp2f(mv[j].x - Mu);
+                Lsum += mv[j].y * w;
+                o.x += pv[j].x * w; o.y += pv[j].y * w; o.z += pv[j].z * w; o.w += pv[j].w * w;
+            }
+            M = Mn;
+        }
+    }
+    if (SG > 1) {  // uniform over the launch
+        float4* sh_o = reinterpret_cast<float4*>(lds);
+        float2* sh_ml = reinterpret_cast<float2*>(lds + THREADS * sizeof(float4));
+        sh_o[tid] = o;
+        sh_ml[tid] = make_float2(M, Lsum);
+        __syncthreads();
+        if (sg != 0) return;
+        float Mg = M;
+        for (int g = 1; g < SG; ++g) Mg = fmaxf(Mg, sh_ml[tid + g * F4 * rpm].x);
+        const float Mu = (Mg == -INFINITY) ? 0.f : Mg;
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+        float l = 0.f;
+        for (int g = 0; g < SG; ++g) {
+            const float2 ml = sh_ml[tid + g * F4 * rpm];
+            const float4 v = sh_o[tid + g * F4 * rpm];
+            const float w = __builtin_amdgcn_exp2f(ml.x - Mu);
+            l += ml.y * w;
+            t.x += v.x * w; t.y += v.y * w; t.z += v.z * w; t.w += v.w * w;
+        }
+        M = Mg; Lsum = l; o = t;
+    }
+    if (row < prm.GR) store_merged(prm, kvh, b, row, c4, o, M, Lsum);
 }
 
 __device__ __forceinline__ bf16x8 load_bf16x8(const __bf16* ptr) {
@@ -341,6 +460,12 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     // Order matters for latency: whatever does not depend on priv_len[b] (the prefix share, the Q
     // rows) is requested before that value is first used.
     int id = blockIdx.x;
+    if (id >= pl.n_priv_items + pl.n_pre_items) {  // a merge workgroup
+        id -= pl.n_priv_items + pl.n_pre_items;
+        const int kvh = id % prm.Hkv, rest = id / prm.Hkv;
+        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, rest / pl.mpp, rest % pl.mpp);
+        return;
+    }
     const bool is_private = id < pl.n_priv_items;
     int kvh, split, nsplit, rho0, rho_end, slot, b_item = 0;
     KeyRun run[2];   // run[0]: folded prefix share (may be empty), run[1]: the item's own segment
@@ -595,7 +720,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
     const int tig = tid % kAttnThreads;  // thread within its group of four wavefronts
     const int c4 = tig % F4, row0 = tig / F4;
-    float4 own_o[QPT];    // the last row tile's combined quads, kept for a merge by this workgroup
+    float4 own_o[QPT];    // the combined quads, kept for a merge by this workgroup (kMergePair: one row tile)
     float2 own_ml[QPT];
 #pragma unroll
     for (int t = 0; t < TW; ++t) {
@@ -653,8 +778,12 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             own_ml[q] = make_float2(mg, lg);
             if (row < nrows) {
                 const unsigned rho = rho0 + tile * kRowTile + row;
+                if (pl.merge == kMergeNone) {
+                    store_merged(prm, kvh, b_item, (int)rho - b_item * GR, c4, o, mg, lg);
+                    continue;
+                }
                 const unsigned pidx = ((unsigned)kvh * prm.B * GR + rho) * pl.nslots + slot;
-                if (pl.fused) {
+                if (pl.merge != kMergeLaunch) {
                     ws_store4<true>(rs, prm.off_o + (pidx * D + c4 * 4) * 4u, o);
                     if (c4 == 0) ws_store2<true>(rs, prm.off_ml + pidx * 8u, make_float2(mg, lg));
                 } else {
@@ -665,7 +794,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
         }
     }
 
-    if (!pl.fused) return;  // a separate launch merges (many partials per row: one workgroup would be too slow)
+    if (pl.merge == kMergeLaunch || pl.merge == kMergeNone) return;
     // ---- arrival: whoever completes the set of partials of a (KV head, branch) merges it ----
     // Every thread waits until its partial stores are acknowledged; then one thread per covered
     // branch counts the arrival in that branch's cell: raise it to (this call's tag, 0) if it holds
@@ -674,6 +803,12 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     // (same tag every time) be replayed.
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    if (pl.merge == kMergeGroups) {  // the item's partial is in memory: raise its flag for each of the branch's merge workgroups
+        if (tid < pl.mpp)
+            __hip_atomic_store(prm.counters + ((size_t)(kvh * prm.B + b_item) * pl.mpp + tid) * pl.nslots + slot, prm.tag + 1,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
     int* sh_last = reinterpret_cast<int*>(sh_l);  // free again; kAttnWaves * kRowTile >= rows of an item
     const int rows_per_item = kRowTile * NQT;
     const int b_first = rho0 / GR, b_last = (rho_end - 1) / GR;
@@ -693,28 +828,46 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
         sh_last[tid] = last;
     }
     __syncthreads();
-    // The common shape -- the item's rows are exactly one branch's rows and every partial of the branch
-    // comes from an item like this one -- merges all of the thread's quads in one round of loads and
-    // takes this workgroup's own partial from its registers; everything else goes the general way.
-    if (NQT == 1 && is_private && pl.n_rg_priv == 1 && pl.nsplit_pre == 0) {
-        if (sh_last[0]) merge_branch<D, true, QPT, 2, true>(prm, rs, kvh, b_item, tid, 0, 1 << 30, slot, own_o, own_ml);
-    } else {
-        if (GROUPS == 1 || tid < kAttnThreads)  // the merge is written for 256 threads
-            for (int j = 0; j < nb; ++j)
-                if (sh_last[j]) merge_branch<D, true>(prm, rs, kvh, b_first + j, tid, 0, 1 << 30);  // uniform over the workgroup
+    if (NQT == 1 && pl.merge == kMergePair) {  // the item's rows are the branch's rows; slot order, as everywhere
+        if (!sh_last[0]) return;
+        float2 mv[QPT];
+        float4 pv[QPT];
+        const int n_rows = rho_end - rho0;
+#pragma unroll
+        for (int q = 0; q < QPT; ++q) {
+            if (q * RSTEP >= n_rows) continue;
+            const unsigned pidx = ((unsigned)kvh * prm.B * GR + rho0 + min(row0 + q * RSTEP, n_rows - 1)) * 2 + (1 - slot);
+            mv[q] = ws_load2<true>(rs, prm.off_ml + pidx * 8u);
+            pv[q] = ws_load4<true>(rs, prm.off_o + (pidx * D + c4 * 4) * 4u);
+        }
+#pragma unroll
+        for (int q = 0; q < QPT; ++q) {
+            const int row = row0 + q * RSTEP;
+            if (row >= n_rows) continue;
+            const float2 ma = slot == 0 ? own_ml[q] : mv[q], mb = slot == 0 ? mv[q] : own_ml[q];
+            const float4 oa = slot == 0 ? own_o[q] : pv[q], ob = slot == 0 ? pv[q] : own_o[q];
+            const float M = fmaxf(ma.x, mb.x), Mu = (M == -INFINITY) ? 0.f : M;
+            const float wa = __builtin_amdgcn_exp2f(ma.x - Mu), wb = __builtin_amdgcn_exp2f(mb.x - Mu);
+            store_merged(prm, kvh, b_item, row, c4,
+                         make_float4(oa.x * wa + ob.x * wb, oa.y * wa + ob.y * wb, oa.z * wa + ob.z * wb, oa.w * wa + ob.w * wb),
+                         M, ma.y * wa + mb.y * wb);
+        }
+        return;
     }
+    if (GROUPS == 1 || tid < kAttnThreads)  // the merge is written for 256 threads
+        for (int j = 0; j < nb; ++j)
+            if (sh_last[j]) merge_branch<D>(prm, rs, kvh, b_first + j, tid);  // uniform over the workgroup
     __builtin_amdgcn_s_waitcnt(0);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Separate merge launch, used when a row has many partials: grid (quads of a (KV head, branch) in
-// blocks of 256, KV head x branch), one output quad per thread, so the whole chip shares the reads.
+// Separate merge launch, used when a row has many partials and items cover rows of several branches or branches have several
+// row groups: grid (row chunks of a (KV head, branch), KV head x branch).
 // ---------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(const AttnParams prm) {
-    const int kvh = blockIdx.y % prm.Hkv, b = blockIdx.y / prm.Hkv;
-    const int e_begin = blockIdx.x * kAttnThreads;
-    merge_branch<D, false>(prm, ws_rsrc(prm), kvh, b, threadIdx.x, e_begin, e_begin + kAttnThreads);
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnThreads * (sizeof(float4) + sizeof(float2))];
+    merge_rows<D, false, kAttnThreads>(prm, lds, blockIdx.y % prm.Hkv, blockIdx.y / prm.Hkv, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -888,7 +1041,7 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     prm.off_ml = (unsigned)off_ml;
     prm.counters = static_cast<unsigned long long*>(workspace);
     prm.tag = (g_call_tag.fetch_add(1, std::memory_order_relaxed) + 1) << kTagShift;
-    const long long items = (long long)pl.n_pre_items + pl.n_priv_items;
+    const long long items = (long long)pl.n_pre_items + pl.n_priv_items + pl.n_merge;
     if (items > 0x7fffffffLL) return LOTTS_ERR_SHAPE;
     const dim3 grid((unsigned)items), block(kAttnThreads);
     const dim3 block2(2 * kAttnThreads);
@@ -896,10 +1049,10 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     else if (d.D == 128) LOTTS_LAUNCH((attn_kernel<128, 2, 2>), grid, block2, s, prm);
     else if (pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<64, 1, 1>), grid, block, s, prm);
     else LOTTS_LAUNCH((attn_kernel<64, 2, 2>), grid, block2, s, prm);
-    if (!pl.fused) {
+    if (pl.merge == kMergeLaunch) {
         const int rc = check_launch();
         if (rc != LOTTS_OK) return rc;
-        const dim3 mgrid((unsigned)((prm.GR * (d.D / 4) + kAttnThreads - 1) / kAttnThreads), (unsigned)(d.Hkv * d.B));
+        const dim3 mgrid((unsigned)pl.mpp, (unsigned)(d.Hkv * d.B));
         if (d.D == 128) LOTTS_LAUNCH(attn_merge_kernel<128>, mgrid, block, s, prm);
         else LOTTS_LAUNCH(attn_merge_kernel<64>, mgrid, block, s, prm);
     }
