@@ -74,4 +74,20 @@ __device__ __forceinline__ unsigned long long wave_incl_scan_u64(unsigned long l
     return v;
 }
 
+// Adds a lane's neighbour's value in one instruction: the wavefront-wide steps of a scan without a trip through LDS.  Lanes
+// without a source, and rows that ROWS masks out, add nothing.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_add(unsigned v) {
+    return v + (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+// inclusive prefix sum over the wavefront of 32-bit values whose total fits 32 bits; lane 63 holds the total
+__device__ __forceinline__ unsigned wave_incl_scan_u32(unsigned v) {
+    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: inside each row of 16 lanes
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast 15: rows 1 and 3 take the last lane of the row before
+    return dpp_add<0x143, 0xc>(v);  // row_bcast 31: rows 2 and 3 take lane 31
+}
+
 }  // namespace lotts

@@ -12,16 +12,19 @@
 // U = trunc(u * 2^24); residual weights W_v = max(0, Ep_v * Sq - Eq_v * Sp); bonus weights Ep_v;
 // token = first v whose prefix sum exceeds floor(U_k * sum W / 2^24).  128-bit integers.
 //
-// Three launches:
-//   lg_max_kernel, lg_sum_kernel   grid (pieces of 16384 logits, B * (2k + 1) rows): piece maxima, then --
-//                       with the row maximum known -- the pieces' integer weight sums, added into one
-//                       64-bit sum per row with device-scope atomics (integers: any order gives the same
-//                       sum); the second sweep of the logits is served by the L2 / memory-side cache.
+// Two launches:
+//   lg_stat_kernel      grid (pieces of 8192 or 16384 logits, B * (2k + 1) rows, the pieces of a row next to each other): a
+//                       workgroup reads its piece ONCE into registers, publishes the piece's maximum under this call's tag,
+//                       collects the maxima of the row's other pieces, and forms the integer weight sum from the registers;
+//                       the pieces' sums meet in one 64-bit sum per row by device-scope atomics (integers: any order gives
+//                       the same sum).
 //   lg_scan_pick_kernel grid (chunks, B): accept tests -> n; 128-bit chunk sums of the weights of row n, published as
 //                       six 8-byte words that each carry 32 bits of a sum and this call's tag.  The workgroup of a
 //                       branch's LAST chunk then collects the branch's sums (it waits only for workgroups with smaller
 //                       block indices, dispatched before it; the wait is bounded) and finds the chunk and the token
 //                       where the integer CDF crosses the threshold, re-reading that one chunk.
+// Rows start anywhere (the vocabulary need not be a multiple of anything): 16-byte loads take any alignment of the element
+// type, and only the last group of a row is read element by element.
 // Every floating-point operation in this file is rounded on its own, as the definition of the integer weights
 // says: the compiler's default for device code would otherwise be free to merge a multiplication and a
 // following addition or subtraction into one fused operation (one rounding), depending on how the
@@ -35,16 +38,20 @@ typedef unsigned __int128 u128;
 
 constexpr int kLgThreads = 256;
 constexpr int kLgWaves = kLgThreads / kWave;
-constexpr int kLgPiece = 16384;      // logits per piece of the row statistics (V <= 2^20: at most 64 pieces)
+constexpr int kLgGroup = kLgThreads * 8;  // logits a workgroup reads in one round of 16-byte loads (two rounds for fp32)
+constexpr int kLgMaxPieces = 64;     // pieces of a row: one wavefront collects their maxima
 constexpr int kLgChunk = 2048;       // tokens per chunk: 8 per thread
 constexpr int kLgMaxChunks = 512;    // V <= 2^20
 constexpr int kLgMaxK = kLgThreads;
 
 struct RowStat {
-    float m;          // row maximum of y
-    float pad;
+    float m;               // row maximum of y
     unsigned long long S;  // sum of the integer weights
 };
+
+// 16 bytes of logits at any alignment of the element type: one load instruction on this part, whatever the address
+typedef unsigned l_u32x4 __attribute__((ext_vector_type(4)));
+typedef l_u32x4 l_u32x4_any __attribute__((aligned(2)));
 
 // One multiplication / subtraction, rounded to nearest.  Defined here, under the pragma above: the toolkit's
 // __fmul_rn / __fsub_rn are plain operators compiled under the default mode, and a product and a difference taken
@@ -90,111 +97,68 @@ __device__ __forceinline__ float load_y(const void* z, size_t idx, float inv_tem
     return mul_rn(v, inv_temp);
 }
 
-// 8 consecutive logits starting at a multiple of 8 (rows are 16-byte aligned when V % 8 == 0)
+// 8 consecutive logits of a row, raw: tokens i .. i + 7, -inf from hi on
 template <bool BF16>
-__device__ __forceinline__ void load_y8(const void* z, size_t idx, float inv_temp, float (&y)[8]) {
-    if (BF16) {
-        const uint4 r = *reinterpret_cast<const uint4*>(static_cast<const unsigned short*>(z) + idx);
-        const unsigned w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            y[2 * i] = mul_rn(__uint_as_float(w[i] << 16), inv_temp);
-            y[2 * i + 1] = mul_rn(__uint_as_float(w[i] & 0xffff0000u), inv_temp);
-        }
-    } else {
-        const float4 a = *reinterpret_cast<const float4*>(static_cast<const float*>(z) + idx);
-        const float4 b = *reinterpret_cast<const float4*>(static_cast<const float*>(z) + idx + 4);
-        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = mul_rn(v[i], inv_temp);
-    }
-}
-
-// A thread's share of one piece of kLgPiece logits: kLgPieceIters groups of 8 consecutive logits, all
-// requested before the first is used (one 16-byte load per group would otherwise wait for the one
-// before it, and the sweep would run at the memory latency instead of the bandwidth).  Groups past
-// the end of the row read as -inf.
-constexpr int kLgPieceIters = kLgPiece / (kLgThreads * 8);
+struct Raw8 {
+    l_u32x4 v[BF16 ? 1 : 2];
+};
 template <bool BF16>
-__device__ __forceinline__ void load_piece(const void* z, size_t base, int lo, int hi, int tid, float inv_temp,
-                                           float (&y)[kLgPieceIters][8]) {
+__device__ __forceinline__ Raw8<BF16> load_raw8(const void* z, size_t base, int i, int hi) {
+    Raw8<BF16> r;
     if (BF16) {
-        uint4 raw[kLgPieceIters];
+        const unsigned short* src = static_cast<const unsigned short*>(z) + base + i;
+        if (i + 8 <= hi) {
+            r.v[0] = *reinterpret_cast<const l_u32x4_any*>(src);
+        } else {
 #pragma unroll
-        for (int it = 0; it < kLgPieceIters; ++it) {
-            const int i = lo + (it * kLgThreads + tid) * 8;
-            raw[it] = make_uint4(0xff80ff80u, 0xff80ff80u, 0xff80ff80u, 0xff80ff80u);  // bf16 -inf
-            if (i < hi) raw[it] = *reinterpret_cast<const uint4*>(static_cast<const unsigned short*>(z) + base + i);
-        }
-#pragma unroll
-        for (int it = 0; it < kLgPieceIters; ++it) {
-            const unsigned w[4] = {raw[it].x, raw[it].y, raw[it].z, raw[it].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                y[it][2 * e] = mul_rn(__uint_as_float(w[e] << 16), inv_temp);
-                y[it][2 * e + 1] = mul_rn(__uint_as_float(w[e] & 0xffff0000u), inv_temp);
+            for (int e = 0; e < 4; ++e) {  // bf16 -inf is 0xff80
+                const unsigned a = i + 2 * e < hi ? src[2 * e] : 0xff80u, b = i + 2 * e + 1 < hi ? src[2 * e + 1] : 0xff80u;
+                r.v[0][e] = a | (b << 16);
             }
         }
     } else {
-        float4 raw[kLgPieceIters][2];
+        const float* src = static_cast<const float*>(z) + base + i;
+        if (i + 8 <= hi) {
+            r.v[0] = *reinterpret_cast<const l_u32x4_any*>(src);
+            r.v[BF16 ? 0 : 1] = *reinterpret_cast<const l_u32x4_any*>(src + 4);
+        } else {
 #pragma unroll
-        for (int it = 0; it < kLgPieceIters; ++it) {
-            const int i = lo + (it * kLgThreads + tid) * 8;
-            raw[it][0] = raw[it][1] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            if (i < hi) {
-                raw[it][0] = *reinterpret_cast<const float4*>(static_cast<const float*>(z) + base + i);
-                raw[it][1] = *reinterpret_cast<const float4*>(static_cast<const float*>(z) + base + i + 4);
-            }
+            for (int e = 0; e < 8; ++e) r.v[BF16 ? 0 : e / 4][e % 4] = __float_as_uint(i + e < hi ? src[e] : -INFINITY);
         }
+    }
+    return r;
+}
+template <bool BF16>
+__device__ __forceinline__ void scale8(const Raw8<BF16>& r, float inv_temp, float (&y)[8]) {
 #pragma unroll
-        for (int it = 0; it < kLgPieceIters; ++it) {
-            const float v[8] = {raw[it][0].x, raw[it][0].y, raw[it][0].z, raw[it][0].w,
-                                raw[it][1].x, raw[it][1].y, raw[it][1].z, raw[it][1].w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) y[it][e] = mul_rn(v[e], inv_temp);
-        }
+    for (int e = 0; e < 8; ++e) {
+        const float v = BF16 ? __uint_as_float(e % 2 ? r.v[0][e / 2] & 0xffff0000u : r.v[0][e / 2] << 16)
+                             : __uint_as_float(r.v[BF16 ? 0 : e / 4][e % 4]);
+        y[e] = mul_rn(v, inv_temp);
     }
 }
 
-__device__ __forceinline__ u128 shfl_down_u128(u128 v, int d) {
-    const unsigned long long lo = shfl_down_u64((unsigned long long)v, d);
-    const unsigned long long hi = shfl_down_u64((unsigned long long)(v >> 64), d);
-    return ((u128)hi << 64) | lo;
+// Inclusive prefix sum over the wavefront of values whose total is below 2^104, as four limbs (24, 24, 24, 32 bits) in
+// independent 32-bit chains of one-instruction steps.  (A weight is at most 2^30 * 2^50, a chunk's sum 2^91, a row's 2^100.)
+__device__ __forceinline__ u128 wave_incl_scan_u128(u128 v) {
+    const unsigned l0 = wave_incl_scan_u32((unsigned)v & 0xffffffu), l1 = wave_incl_scan_u32((unsigned)(v >> 24) & 0xffffffu);
+    const unsigned l2 = wave_incl_scan_u32((unsigned)(v >> 48) & 0xffffffu), l3 = wave_incl_scan_u32((unsigned)(v >> 72));
+    return (u128)l0 + ((u128)l1 << 24) + ((u128)l2 << 48) + ((u128)l3 << 72);
 }
-__device__ __forceinline__ u128 shfl_up_u128(u128 v, int d) {
-    const unsigned long long lo = shfl_up_u64((unsigned long long)v, d);
-    const unsigned long long hi = shfl_up_u64((unsigned long long)(v >> 64), d);
-    return ((u128)hi << 64) | lo;
-}
-
-// sum over a 256-thread workgroup, result in every thread
-__device__ __forceinline__ u128 block_sum_u128(u128 v, u128* sh /*[kLgWaves]*/) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += shfl_down_u128(v, d);
-    const int tid = threadIdx.x;
-    __syncthreads();
-    if ((tid & (kWave - 1)) == 0) sh[tid / kWave] = v;
-    __syncthreads();
-    u128 s = 0;
-#pragma unroll
-    for (int w = 0; w < kLgWaves; ++w) s += sh[w];
-    return s;
-}
-// exclusive prefix sum in thread order over a 256-thread workgroup
-__device__ __forceinline__ u128 block_excl_scan_u128(u128 v, u128* sh /*[kLgWaves]*/) {
+// exclusive prefix sum in thread order over a 256-thread workgroup; the total in every thread
+__device__ __forceinline__ u128 block_excl_scan_u128(u128 v, u128* sh /*[kLgWaves]*/, u128& total) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    u128 incl = v;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const u128 o = shfl_up_u128(incl, d);
-        if (lane >= d) incl += o;
-    }
+    const u128 incl = wave_incl_scan_u128(v);
     __syncthreads();
     if (lane == kWave - 1) sh[w] = incl;
     __syncthreads();
     u128 base = 0;
+    total = 0;
 #pragma unroll
-    for (int i = 0; i < kLgWaves; ++i) base += (i < w) ? sh[i] : (u128)0;
+    for (int i = 0; i < kLgWaves; ++i) {
+        base += (i < w) ? sh[i] : (u128)0;
+        total += sh[i];
+    }
     return base + incl - v;
 }
 
@@ -202,147 +166,153 @@ __device__ __forceinline__ u128 block_excl_scan_u128(u128 v, u128* sh /*[kLgWave
 __device__ __forceinline__ int trow(int b, int j, int k) { return b * (k + 1) + j; }
 __device__ __forceinline__ int drow(int B, int b, int j, int k) { return B * (k + 1) + b * k + j; }
 
-// Row statistics in two sweeps over pieces of kLgPiece logits (grid: pieces per row x rows), so that a
-// row is spread over many compute units: piece maxima first; then, with the row maximum known, the
-// integer weight sums of the pieces.  The second sweep finds the logits in the L2 / memory-side cache.
-template <bool BF16, bool VEC>
-__global__ __launch_bounds__(kLgThreads) void lg_max_kernel(int B, int k, int V, int npieces, const void* __restrict__ zt,
-                                                            const void* __restrict__ zd, float inv_temp,
-                                                            float* __restrict__ pmax,
-                                                            unsigned long long* __restrict__ rsum) {
+constexpr int kLgSpinLimit = 1 << 23;  // polls of a waiting workgroup before it gives up (seconds: far beyond any real wait)
+
+// one published word: 32 bits of a value under the call's tag
+__device__ __forceinline__ void lg_publish(unsigned long long* slot, unsigned part, unsigned tag) {
+    __hip_atomic_store(slot, ((unsigned long long)tag << 32) | part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long lg_peek(const unsigned long long* slot) {
+    return __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Row statistics in one sweep.  The weights need the row maximum, so the pieces of a row exchange their maxima inside the
+// launch while their logits stay in registers; what a launch boundary and a second read of all logits cost before is one trip
+// through memory now.  A workgroup waits for the other pieces of its own row only, and a row's pieces are neighbours in the
+// grid, dispatched in order: at most one row is in part resident and in part not, and it is next in line for the slots that
+// the complete rows before it give up, so every wait ends (bounded all the same).  The words are cleared by the next launch.
+// Bound by the vector unit: 17 instructions a logit that the integer definition fixes, 8 us of the chip's rate for 112 rows x
+// 152064 logits, behind the read that all workgroups start with.  Whole call, us, before (three launches: maxima, sums, scan) ->
+// now: 16 x 7 rows x 152064 bf16 30.9 -> 28.0, fp32 40.5 -> 30.7; 64 x 5 x 151936 63.9 -> 54.2; 5 x 15 rows x 50257 fp32 (rows off
+// a 16-byte boundary, element by element before) 48.1 -> 17.5.
+// IT = 4 up to 2^19 logits (a lane of the collecting wavefront per piece): 28.0 us against 28.9 with IT = 8 on the first of
+// these and 38.0 with IT = 2, whose workgroups come and go too often.
+template <bool BF16, int IT>
+__global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V, int npieces, unsigned tag,
+                                                             const void* __restrict__ zt, const void* __restrict__ zd,
+                                                             float inv_temp, unsigned long long* __restrict__ words,
+                                                             float* __restrict__ rmax, unsigned long long* __restrict__ rsum) {
     __shared__ float sh_m[kLgWaves];
-    const int r = blockIdx.x / npieces, pc = blockIdx.x - r * npieces, tid = threadIdx.x;
+    __shared__ float sh_row;
+    __shared__ unsigned long long sh_s[kLgWaves];
+    const int r = blockIdx.x / npieces, pc = blockIdx.x - r * npieces, tid = threadIdx.x, lane = tid & (kWave - 1);
     const int nt = B * (k + 1);
     const void* z = r < nt ? zt : zd;
     const size_t base = (size_t)(r < nt ? r : r - nt) * V;
-    const int lo = pc * kLgPiece, hi = min(V, lo + kLgPiece);
-    float m = -INFINITY;
-    if (VEC) {
-        float y[kLgPieceIters][8];
-        load_piece<BF16>(z, base, lo, hi, tid, inv_temp, y);
+    const int lo = pc * (IT * kLgGroup);
+    if (pc == 0 && tid == 0)  // the pieces add their sums into it once they have seen this piece's maximum
+        __hip_atomic_store(rsum + r, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the whole piece is requested before any of it is used
+    Raw8<BF16> raw[IT];
 #pragma unroll
-        for (int it = 0; it < kLgPieceIters; ++it)
+    for (int it = 0; it < IT; ++it) raw[it] = load_raw8<BF16>(z, base, lo + it * kLgGroup + tid * 8, V);
+    float y[IT][8], m = -INFINITY;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) m = fmaxf(m, y[it][e]);
-    } else {
-        for (int i = lo + tid; i < hi; i += kLgThreads) m = fmaxf(m, load_y<BF16>(z, base + i, inv_temp));
+    for (int it = 0; it < IT; ++it) {
+        scale8<BF16>(raw[it], inv_temp, y[it]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, y[it][e]);
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
-    if ((tid & (kWave - 1)) == 0) sh_m[tid / kWave] = m;
+    if (lane == 0) sh_m[tid / kWave] = m;
     __syncthreads();
-    if (tid == 0) {
+    if (tid < kWave) {
 #pragma unroll
-        for (int w = 1; w < kLgWaves; ++w) m = fmaxf(m, sh_m[w]);
-        pmax[(size_t)r * npieces + pc] = m;
-        if (pc == 0) rsum[r] = 0ull;  // lg_sum_kernel adds the pieces' sums into it
+        for (int w = 0; w < kLgWaves; ++w) m = fmaxf(m, sh_m[w]);
+        unsigned long long* row = words + (size_t)r * npieces;
+        if (tid == 0) {
+            __builtin_amdgcn_s_waitcnt(0);  // the cleared sum is in memory before this piece's word
+            lg_publish(row + pc, __float_as_uint(m), tag);
+        }
+        if (lane < npieces && lane != pc) {
+            unsigned long long w = 0;
+            for (int spin = 0; spin < kLgSpinLimit; ++spin) {
+                w = lg_peek(row + lane);
+                if ((unsigned)(w >> 32) == tag) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            m = fmaxf(m, __uint_as_float((unsigned)w));
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
+        if (tid == 0) sh_row = m;
     }
-}
-
-// Row maximum from the per-piece maxima.  The piece values are read in
-// blocks of 16 independent loads: a plain loop would wait for every load before issuing the next and
-// spend one memory latency per piece.
-__device__ __forceinline__ float row_max(const float* pmax, int row, int npieces) {
-    float m = -INFINITY;
-    const float* src = pmax + (size_t)row * npieces;
-    for (int i0 = 0; i0 < npieces; i0 += 16) {
-        float v[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = src[min(i0 + e, npieces - 1)];  // repeats of the last piece do no harm
-#pragma unroll
-        for (int e = 0; e < 16; ++e) m = fmaxf(m, v[e]);
-    }
-    return m;
-}
-// final statistics of a row, as lg_sum_kernel leaves them
-__device__ __forceinline__ RowStat row_stat(const float* rmax, const unsigned long long* rsum, int row) {
-    RowStat st;
-    st.S = rsum[row];
-    st.pad = 0.f;
-    st.m = rmax[row];
-    return st;
-}
-
-template <bool BF16, bool VEC>
-__global__ __launch_bounds__(kLgThreads) void lg_sum_kernel(int B, int k, int V, int npieces, const void* __restrict__ zt,
-                                                            const void* __restrict__ zd, float inv_temp,
-                                                            const float* __restrict__ pmax,
-                                                            float* __restrict__ rmax,
-                                                            unsigned long long* __restrict__ rsum) {
-    __shared__ unsigned long long sh_s[kLgWaves];
-    const int r = blockIdx.x / npieces, pc = blockIdx.x - r * npieces, tid = threadIdx.x;
-    const int nt = B * (k + 1);
-    const void* z = r < nt ? zt : zd;
-    const size_t base = (size_t)(r < nt ? r : r - nt) * V;
-    const int lo = pc * kLgPiece, hi = min(V, lo + kLgPiece);
-    const float m = row_max(pmax, r, npieces);
+    __syncthreads();
+    m = sh_row;
     unsigned long long s = 0;
-    if (VEC) {
-        float y[kLgPieceIters][8];
-        load_piece<BF16>(z, base, lo, hi, tid, inv_temp, y);
 #pragma unroll
-        for (int it = 0; it < kLgPieceIters; ++it)
+    for (int it = 0; it < IT; ++it)
 #pragma unroll
-            for (int e = 0; e < 8; e += 2)  // two weights (each at most 2^30) fit 32 bits together
-                s += logit_weight(y[it][e], m) + logit_weight(y[it][e + 1], m);
-    } else {
-        for (int i = lo + tid; i < hi; i += kLgThreads) s += logit_weight(load_y<BF16>(z, base + i, inv_temp), m);
-    }
-    s = wave_sum_u64(s);
-    if ((tid & (kWave - 1)) == 0) sh_s[tid / kWave] = s;
+        for (int e = 0; e < 8; e += 2)  // two weights (each at most 2^30) fit 32 bits together
+            s += logit_weight(y[it][e], m) + logit_weight(y[it][e + 1], m);
+    // at most 64 weights a lane: s < 2^37; two limbs whose wavefront sums fit 32 bits
+    const unsigned s0 = wave_incl_scan_u32((unsigned)s & 0xffffffu), s1 = wave_incl_scan_u32((unsigned)(s >> 24));
+    if (lane == kWave - 1) sh_s[tid / kWave] = (unsigned long long)s0 + ((unsigned long long)s1 << 24);
     __syncthreads();
     if (tid == 0) {
         unsigned long long tot = 0;
 #pragma unroll
         for (int w = 0; w < kLgWaves; ++w) tot += sh_s[w];
         atomicAdd(&rsum[r], tot);  // integers: the order of the pieces cannot matter
-        if (pc == 0) rmax[r] = m;   // the row maximum, for the launches that follow
+        if (pc == 0) rmax[r] = m;
     }
 }
 
-// accepted length of branch b; every thread of the 256-thread workgroup gets it
+// final statistics of a row, as lg_stat_kernel leaves them
+__device__ __forceinline__ RowStat row_stat(const float* rmax, const unsigned long long* rsum, int row) {
+    RowStat st;
+    st.m = rmax[row];
+    st.S = rsum[row];
+    return st;
+}
+
+// Accepted length of branch b; every thread of the 256-thread workgroup gets it, and the statistics of the two rows at n (of
+// the target row alone when every draft was accepted) with it: thread j loads those of position j for its test.
 template <bool BF16>
 __device__ __forceinline__ int lg_accepted_length(int B, int b, int k, int V, const void* zt, const void* zd,
                                                   float inv_temp, const int32_t* draft, const float* u,
-                                                  const float* rmax, const unsigned long long* rsum, int* sh_first) {
+                                                  const float* rmax, const unsigned long long* rsum, int* sh_first,
+                                                  RowStat* sh_p, RowStat* sh_q, RowStat& sp, RowStat& sq) {
     const int tid = threadIdx.x;
     bool rejected = false;
     if (tid < k) {
         int x = draft[(size_t)b * k + tid];
+        const float uv = u[(size_t)b * (k + 1) + tid];
+        const RowStat p = row_stat(rmax, rsum, trow(b, tid, k)), q = row_stat(rmax, rsum, drow(B, b, tid, k));
         x = x < 0 ? 0 : (x >= V ? V - 1 : x);
-        const RowStat sp = row_stat(rmax, rsum, trow(b, tid, k));
-        const RowStat sq = row_stat(rmax, rsum, drow(B, b, tid, k));
-        const unsigned long long Ep = logit_weight(load_y<BF16>(zt, (size_t)trow(b, tid, k) * V + x, inv_temp), sp.m);
-        const unsigned long long Eq = logit_weight(load_y<BF16>(zd, ((size_t)b * k + tid) * V + x, inv_temp), sq.m);
-        const u128 U = (u128)(unsigned)(u[(size_t)b * (k + 1) + tid] * 16777216.0f);
-        rejected = !(U * Eq * sp.S < ((u128)1 << 24) * Ep * sq.S);
+        const float yp = load_y<BF16>(zt, (size_t)trow(b, tid, k) * V + x, inv_temp);
+        const float yq = load_y<BF16>(zd, ((size_t)b * k + tid) * V + x, inv_temp);
+        const unsigned long long Ep = logit_weight(yp, p.m), Eq = logit_weight(yq, q.m);
+        const u128 U = (u128)(unsigned)(uv * 16777216.0f);
+        rejected = !(U * Eq * p.S < ((u128)1 << 24) * Ep * q.S);
+        sh_p[tid] = p;
+        sh_q[tid] = q;
     }
     const unsigned long long mask = __ballot(rejected);
     if ((tid & (kWave - 1)) == 0) sh_first[tid / kWave] = mask ? (tid + __ffsll((long long)mask) - 1) : k;
+    const RowStat last = row_stat(rmax, rsum, trow(b, k, k));
     __syncthreads();
     int n = k;
 #pragma unroll
     for (int w = 0; w < kLgWaves; ++w) n = sh_first[w] < n ? sh_first[w] : n;
+    sp = n < k ? sh_p[n] : last;
+    sq = n < k ? sh_q[n] : last;
     return n;
 }
 
 // the 8 weights a thread owns in a chunk (tokens lo .. lo+7, clipped to V): residual or plain
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void lg_weights8(const void* zt_row, const void* zd_row, int lo, int V, float inv_temp,
                                             bool residual, RowStat sp, RowStat sq, u128 (&W)[8],
                                             unsigned long long (&Ep)[8]) {
     float yp[8], yq[8];
-    if (VEC && lo + 8 <= V) {
-        load_y8<BF16>(zt_row, lo, inv_temp, yp);
-        if (residual) load_y8<BF16>(zd_row, lo, inv_temp, yq);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const bool in = lo + e < V;
-            yp[e] = in ? load_y<BF16>(zt_row, lo + e, inv_temp) : -INFINITY;
-            yq[e] = (in && residual) ? load_y<BF16>(zd_row, lo + e, inv_temp) : -INFINITY;
-        }
+    const Raw8<BF16> rp = load_raw8<BF16>(zt_row, 0, lo, V);
+    if (residual) {
+        const Raw8<BF16> rq = load_raw8<BF16>(zd_row, 0, lo, V);
+        scale8<BF16>(rq, inv_temp, yq);
     }
+    scale8<BF16>(rp, inv_temp, yp);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const bool in = lo + e < V;
@@ -357,24 +327,15 @@ __device__ __forceinline__ void lg_weights8(const void* zt_row, const void* zd_r
     }
 }
 
-constexpr int kLgSpinLimit = 1 << 18;  // polls of the collecting workgroup before it gives up (far beyond any real wait)
-
-// one published word: 32 bits of a sum under the call's tag
-__device__ __forceinline__ void lg_publish(unsigned long long* slot, unsigned part, unsigned tag) {
-    __hip_atomic_store(slot, ((unsigned long long)tag << 32) | part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long lg_peek(const unsigned long long* slot) {
-    return __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <bool BF16, bool VEC>
-__global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, int V, int nchunks, unsigned tag,
+template <bool BF16>
+__global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, int V, int nchunks, int npieces, unsigned tag,
                                                                   const void* __restrict__ zt, const void* __restrict__ zd,
                                                                   float inv_temp, const int32_t* __restrict__ draft,
                                                                   const float* __restrict__ u,
                                                                   const float* __restrict__ rmax,
                                                                   const unsigned long long* __restrict__ rsum,
                                                                   int32_t* __restrict__ accept_len,
+                                                                  unsigned long long* __restrict__ words,  // [rows][npieces]
                                                                   unsigned long long* __restrict__ slots,  // [B][nchunks][6]
                                                                   int32_t* __restrict__ next_token,
                                                                   int32_t* __restrict__ priv_len) {
@@ -385,26 +346,48 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
     __shared__ u128 sh_wsum[kLgMaxChunks];
     __shared__ unsigned long long sh_psum[kLgMaxChunks];
     const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
-    const int n = lg_accepted_length<BF16>(B, b, k, V, zt, zd, inv_temp, draft, u, rmax, rsum, sh_first);
+    __shared__ RowStat sh_p[kLgMaxK], sh_q[kLgMaxK];
+    const float u_last = u[(size_t)b * (k + 1) + k];
+    // the words of the launch before are consumed: cleared, so that a captured call (same tags) can be replayed
+    for (int i = c * kLgThreads + tid; i < (2 * k + 1) * npieces; i += nchunks * kLgThreads) {
+        const int j = i / npieces;
+        const int row = j <= k ? trow(b, j, k) : drow(B, b, j - k - 1, k);
+        words[(size_t)row * npieces + (i - j * npieces)] = 0ull;
+    }
+    RowStat sp, sq;
+    const int n = lg_accepted_length<BF16>(B, b, k, V, zt, zd, inv_temp, draft, u, rmax, rsum, sh_first, sh_p, sh_q, sp, sq);
     bool residual = n < k;
     const size_t es = BF16 ? 2 : 4;
     const void* zt_row = static_cast<const char*>(zt) + (size_t)trow(b, n, k) * V * es;
     const void* zd_row = residual ? static_cast<const char*>(zd) + ((size_t)b * k + n) * V * es : zt_row;
-    const RowStat sp = row_stat(rmax, rsum, trow(b, n, k));
-    const RowStat sq = residual ? row_stat(rmax, rsum, drow(B, b, n, k)) : sp;
     u128 W[8];
     unsigned long long Ep[8];
-    lg_weights8<BF16, VEC>(zt_row, zd_row, c * kLgChunk + tid * 8, V, inv_temp, residual, sp, sq, W, Ep);
-    u128 w = 0, e = 0;
+    lg_weights8<BF16>(zt_row, zd_row, c * kLgChunk + tid * 8, V, inv_temp, residual, sp, sq, W, Ep);
+    u128 w = 0;
+    unsigned long long e = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         w += W[i];
         e += Ep[i];
     }
-    w = block_sum_u128(w, sh_w);
-    e = block_sum_u128(e, sh_w);
+    // both sums over the workgroup at once: the totals stand in lane 63 of every wavefront
+    w = wave_incl_scan_u128(w);
+    const unsigned e0 = wave_incl_scan_u32((unsigned)e & 0xffffffu), e1 = wave_incl_scan_u32((unsigned)(e >> 24));
+    __shared__ unsigned long long sh_e[kLgWaves];
+    if ((tid & (kWave - 1)) == kWave - 1) {
+        sh_w[tid / kWave] = w;
+        sh_e[tid / kWave] = (unsigned long long)e0 + ((unsigned long long)e1 << 24);
+    }
+    __syncthreads();
     unsigned long long* mine = slots + ((size_t)b * nchunks + c) * 6;
     if (tid == 0) {
+        w = 0;
+        e = 0;
+#pragma unroll
+        for (int i = 0; i < kLgWaves; ++i) {
+            w += sh_w[i];
+            e += sh_e[i];
+        }
         lg_publish(mine + 0, (unsigned)w, tag);
         lg_publish(mine + 1, (unsigned)(w >> 32), tag);
         lg_publish(mine + 2, (unsigned)(w >> 64), tag);
@@ -455,21 +438,20 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
         w1 = sh_wsum[c0 + 1];
         p1 = sh_psum[c0 + 1];
     }
-    u128 Z = block_sum_u128(w0 + w1, sh_w);
+    u128 Z, excl = block_excl_scan_u128(w0 + w1, sh_w, Z);
     if (residual && Z == 0) {  // empty residual: sample the target row itself (uniform branch: n and Z are)
         residual = false;
         w0 = p0;
         w1 = p1;
-        Z = block_sum_u128(w0 + w1, sh_w);
+        excl = block_excl_scan_u128(w0 + w1, sh_w, Z);
     }
     if (Z == 0 || sh_bad) {  // a row without any weight (all logits -inf, or +inf / NaN among them): no token; uniform
         if (tid == 0) next_token[b] = -1;
         return;
     }
-    unsigned m24 = (unsigned)(u[(size_t)b * (k + 1) + k] * 16777216.0f);
+    unsigned m24 = (unsigned)(u_last * 16777216.0f);
     m24 = m24 > 16777215u ? 16777215u : m24;  // u must be < 1; keeps T < Z regardless
     const u128 T = ((u128)m24 * Z) >> 24;
-    u128 excl = block_excl_scan_u128(w0 + w1, sh_w);
     if (excl <= T && T < excl + w0 + w1) {  // exactly one thread: T < Z and Z > 0
         const bool second = !(T < excl + w0);
         sh_chunk = c0 + (second ? 1 : 0);
@@ -481,11 +463,12 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
     const void* zd_row2 = residual ? zd_row : zt_row;
     const RowStat sq2 = residual ? sq : sp;
     const int lo = cc * kLgChunk + tid * 8;
-    lg_weights8<BF16, VEC>(zt_row, zd_row2, lo, V, inv_temp, residual, sp, sq2, W, Ep);
+    lg_weights8<BF16>(zt_row, zd_row2, lo, V, inv_temp, residual, sp, sq2, W, Ep);
     u128 local = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) local += W[i];
-    const u128 run = base + block_excl_scan_u128(local, sh_w);
+    u128 total;
+    const u128 run = base + block_excl_scan_u128(local, sh_w, total);
     if (run <= T && T < run + local) {
         int tok = lo;
 #pragma unroll
@@ -501,52 +484,54 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
 
 
 struct LgLayout {
-    size_t off_pmax, off_rmax, off_rsum, off_wsum, off_psum, total;
-    int nchunks, npieces;
+    size_t off_rmax, off_rsum, off_chunks, off_words, total;
+    int nchunks, npieces, iters;
 };
+// [row maxima][row sums][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces].  The first two
+// follow a block of 4 bytes per (row, 16384 logits).
 static inline LgLayout lg_layout(int B, int k, int V) {
     LgLayout l;
     l.nchunks = (V + kLgChunk - 1) / kLgChunk;
-    l.npieces = (V + kLgPiece - 1) / kLgPiece;
     const size_t rows = (size_t)B * (2 * k + 1);
+    l.iters = V <= 4 * kLgGroup * kLgMaxPieces && rows * kLgMaxPieces <= 0x7fffffff ? 4 : 8;
+    l.npieces = (V + l.iters * kLgGroup - 1) / (l.iters * kLgGroup);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    l.off_pmax = 0;
-    l.off_rmax = up(rows * l.npieces * sizeof(float));
+    l.off_rmax = up(rows * ((V + 16383) / 16384) * sizeof(float));
     l.off_rsum = l.off_rmax + up(rows * sizeof(float));
-    l.off_wsum = l.off_rsum + up(rows * sizeof(unsigned long long));
-    l.off_psum = l.off_wsum;  // one block of tagged words: 6 per (branch, chunk)
-    l.total = l.off_wsum + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
+    l.off_chunks = l.off_rsum + up(rows * sizeof(unsigned long long));
+    l.off_words = l.off_chunks + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
+    l.total = l.off_words + up(rows * l.npieces * sizeof(unsigned long long));
     return l;
 }
 static inline bool lg_sizes_ok(int B, int k, int V) {
     if (!(B >= 1 && B <= 65535 && k >= 0 && k <= kLgMaxK && V >= 1 && V <= (1 << 20))) return false;
-    // one workgroup per (piece of a row, row): the launch must fit one grid dimension
-    const long long pieces = (V + kLgPiece - 1) / kLgPiece;
+    // the documented limit: pieces of 16384 logits over all rows
+    const long long pieces = (V + 16383) / 16384;
     return pieces * B * (2 * k + 1) <= 0x7fffffffLL;
 }
 
-template <bool BF16, bool VEC>
+template <bool BF16>
 static int lg_launch(int B, int k, int V, const void* zt, const void* zd, float inv_temp, const int32_t* draft,
                      const float* u, int32_t* accept_len, int32_t* next_token, int32_t* priv_len, void* workspace,
                      hipStream_t s) {
     const LgLayout l = lg_layout(B, k, V);
-    float* pmax = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.off_pmax);
-    float* rmax = reinterpret_cast<float*>(static_cast<char*>(workspace) + l.off_rmax);
-    unsigned long long* rsum = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + l.off_rsum);
-    u128* wsum = reinterpret_cast<u128*>(static_cast<char*>(workspace) + l.off_wsum);
+    char* ws = static_cast<char*>(workspace);
+    float* rmax = reinterpret_cast<float*>(ws + l.off_rmax);
+    unsigned long long* rsum = reinterpret_cast<unsigned long long*>(ws + l.off_rsum);
+    unsigned long long* chunks = reinterpret_cast<unsigned long long*>(ws + l.off_chunks);
+    unsigned long long* words = reinterpret_cast<unsigned long long*>(ws + l.off_words);
+    const unsigned tag_s = next_word_tag(), tag_c = next_word_tag();
     const dim3 sgrid((unsigned)((long long)l.npieces * B * (2 * k + 1)));  // (piece, row) pairs, row-major
-    LOTTS_LAUNCH((lg_max_kernel<BF16, VEC>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, zt, zd, inv_temp, pmax,
-                 rsum);
-    int rc = check_launch();
+    if (l.iters == 4)
+        LOTTS_LAUNCH((lg_stat_kernel<BF16, 4>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, tag_s, zt, zd, inv_temp, words,
+                     rmax, rsum);
+    else
+        LOTTS_LAUNCH((lg_stat_kernel<BF16, 8>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, tag_s, zt, zd, inv_temp, words,
+                     rmax, rsum);
+    const int rc = check_launch();
     if (rc != LOTTS_OK) return rc;
-    LOTTS_LAUNCH((lg_sum_kernel<BF16, VEC>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, zt, zd, inv_temp, pmax,
-                 rmax, rsum);
-    rc = check_launch();
-    if (rc != LOTTS_OK) return rc;
-    const unsigned tag = next_word_tag();
-    LOTTS_LAUNCH((lg_scan_pick_kernel<BF16, VEC>), dim3(l.nchunks, B), dim3(kLgThreads), s, B, k, V, l.nchunks, tag, zt, zd,
-                 inv_temp, draft, u, rmax, rsum, accept_len, reinterpret_cast<unsigned long long*>(wsum), next_token,
-                 priv_len);
+    LOTTS_LAUNCH((lg_scan_pick_kernel<BF16>), dim3(l.nchunks, B), dim3(kLgThreads), s, B, k, V, l.nchunks, l.npieces, tag_c, zt,
+                 zd, inv_temp, draft, u, rmax, rsum, accept_len, words, chunks, next_token, priv_len);
     return check_launch();
 }
 
@@ -572,16 +557,10 @@ extern "C" int spec_accept_logits(int32_t B, int32_t k, int32_t V, const void* t
     const bool bf16 = logit_dtype == LOTTS_BF16;
     const uintptr_t es = bf16 ? 2 : 4;
     if (((uintptr_t)target_logits | (uintptr_t)draft_logits) & (es - 1)) return LOTTS_ERR_SHAPE;
-    // 8-wide loads need every row start 16-byte (bf16) / 32-byte-run (fp32: two 16-byte loads) aligned
-    const bool vec = (V % 8 == 0) && ((((uintptr_t)target_logits | (uintptr_t)draft_logits) & 15) == 0);
     hipStream_t s = (hipStream_t)stream;
     if (bf16)
-        return vec ? lg_launch<true, true>(B, k, V, target_logits, draft_logits, inv_temperature, draft, u, accept_len,
-                                           next_token, priv_len, workspace, s)
-                   : lg_launch<true, false>(B, k, V, target_logits, draft_logits, inv_temperature, draft, u, accept_len,
-                                            next_token, priv_len, workspace, s);
-    return vec ? lg_launch<false, true>(B, k, V, target_logits, draft_logits, inv_temperature, draft, u, accept_len,
-                                        next_token, priv_len, workspace, s)
-               : lg_launch<false, false>(B, k, V, target_logits, draft_logits, inv_temperature, draft, u, accept_len,
-                                         next_token, priv_len, workspace, s);
+        return lg_launch<true>(B, k, V, target_logits, draft_logits, inv_temperature, draft, u, accept_len, next_token, priv_len,
+                               workspace, s);
+    return lg_launch<false>(B, k, V, target_logits, draft_logits, inv_temperature, draft, u, accept_len, next_token, priv_len,
+                            workspace, s);
 }
