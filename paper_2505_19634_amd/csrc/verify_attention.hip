@@ -36,7 +36,7 @@
 //   attn_merge_kernel     second launch, where prefix items or several row groups add partials of their own and a row has many
 //       of them, and for the smallest contexts.
 // fp32 path: attn_f32_kernel, plain fp32 VALU arithmetic, one workgroup per output row; it
-// exists for exactness checks on small fp32 problems, not for speed.
+// exists for exactness checks on small fp32 problems.
 // Two entry points share all of this: verify_attention (the caller brings the workspace) and
 // verify_attention_noalloc (arrival cells and partials in a static device array of this file).
 #include <atomic>
@@ -872,15 +872,27 @@ __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(const AttnPara
 
 // ---------------------------------------------------------------------------------------------
 // fp32 path: one workgroup per output row, fp32 arithmetic throughout (no matrix cores).
-// Wavefront w takes keys w, w+4, ...; lanes split the head dimension; flash-style running state
-// per wavefront, merged through LDS.
+// A key row is D / 4 lanes of 16 bytes, so one load of a wavefront covers KPL = 256 / D keys; a wavefront takes chunks of
+// 4 * KPL keys (every fourth chunk is its own), K and V of a chunk requested together, and keeps a flash-style running state
+// per group of D / 4 lanes -- the groups' and the wavefronts' states meet at the end.  Bound by memory latency at the sizes
+// this path exists for: with one key of 4 bytes a lane at a time, a chain of two loads, six shuffles and two exponentials per
+// key, 2 branches x 4 heads x 96 keys took 13.4 us; in chunks it takes 5.3.
 // ---------------------------------------------------------------------------------------------
+typedef u32x4 u32x4_any __attribute__((aligned(4)));  // fp32 rows start at any multiple of 4 bytes
+__device__ __forceinline__ float4 load_f4_any(const float* p) {
+    const u32x4 u = *reinterpret_cast<const u32x4_any*>(p);
+    return make_float4(__uint_as_float(u[0]), __uint_as_float(u[1]), __uint_as_float(u[2]), __uint_as_float(u[3]));
+}
 template <int D>
 __global__ __launch_bounds__(kAttnThreads) void attn_f32_kernel(const AttnParams prm) {
-    constexpr int EPL = D / kWave;  // head-dim elements per lane
-    __shared__ float sh_acc[kAttnWaves][D];
+    constexpr int LPK = D / 4;         // lanes per key row
+    constexpr int KPL = kWave / LPK;   // keys per load instruction
+    constexpr int NJ = 4;              // load instructions per chunk and operand
+    constexpr int CHUNK = NJ * KPL;
+    __shared__ __attribute__((aligned(16))) float sh_acc[kAttnWaves][D];
     __shared__ float sh_ml[kAttnWaves][2];
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
+    const int grp = lane / LPK, c4 = lane % LPK;
     const long long row = blockIdx.x;
     const int h = (int)(row % prm.Hq);
     const long long br = row / prm.Hq;
@@ -891,47 +903,60 @@ __global__ __launch_bounds__(kAttnThreads) void attn_f32_kernel(const AttnParams
     const int n_priv = L - prm.k + r;
     const int n = prm.P + n_priv;
     const float scale = prm.scale_log2 * 0.69314718055994530942f;  // back to the natural-log scale
-    const float* qp = (const float*)prm.Q + (long long)b * prm.q_stride_b + (long long)r * prm.q_stride_r +
-                      (long long)h * prm.q_stride_h;
-    float qv[EPL], acc[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        qv[e] = qp[lane + e * kWave];
-        acc[e] = 0.f;
-    }
+    const float4 qv = load_f4_any((const float*)prm.Q + (long long)b * prm.q_stride_b + (long long)r * prm.q_stride_r +
+                                  (long long)h * prm.q_stride_h + c4 * 4);
+    const long long pre = (long long)kvh * prm.kpre_stride_h + c4 * 4;
+    const long long prv = (long long)b * prm.kpriv_stride_b + (long long)kvh * prm.kpriv_stride_h + c4 * 4;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float m = -INFINITY, l = 0.f;
-    for (int j = wave; j < n; j += kAttnWaves) {
-        const float *kp, *vp;
-        if (j < prm.P) {
-            const long long off = (long long)kvh * prm.kpre_stride_h + (long long)j * prm.kpre_stride_t;
-            kp = (const float*)prm.Kpre + off;
-            vp = (const float*)prm.Vpre + off;
-        } else {
-            const long long off = (long long)b * prm.kpriv_stride_b + (long long)kvh * prm.kpriv_stride_h +
-                                  (long long)(j - prm.P) * prm.kpriv_stride_t;
-            kp = (const float*)prm.Kpriv + off;
-            vp = (const float*)prm.Vpriv + off;
+    for (int j0 = wave * CHUNK; j0 < n; j0 += kAttnWaves * CHUNK) {
+        float4 kv[NJ], vv[NJ];
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) {
+            int j = j0 + i * KPL + grp;
+            j = j < n ? j : n - 1;  // keys past the end re-read the last one; masked below
+            const bool prefix = j < prm.P;
+            const long long off = prefix ? pre + (long long)j * prm.kpre_stride_t : prv + (long long)(j - prm.P) * prm.kpriv_stride_t;
+            kv[i] = load_f4_any((const float*)(prefix ? prm.Kpre : prm.Kpriv) + off);
+            vv[i] = load_f4_any((const float*)(prefix ? prm.Vpre : prm.Vpriv) + off);
         }
-        float s = 0.f;
+        float s[NJ], mx = m;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) s += qv[e] * kp[lane + e * kWave];
+        for (int i = 0; i < NJ; ++i) {
+            s[i] = qv.x * kv[i].x + qv.y * kv[i].y + qv.z * kv[i].z + qv.w * kv[i].w;
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) s += shfl_xor_f(s, d);
-        s *= scale;
-        const float m_new = fmaxf(m, s);
-        const float alpha = expf(m - m_new);
-        const float pv = expf(s - m_new);
-        l = l * alpha + pv;
-        m = m_new;
+            for (int d = LPK / 2; d >= 1; d >>= 1) s[i] += shfl_xor_f(s[i], d);
+            s[i] = j0 + i * KPL + grp < n ? s[i] * scale : -INFINITY;
+            mx = fmaxf(mx, s[i]);
+        }
+        if (mx == -INFINITY) continue;  // this group has seen no key yet
+        const float alpha = expf(m - mx);
+        l *= alpha;
+        acc.x *= alpha; acc.y *= alpha; acc.z *= alpha; acc.w *= alpha;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = acc[e] * alpha + pv * vp[lane + e * kWave];
+        for (int i = 0; i < NJ; ++i) {
+            const float pv = expf(s[i] - mx);
+            l += pv;
+            acc.x += pv * vv[i].x; acc.y += pv * vv[i].y; acc.z += pv * vv[i].z; acc.w += pv * vv[i].w;
+        }
+        m = mx;
+    }
+    // the wavefront's groups of lanes
+#pragma unroll
+    for (int d = LPK; d < kWave; d <<= 1) {
+        const float mo = shfl_xor_f(m, d), lo = shfl_xor_f(l, d);
+        const float4 ao = make_float4(shfl_xor_f(acc.x, d), shfl_xor_f(acc.y, d), shfl_xor_f(acc.z, d), shfl_xor_f(acc.w, d));
+        const float M = fmaxf(m, mo);
+        const float wa = m == -INFINITY ? 0.f : expf(m - M), wb = mo == -INFINITY ? 0.f : expf(mo - M);
+        l = l * wa + lo * wb;
+        acc.x = acc.x * wa + ao.x * wb; acc.y = acc.y * wa + ao.y * wb; acc.z = acc.z * wa + ao.z * wb; acc.w = acc.w * wa + ao.w * wb;
+        m = M;
     }
     if (lane == 0) {
         sh_ml[wave][0] = m;
         sh_ml[wave][1] = l;
     }
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) sh_acc[wave][lane + e * kWave] = acc[e];
+    if (grp == 0) *reinterpret_cast<float4*>(&sh_acc[wave][c4 * 4]) = acc;
     __syncthreads();
     if (tid < D) {
         float M = -INFINITY;
