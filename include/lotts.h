@@ -147,7 +147,7 @@ size_t spec_accept_workspace_bytes(int32_t B, int32_t k, int32_t V);
  *   accept_len [B] int32 out, in [0, k];  next_token [B] int32 out, in [0, V) or -1
  *   workspace: >= spec_accept_workspace_bytes(B, k, V), 8-byte aligned, any contents (what the kernels
  *       exchange through it is validated by a tag that differs from call to call)
- * One launch when V is a multiple of 4, at most 2^18, and the rows are 16-byte aligned; two otherwise.
+ * One launch when V is at most 2^18; two otherwise.
  */
 int spec_accept(int32_t B, int32_t k, int32_t V, const float *p, const float *q, const int32_t *draft,
                 const float *u, int32_t *accept_len, int32_t *next_token, void *workspace,
@@ -278,8 +278,7 @@ int skinny_gemm(int32_t M, int32_t N, int32_t K, const void *X, int64_t ldx, con
  *       order (HOST array of at least max_launches floats).  Switches the timer off.
  * The order of launches inside one call: verify_attention 1 (2 -- attention, then merge -- when the partials
  * of a row are many and come from several row groups or from a long prefix, or when at most four (KV
- * head, branch) pairs share contexts of up to 4096 tokens); spec_accept 1 (2 -- scan, pick -- when V is not a multiple of 4, beyond
- * 2^18, or the rows are not 16-byte aligned); spec_accept_logits 2 (row
+ * head, branch) pairs share contexts of up to 4096 tokens); spec_accept 1 (2 -- scan, pick -- when V is beyond 2^18); spec_accept_logits 2 (row
  * statistics, scan and pick); majority_vote 1; confidence_vote 1; skinny_gemm 1 (2 when K is split: GEMM, reduce).
  */
 int lotts_timer_start(int32_t max_launches);

@@ -16,7 +16,7 @@
 //       row p_n.  One read of the stop row(s) -- the only
 //       V-sized traffic -- and one launch: at these sizes the pass is bound by launch and memory
 //       latency, not by bandwidth.
-//   accept_scan_kernel + accept_pick_kernel  (V not a multiple of 4, unaligned rows, V > 2^18):
+//   accept_scan_kernel + accept_pick_kernel  (V > 2^18):
 //       grid (chunks, B) writes chunk sums; a second launch (B) picks.
 // All sums are 64-bit integers, so the result is independent of reduction order and equals a
 // sequential scan bit for bit.
@@ -306,30 +306,17 @@ __device__ __forceinline__ void fixed_weight_split(float r, unsigned& hi, unsign
 }
 
 // Sum over the wavefront of hi * 2^24 + lo with hi < 2^26 and lo < 2^30 per lane: the carry of lo moves into hi first, then
-// both halves are summed as 32-bit values in two independent shuffle chains.  The total is valid in lane 0.
+// both halves are summed as 32-bit values in two independent chains.  The total is valid in the last lane.
 __device__ __forceinline__ unsigned long long wave_sum_split(unsigned hi, unsigned lo) {
-    hi += lo >> 24;
-    lo &= 0xffffffu;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        hi += __shfl_down(hi, d, kWave);
-        lo += __shfl_down(lo, d, kWave);
-    }
+    hi = wave_incl_scan_u32(hi + (lo >> 24));
+    lo = wave_incl_scan_u32(lo & 0xffffffu);
     return ((unsigned long long)hi << 24) + lo;
 }
-// Inclusive prefix sum over the wavefront of values below 2^58, as three limbs of 24 bits in independent 32-bit chains
-// (a 64-bit shuffle chain costs twice the dependent steps).
-__device__ __forceinline__ unsigned long long wave_incl_scan_limbs(unsigned long long v, int lane) {
-    unsigned l0 = (unsigned)v & 0xffffffu, l1 = (unsigned)(v >> 24) & 0xffffffu, l2 = (unsigned)(v >> 48);
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const unsigned o0 = __shfl_up(l0, d, kWave), o1 = __shfl_up(l1, d, kWave), o2 = __shfl_up(l2, d, kWave);
-        if (lane >= d) {
-            l0 += o0;
-            l1 += o1;
-            l2 += o2;
-        }
-    }
+// Inclusive prefix sum over the wavefront of values whose total is below 2^72 before it wraps to 64 bits, as three limbs of 24
+// bits in independent 32-bit chains of one-instruction steps.
+__device__ __forceinline__ unsigned long long wave_incl_scan_limbs(unsigned long long v) {
+    const unsigned l0 = wave_incl_scan_u32((unsigned)v & 0xffffffu), l1 = wave_incl_scan_u32((unsigned)(v >> 24) & 0xffffffu);
+    const unsigned l2 = wave_incl_scan_u32((unsigned)(v >> 48));
     return (unsigned long long)l0 + ((unsigned long long)l1 << 24) + ((unsigned long long)l2 << 48);
 }
 
@@ -377,6 +364,18 @@ __device__ __noinline__ int pick_plain_row(const float* __restrict__ prow, int V
     return sh_tok;
 }
 
+// Four probabilities of a row from token idx < V on, zeros past its end.  Rows start at any multiple of 4 bytes: the 16-byte load
+// takes that in one instruction, and only a ragged last group is read element by element.
+typedef unsigned c_u32x4 __attribute__((ext_vector_type(4)));
+typedef c_u32x4 c_u32x4_any __attribute__((aligned(4)));
+__device__ __forceinline__ float4 load_row4(const float* row, int idx, int V) {
+    if (idx + 4 <= V) {
+        const c_u32x4 v = *reinterpret_cast<const c_u32x4_any*>(row + idx);
+        return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+    }
+    return make_float4(row[idx], idx + 1 < V ? row[idx + 1] : 0.f, idx + 2 < V ? row[idx + 2] : 0.f, 0.f);
+}
+
 template <int MAXIT>
 __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k, int V, FusedPlan pl, unsigned tag,
                                                                    const float* __restrict__ p,
@@ -405,11 +404,11 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
 #pragma unroll
     for (int i = 0; i < MAXIT; ++i) {
         const int idx = lo + (i * kWave + lane) * 4;
-        const bool in = i < pl.iters && idx < V;   // V is a multiple of 4 here: a group is inside or outside as a whole
+        const bool in = i < pl.iters && idx < V;
         pv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (in) pv[i] = *reinterpret_cast<const float4*>(prow + idx);
-        if (in && has_q) qv[i] = *reinterpret_cast<const float4*>(qrow + idx);
+        if (in) pv[i] = load_row4(prow, idx, V);
+        if (in && has_q) qv[i] = load_row4(qrow, idx, V);
     }
     // per lane: at most 64 weights; their high parts (<= 2^16) and low parts (< 2^24) add up in 32 bits
     unsigned w_hi = 0, w_lo = 0;
@@ -427,7 +426,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     }
     const unsigned long long s_sub = wave_sum_split(w_hi, w_lo);
     unsigned long long* mine = slots + ((size_t)b * kFuMaxSub + sub) * 2;
-    if (lane == 0 && sub < pl.nsub) {
+    if (lane == kWave - 1 && sub < pl.nsub) {
         publish(mine + 0, tagged((unsigned)s_sub, tag));
         publish(mine + 1, tagged((unsigned)(s_sub >> 32), tag));
     }
@@ -460,7 +459,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
             publish(e + 0, 0ull);
             publish(e + 1, 0ull);
         }
-        const unsigned long long incl = wave_incl_scan_limbs(v, lane);
+        const unsigned long long incl = wave_incl_scan_limbs(v);
         const unsigned long long Z = shfl_u64(incl, kWave - 1);
         const unsigned long long T = (__umul64hi((unsigned long long)m, Z) << 40) | (((unsigned long long)m * Z) >> 24);
         if (lane == 0) {
@@ -504,7 +503,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
         local += w[i];
     }
     // exclusive prefix over the workgroup in thread order
-    const unsigned long long incl = wave_incl_scan_limbs(local, lane);
+    const unsigned long long incl = wave_incl_scan_limbs(local);
     if (lane == kWave - 1) sh_scan[wave] = incl;
     __syncthreads();
     unsigned long long run = base + incl - local;
@@ -551,7 +550,7 @@ extern "C" int spec_accept(int32_t B, int32_t k, int32_t V, const float* p, cons
     hipStream_t s = (hipStream_t)stream;
     // float4 loads need every row start 16-byte aligned
     const bool vec = (V % 4 == 0) && (((uintptr_t)p & 15) == 0) && (k == 0 || ((uintptr_t)q & 15) == 0);
-    if (vec && V <= kFuMaxV) {  // one launch
+    if (V <= kFuMaxV) {  // one launch
         const FusedPlan fp = plan_fused(V);
         const unsigned tag = next_word_tag();
         const dim3 fgrid((unsigned)((long long)B * fp.S));
