@@ -98,9 +98,14 @@ def strerror(status: int) -> str:
     return load().lotts_strerror(int(status)).decode()
 
 
+# The current stream's handle and the current device without the Python objects that torch.cuda.current_stream() makes: at
+# these call rates every microsecond of the host shows (a call of a few microseconds of GPU time waits for the next one).
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    return _raw_stream(_current_device()) if stream is None else int(stream.cuda_stream)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -110,19 +115,29 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 _workspaces: Dict[Tuple[str, int, int], torch.Tensor] = {}
 _retired = []   # grown-out workspaces: kept alive, a kernel enqueued earlier may still be using them
 
+# What depends on sizes, strides and types alone -- a checked descriptor, a workspace size -- keyed by those values; bounded.
+_sized: Dict[tuple, object] = {}
+_SIZED_MAX = 4096
 
-def _workspace(kind: str, device: torch.device, nbytes: int, stream: Optional[torch.cuda.Stream]) -> torch.Tensor:
+
+def _remember(key: tuple, value):
+    if len(_sized) >= _SIZED_MAX:
+        _sized.clear()
+    _sized[key] = value
+    return value
+
+
+def _workspace(kind: str, index: int, nbytes: int, stream: Optional[torch.cuda.Stream]) -> torch.Tensor:
     """One cached scratch tensor per entry point, device and stream, grown on demand.  Calls on different streams
     may overlap in time, so they never share one.  The tensor is allocated and zero-filled on the stream that will
     use it (verify_attention wants its arrival cells zero at first use), so the fill is ordered before the kernel."""
-    s = torch.cuda.current_stream(device) if stream is None else stream
-    key = (kind, device.index if device.index is not None else torch.cuda.current_device(), int(s.cuda_stream))
+    key = (kind, index, _raw_stream(index) if stream is None else int(stream.cuda_stream))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         if ws is not None:
             _retired.append(ws)
-        with torch.cuda.stream(s):
-            ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=device)
+        with torch.cuda.stream(torch.cuda.current_stream(index) if stream is None else stream):
+            ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=torch.device("cuda", index))
         _workspaces[key] = ws
     return ws
 
@@ -153,6 +168,25 @@ def make_attn_desc(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Kpriv: torch.T
     return d
 
 
+def _attn_call(lib, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, out, scale):
+    """(pointer to the descriptor, workspace bytes, Kpre, Vpre) of a call, checked: everything that the checks and the
+    descriptor look at is in the key, so a call of sizes, strides and types seen before is only looked up."""
+    if Kpre is not None and Kpre.shape[1] == 0:
+        Kpre, Vpre = None, None
+    scale = float(scale)
+    key = (Q.shape, Q.stride(), Q.dtype, Kpriv.shape, Kpriv.stride(), Vpriv.stride(), out.stride(), priv_len.dtype, scale,
+           None if Kpre is None else (Kpre.shape, Kpre.stride(), Vpre.stride()))
+    hit = _sized.get(key)
+    if hit is None:
+        if Vpriv.stride() != Kpriv.stride() or (Kpre is not None and Vpre.stride() != Kpre.stride()):
+            raise ValueError("K and V of a segment must share strides")
+        if priv_len.dtype != torch.int32:
+            raise TypeError("priv_len must be int32")
+        desc = ctypes.pointer(make_attn_desc(Q, Kpre, Kpriv, out, scale))   # read only from here on, also by other threads
+        hit = _remember(key, (desc, lib.verify_attention_workspace_bytes(desc)))
+    return hit[0], hit[1], Kpre, Vpre
+
+
 def verify_attention(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Vpre: Optional[torch.Tensor],
                      Kpriv: torch.Tensor, Vpriv: torch.Tensor, priv_len: torch.Tensor, *, scale: float = 0.0,
                      out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None,
@@ -163,23 +197,17 @@ def verify_attention(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Vpre: Option
     lib = load()
     if not Q.is_cuda:
         raise ValueError("verify_attention runs on the GPU only")
-    if Kpre is not None and Kpre.shape[1] == 0:
-        Kpre, Vpre = None, None
-    if Vpriv.stride() != Kpriv.stride() or (Kpre is not None and Vpre.stride() != Kpre.stride()):
-        raise ValueError("K and V of a segment must share strides")
-    if priv_len.dtype != torch.int32:
-        raise TypeError("priv_len must be int32")
     if out is None:
         out = torch.empty(Q.shape, dtype=Q.dtype, device=Q.device)
     if return_lse and lse is None:
         lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
-    desc = make_attn_desc(Q, Kpre, Kpriv, out, scale)
-    need = lib.verify_attention_workspace_bytes(ctypes.byref(desc))
+    desc, need, Kpre, Vpre = _attn_call(lib, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, out, scale)
     if need == 0:
         raise LottsError(-2, "verify_attention_workspace_bytes")
-    ws = _workspace("attn", Q.device, need, stream) if workspace is None else workspace
-    rc = lib.verify_attention(ctypes.byref(desc), _ptr(Q), _ptr(Kpre), _ptr(Vpre), _ptr(Kpriv), _ptr(Vpriv),
-                              _ptr(priv_len), _ptr(out), _ptr(lse), _ptr(ws), ws.numel() * ws.element_size(),
+    if workspace is None:
+        workspace = _workspace("attn", Q.get_device(), need, stream)
+    rc = lib.verify_attention(desc, Q.data_ptr(), _ptr(Kpre), _ptr(Vpre), Kpriv.data_ptr(), Vpriv.data_ptr(),
+                              priv_len.data_ptr(), out.data_ptr(), _ptr(lse), workspace.data_ptr(), workspace.nbytes,
                               _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "verify_attention")
@@ -195,15 +223,9 @@ def verify_attention_noalloc(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Vpre
     lib = load()
     if not Q.is_cuda:
         raise ValueError("verify_attention_noalloc runs on the GPU only")
-    if Kpre is not None and Kpre.shape[1] == 0:
-        Kpre, Vpre = None, None
-    if Vpriv.stride() != Kpriv.stride() or (Kpre is not None and Vpre.stride() != Kpre.stride()):
-        raise ValueError("K and V of a segment must share strides")
-    if priv_len.dtype != torch.int32:
-        raise TypeError("priv_len must be int32")
-    desc = make_attn_desc(Q, Kpre, Kpriv, out, scale)
-    rc = lib.verify_attention_noalloc(ctypes.byref(desc), _ptr(Q), _ptr(Kpre), _ptr(Vpre), _ptr(Kpriv), _ptr(Vpriv),
-                                      _ptr(priv_len), _ptr(out), _ptr(lse), _stream_handle(stream))
+    desc, _, Kpre, Vpre = _attn_call(lib, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, out, scale)
+    rc = lib.verify_attention_noalloc(desc, Q.data_ptr(), _ptr(Kpre), _ptr(Vpre), Kpriv.data_ptr(), Vpriv.data_ptr(),
+                                      priv_len.data_ptr(), out.data_ptr(), _ptr(lse), _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "verify_attention_noalloc")
     return out
@@ -221,10 +243,10 @@ def spec_accept(p: torch.Tensor, q: Optional[torch.Tensor], draft: Optional[torc
     k = R - 1
     if p.dtype != torch.float32 or u.dtype != torch.float32 or not p.is_contiguous() or not u.is_contiguous():
         raise TypeError("p and u must be contiguous float32")
-    if tuple(u.shape) != (B, R):
+    if u.shape != (B, R):
         raise ValueError("u must be [B][k+1]")
     if k > 0:
-        if q is None or draft is None or tuple(q.shape) != (B, k, V) or tuple(draft.shape) != (B, k):
+        if q is None or draft is None or q.shape != (B, k, V) or draft.shape != (B, k):
             raise ValueError("q must be [B][k][V] and draft [B][k]")
         if q.dtype != torch.float32 or draft.dtype != torch.int32 or not q.is_contiguous() or not draft.is_contiguous():
             raise TypeError("q must be contiguous float32 and draft contiguous int32")
@@ -234,12 +256,14 @@ def spec_accept(p: torch.Tensor, q: Optional[torch.Tensor], draft: Optional[torc
         accept_len = torch.empty((B,), dtype=torch.int32, device=p.device)
     if next_token is None:
         next_token = torch.empty((B,), dtype=torch.int32, device=p.device)
-    need = lib.spec_accept_workspace_bytes(B, k, V)
+    need = _sized.get(("accept", B, k, V))
+    if need is None:
+        need = _remember(("accept", B, k, V), lib.spec_accept_workspace_bytes(B, k, V))
     if need == 0:
         raise LottsError(-2, "spec_accept_workspace_bytes")
-    ws = _workspace("accept", p.device, need, stream) if workspace is None else workspace
-    rc = lib.spec_accept(B, k, V, _ptr(p), _ptr(q), _ptr(draft), _ptr(u), _ptr(accept_len), _ptr(next_token),
-                         _ptr(ws), ws.numel() * ws.element_size(), _stream_handle(stream))
+    ws = _workspace("accept", p.get_device(), need, stream) if workspace is None else workspace
+    rc = lib.spec_accept(B, k, V, p.data_ptr(), _ptr(q), _ptr(draft), u.data_ptr(), accept_len.data_ptr(),
+                         next_token.data_ptr(), ws.data_ptr(), ws.nbytes, _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "spec_accept")
     return accept_len, next_token
@@ -260,7 +284,7 @@ def majority_vote(answers: torch.Tensor, *, winner: Optional[torch.Tensor] = Non
         winner = torch.empty((N,), dtype=torch.int32, device=answers.device)
     if winner_count is None:
         winner_count = torch.empty((N,), dtype=torch.int32, device=answers.device)
-    rc = lib.majority_vote(N, B, _ptr(answers), _ptr(winner), _ptr(winner_count), _stream_handle(stream))
+    rc = lib.majority_vote(N, B, answers.data_ptr(), winner.data_ptr(), winner_count.data_ptr(), _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "majority_vote")
     return winner, winner_count
@@ -300,13 +324,15 @@ def spec_accept_logits(target_logits: torch.Tensor, draft_logits: Optional[torch
     if priv_len is not None and (priv_len.dtype != torch.int32 or tuple(priv_len.shape) != (B,) or
                                  not priv_len.is_contiguous() or priv_len.device != u.device):
         raise TypeError("priv_len must be a contiguous int32 [B] tensor on the same GPU")
-    need = lib.spec_accept_logits_workspace_bytes(B, k, V)
+    need = _sized.get(("accept_logits", B, k, V))
+    if need is None:
+        need = _remember(("accept_logits", B, k, V), lib.spec_accept_logits_workspace_bytes(B, k, V))
     if need == 0:
         raise LottsError(-2, "spec_accept_logits_workspace_bytes")
-    ws = _workspace("accept_logits", u.device, need, stream) if workspace is None else workspace
+    ws = _workspace("accept_logits", u.get_device(), need, stream) if workspace is None else workspace
     rc = lib.spec_accept_logits(B, k, V, _ptr(target_logits), _ptr(draft_logits), dt, float(inv_temperature), _ptr(draft),
                                 _ptr(u), _ptr(accept_len), _ptr(next_token), _ptr(priv_len), _ptr(ws),
-                                ws.numel() * ws.element_size(), _stream_handle(stream))
+                                ws.nbytes, _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "spec_accept_logits")
     return accept_len, next_token
@@ -363,12 +389,14 @@ def skinny_gemm(X: torch.Tensor, W: torch.Tensor, *, out: Optional[torch.Tensor]
         raise ValueError("X [M][K] and W [N][K] must share K and have contiguous rows")
     if out is None:
         out = torch.empty((M, N), dtype=torch.bfloat16, device=X.device)
-    need = lib.skinny_gemm_workspace_bytes(M, N, K)
+    need = _sized.get(("gemm", M, N, K))
+    if need is None:
+        need = _remember(("gemm", M, N, K), lib.skinny_gemm_workspace_bytes(M, N, K))
     if need == 0:
         raise LottsError(-2, "skinny_gemm_workspace_bytes")
-    ws = _workspace("gemm", X.device, need, stream) if workspace is None else workspace
-    rc = lib.skinny_gemm(M, N, K, _ptr(X), X.stride(0), _ptr(W), W.stride(0), _ptr(out), out.stride(0), _ptr(ws),
-                         ws.numel() * ws.element_size(), _stream_handle(stream))
+    ws = _workspace("gemm", X.get_device(), need, stream) if workspace is None else workspace
+    rc = lib.skinny_gemm(M, N, K, X.data_ptr(), X.stride(0), W.data_ptr(), W.stride(0), out.data_ptr(), out.stride(0),
+                         ws.data_ptr(), ws.nbytes, _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "skinny_gemm")
     return out
