@@ -27,6 +27,11 @@ constexpr int kGemmChunk = 128;  // K elements per chunk
 constexpr int kGemmMaxM = 256;
 constexpr int kGemmMaxSplit = 32;
 constexpr int kGemmTileFloats = 32 * 32;  // one accumulator tile: 32 weight rows x 32 tokens
+// W row strides (elements) at which every row of a step starts in the same few memory channels: with all blocks at the same k
+// they queue there.  Starting the blocks at different steps: 152064 x 2048 at 3 / 40 / 192 tokens 127 / 139 / 176 us -> 103 / 115 /
+// 162; 28672 x 4096 49.5 / 48.9 / 65.3 -> 37.5 / 37.9 / 62.7; 22016 x 2048 19.3 / 20.4 / 31.4 -> 17.4 / 18.7 / 31.7.  At other strides
+// it gives nothing and X is shared worse (55296 x 5120 87.1 / 128 -> 88.9 / 131 us at 40 / 192 tokens; 33280 x 3072 level).
+constexpr int kStaggerStride = 2048;
 constexpr int kGemmOutRow = 80;           // bytes per token row of a 32 x 32 bf16 tile on its way out through LDS (64 + pad)
 
 struct GemmParams {
@@ -36,6 +41,7 @@ struct GemmParams {
     int M, N, K, ksplit;
     int rows;     // weight rows a wavefront owns: 32, or fewer (a multiple of 4) when that fills the chip better
     int nblocks, roww, rt, tt;  // launch geometry, for the reduce kernel: blocks, row wavefronts, row / token tiles per wavefront
+    int stagger;                // stream forms: blocks start their K loop at different steps
     long long ldx, ldw, ldy;
 };
 
@@ -70,15 +76,20 @@ static inline int plan_rows(int N, int roww, int mt) {
     return kGemmRows;
 }
 
+// Direct form: wavefronts of a workgroup, and 32-wide k steps of a batch of loads, by weight and token tiles (of 16).
+static inline int direct_waves(int rn) { return rn == 4 ? 4 : 8; }
+static inline int direct_batch(int rn, int tt) { return rn == 4 ? 2 : (tt == 1 ? 8 : 4); }
+
 // Direct form: the tile that leaves the fewest bytes (its weight rows plus its tokens, over the whole K) to a workgroup with
-// at most one workgroup per unit.  Returns those KB, or 0 if no tile fits.
+// at most one workgroup per unit.  Returns those KB, with a wavefront's share of K in whole batches, or 0 if no tile fits.
 static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
     static const int tiles[][2] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 3}, {4, 2}, {4, 3}};
     double best = 0.0;
     for (const auto& t : tiles) {
         const long long nx = (N + 16 * t[0] - 1) / (16 * t[0]), ny = (M + 16 * t[1] - 1) / (16 * t[1]);
         if (nx * ny > kNumCU) continue;
-        const double kb = (16.0 * t[0] + (16 * t[1] < M ? 16 * t[1] : M)) * K * 2.0 / 1024.0;
+        const int unit = direct_waves(t[0]) * direct_batch(t[0], t[1]) * 32;
+        const double kb = (16.0 * t[0] + (16 * t[1] < M ? 16 * t[1] : M)) * ((K + unit - 1) / unit * unit) * 2.0 / 1024.0;
         if (best == 0.0 || kb < best) {
             best = kb;
             pl->rn = t[0]; pl->tt = t[1]; pl->nblocks = (int)nx; pl->nby = (int)ny;
@@ -89,11 +100,11 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
 
 // Which form, and how it is cut.  Measured on 16 matrices between 1536 x 1536 and 152064 x 5120 at 1 .. 256 tokens, calls
 // back to back over rotated weights, reduce launch included.
-//   Direct: while everything a wavefront needs is in flight at once (K <= 4096) it takes 3.4 us + 0.026 us per KB of a
-//     workgroup's W and X, against 6.4 us + 0.13 us per MB of W + 7e-6 us per token and (N + K) of the split stream forms:
-//     2560 x 2048 at 1 / 40 / 192 tokens 5.2 / 7.8 / 13.5 us against 7.9 / 9.2 / 15.0; 4096 x 4096 at 1 token 8.8 against
-//     11.5, at 40 tokens 17.5 against 13.5.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1
-//     token 19.8 us against 14.2.
+//   Direct: while everything a wavefront needs is in flight at once (K <= 4096) it takes 2.9 us + 0.022 us per KB of a
+//     workgroup's W and X (whole batches of loads) + 0.14 us per MB of W, against 7 us + 0.125 us per MB of W + 7e-6 us per token
+//     and (N + K) of the split stream forms: 2560 x 2048 at 1 / 40 / 192 tokens 5.2 / 7.8 / 13.5 us against 7.9 / 9.2 / 15.0; 4096 x
+//     4096 at 2 / 16 tokens 9.9 / 13.1 against 11.4 / 11.6; 6144 x 4096 at 2 tokens 17.7 against 13.9; 4096 x 2560 at 16 tokens 13.3
+//     against 10.0.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1 token 19.8 us against 14.2.
 //   256-row stream form: more than 256 blocks of 128 rows; an X chunk in LDS serves the most rows.  55296 x 5120 at 64
 //     tokens 92 us, 128-row form 104.
 //   128-row form below that, 64-row form when it would have to be split more than sevenfold (N <= 4608): the fewer splits,
@@ -108,7 +119,7 @@ static inline GemmPlan plan_gemm(int M, int N, int K) {
     pl.ksplit = 1;
     if (K <= 4096) {
         const double kb = plan_direct(M, N, K, &pl);
-        if (kb > 0.0 && 3.4 + 0.026 * kb < 6.4 + 0.13 * (2e-6 * N * K) + 7e-6 * M * (N + K)) {
+        if (kb > 0.0 && 2.9 + 0.022 * kb + 0.14 * (2e-6 * N * K) < 7.0 + 0.125 * (2e-6 * N * K) + 7e-6 * M * (N + K)) {
             pl.form = kDirect;
             return pl;
         }
@@ -150,9 +161,10 @@ static inline size_t split_floats(const GemmPlan& pl) { return (size_t)pl.nblock
 // workgroups of the 128-row form from half the K splits.
 // Neither operand passes through registers: global-to-LDS loads (16 bytes per lane, landing at a wavefront-uniform
 // LDS base + 16 * lane) fill stages of half a chunk (64 k) --
-//   X: two stages per workgroup, one multiplied while the other is filled, one barrier per stage;
-//   W: three stages per row wavefront (32 rows x 64 k, 4 KB): one multiplied, two on their way, so that a W transfer has
-//      a whole chunk of time to arrive from HBM; non-temporal; private to the wavefront, or to those that share its rows
+//   X: XS stages per workgroup, one multiplied while the others are filled, one barrier per stage; rows of 8 tokens that
+//      are all past the last one stay out (an MFMA column is one token: what their LDS holds reaches no output; with 40 tokens
+//      24 of 64 rows, 22016 x 2048 20.6 -> 19.7 us, 55296 x 5120 at 64 tokens 91 -> 89);
+//   W: XS + 1 stages per row wavefront (32 rows x 64 k, 4 KB): one multiplied, XS on their way; non-temporal; private to the wavefront, or to those that share its rows
 //      (pair and groups: each fills its part; the step barrier that publishes X publishes these too).
 // A stage keeps rows of 128 bytes back to back (a load instruction fills 8 whole rows), so the 16-byte pieces of a
 // row are stored permuted -- piece p of row r at slot p ^ ((r >> 1) & 7) -- which spreads the 16 lanes of a
@@ -164,9 +176,12 @@ static inline size_t split_floats(const GemmPlan& pl) { return (size_t)pl.nblock
 // transfers that are meant to stay in flight; and without a "memory" clobber, with which the same wait comes
 // back: the barrier statements of the step loop, which have it, fence every read of a stage against the transfer
 // that refills it, and volatile statements keep their order among themselves.  M0 carries the LDS base.  Since the
-// compiler does not know of the loads, the waits are written out too: before the barrier of a step, vmcnt(WI) -- the
-// step's X transfers have landed, and with them the older W stage; only the WI W transfers issued after them (the
-// next step's stage) may still be in flight -- or vmcnt(0) in the last step, after which nothing was issued.
+// compiler does not know of the loads, the waits are written out too: before the barrier of a step, vmcnt(n) -- the
+// step's X transfers have landed, and with them the older W stage; only the n transfers issued after them (stages of later
+// steps) may still be in flight -- counted down to vmcnt(0) in the last step.
+// XS = 2 for the 128- and 256-row forms (with 3 or 4 they are level within 1 us: one workgroup has 32 KB of W in flight as it is);
+// XS = 4 for the 64-row form up to 96 tokens, whose two stages of W are half of that: 2048 x 11008 at 3 / 40 / 96 tokens 15.4 /
+// 15.9 / 19.3 -> 13.7 / 14.8 / 18.5 us; beyond, X stages of 16 KB and more crowd the LDS and it loses (192 tokens 23.9 -> 24.4).
 //
 // The way out.  Accumulator lanes hold one token and scattered weight rows, so stores straight from them write 16 bytes
 // per row of Y (32 of a row of fp32 partials), and the launch ended on them: 2560 x 2048 at 192 tokens took 18.6 us for 8
@@ -174,20 +189,22 @@ static inline size_t split_floats(const GemmPlan& pl) { return (size_t)pl.nblock
 // way; Y tiles turn through LDS into 64-byte row pieces.  With the forms above (before: 128 / 256 rows only), reduce launch
 // included, 40 / 192 tokens: 2048 x 11008 20.2 / 34.5 -> 16.8 / 24.5 us; 7168 x 5120 21.5 / 40 -> 20.0 / 29.7; 22016 x 2048
 // 25.4 / 41.5 -> 21.6 / 31.0.
-template <int MT, int RT, int WAVES, int KG>
+template <int MT, int RT, int WAVES, int KG, int XS>
 __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(const GemmParams p) {
     static_assert(RT == 1 || (RT == 2 && MT % 2 == 0), "a pair of wavefronts splits the token tiles evenly");
+    constexpr int WS = XS + 1;        // W stages
     constexpr int ROWW = WAVES / KG;  // wavefronts side by side over the weight rows
     constexpr int WI = 4 / KG;        // W transfers per wavefront and stage
     constexpr int TT = MT / RT;  // token tiles per wavefront
     constexpr int XROWS = 32 * MT;
     constexpr int XINSTR = XROWS / 8;
-    constexpr int XI = (XINSTR + WAVES - 1) / WAVES;
+    // X transfers per wavefront and stage: the most, and the fewest (of 8 token rows each; rows past the last token stay out)
+    constexpr int XI = (XINSTR + WAVES - 1) / WAVES, XMIN = (XINSTR - 3) / WAVES;
     constexpr int kStageRow = 128;
     constexpr int XSTAGE = XROWS * kStageRow, WSTAGE = 32 * kStageRow;
     constexpr int TILES = RT * TT;   // accumulator tiles per wavefront
     constexpr int TILE_Q = kGemmTileFloats / 4;
-    constexpr int STAGES = 2 * XSTAGE + ROWW * 3 * WSTAGE, PARK = ROWW * TILES * (KG - 1) * TILE_Q * 16;
+    constexpr int STAGES = XS * XSTAGE + ROWW * WS * WSTAGE, PARK = ROWW * TILES * (KG - 1) * TILE_Q * 16;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES > PARK ? STAGES : PARK];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
     const int kgrp = KG == 1 ? 0 : wave / ROWW, wr = KG == 1 ? wave : wave % ROWW;
@@ -200,10 +217,15 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
     const int c_lo = (int)((long long)blockIdx.y * chunks / p.ksplit);
     const int c_hi = (int)((long long)(blockIdx.y + 1) * chunks / p.ksplit);
     const int G = 2 * (c_hi - c_lo);  // half-chunk steps
+    // Staggered start: block x begins 5 x steps into its K range and wraps around; the pointers go back once, at that step.  (A
+    // select of the offset in every transfer instead cost 2 % of 55296 x 5120.)
+    const int turn = (int)blockIdx.x * 5;
+    const int first = p.stagger && G > 0 ? (turn + turn / G) % G : 0;
+    const int wrap = first > 0 ? G - first : -1;  // the step that is back at the start of the range
     unsigned char* xs = lds;
-    unsigned char* wsl = lds + 2 * XSTAGE + grp * (3 * RT * WSTAGE);
+    unsigned char* wsl = lds + XS * XSTAGE + grp * (WS * RT * WSTAGE);
 
-    // Per-lane source addresses of the transfers, for K offset 0 of the workgroup's range: 64-bit, so that neither
+    // Per-lane source addresses of the transfers, for step 0: 64-bit, so that neither
     // operand is limited to 4 GB.  lane -> (row of the instruction's 8, slot); the piece fetched for a slot is
     // slot ^ swizzle(row).
     const int l_row = lane >> 3, l_slot = lane & 7;
@@ -213,23 +235,27 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
     for (int i = 0; i < XI; ++i) {
         const int r = (wave + i * WAVES) * 8 + l_row;
         const int m = r < p.M ? r : p.M - 1;
-        x_src[i] = p.X + (long long)m * p.ldx + (long long)c_lo * kGemmChunk + (l_slot ^ ((r >> 1) & 7)) * 8;
+        x_src[i] = p.X + (long long)m * p.ldx + (long long)c_lo * kGemmChunk + first * 64 + (l_slot ^ ((r >> 1) & 7)) * 8;
     }
 #pragma unroll
     for (int i = 0; i < WI; ++i) {
         const int r = th * 32 + (kgrp * WI + i) * 8 + l_row;  // of a pair, each wavefront brings in 32 of the 64 rows
         int n = n0 + (RT == 1 && r >= p.rows ? p.rows - 1 : r);  // a short tile re-reads its last row
         n = n < p.N ? n : p.N - 1;  // rows past the end re-read the last row; never stored
-        w_src[i] = p.W + (long long)n * p.ldw + (long long)c_lo * kGemmChunk + (l_slot ^ ((r >> 1) & 7)) * 8;
+        w_src[i] = p.W + (long long)n * p.ldw + (long long)c_lo * kGemmChunk + first * 64 + (l_slot ^ ((r >> 1) & 7)) * 8;
     }
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"  // M0 is on the clobber list on purpose
     auto fetch_x = [&](int g) {
-        unsigned char* stage = xs + (g & 1) * XSTAGE;
+        if (g == wrap) {
+#pragma unroll
+            for (int i = 0; i < XI; ++i) x_src[i] -= (long long)G * 64;
+        }
+        unsigned char* stage = xs + (g % XS) * XSTAGE;
 #pragma unroll
         for (int i = 0; i < XI; ++i) {
             const int j = wave + i * WAVES;
-            if (j < XINSTR) {
+            if ((i + 1) * WAVES <= XINSTR - 3 || j * 8 < p.M) {  // (all but the last 3 are rows of tokens that exist)
                 const unsigned lds_base = __builtin_amdgcn_readfirstlane(
                     (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)(stage + j * 8 * kStageRow));
                 asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
@@ -240,7 +266,11 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
         }
     };
     auto fetch_w = [&](int g) {
-        unsigned char* stage = wsl + (g % 3) * (RT * WSTAGE) + th * WSTAGE;
+        if (g == wrap) {
+#pragma unroll
+            for (int i = 0; i < WI; ++i) w_src[i] -= (long long)G * 64;
+        }
+        unsigned char* stage = wsl + (g % WS) * (RT * WSTAGE) + th * WSTAGE;
 #pragma unroll
         for (int i = 0; i < WI; ++i) {
             const unsigned lds_base = __builtin_amdgcn_readfirstlane(
@@ -286,20 +316,25 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    if (G > 0) {
-        fetch_x(0);
-        fetch_w(0);
-        fetch_w(1);  // G is even: step 1 exists
+    if (G > 0) fetch_w(0);
+#pragma unroll
+    for (int i = 0; i + 1 < XS; ++i) {
+        if (i < G) fetch_x(i);
+        if (i + 1 < G) fetch_w(i + 1);
     }
     for (int g = 0; g < G; ++g) {
-        // issued after step g's X: the 4 W transfers of step g + 1, unless there is none
-        if (g + 1 < G)
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(WI) : "memory");
+        // issued after step g's X: W of the steps up to g + XS - 1 and X of those up to g + XS - 2, as far as there are any
+        if (g + XS - 1 < G)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((XS - 1) * WI + (XS - 2) * XMIN) : "memory");
+        else if (XS > 3 && g + 2 < G)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * (WI + XMIN)) : "memory");
+        else if (XS > 2 && g + 1 < G)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(WI + XMIN) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (g + 1 < G) fetch_x(g + 1);
-        if (g + 2 < G) fetch_w(g + 2);
-        multiply(xs + (g & 1) * XSTAGE, wsl + (g % 3) * (RT * WSTAGE));
+        if (g + XS - 1 < G) fetch_x(g + XS - 1);
+        if (g + XS < G) fetch_w(g + XS);
+        multiply(xs + (g % XS) * XSTAGE, wsl + (g % WS) * (RT * WSTAGE));
     }
     // KG = 2: the groups add up.  Group g finishes the tiles j with j % KG == g; each wavefront parks the others in LDS (the
     // stages are free: no transfer is in flight after the last step) and adds what its partner parked, groups in order.
@@ -523,18 +558,19 @@ static inline bool gemm_sizes_ok(int M, int N, int K) {
            (long long)M * N < (1LL << 40);
 }
 
-template <int WAVES, int KG>
+// XS stages of X up to 96 tokens, XSM beyond
+template <int WAVES, int KG, int XS, int XSM>
 static void launch_stream(int mt, dim3 grid, hipStream_t s, const GemmParams& p) {
     const dim3 block(WAVES * kWave);
     switch (mt) {
-        case 1: LOTTS_LAUNCH((skinny_gemm_stream_kernel<1, 1, WAVES, KG>), grid, block, s, p); break;
-        case 2: LOTTS_LAUNCH((skinny_gemm_stream_kernel<2, 1, WAVES, KG>), grid, block, s, p); break;
-        case 3: LOTTS_LAUNCH((skinny_gemm_stream_kernel<3, 1, WAVES, KG>), grid, block, s, p); break;
-        case 4: LOTTS_LAUNCH((skinny_gemm_stream_kernel<4, 2, WAVES, KG>), grid, block, s, p); break;
-        case 5: LOTTS_LAUNCH((skinny_gemm_stream_kernel<5, 1, WAVES, KG>), grid, block, s, p); break;
-        case 6: LOTTS_LAUNCH((skinny_gemm_stream_kernel<6, 2, WAVES, KG>), grid, block, s, p); break;
-        case 7: LOTTS_LAUNCH((skinny_gemm_stream_kernel<7, 1, WAVES, KG>), grid, block, s, p); break;
-        default: LOTTS_LAUNCH((skinny_gemm_stream_kernel<8, 2, WAVES, KG>), grid, block, s, p); break;
+        case 1: LOTTS_LAUNCH((skinny_gemm_stream_kernel<1, 1, WAVES, KG, XS>), grid, block, s, p); break;
+        case 2: LOTTS_LAUNCH((skinny_gemm_stream_kernel<2, 1, WAVES, KG, XS>), grid, block, s, p); break;
+        case 3: LOTTS_LAUNCH((skinny_gemm_stream_kernel<3, 1, WAVES, KG, XS>), grid, block, s, p); break;
+        case 4: LOTTS_LAUNCH((skinny_gemm_stream_kernel<4, 2, WAVES, KG, XSM>), grid, block, s, p); break;
+        case 5: LOTTS_LAUNCH((skinny_gemm_stream_kernel<5, 1, WAVES, KG, XSM>), grid, block, s, p); break;
+        case 6: LOTTS_LAUNCH((skinny_gemm_stream_kernel<6, 2, WAVES, KG, XSM>), grid, block, s, p); break;
+        case 7: LOTTS_LAUNCH((skinny_gemm_stream_kernel<7, 1, WAVES, KG, XSM>), grid, block, s, p); break;
+        default: LOTTS_LAUNCH((skinny_gemm_stream_kernel<8, 2, WAVES, KG, XSM>), grid, block, s, p); break;
     }
 }
 
@@ -571,13 +607,14 @@ extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64
     p.part = static_cast<float*>(workspace);
     p.M = M; p.N = N; p.K = K; p.ksplit = pl.ksplit; p.rows = pl.rows;
     p.nblocks = pl.nblocks; p.roww = pl.roww; p.rt = pl.rt; p.tt = pl.mt / pl.rt;
+    p.stagger = ldw % kStaggerStride == 0;
     p.ldx = ldx; p.ldw = ldw; p.ldy = ldy;
     hipStream_t s = (hipStream_t)stream;
     const dim3 grid(pl.nblocks, pl.form == kDirect ? pl.nby : pl.ksplit);
     switch (pl.form) {
-        case kStream256: launch_stream<8, 1>(pl.mt, grid, s, p); break;
-        case kStream128: launch_stream<4, 1>(pl.mt, grid, s, p); break;
-        case kStream64: launch_stream<4, 2>(pl.mt, grid, s, p); break;
+        case kStream256: launch_stream<8, 1, 2, 2>(pl.mt, grid, s, p); break;
+        case kStream128: launch_stream<4, 1, 2, 2>(pl.mt, grid, s, p); break;
+        case kStream64: launch_stream<4, 2, 4, 2>(pl.mt, grid, s, p); break;
         case kDirect:
             switch (pl.rn * 10 + pl.tt) {
                 case 11: launch_direct<1, 1, 8, 8>(grid, s, p); break;

@@ -1,5 +1,5 @@
 """skinny_gemm at the edges of each form that its plan can take: single-workgroup K ranges straight from memory, 64-, 128- and
-256-row streaming blocks, split and unsplit, short row tiles, ragged last tiles.  Against the CPU oracle."""
+256-row streaming blocks, split and unsplit, short row tiles, ragged last tiles, staggered starts.  Against the CPU oracle."""
 import numpy as np
 import pytest
 import torch
@@ -22,6 +22,9 @@ pytestmark = pytest.mark.gpu
     (90, 32768, 128), (128, 18440, 256), (224, 18448, 128), (256, 20488, 128),
     # 256-row blocks: 20 .. 32 rows per wavefront, more than one round of workgroups
     (1, 32776, 256), (40, 49160, 128), (96, 57352, 128), (64, 65544, 128), (66, 98312, 128), (97, 33032, 128), (200, 33000, 256),
+    # W rows a multiple of 4 KB apart (blocks start at different k): each form, split and unsplit, uneven splits
+    (40, 2056, 8192), (33, 2056, 6144), (96, 1032, 10240), (193, 520, 6144), (70, 10248, 2048), (7, 5128, 6144), (130, 4744, 4096),
+    (40, 36872, 2048), (100, 33032, 2048),
 ])
 def test_every_form(oracle, M, N, K):
     import paper_2505_19634_amd as lotts
