@@ -929,13 +929,14 @@ __global__ __launch_bounds__(kAttnThreads) void attn_f32_kernel(const AttnParams
             s[i] = j0 + i * KPL + grp < n ? s[i] * scale : -INFINITY;
             mx = fmaxf(mx, s[i]);
         }
-        if (mx == -INFINITY) continue;  // this group has seen no key yet
-        const float alpha = expf(m - mx);
+        const float mu = mx == -INFINITY ? 0.f : mx;  // no key yet, or none but NaN scores: those stay NaN
+        const float alpha = expf(m - mu);
         l *= alpha;
         acc.x *= alpha; acc.y *= alpha; acc.z *= alpha; acc.w *= alpha;
 #pragma unroll
         for (int i = 0; i < NJ; ++i) {
-            const float pv = expf(s[i] - mx);
+            const float pv = expf(s[i] - mu);
+            if (j0 + i * KPL + grp >= n) vv[i] = make_float4(0.f, 0.f, 0.f, 0.f);  // an infinity counts once
             l += pv;
             acc.x += pv * vv[i].x; acc.y += pv * vv[i].y; acc.z += pv * vv[i].z; acc.w += pv * vv[i].w;
         }

@@ -67,3 +67,23 @@ def test_merge_flags_are_cleared_for_a_replay(oracle):
         assert torch.equal(out, want[i]), i
         assert torch.equal(got2, want2)
     assert int(ws[:131072].to(torch.int32).sum()) == 0  # every cell is down again
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_fp32_keeps_nan_and_infinities(D):
+    """NaN in all keys that a group of lanes sees in its first chunk stays NaN; an infinite value in the last row is that
+    infinity, not NaN from the rows that stand in for absent keys."""
+    import paper_2505_19634_amd as lotts
+    cfg = S.CONFIGS["C1"].with_(B=1, Hq=2, Hkv=2, D=D, k=0, P=0, L=70)
+    d = attn_to_dev(cfg, S.attention_inputs(cfg))
+    call = lambda: lotts.verify_attention(*(d[n] for n in ("Q", "Kpre", "Vpre", "Kpriv", "Vpriv", "priv_len")))
+    K = d["Kpriv"].clone()
+    for step in (2, 4, 8, 16):
+        d["Kpriv"].copy_(K)
+        d["Kpriv"][0, 0, 0:4 * step:step] = float("nan")
+        O = call()
+        assert torch.isnan(O[0, 0, 0]).all() and torch.isfinite(O[0, 0, 1]).all()
+    d["Kpriv"].copy_(K)
+    d["Vpriv"][0, 0, 69] = float("inf")
+    O = call()
+    assert (O[0, 0, 0] == float("inf")).all() and torch.isfinite(O[0, 0, 1]).all()
