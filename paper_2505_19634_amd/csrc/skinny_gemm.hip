@@ -66,8 +66,8 @@ static inline int plan_ksplit(int nblocks, int chunks) {
 }
 
 // Fewest weight rows per wavefront (20 .. 32) that still give at most one workgroup per unit: up to 96 tokens the launch
-// is bound by how fast each unit takes in its share of W and X, not by the padded MFMA rows.  Measured at 40 tokens:
-// 22016 x 2048 in 230 workgroups of 96 rows 21.6 us, in 172 of 128 rows 22.2; 33280 x 3072 in 208 of 160 rows 41.7 us, in
+// is bound by how fast each unit takes in its share of W and X, not by the padded MFMA rows.  Measured at 40 tokens, before
+// the staggered starts: 22016 x 2048 in 230 workgroups of 96 rows 21.6 us, in 172 of 128 rows 22.2; 33280 x 3072 in 208 of 160 rows 41.7 us, in
 // 130 of 256 48.9.
 static inline int plan_rows(int N, int roww, int mt) {
     if (mt > 3) return kGemmRows;
@@ -109,7 +109,8 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
 //     tokens 92 us, 128-row form 104.
 //   128-row form below that, 64-row form when it would have to be split more than sevenfold (N <= 4608): the fewer splits,
 //     the fewer fp32 partials, but the more often a unit reads X.  2048 x 11008 at 40 / 192 tokens in 64-row blocks x 8
-//     splits 16.8 / 24.5 us, 128 x 16 17.6 / 26.7; 5120 x 5120 at 64 / 192 tokens 128 x 6 18.4 / 25.9, 64 x 3 19.4 / 28.9.
+//     splits 14.8 / 24.3 us, 128 x 16 17.1 / 26.5; 5120 x 5120 at 64 / 192 tokens 128 x 6 17.9 / 26.0, 64 x 3 17.4 / 28.6; 6144 x 6144
+//     21.5 / 31.0 against 23.4 / 38.1.
 static inline GemmPlan plan_gemm(int M, int N, int K) {
     GemmPlan pl = {};
     const int chunks = K / kGemmChunk;
@@ -188,7 +189,7 @@ static inline size_t split_floats(const GemmPlan& pl) { return (size_t)pl.nblock
 // steps.  Partials now go out as they lie in the registers, 1 KB per store, and the reduce kernel reads them back the same
 // way; Y tiles turn through LDS into 64-byte row pieces.  With the forms above (before: 128 / 256 rows only), reduce launch
 // included, 40 / 192 tokens: 2048 x 11008 20.2 / 34.5 -> 16.8 / 24.5 us; 7168 x 5120 21.5 / 40 -> 20.0 / 29.7; 22016 x 2048
-// 25.4 / 41.5 -> 21.6 / 31.0.
+// 25.4 / 41.5 -> 21.6 / 31.0 (with what came since 14.8 / 24.3, 19.2 / 29.9, 18.8 / 31.7).
 template <int MT, int RT, int WAVES, int KG, int XS>
 __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(const GemmParams p) {
     static_assert(RT == 1 || (RT == 2 && MT % 2 == 0), "a pair of wavefronts splits the token tiles evenly");
