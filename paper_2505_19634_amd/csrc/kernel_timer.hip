@@ -19,9 +19,7 @@ static thread_local KernelTimer g_timer;
 
 static std::atomic<unsigned> g_word_tag{0};
 unsigned next_word_tag() {
-    unsigned tag = g_word_tag.fetch_add(1, std::memory_order_relaxed) + 1;
-    if (tag == 0) tag = g_word_tag.fetch_add(1, std::memory_order_relaxed) + 1;  // 0 is what cleared words hold
-    return tag;
+    return 0x80000000u | g_word_tag.fetch_add(1, std::memory_order_relaxed);
 }
 
 bool timer_take(hipEvent_t* start, hipEvent_t* stop) {

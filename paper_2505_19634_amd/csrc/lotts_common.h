@@ -20,8 +20,10 @@ constexpr int kNumXCD = 8;
 bool timer_take(hipEvent_t* start, hipEvent_t* stop);
 
 // Tag of a call whose workgroups exchange tagged words through the workspace (spec_accept,
-// spec_accept_logits): never 0, and different for every such call of the process whichever entry point
-// makes it, so one buffer can serve both without either taking the other's leftovers for its own.
+// spec_accept_logits): different for every such call of the process whichever entry point makes it, so one
+// buffer can serve both without either taking the other's leftovers for its own.  The top bit is always set: cleared
+// words hold 0 above, and the 64-bit weight sums that earlier calls leave untagged in the same buffer (at most 2^50 for
+// a row of logits, about 2^40 for a row of probabilities) never show a tag in their upper half.
 unsigned next_word_tag();
 
 // Every launch of the library goes through here: no dynamic LDS, the caller's stream.

@@ -14,7 +14,7 @@
 //
 // Two launches:
 //   lg_stat_kernel      grid (pieces of 8192 or 16384 logits, B * (2k + 1) rows, the pieces of a row next to each other): a
-//                       workgroup reads its piece ONCE into registers, publishes the piece's maximum under this call's tag,
+//                       workgroup reads its piece ONCE into registers, publishes the piece's maximum under this call's tag (two words),
 //                       collects the maxima of the row's other pieces, and forms the integer weight sum from the registers;
 //                       the pieces' sums meet in one 64-bit sum per row by device-scope atomics (integers: any order gives
 //                       the same sum).
@@ -220,19 +220,23 @@ __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V
     if (tid < kWave) {
 #pragma unroll
         for (int w = 0; w < kLgWaves; ++w) m = fmaxf(m, sh_m[w]);
-        unsigned long long* row = words + (size_t)r * npieces;
+        // A piece's maximum stands in two words, under the tag and under its complement, and counts only when both agree: no
+        // single leftover of an earlier call -- a row sum, a maximum, a word of another size's layout -- reads as one.
+        unsigned long long* row = words + (size_t)r * npieces * 2;
         if (tid == 0) {
-            __builtin_amdgcn_s_waitcnt(0);  // the cleared sum is in memory before this piece's word
-            lg_publish(row + pc, __float_as_uint(m), tag);
+            __builtin_amdgcn_s_waitcnt(0);  // the cleared sum is in memory before this piece's words
+            lg_publish(row + pc * 2, __float_as_uint(m), tag);
+            lg_publish(row + pc * 2 + 1, __float_as_uint(m), ~tag);
         }
         if (lane < npieces && lane != pc) {
-            unsigned long long w = 0;
+            unsigned long long w0 = 0, w1 = 0;
             for (int spin = 0; spin < kLgSpinLimit; ++spin) {
-                w = lg_peek(row + lane);
-                if ((unsigned)(w >> 32) == tag) break;
+                w0 = lg_peek(row + lane * 2);
+                w1 = lg_peek(row + lane * 2 + 1);
+                if ((unsigned)(w0 >> 32) == tag && (unsigned)(w1 >> 32) == ~tag && (unsigned)w0 == (unsigned)w1) break;
                 __builtin_amdgcn_s_sleep(1);
             }
-            m = fmaxf(m, __uint_as_float((unsigned)w));
+            m = fmaxf(m, __uint_as_float((unsigned)w0));
         }
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
@@ -335,7 +339,7 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
                                                                   const float* __restrict__ rmax,
                                                                   const unsigned long long* __restrict__ rsum,
                                                                   int32_t* __restrict__ accept_len,
-                                                                  unsigned long long* __restrict__ words,  // [rows][npieces]
+                                                                  unsigned long long* __restrict__ words,  // [rows][npieces][2]
                                                                   unsigned long long* __restrict__ slots,  // [B][nchunks][6]
                                                                   int32_t* __restrict__ next_token,
                                                                   int32_t* __restrict__ priv_len) {
@@ -349,10 +353,10 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
     __shared__ RowStat sh_p[kLgMaxK], sh_q[kLgMaxK];
     const float u_last = u[(size_t)b * (k + 1) + k];
     // the words of the launch before are consumed: cleared, so that a captured call (same tags) can be replayed
-    for (int i = c * kLgThreads + tid; i < (2 * k + 1) * npieces; i += nchunks * kLgThreads) {
-        const int j = i / npieces;
+    for (int i = c * kLgThreads + tid; i < (2 * k + 1) * npieces * 2; i += nchunks * kLgThreads) {
+        const int j = i / (npieces * 2);
         const int row = j <= k ? trow(b, j, k) : drow(B, b, j - k - 1, k);
-        words[(size_t)row * npieces + (i - j * npieces)] = 0ull;
+        words[(size_t)row * npieces * 2 + (i - j * npieces * 2)] = 0ull;
     }
     RowStat sp, sq;
     const int n = lg_accepted_length<BF16>(B, b, k, V, zt, zd, inv_temp, draft, u, rmax, rsum, sh_first, sh_p, sh_q, sp, sq);
@@ -487,7 +491,7 @@ struct LgLayout {
     size_t off_rmax, off_rsum, off_chunks, off_words, total;
     int nchunks, npieces, iters;
 };
-// [row maxima][row sums][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces].  The first two
+// [row maxima][row sums][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces: 2 per (row, piece)].  The first two
 // follow a block of 4 bytes per (row, 16384 logits).
 static inline LgLayout lg_layout(int B, int k, int V) {
     LgLayout l;
@@ -500,7 +504,7 @@ static inline LgLayout lg_layout(int B, int k, int V) {
     l.off_rsum = l.off_rmax + up(rows * sizeof(float));
     l.off_chunks = l.off_rsum + up(rows * sizeof(unsigned long long));
     l.off_words = l.off_chunks + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
-    l.total = l.off_words + up(rows * l.npieces * sizeof(unsigned long long));
+    l.total = l.off_words + up(rows * l.npieces * 2 * sizeof(unsigned long long));
     return l;
 }
 static inline bool lg_sizes_ok(int B, int k, int V) {
