@@ -488,11 +488,10 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
 
 
 struct LgLayout {
-    size_t off_rmax, off_rsum, off_chunks, off_words, total;
+    size_t off_rsum, off_chunks, off_words, total;
     int nchunks, npieces, iters;
 };
-// [row maxima][row sums][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces: 2 per (row, piece)].  The first two
-// follow a block of 4 bytes per (row, 16384 logits).
+// [row maxima][row sums][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces: 2 per (row, piece)]
 static inline LgLayout lg_layout(int B, int k, int V) {
     LgLayout l;
     l.nchunks = (V + kLgChunk - 1) / kLgChunk;
@@ -500,8 +499,7 @@ static inline LgLayout lg_layout(int B, int k, int V) {
     l.iters = V <= 4 * kLgGroup * kLgMaxPieces && rows * kLgMaxPieces <= 0x7fffffff ? 4 : 8;
     l.npieces = (V + l.iters * kLgGroup - 1) / (l.iters * kLgGroup);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    l.off_rmax = up(rows * ((V + 16383) / 16384) * sizeof(float));
-    l.off_rsum = l.off_rmax + up(rows * sizeof(float));
+    l.off_rsum = up(rows * sizeof(float));
     l.off_chunks = l.off_rsum + up(rows * sizeof(unsigned long long));
     l.off_words = l.off_chunks + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
     l.total = l.off_words + up(rows * l.npieces * 2 * sizeof(unsigned long long));
@@ -520,7 +518,7 @@ static int lg_launch(int B, int k, int V, const void* zt, const void* zd, float 
                      hipStream_t s) {
     const LgLayout l = lg_layout(B, k, V);
     char* ws = static_cast<char*>(workspace);
-    float* rmax = reinterpret_cast<float*>(ws + l.off_rmax);
+    float* rmax = reinterpret_cast<float*>(ws);
     unsigned long long* rsum = reinterpret_cast<unsigned long long*>(ws + l.off_rsum);
     unsigned long long* chunks = reinterpret_cast<unsigned long long*>(ws + l.off_chunks);
     unsigned long long* words = reinterpret_cast<unsigned long long*>(ws + l.off_words);

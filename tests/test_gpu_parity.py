@@ -354,14 +354,12 @@ def test_accept_logits_row_sums_are_the_definitions(lotts, oracle, bf16, inv_tem
     zt, zd, draft, u = logit_inputs(cfg, 1.0, salt=77, bf16=bf16)
     rows = cfg.B * (2 * cfg.k + 1)
     up = lambda x: (x + 255) & ~255
-    npieces = (cfg.V + 16383) // 16384
-    off_rmax = up(rows * npieces * 4)                      # piece maxima come first
-    off_rsum = off_rmax + up(rows * 4)
+    off_rsum = up(rows * 4)                                # the row maxima come first
     ws = torch.zeros((lotts.load().spec_accept_logits_workspace_bytes(cfg.B, cfg.k, cfg.V),), dtype=torch.uint8, device=DEV)
     lotts.spec_accept_logits(to_dev(zt, bf16), to_dev(zd, bf16), to_dev(draft), to_dev(u), inv_temperature=inv_temp,
                              workspace=ws)
     torch.cuda.synchronize()
-    rmax = ws[off_rmax:off_rmax + rows * 4].view(torch.float32).cpu().numpy()
+    rmax = ws[:rows * 4].view(torch.float32).cpu().numpy()
     rsum = ws[off_rsum:off_rsum + rows * 8].view(torch.int64).cpu().numpy()
     all_rows = [zt[b, j] for b in range(cfg.B) for j in range(cfg.k + 1)] + \
                [zd[b, j] for b in range(cfg.B) for j in range(cfg.k)]
