@@ -8,38 +8,37 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "liblotts.so")
+LIB_NO_POLLS = os.path.join(_HERE, "liblotts_no_polls.so")
 CALIB = os.path.join(_HERE, "calib_copy")
 PROBE = os.path.join(_HERE, "libread_probe.so")
 SOURCES = ["verify_attention.hip", "spec_accept.hip", "spec_accept_logits.hip", "majority_vote.hip",
            "confidence_vote.hip", "skinny_gemm.hip", "kv_append.hip", "kernel_timer.hip", "greedy_search.cpp"]
 
 
+FLAGS = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+
+
 def build(verbose: bool = False) -> str:
     """Cross-compiles on a machine without a GPU too.  Packed-fp32 code generation is switched
     off for all device code."""
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
-    cmd += [os.path.join(CSRC, s) for s in SOURCES]
-    cmd += ["-o", LIB]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    out = "\n".join(l for l in res.stdout.splitlines() if "not a recognized feature" not in l)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
-    if verbose and out.strip():
-        print(out)
-    # the counter-calibration copy program (profiling aid, not part of the library)
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-           "-packed-fp32-ops", os.path.join(CSRC, "calib_copy.hip"), "-o", CALIB]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
-    # the read-only streaming probe bench.py puts next to the attention kernel (measurement aid, its own library)
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Xclang", "-target-feature", "-Xclang",
-           "-packed-fp32-ops", os.path.join(CSRC, "read_probe.hip"), "-o", PROBE]
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
+    lib = FLAGS + ["-fPIC", "-shared", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
+    sources = [os.path.join(CSRC, s) for s in SOURCES]
+    jobs = [
+        lib + sources + ["-o", LIB],
+        # the same library without patience, for the tests: whatever waits for another workgroup gives up at once
+        lib + ["-DLOTTS_WAIT_POLLS=0"] + sources + ["-o", LIB_NO_POLLS],
+        # the counter-calibration copy program (profiling aid, not part of the library)
+        FLAGS + [os.path.join(CSRC, "calib_copy.hip"), "-o", CALIB],
+        # the read-only streaming probe bench.py puts next to the attention kernel (measurement aid, its own library)
+        FLAGS + ["-fPIC", "-shared", os.path.join(CSRC, "read_probe.hip"), "-o", PROBE],
+    ]
+    running = [subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True) for cmd in jobs]
+    outputs = ["\n".join(l for l in p.communicate()[0].splitlines() if "not a recognized feature" not in l) for p in running]
+    for p, out in zip(running, outputs):
+        if p.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + out)
+    if verbose and outputs[0].strip():
+        print(outputs[0])
     return LIB
 
 

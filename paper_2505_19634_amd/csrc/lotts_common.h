@@ -26,6 +26,17 @@ bool timer_take(hipEvent_t* start, hipEvent_t* stop);
 // a row of logits, about 2^40 for a row of probabilities) never show a tag in their upper half.
 unsigned next_word_tag();
 
+// Polls after which a workgroup that waits for another one's words stops waiting.  The end of such a wait is not certain:
+// every XCD dispatches its own share of a grid, so with two launches in flight one XCD can be full of the first one's
+// waiting workgroups and another one full of the second's.  So nobody depends on it: after these polls (about a
+// millisecond; ordinary waits are a few microseconds) a workgroup does the missing part itself, or leaves its own part to
+// whoever comes last, and gives its place up.  Results are the same either way.  The test build sets 0: everything
+// takes the other way.
+#ifndef LOTTS_WAIT_POLLS
+#define LOTTS_WAIT_POLLS 1024
+#endif
+constexpr int kWaitPolls = LOTTS_WAIT_POLLS;
+
 // Every launch of the library goes through here: no dynamic LDS, the caller's stream.
 #define LOTTS_LAUNCH(kernel, grid, block, stream, ...)                                                        \
     do {                                                                                                      \

@@ -15,14 +15,13 @@
 // Two launches:
 //   lg_stat_kernel      grid (pieces of 8192 or 16384 logits, B * (2k + 1) rows, the pieces of a row next to each other): a
 //                       workgroup reads its piece ONCE into registers, publishes the piece's maximum under this call's tag (two words),
-//                       collects the maxima of the row's other pieces, and forms the integer weight sum from the registers;
-//                       the pieces' sums meet in one 64-bit sum per row by device-scope atomics (integers: any order gives
-//                       the same sum).
+//                       collects the maxima of the row's other pieces (one that stays out for long it forms itself, from
+//                       the logits), and stores the piece's integer weight sum, formed from the registers.
 //   lg_scan_pick_kernel grid (chunks, B): accept tests -> n; 128-bit chunk sums of the weights of row n, published as
 //                       six 8-byte words that each carry 32 bits of a sum and this call's tag.  The workgroup of a
-//                       branch's LAST chunk then collects the branch's sums (it waits only for workgroups with smaller
-//                       block indices, dispatched before it; the wait is bounded) and finds the chunk and the token
-//                       where the integer CDF crosses the threshold, re-reading that one chunk.
+//                       branch's LAST chunk then collects the branch's sums (one that stays out for long it forms itself)
+//                       and finds the chunk and the token where the integer CDF crosses the threshold, re-reading that one
+//                       chunk.
 // Rows start anywhere (the vocabulary need not be a multiple of anything): 16-byte loads take any alignment of the element
 // type, and only the last group of a row is read element by element.
 // Every floating-point operation in this file is rounded on its own, as the definition of the integer weights
@@ -43,6 +42,7 @@ constexpr int kLgMaxPieces = 64;     // pieces of a row: one wavefront collects 
 constexpr int kLgChunk = 2048;       // tokens per chunk: 8 per thread
 constexpr int kLgMaxChunks = 512;    // V <= 2^20
 constexpr int kLgMaxK = kLgThreads;
+constexpr unsigned long long kLgNoSum = ~0ull;  // no sum of a chunk: those are below 2^41
 
 struct RowStat {
     float m;               // row maximum of y
@@ -166,8 +166,6 @@ __device__ __forceinline__ u128 block_excl_scan_u128(u128 v, u128* sh /*[kLgWave
 __device__ __forceinline__ int trow(int b, int j, int k) { return b * (k + 1) + j; }
 __device__ __forceinline__ int drow(int B, int b, int j, int k) { return B * (k + 1) + b * k + j; }
 
-constexpr int kLgSpinLimit = 1 << 23;  // polls of a waiting workgroup before it gives up (seconds: far beyond any real wait)
-
 // one published word: 32 bits of a value under the call's tag
 __device__ __forceinline__ void lg_publish(unsigned long long* slot, unsigned part, unsigned tag) {
     __hip_atomic_store(slot, ((unsigned long long)tag << 32) | part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -178,9 +176,8 @@ __device__ __forceinline__ unsigned long long lg_peek(const unsigned long long* 
 
 // Row statistics in one sweep.  The weights need the row maximum, so the pieces of a row exchange their maxima inside the
 // launch while their logits stay in registers; what a launch boundary and a second read of all logits cost before is one trip
-// through memory now.  A workgroup waits for the other pieces of its own row only, and a row's pieces are neighbours in the
-// grid, dispatched in order: at most one row is in part resident and in part not, and it is next in line for the slots that
-// the complete rows before it give up, so every wait ends (bounded all the same).  The words are cleared by the next launch.
+// through memory now.  A row's pieces are neighbours in the grid, so the others' words are mostly there when they are looked
+// for; that they come at all is not relied on (kWaitPolls).  The words are cleared by the next launch.
 // Bound by the vector unit: 17 instructions a logit that the integer definition fixes, 8 us of the chip's rate for 112 rows x
 // 152064 logits, behind the read that all workgroups start with.  Whole call, us, before (three launches: maxima, sums, scan) ->
 // now: 16 x 7 rows x 152064 bf16 30.9 -> 28.0, fp32 40.5 -> 30.7; 64 x 5 x 151936 63.9 -> 54.2; 5 x 15 rows x 50257 fp32 (rows off
@@ -191,17 +188,20 @@ template <bool BF16, int IT>
 __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V, int npieces, unsigned tag,
                                                              const void* __restrict__ zt, const void* __restrict__ zd,
                                                              float inv_temp, unsigned long long* __restrict__ words,
-                                                             float* __restrict__ rmax, unsigned long long* __restrict__ rsum) {
+                                                             float* __restrict__ rmax, unsigned long long* __restrict__ psum,
+                                                             unsigned long long* __restrict__ slots, long long nslots) {
     __shared__ float sh_m[kLgWaves];
     __shared__ float sh_row;
-    __shared__ unsigned long long sh_s[kLgWaves];
+    __shared__ unsigned long long sh_miss, sh_s[kLgWaves];
     const int r = blockIdx.x / npieces, pc = blockIdx.x - r * npieces, tid = threadIdx.x, lane = tid & (kWave - 1);
     const int nt = B * (k + 1);
     const void* z = r < nt ? zt : zd;
     const size_t base = (size_t)(r < nt ? r : r - nt) * V;
     const int lo = pc * (IT * kLgGroup);
-    if (pc == 0 && tid == 0)  // the pieces add their sums into it once they have seen this piece's maximum
-        __hip_atomic_store(rsum + r, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The next launch's words are cleared, so that a captured call (same tags) can be replayed.  (A piece is at most 8 chunks of
+    // a row, 48 words: a word per thread is enough.)
+    const long long slot = (long long)blockIdx.x * kLgThreads + tid;
+    if (slot < nslots) slots[slot] = 0ull;
     // the whole piece is requested before any of it is used
     Raw8<BF16> raw[IT];
 #pragma unroll
@@ -224,26 +224,47 @@ __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V
         // single leftover of an earlier call -- a row sum, a maximum, a word of another size's layout -- reads as one.
         unsigned long long* row = words + (size_t)r * npieces * 2;
         if (tid == 0) {
-            __builtin_amdgcn_s_waitcnt(0);  // the cleared sum is in memory before this piece's words
             lg_publish(row + pc * 2, __float_as_uint(m), tag);
             lg_publish(row + pc * 2 + 1, __float_as_uint(m), ~tag);
         }
-        if (lane < npieces && lane != pc) {
-            unsigned long long w0 = 0, w1 = 0;
-            for (int spin = 0; spin < kLgSpinLimit; ++spin) {
-                w0 = lg_peek(row + lane * 2);
-                w1 = lg_peek(row + lane * 2 + 1);
-                if ((unsigned)(w0 >> 32) == tag && (unsigned)(w1 >> 32) == ~tag && (unsigned)w0 == (unsigned)w1) break;
+        bool missing = lane < npieces && lane != pc;
+        for (int polls = 0; missing && polls < kWaitPolls; ++polls) {
+            const unsigned long long w0 = lg_peek(row + lane * 2), w1 = lg_peek(row + lane * 2 + 1);
+            if ((unsigned)(w0 >> 32) == tag && (unsigned)(w1 >> 32) == ~tag && (unsigned)w0 == (unsigned)w1) {
+                m = fmaxf(m, __uint_as_float((unsigned)w0));
+                missing = false;
+            } else {
                 __builtin_amdgcn_s_sleep(1);
             }
-            m = fmaxf(m, __uint_as_float((unsigned)w0));
         }
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
-        if (tid == 0) sh_row = m;
+        const unsigned long long miss = __ballot(missing);
+        if (tid == 0) {
+            sh_row = m;
+            sh_miss = miss;
+        }
     }
     __syncthreads();
     m = sh_row;
+    if (sh_miss) {  // uniform over the workgroup: the maxima that have not come, from the logits
+        for (unsigned long long left = sh_miss; left; left &= left - 1) {
+            const int at = (__ffsll((long long)left) - 1) * (IT * kLgGroup);
+#pragma unroll 1
+            for (int it = 0; it < IT; ++it) {
+                float v[8];
+                scale8<BF16>(load_raw8<BF16>(z, base, at + it * kLgGroup + tid * 8, V), inv_temp, v);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m = fmaxf(m, v[e]);
+            }
+        }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
+        if (lane == 0) sh_m[tid / kWave] = m;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kLgWaves; ++w) m = fmaxf(m, sh_m[w]);
+    }
     unsigned long long s = 0;
 #pragma unroll
     for (int it = 0; it < IT; ++it)
@@ -258,50 +279,81 @@ __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V
         unsigned long long tot = 0;
 #pragma unroll
         for (int w = 0; w < kLgWaves; ++w) tot += sh_s[w];
-        atomicAdd(&rsum[r], tot);  // integers: the order of the pieces cannot matter
+        psum[(size_t)r * npieces + pc] = tot;
         if (pc == 0) rmax[r] = m;
     }
 }
 
-// final statistics of a row, as lg_stat_kernel leaves them
-__device__ __forceinline__ RowStat row_stat(const float* rmax, const unsigned long long* rsum, int row) {
-    RowStat st;
-    st.m = rmax[row];
-    st.S = rsum[row];
-    return st;
+// Statistics of branch b's 2k + 1 rows (targets 0 .. k, then drafts) into LDS, from what lg_stat_kernel leaves: the row
+// maxima and the sums of the rows' pieces.  As many lanes to a row as the workgroup has, so that one load latency covers
+// nearly all of it (a thread per row, 16 loads at a time, cost a 16 x 7 rows x 152064 call 1.5 us more).  lg: log2 of the lanes.
+__device__ __forceinline__ void lg_row_stats(int B, int b, int k, int npieces, int lg, const float* rmax, const unsigned long long* psum,
+                                             RowStat* sh_stat) {
+    const int rows = 2 * k + 1;
+    const int sub = threadIdx.x & ((1 << lg) - 1);
+    for (int j = threadIdx.x >> lg; j < rows; j += kLgThreads >> lg) {
+        const int row = j <= k ? trow(b, j, k) : drow(B, b, j - k - 1, k);
+        const unsigned long long* src = psum + (size_t)row * npieces;
+        RowStat st;
+        st.m = rmax[row];
+        st.S = 0;
+        if (npieces <= (1 << lg)) {
+            if (sub < npieces) st.S = src[sub];
+        } else {
+            for (int i0 = sub; i0 < npieces; i0 += 8 << lg) {  // eight loads in flight
+                unsigned long long v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = src[min(i0 + (e << lg), npieces - 1)];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) st.S += i0 + (e << lg) < npieces ? v[e] : 0ull;
+            }
+        }
+        // a row's lanes are here together: their sum (below 2^50, two limbs) in the last of them
+        unsigned s0 = (unsigned)st.S & 0xffffffu, s1 = (unsigned)(st.S >> 24);
+        if (lg > 0) { s0 = dpp_add<0x111, 0xf>(s0); s1 = dpp_add<0x111, 0xf>(s1); }  // row_shr 1, 2, 4, 8
+        if (lg > 1) { s0 = dpp_add<0x112, 0xf>(s0); s1 = dpp_add<0x112, 0xf>(s1); }
+        if (lg > 2) { s0 = dpp_add<0x114, 0xf>(s0); s1 = dpp_add<0x114, 0xf>(s1); }
+        if (lg > 3) { s0 = dpp_add<0x118, 0xf>(s0); s1 = dpp_add<0x118, 0xf>(s1); }
+        if (lg > 4) { s0 = dpp_add<0x142, 0xa>(s0); s1 = dpp_add<0x142, 0xa>(s1); }  // row_bcast 15, 31
+        if (lg > 5) { s0 = dpp_add<0x143, 0xc>(s0); s1 = dpp_add<0x143, 0xc>(s1); }
+        st.S = ((unsigned long long)s1 << 24) + s0;
+        if (sub == (1 << lg) - 1) sh_stat[j] = st;
+    }
 }
 
 // Accepted length of branch b; every thread of the 256-thread workgroup gets it, and the statistics of the two rows at n (of
-// the target row alone when every draft was accepted) with it: thread j loads those of position j for its test.
+// the target row alone when every draft was accepted) with it.
 template <bool BF16>
 __device__ __forceinline__ int lg_accepted_length(int B, int b, int k, int V, const void* zt, const void* zd,
                                                   float inv_temp, const int32_t* draft, const float* u,
-                                                  const float* rmax, const unsigned long long* rsum, int* sh_first,
-                                                  RowStat* sh_p, RowStat* sh_q, RowStat& sp, RowStat& sq) {
+                                                  const float* rmax, const unsigned long long* psum, int npieces,
+                                                  int lg, int* sh_first, RowStat* sh_stat, RowStat& sp, RowStat& sq) {
     const int tid = threadIdx.x;
+    float uv = 0.f, yp = 0.f, yq = 0.f;
+    if (tid < k) {  // on their way while the sums come
+        int x = draft[(size_t)b * k + tid];
+        uv = u[(size_t)b * (k + 1) + tid];
+        x = x < 0 ? 0 : (x >= V ? V - 1 : x);
+        yp = load_y<BF16>(zt, (size_t)trow(b, tid, k) * V + x, inv_temp);
+        yq = load_y<BF16>(zd, ((size_t)b * k + tid) * V + x, inv_temp);
+    }
+    lg_row_stats(B, b, k, npieces, lg, rmax, psum, sh_stat);
+    __syncthreads();
     bool rejected = false;
     if (tid < k) {
-        int x = draft[(size_t)b * k + tid];
-        const float uv = u[(size_t)b * (k + 1) + tid];
-        const RowStat p = row_stat(rmax, rsum, trow(b, tid, k)), q = row_stat(rmax, rsum, drow(B, b, tid, k));
-        x = x < 0 ? 0 : (x >= V ? V - 1 : x);
-        const float yp = load_y<BF16>(zt, (size_t)trow(b, tid, k) * V + x, inv_temp);
-        const float yq = load_y<BF16>(zd, ((size_t)b * k + tid) * V + x, inv_temp);
+        const RowStat p = sh_stat[tid], q = sh_stat[k + 1 + tid];
         const unsigned long long Ep = logit_weight(yp, p.m), Eq = logit_weight(yq, q.m);
         const u128 U = (u128)(unsigned)(uv * 16777216.0f);
         rejected = !(U * Eq * p.S < ((u128)1 << 24) * Ep * q.S);
-        sh_p[tid] = p;
-        sh_q[tid] = q;
     }
     const unsigned long long mask = __ballot(rejected);
     if ((tid & (kWave - 1)) == 0) sh_first[tid / kWave] = mask ? (tid + __ffsll((long long)mask) - 1) : k;
-    const RowStat last = row_stat(rmax, rsum, trow(b, k, k));
     __syncthreads();
     int n = k;
 #pragma unroll
     for (int w = 0; w < kLgWaves; ++w) n = sh_first[w] < n ? sh_first[w] : n;
-    sp = n < k ? sh_p[n] : last;
-    sq = n < k ? sh_q[n] : last;
+    sp = sh_stat[n];
+    sq = n < k ? sh_stat[k + 1 + n] : sp;
     return n;
 }
 
@@ -332,12 +384,12 @@ __device__ __forceinline__ void lg_weights8(const void* zt_row, const void* zd_r
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, int V, int nchunks, int npieces, unsigned tag,
+__global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, int V, int nchunks, int npieces, int lg, unsigned tag,
                                                                   const void* __restrict__ zt, const void* __restrict__ zd,
                                                                   float inv_temp, const int32_t* __restrict__ draft,
                                                                   const float* __restrict__ u,
                                                                   const float* __restrict__ rmax,
-                                                                  const unsigned long long* __restrict__ rsum,
+                                                                  const unsigned long long* __restrict__ psum,  // [rows][npieces]
                                                                   int32_t* __restrict__ accept_len,
                                                                   unsigned long long* __restrict__ words,  // [rows][npieces][2]
                                                                   unsigned long long* __restrict__ slots,  // [B][nchunks][6]
@@ -346,11 +398,11 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
     __shared__ int sh_first[kLgWaves];
     __shared__ u128 sh_w[kLgWaves];
     __shared__ u128 sh_base;
-    __shared__ int sh_chunk, sh_bad;
+    __shared__ int sh_chunk, sh_missing;
     __shared__ u128 sh_wsum[kLgMaxChunks];
     __shared__ unsigned long long sh_psum[kLgMaxChunks];
     const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
-    __shared__ RowStat sh_p[kLgMaxK], sh_q[kLgMaxK];
+    __shared__ RowStat sh_stat[2 * kLgMaxK + 1];
     const float u_last = u[(size_t)b * (k + 1) + k];
     // the words of the launch before are consumed: cleared, so that a captured call (same tags) can be replayed
     for (int i = c * kLgThreads + tid; i < (2 * k + 1) * npieces * 2; i += nchunks * kLgThreads) {
@@ -359,39 +411,47 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
         words[(size_t)row * npieces * 2 + (i - j * npieces * 2)] = 0ull;
     }
     RowStat sp, sq;
-    const int n = lg_accepted_length<BF16>(B, b, k, V, zt, zd, inv_temp, draft, u, rmax, rsum, sh_first, sh_p, sh_q, sp, sq);
+    const int n = lg_accepted_length<BF16>(B, b, k, V, zt, zd, inv_temp, draft, u, rmax, psum, npieces, lg, sh_first, sh_stat, sp, sq);
     bool residual = n < k;
     const size_t es = BF16 ? 2 : 4;
     const void* zt_row = static_cast<const char*>(zt) + (size_t)trow(b, n, k) * V * es;
     const void* zd_row = residual ? static_cast<const char*>(zd) + ((size_t)b * k + n) * V * es : zt_row;
     u128 W[8];
     unsigned long long Ep[8];
-    lg_weights8<BF16>(zt_row, zd_row, c * kLgChunk + tid * 8, V, inv_temp, residual, sp, sq, W, Ep);
-    u128 w = 0;
-    unsigned long long e = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        w += W[i];
-        e += Ep[i];
-    }
-    // both sums over the workgroup at once: the totals stand in lane 63 of every wavefront
-    w = wave_incl_scan_u128(w);
-    const unsigned e0 = wave_incl_scan_u32((unsigned)e & 0xffffffu), e1 = wave_incl_scan_u32((unsigned)(e >> 24));
     __shared__ unsigned long long sh_e[kLgWaves];
-    if ((tid & (kWave - 1)) == kWave - 1) {
-        sh_w[tid / kWave] = w;
-        sh_e[tid / kWave] = (unsigned long long)e0 + ((unsigned long long)e1 << 24);
-    }
-    __syncthreads();
-    unsigned long long* mine = slots + ((size_t)b * nchunks + c) * 6;
-    if (tid == 0) {
+    // sums of a chunk's weights (residual after a rejection) and of its plain ones; complete in thread 0 only
+    auto chunk_sums = [&](int chunk, u128& w, unsigned long long& e) {
+        lg_weights8<BF16>(zt_row, zd_row, chunk * kLgChunk + tid * 8, V, inv_temp, n < k, sp, sq, W, Ep);
         w = 0;
         e = 0;
 #pragma unroll
-        for (int i = 0; i < kLgWaves; ++i) {
-            w += sh_w[i];
-            e += sh_e[i];
+        for (int i = 0; i < 8; ++i) {
+            w += W[i];
+            e += Ep[i];
         }
+        // both sums over the workgroup at once: the totals stand in lane 63 of every wavefront
+        w = wave_incl_scan_u128(w);
+        const unsigned e0 = wave_incl_scan_u32((unsigned)e & 0xffffffu), e1 = wave_incl_scan_u32((unsigned)(e >> 24));
+        if ((tid & (kWave - 1)) == kWave - 1) {
+            sh_w[tid / kWave] = w;
+            sh_e[tid / kWave] = (unsigned long long)e0 + ((unsigned long long)e1 << 24);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            w = 0;
+            e = 0;
+#pragma unroll
+            for (int i = 0; i < kLgWaves; ++i) {
+                w += sh_w[i];
+                e += sh_e[i];
+            }
+        }
+    };
+    u128 w;
+    unsigned long long e;
+    chunk_sums(c, w, e);
+    unsigned long long* mine = slots + ((size_t)b * nchunks + c) * 6;
+    if (tid == 0) {
         lg_publish(mine + 0, (unsigned)w, tag);
         lg_publish(mine + 1, (unsigned)(w >> 32), tag);
         lg_publish(mine + 2, (unsigned)(w >> 64), tag);
@@ -401,35 +461,45 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
     }
     if (c != nchunks - 1) return;  // uniform over the workgroup
 
-    // ---- the branch's last chunk collects: it waits only for workgroups dispatched before it ----
+    // ---- the branch's last chunk collects ----
     if (tid == 0) {
         accept_len[b] = n;
         if (priv_len) priv_len[b] -= k - n;  // the rejected drafts leave the branch's KV cache
-        sh_bad = 0;
+        sh_wsum[c] = w;
+        sh_psum[c] = e;
+        sh_missing = 0;
     }
     __syncthreads();
-    for (int j = tid; j < nchunks; j += kLgThreads) {
-        unsigned long long* en = slots + ((size_t)b * nchunks + j) * 6;
-        unsigned long long v[6];
+    for (int j = tid; j < c; j += kLgThreads) {
+        const unsigned long long* en = slots + ((size_t)b * nchunks + j) * 6;
+        unsigned long long v[6] = {};
         bool ok = false;
-        for (int spin = 0; spin < kLgSpinLimit; ++spin) {
+        for (int polls = 0; !ok && polls < kWaitPolls; ++polls) {
             ok = true;
 #pragma unroll
             for (int i = 0; i < 6; ++i) {
                 v[i] = lg_peek(en + i);
                 ok = ok && (unsigned)(v[i] >> 32) == tag;
             }
-            if (ok) break;
-            __builtin_amdgcn_s_sleep(1);
+            if (!ok) __builtin_amdgcn_s_sleep(1);
         }
-        if (!ok) sh_bad = 1;  // never seen in practice: the producers were dispatched first and wait for nothing
+        if (!ok) sh_missing = 1;
         sh_wsum[j] = (u128)(unsigned)v[0] | ((u128)(unsigned)v[1] << 32) | ((u128)(unsigned)v[2] << 64) | ((u128)(unsigned)v[3] << 96);
-        sh_psum[j] = (unsigned long long)(unsigned)v[4] | ((unsigned long long)(unsigned)v[5] << 32);
-#pragma unroll
-        for (int i = 0; i < 6; ++i)  // consumed: cleared, so that a captured launch (same tag) can be replayed
-            __hip_atomic_store(en + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh_psum[j] = ok ? (unsigned long long)(unsigned)v[4] | ((unsigned long long)(unsigned)v[5] << 32) : kLgNoSum;
     }
     __syncthreads();
+    if (sh_missing) {  // uniform over the workgroup: the sums that have not come, from the logits
+        for (int j = 0; j < c; ++j) {
+            if (sh_psum[j] != kLgNoSum) continue;
+            chunk_sums(j, w, e);
+            __syncthreads();  // everybody has seen the mark of chunk j, thread 0 has read the wavefronts' parts
+            if (tid == 0) {
+                sh_wsum[j] = w;
+                sh_psum[j] = e;
+            }
+        }
+        __syncthreads();
+    }
     // kLgMaxChunks = 2 * kLgThreads: every thread owns two consecutive chunk sums
     const int c0 = tid * 2;
     u128 w0 = 0, w1 = 0;
@@ -449,7 +519,7 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
         w1 = p1;
         excl = block_excl_scan_u128(w0 + w1, sh_w, Z);
     }
-    if (Z == 0 || sh_bad) {  // a row without any weight (all logits -inf, or +inf / NaN among them): no token; uniform
+    if (Z == 0) {  // a row without any weight (all logits -inf, or +inf / NaN among them): no token; uniform
         if (tid == 0) next_token[b] = -1;
         return;
     }
@@ -488,10 +558,10 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
 
 
 struct LgLayout {
-    size_t off_rsum, off_chunks, off_words, total;
+    size_t off_psum, off_chunks, off_words, total;
     int nchunks, npieces, iters;
 };
-// [row maxima][row sums][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces: 2 per (row, piece)]
+// [row maxima][sums of the pieces][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces: 2 per (row, piece)]
 static inline LgLayout lg_layout(int B, int k, int V) {
     LgLayout l;
     l.nchunks = (V + kLgChunk - 1) / kLgChunk;
@@ -499,8 +569,8 @@ static inline LgLayout lg_layout(int B, int k, int V) {
     l.iters = V <= 4 * kLgGroup * kLgMaxPieces && rows * kLgMaxPieces <= 0x7fffffff ? 4 : 8;
     l.npieces = (V + l.iters * kLgGroup - 1) / (l.iters * kLgGroup);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    l.off_rsum = up(rows * sizeof(float));
-    l.off_chunks = l.off_rsum + up(rows * sizeof(unsigned long long));
+    l.off_psum = up(rows * sizeof(float));
+    l.off_chunks = l.off_psum + up(rows * l.npieces * sizeof(unsigned long long));
     l.off_words = l.off_chunks + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
     l.total = l.off_words + up(rows * l.npieces * 2 * sizeof(unsigned long long));
     return l;
@@ -519,21 +589,24 @@ static int lg_launch(int B, int k, int V, const void* zt, const void* zd, float 
     const LgLayout l = lg_layout(B, k, V);
     char* ws = static_cast<char*>(workspace);
     float* rmax = reinterpret_cast<float*>(ws);
-    unsigned long long* rsum = reinterpret_cast<unsigned long long*>(ws + l.off_rsum);
+    unsigned long long* psum = reinterpret_cast<unsigned long long*>(ws + l.off_psum);
     unsigned long long* chunks = reinterpret_cast<unsigned long long*>(ws + l.off_chunks);
     unsigned long long* words = reinterpret_cast<unsigned long long*>(ws + l.off_words);
     const unsigned tag_s = next_word_tag(), tag_c = next_word_tag();
+    const long long nslots = (long long)B * l.nchunks * 6;
     const dim3 sgrid((unsigned)((long long)l.npieces * B * (2 * k + 1)));  // (piece, row) pairs, row-major
     if (l.iters == 4)
         LOTTS_LAUNCH((lg_stat_kernel<BF16, 4>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, tag_s, zt, zd, inv_temp, words,
-                     rmax, rsum);
+                     rmax, psum, chunks, nslots);
     else
         LOTTS_LAUNCH((lg_stat_kernel<BF16, 8>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, tag_s, zt, zd, inv_temp, words,
-                     rmax, rsum);
+                     rmax, psum, chunks, nslots);
     const int rc = check_launch();
     if (rc != LOTTS_OK) return rc;
-    LOTTS_LAUNCH((lg_scan_pick_kernel<BF16>), dim3(l.nchunks, B), dim3(kLgThreads), s, B, k, V, l.nchunks, l.npieces, tag_c, zt,
-                 zd, inv_temp, draft, u, rmax, rsum, accept_len, words, chunks, next_token, priv_len);
+    int lg = 6;  // lanes that add up a row's pieces: not more than there are pieces, all rows at once if they fit
+    while (lg > 0 && (((2 * k + 1) << lg) > kLgThreads || (1 << lg) >= 2 * l.npieces)) --lg;
+    LOTTS_LAUNCH((lg_scan_pick_kernel<BF16>), dim3(l.nchunks, B), dim3(kLgThreads), s, B, k, V, l.nchunks, l.npieces, lg, tag_c, zt,
+                 zd, inv_temp, draft, u, rmax, psum, accept_len, words, chunks, next_token, priv_len);
     return check_launch();
 }
 

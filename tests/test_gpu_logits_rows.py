@@ -58,3 +58,20 @@ def test_captured_call_replayed_on_changing_logits(oracle):
         call()                                    # an eager call on the same workspace in between
         torch.cuda.synchronize()
         assert np.array_equal(n.cpu().numpy(), want[i][0]) and np.array_equal(t.cpu().numpy(), want[i][1]), i
+
+
+def test_calls_side_by_side(oracle):
+    """Calls on several streams overlap, and their launches may find any part of the chip taken by the others' waiting workgroups:
+    every one ends with the right result."""
+    import paper_2505_19634_amd as lotts
+    cfg = S.CONFIGS["C2"].with_(B=16, V=152064, k=3)
+    sets = [logit_inputs(cfg, 1.0, salt=i, bf16=True) for i in range(3)]
+    want = [oracle.spec_accept_logits(*s) for s in sets]
+    d = [[to_dev(x, bf) for x, bf in zip(s, (True, True, False, False))] for s in sets]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in sets]
+    got = [[lotts.spec_accept_logits(*x, stream=s) for x, s in zip(d, streams)] for _ in range(20)]
+    torch.cuda.synchronize()
+    for i, (n_ref, t_ref) in enumerate(want):
+        for round_ in got:
+            assert np.array_equal(round_[i][0].cpu().numpy(), n_ref) and np.array_equal(round_[i][1].cpu().numpy(), t_ref), i

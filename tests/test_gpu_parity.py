@@ -346,7 +346,7 @@ def test_accept_logits_degenerate(lotts, oracle):
 
 @pytest.mark.parametrize("bf16,inv_temp", [(False, 0.8), (True, 1.3), (True, 1.0)])
 def test_accept_logits_row_sums_are_the_definitions(lotts, oracle, bf16, inv_temp):
-    """White box: the integer weight sum S and the maximum of every row, as the launches leave them in the
+    """White box: the integer weight sum S (by pieces) and the maximum of every row, as the launches leave them in the
     workspace, against the oracle's bit for bit.  The outputs alone hardly see a weight that is off by one (a
     token changes only if the threshold falls into that sliver of the CDF), and that is what a scaling and a
     subtraction merged into one fused operation -- one rounding instead of the definition's two -- produces."""
@@ -354,13 +354,13 @@ def test_accept_logits_row_sums_are_the_definitions(lotts, oracle, bf16, inv_tem
     zt, zd, draft, u = logit_inputs(cfg, 1.0, salt=77, bf16=bf16)
     rows = cfg.B * (2 * cfg.k + 1)
     up = lambda x: (x + 255) & ~255
-    off_rsum = up(rows * 4)                                # the row maxima come first
+    off_psum, npieces = up(rows * 4), (cfg.V + 8191) // 8192   # the row maxima come first, then the sums of a row's pieces
     ws = torch.zeros((lotts.load().spec_accept_logits_workspace_bytes(cfg.B, cfg.k, cfg.V),), dtype=torch.uint8, device=DEV)
     lotts.spec_accept_logits(to_dev(zt, bf16), to_dev(zd, bf16), to_dev(draft), to_dev(u), inv_temperature=inv_temp,
                              workspace=ws)
     torch.cuda.synchronize()
     rmax = ws[:rows * 4].view(torch.float32).cpu().numpy()
-    rsum = ws[off_rsum:off_rsum + rows * 8].view(torch.int64).cpu().numpy()
+    rsum = ws[off_psum:off_psum + rows * npieces * 8].view(torch.int64).view(rows, npieces).sum(1).cpu().numpy()
     all_rows = [zt[b, j] for b in range(cfg.B) for j in range(cfg.k + 1)] + \
                [zd[b, j] for b in range(cfg.B) for j in range(cfg.k)]
     for r, z in enumerate(all_rows):
