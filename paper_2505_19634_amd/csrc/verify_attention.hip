@@ -28,8 +28,8 @@
 //       Who merges the partials of a row depends on how many there are: of two, the item that finishes later (arrivals are
 //       counted per (KV head, branch) in a cell that carries the call's tag: what an earlier call left there, complete
 //       or not, counts as zero arrivals); of more, merge workgroups at the end of the grid, which wait for a flag of
-//       every partial they read (they only ever wait for workgroups with smaller block indices, which were dispatched before
-//       them) and share the rows among them.  Partials cross workgroups -- and XCDs,
+//       every partial they read and share the rows among them; one whose flags stay out for long leaves, and the item that
+//       delivers the last partial merges in its place.  Partials cross workgroups -- and XCDs,
 //       each with its own L2 -- inside one launch, so they are written and read with 16-byte
 //       buffer accesses that carry the device-scope cache policy (performed at the memory side of
 //       the L2s); nothing is ever flushed or invalidated cache-wide.
@@ -175,8 +175,17 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
         pl.mpp = ceil_div(GR, pl.rpm);
     };
     if (pl.merge == kMergeGroups) {
-        rows_per_merger(kAttnThreads * pl.nqt);
-        if ((long long)d.B * d.Hkv * pl.mpp * pl.nsplit_priv > kMaxCounters) pl.merge = kMergeLaunch;  // flags would not fit
+        const int threads = kAttnThreads * pl.nqt;
+        rows_per_merger(threads);
+        // Cells of the merge workgroups: a flag per key share and a count.  Where only the counts are too many (64 shares for 256
+        // merge workgroups), twice the rows for half of the workgroups.
+        auto cells = [&](int per_merger) { return (long long)d.B * d.Hkv * pl.mpp * per_merger; };
+        const bool flags_fit = cells(pl.nslots) <= kMaxCounters;
+        while (flags_fit && cells(pl.nslots + 1) > kMaxCounters && pl.rpm * 2 * (d.D / 4) <= threads) {
+            pl.rpm *= 2;
+            pl.mpp = ceil_div(GR, pl.rpm);
+        }
+        if (cells(pl.nslots + 1) > kMaxCounters) pl.merge = kMergeLaunch;
     }
     if (pl.merge == kMergeLaunch) rows_per_merger(kAttnThreads);
     pl.n_merge = pl.merge == kMergeGroups ? d.B * d.Hkv * pl.mpp : 0;
@@ -200,9 +209,10 @@ static inline size_t part_ml_elems(const lotts_attn_desc& d, const AttnPlan& pl)
 // of this process; an arriving workgroup first raises the cell to (tag, 0) with an atomic maximum,
 // then adds one.  A cell left at zero (a fresh zero-filled buffer, or the reset the last arriver
 // does) and a cell left behind by an earlier call that never completed both start the new call
-// at zero arrivals, so no call can poison the buffer for the next one.  With merge workgroups the same cells are flags, one
-// per (KV head, branch, merge workgroup, key share): an item stores (tag << 16) | 1 into its flag of every merge workgroup
-// that reads its partial, and that workgroup puts the zero back; any other content counts as not arrived.
+// at zero arrivals, so no call can poison the buffer for the next one.  With merge workgroups the same cells are, for
+// every merge workgroup of a (KV head, branch), one flag per key share and one arrival cell.  An item sets its flag of every
+// merge workgroup that reads its partial to (tag << 16) | 1; a merge workgroup that leaves sets its flags to (tag << 16) | 2;
+// whoever merges puts the zeros back.  Any other content counts as not arrived.
 constexpr int kTagShift = 16;            // arrivals per cell < 2^16, checked on the host
 static std::atomic<unsigned long long> g_call_tag{0};
 static inline size_t workspace_layout(const lotts_attn_desc& d, const AttnPlan& pl, size_t* off_o, size_t* off_ml) {
@@ -333,30 +343,16 @@ __device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buf
 // A thread takes every SG-th slot, eight 16-byte loads in flight; the groups meet in LDS and are added in group order, so
 // the result does not depend on timing.  A row's slots are read by many threads at once: with one thread per quad the
 // reads of 64 slots were eight dependent rounds and the launch took 9 us more than at 16 slots.
-// DEV: inside the attention launch (merge workgroups): wait for the flags, device-scope loads.
+// DEV: inside the attention launch: device-scope loads.  keep = false: nothing is stored (known only late: see merger_stays).
 // ---------------------------------------------------------------------------------------------
-constexpr int kSpinLimit = 1 << 23;  // polls of a merge workgroup before it gives up: seconds, whatever else keeps the items from starting
 template <int D, bool DEV, int THREADS>
-__device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char* lds, int kvh, int b, int chunk) {
+__device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char* lds, int kvh, int b, int chunk, bool keep) {
     constexpr int F4 = D / 4, CH = 8;
     const AttnPlan& pl = prm.plan;
     const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
     const int tid = threadIdx.x, ns = pl.nslots, rpm = pl.rpm;
     const int c4 = tid % F4, r = (tid / F4) & (rpm - 1), sg = tid / (F4 * rpm), SG = THREADS / (F4 * rpm);
     const int row = chunk * rpm + r;
-    if (DEV) {
-        // Every item of this (KV head, branch) has a smaller block index, so it was dispatched before this workgroup, and an
-        // item waits for nobody: the flags come.  Bounded all the same.
-        if (tid < ns) {  // ns <= kMaxSplit: lanes of the first wavefront
-            unsigned long long* flag = prm.counters + ((size_t)(kvh * prm.B + b) * pl.mpp + chunk) * ns + tid;
-            for (int spin = 0; spin < kSpinLimit; ++spin) {
-                if (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == prm.tag + 1) break;
-                __builtin_amdgcn_s_sleep(4);
-            }
-            __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // a captured launch is replayed with the same tag
-        }
-        __syncthreads();
-    }
     float M = -INFINITY, Lsum = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     if (row < prm.GR) {
@@ -408,7 +404,56 @@ __device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char*
         }
         M = Mg; Lsum = l; o = t;
     }
-    if (row < prm.GR) store_merged(prm, kvh, b, row, c4, o, M, Lsum);
+    if (row < prm.GR && keep) store_merged(prm, kvh, b, row, c4, o, M, Lsum);
+}
+
+// Cells of a merge workgroup: a flag per key share, and, behind all flags, the count that is used once it has left.
+__device__ __forceinline__ unsigned long long* merger_flags(const AttnParams& prm, int kvh, int b, int chunk) {
+    return prm.counters + ((kvh * prm.B + b) * prm.plan.mpp + chunk) * prm.plan.nslots;
+}
+__device__ __forceinline__ unsigned long long* merger_count(const AttnParams& prm, int kvh, int b, int chunk) {
+    return prm.counters + prm.plan.n_merge * prm.plan.nslots + (kvh * prm.B + b) * prm.plan.mpp + chunk;
+}
+// whoever merges takes the cells down: a captured launch is replayed with the same tag
+__device__ __forceinline__ void cell_clear(unsigned long long* cell) {
+    __hip_atomic_store(cell, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Counts n partials of a merge workgroup that has left; true for whoever counts the last one.  (Raised to this call's tag first, as
+// the arrival cells are.)
+__device__ __forceinline__ bool count_partials(const AttnParams& prm, unsigned long long* count, int n) {
+    atomicMax(count, prm.tag);
+    return atomicAdd(count, (unsigned long long)n) + n == prm.tag + prm.plan.nslots;
+}
+// A merge workgroup: all its flags have come (true), or it leaves and takes its marks with it: it exchanges every flag for one, and
+// so does every item that raises a flag, so each side knows from what it finds there which of the two came first.  The
+// partials that were there it counts, the others are counted by the items that find a mark; who counts the last one merges.
+// The answer is in LDS, so that the first loads of the merge need not wait for it.
+__device__ __forceinline__ bool merger_stays(const AttnParams& prm, int* sh, int kvh, int b, int chunk) {
+    const int tid = threadIdx.x, ns = prm.plan.nslots;
+    if (tid < kWave) {  // ns <= kMaxSplit: a lane per flag
+        unsigned long long* flags = merger_flags(prm, kvh, b, chunk);
+        bool missing = tid < ns;
+        // (eight times the patience: with two to a unit these workgroups start together with the items)
+        for (int polls = 0; missing && polls < 8 * kWaitPolls; ++polls) {
+            missing = __hip_atomic_load(flags + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != prm.tag + 1;
+            if (missing) __builtin_amdgcn_s_sleep(4);
+        }
+        bool all = __ballot(missing) == 0;
+        if (!all) {
+            const bool there = tid < ns && atomicExch(flags + tid, prm.tag + 2) == prm.tag + 1;
+            const int n = __popcll(__ballot(there));
+            if (tid == 0 && n > 0) {
+                unsigned long long* count = merger_count(prm, kvh, b, chunk);
+                all = count_partials(prm, count, n);
+                if (all) cell_clear(count);
+            }
+            all = __ballot(all) != 0;
+        }
+        if (tid == 0) *sh = all;
+        if (all && tid < ns) cell_clear(flags + tid);
+    }
+    __syncthreads();
+    return *sh != 0;
 }
 
 __device__ __forceinline__ bf16x8 load_bf16x8(const __bf16* ptr) {
@@ -445,7 +490,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     static_assert(OBUF <= SLAB, "the merge buffer reuses the wavefront's slab");
     __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnWaves * GROUPS * SLAB];
     __shared__ float sh_m[kAttnWaves * GROUPS][kRowTile];
-    __shared__ float sh_l[kAttnWaves * GROUPS][kRowTile];
+    __shared__ __attribute__((aligned(8))) float sh_l[kAttnWaves * GROUPS][kRowTile];
     __shared__ int sh_pair[kAttnWaves];  // GROUPS = 2: half tiles stored by the pair of wavefronts w and w + 4
 
     const int tid = threadIdx.x, wave_all = tid / kWave, lane = tid & (kWave - 1);
@@ -463,7 +508,9 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     if (id >= pl.n_priv_items + pl.n_pre_items) {  // a merge workgroup
         id -= pl.n_priv_items + pl.n_pre_items;
         const int kvh = id % prm.Hkv, rest = id / prm.Hkv;
-        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, rest / pl.mpp, rest % pl.mpp);
+        const int b = rest / pl.mpp, chunk = rest % pl.mpp;
+        const bool stays = merger_stays(prm, reinterpret_cast<int*>(sh_l), kvh, b, chunk);
+        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b, chunk, stays);
         return;
     }
     const bool is_private = id < pl.n_priv_items;
@@ -804,9 +851,24 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (pl.merge == kMergeGroups) {  // the item's partial is in memory: raise its flag for each of the branch's merge workgroups
-        if (tid < pl.mpp)
-            __hip_atomic_store(prm.counters + ((size_t)(kvh * prm.B + b_item) * pl.mpp + tid) * pl.nslots + slot, prm.tag + 1,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned long long* sh_mine = reinterpret_cast<unsigned long long*>(sh_l);  // free again
+        if (tid < kWave) {  // mpp <= rows of an item <= 64
+            bool mine = false;
+            if (tid < pl.mpp) {
+                if (atomicExch(merger_flags(prm, kvh, b_item, tid) + slot, prm.tag + 1) == prm.tag + 2)  // that workgroup has left
+                    mine = count_partials(prm, merger_count(prm, kvh, b_item, tid), 1);
+            }
+            const unsigned long long all = __ballot(mine);
+            if (tid == 0) *sh_mine = all;
+        }
+        __syncthreads();
+        for (unsigned long long left = *sh_mine; left; left &= left - 1) {  // uniform over the workgroup
+            const int c = __ffsll((long long)left) - 1;
+            if (tid < pl.nslots) cell_clear(merger_flags(prm, kvh, b_item, c) + tid);
+            if (tid == 0) cell_clear(merger_count(prm, kvh, b_item, c));
+            merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b_item, c, true);
+            __syncthreads();
+        }
         return;
     }
     int* sh_last = reinterpret_cast<int*>(sh_l);  // free again; kAttnWaves * kRowTile >= rows of an item
@@ -867,7 +929,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
 template <int D>
 __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(const AttnParams prm) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnThreads * (sizeof(float4) + sizeof(float2))];
-    merge_rows<D, false, kAttnThreads>(prm, lds, blockIdx.y % prm.Hkv, blockIdx.y / prm.Hkv, blockIdx.x);
+    merge_rows<D, false, kAttnThreads>(prm, lds, blockIdx.y % prm.Hkv, blockIdx.y / prm.Hkv, blockIdx.x, true);
 }
 
 // ---------------------------------------------------------------------------------------------

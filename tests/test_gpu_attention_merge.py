@@ -22,6 +22,7 @@ CASES = [
     BF.with_(B=8, Hq=16, Hkv=2, k=4, P=512, L=2048), BF.with_(B=12, Hq=40, Hkv=8, k=3, P=100, L=900),
     BF.with_(B=4, Hq=40, Hkv=8, k=8, P=64, L=1500), BF.with_(B=11, Hq=16, Hkv=4, D=64, k=6, P=65, L=1000),
     BF.with_(B=12, Hq=16, Hkv=8, D=64, k=2, P=50, L=2100), BF.with_(B=7, Hq=8, Hkv=4, D=64, k=15, P=31, L=700),
+    BF.with_(B=2, Hq=16, Hkv=2, k=7, P=60, L=9000),                    # as many cells as there are: two rows each instead of one
     # a launch of its own: few pairs, up to 4096 tokens; prefix items; several row groups
     BF.with_(B=1, Hq=8, Hkv=4, k=2, P=96, L=4000), BF.with_(B=2, Hq=16, Hkv=2, k=4, P=1000, L=3000),
     BF.with_(B=3, Hq=24, Hkv=2, k=7, P=100, L=1400),
@@ -67,6 +68,24 @@ def test_merge_flags_are_cleared_for_a_replay(oracle):
         assert torch.equal(out, want[i]), i
         assert torch.equal(got2, want2)
     assert int(ws[:131072].to(torch.int32).sum()) == 0  # every cell is down again
+
+
+def test_merge_workgroups_side_by_side():
+    """Calls on several streams overlap, and the merge workgroups of one may hold the places that the items of another need (with two
+    row tiles a workgroup fills a compute unit): every call ends with the result it has alone."""
+    import paper_2505_19634_amd as lotts
+    cfgs = [BF.with_(B=8, Hq=16, Hkv=2, k=4, P=512, L=2048), BF.with_(B=4, Hq=40, Hkv=8, k=8, P=64, L=1500),
+            BF.with_(B=1, Hq=16, Hkv=2, k=7, P=0, L=7000)]
+    sets = [attn_to_dev(c, S.attention_inputs(c)) for c in cfgs]
+    call = lambda d, **kw: lotts.verify_attention(*(d[n] for n in ("Q", "Kpre", "Vpre", "Kpriv", "Vpriv", "priv_len")), **kw)
+    sets[2]["Kpre"] = sets[2]["Vpre"] = None
+    want = [call(d).clone() for d in sets]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in sets]
+    got = [[call(d, stream=s) for d, s in zip(sets, streams)] for _ in range(20)]
+    torch.cuda.synchronize()
+    for round_ in got:
+        assert all(torch.equal(o, w) for o, w in zip(round_, want))
 
 
 @pytest.mark.parametrize("D", [64, 128])

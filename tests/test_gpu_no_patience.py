@@ -8,8 +8,9 @@ import pytest
 import torch
 
 import synth_inputs as S
-from gpu_util import DEV, to_dev
-from test_gpu_parity import logit_inputs
+from gpu_util import DEV, attn_to_dev, to_dev
+from test_gpu_attention_merge import CASES
+from test_gpu_parity import BF, logit_inputs, run_attention
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +64,35 @@ def test_logits_replayed(lotts, oracle):
             again()
             torch.cuda.synchronize()
             assert np.array_equal(n.cpu().numpy(), want[i][0]) and np.array_equal(t.cpu().numpy(), want[i][1]), i
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: "B%d_k%d_Hq%d_Hkv%d_D%d_P%d_L%d" % (c.B, c.k, c.Hq, c.Hkv, c.D, c.P, c.L))
+def test_attention(lotts, oracle, cfg):
+    lens = np.linspace(cfg.k + 1, cfg.L, cfg.B).astype(np.int32) if cfg.B > 1 else None
+    run_attention(lotts, oracle, cfg, priv_len=lens)
+
+
+def test_attention_replayed(lotts):
+    """Whoever merges takes the flags and the words of the merge workgroups that left down again, and adds in the same order."""
+    cfg = BF.with_(B=8, Hq=16, Hkv=2, k=4, P=512, L=2048)
+    sets = [attn_to_dev(cfg, S.attention_inputs(cfg, salt=i)) for i in range(3)]
+    names = ("Q", "Kpre", "Vpre", "Kpriv", "Vpriv", "priv_len")
+    want = [lotts.verify_attention(*(d[n] for n in names)).clone() for d in sets]
+    buf = {n: sets[0][n].clone() for n in names}
+    out = torch.empty_like(buf["Q"])
+    ws = torch.zeros(16 << 20, dtype=torch.uint8, device=DEV)
+    call = lambda: lotts.verify_attention(*(buf[n] for n in names), out=out, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for i in (1, 2, 0, 1):
+        for n in names:
+            buf[n].copy_(sets[i][n])
+        for again in (graph.replay, call, graph.replay):
+            out.zero_()
+            again()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want[i]), i
+            assert int(ws[:131072].to(torch.int32).sum()) == 0
