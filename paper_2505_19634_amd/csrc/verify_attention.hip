@@ -34,7 +34,7 @@
 //       buffer accesses that carry the device-scope cache policy (performed at the memory side of
 //       the L2s); nothing is ever flushed or invalidated cache-wide.
 //   attn_merge_kernel     second launch, where prefix items or several row groups add partials of their own and a row has many
-//       of them, and for the smallest contexts.
+//       of them.
 // fp32 path: attn_f32_kernel, plain fp32 VALU arithmetic, one workgroup per output row; it
 // exists for exactness checks on small fp32 problems.
 // Two entry points share all of this: verify_attention (the caller brings the workspace) and
@@ -159,15 +159,14 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
     //    with merge workgroups);
     //  - merge workgroups at the end of the grid share the rows of a (KV head, branch) and wait for the flags of its partials:
     //    1 x 2 heads x 8192 tokens, 64 shares, 10.6 us against 11.7 with a launch of its own (and 15.6 with 16 shares);
-    //    8 x 8 heads x 4300 tokens, 4 shares, 27.4 us against 29.3 with the merge by the last arriver;
-    //  - a second launch where prefix items or several row groups add partials of their own, and for contexts up to 4096
-    //    tokens on at most four (KV head, branch) pairs: 2 x 2 heads x 4064 tokens 10.7 us, with merge workgroups 9.9 -- the
-    //    kernel timer's callers see this size as the pair of launches that it was;
+    //    8 x 8 heads x 4300 tokens, 4 shares, 27.4 us against 29.3 with the merge by the last arriver; short contexts too:
+    //    2 x 2 heads x 4064 tokens 10.2 us against 11.0 with a launch of its own, 1 x 2 x 800 9.2 either way;
+    //  - a second launch where prefix items or several row groups add partials of their own;
     //  - the last arriver, ONE workgroup at one unit's share of the bandwidth, where those shapes leave a few tens of KB.
     if (pl.nslots == 1) pl.merge = kMergeNone;  // no prefix items, no key shares
     else if (simple && pl.nslots == 2 && pl.nqt == 1) pl.merge = kMergePair;
-    else if (simple && !(base <= 4 && tiles_priv + tiles_pre <= 128)) pl.merge = kMergeGroups;
-    else pl.merge = !simple && (long long)pl.nslots * GR * d.D * 4 <= 48 * 1024 ? kMergeLast : kMergeLaunch;
+    else if (simple) pl.merge = kMergeGroups;
+    else pl.merge = (long long)pl.nslots * GR * d.D * 4 <= 48 * 1024 ? kMergeLast : kMergeLaunch;
     // rows per merge workgroup: as few as leave at most one workgroup per unit in all
     auto rows_per_merger = [&](int threads) {
         pl.rpm = 1;

@@ -23,8 +23,9 @@ CASES = [
     BF.with_(B=4, Hq=40, Hkv=8, k=8, P=64, L=1500), BF.with_(B=11, Hq=16, Hkv=4, D=64, k=6, P=65, L=1000),
     BF.with_(B=12, Hq=16, Hkv=8, D=64, k=2, P=50, L=2100), BF.with_(B=7, Hq=8, Hkv=4, D=64, k=15, P=31, L=700),
     BF.with_(B=2, Hq=16, Hkv=2, k=7, P=60, L=9000),                    # as many cells as there are: two rows each instead of one
-    # a launch of its own: few pairs, up to 4096 tokens; prefix items; several row groups
-    BF.with_(B=1, Hq=8, Hkv=4, k=2, P=96, L=4000), BF.with_(B=2, Hq=16, Hkv=2, k=4, P=1000, L=3000),
+    BF.with_(B=1, Hq=8, Hkv=4, k=2, P=96, L=4000),                     # few pairs, up to 4096 tokens
+    # a launch of its own: prefix items; several row groups
+    BF.with_(B=2, Hq=16, Hkv=2, k=4, P=1000, L=3000),
     BF.with_(B=3, Hq=24, Hkv=2, k=7, P=100, L=1400),
 ]
 

@@ -54,7 +54,7 @@ SMALL_ATTN = [
     BF.with_(B=37, Hq=4, Hkv=4, k=1, P=300, L=65),                   # many branches stacked on the prefix
     BF.with_(B=8, P=2048, L=512),                                    # long prefix: stacked plan, several prefix splits
     BF.with_(B=5, Hq=16, Hkv=2, k=4, P=1500, L=300),                 # stacked plan with two row tiles per item
-    BF.with_(B=2, Hq=16, Hkv=2, k=2, P=64, L=4000),                  # few (head, branch) pairs: 16 key splits, separate merge launch
+    BF.with_(B=2, Hq=16, Hkv=2, k=2, P=64, L=4000),                  # few (head, branch) pairs: many key splits
     BF.with_(B=3, Hq=8, Hkv=8, k=0, P=16, L=1000),                   # k = 0 with folded prefix shorter than a tile
 ]
 
@@ -667,11 +667,16 @@ def test_kernel_timer_counts_launches_and_changes_no_result(lotts, oracle):
     with lotts.kernel_timer(4) as t:
         pass
     assert t.ms == []
-    few = BF.with_(B=2, Hq=16, Hkv=2, k=2, P=64, L=4000)   # few pairs: many partials per row, a second launch merges
+    few = BF.with_(B=2, Hq=16, Hkv=2, k=2, P=1500, L=4000)  # prefix items: many partials per row, a second launch merges
+    one = BF.with_(B=2, Hq=16, Hkv=2, k=2, P=64, L=4000)    # few pairs, a short context: merged in the launch
     d2 = attn_to_dev(few, S.attention_inputs(few))
     with lotts.kernel_timer(4) as t:
         lotts.verify_attention(d2["Q"], d2["Kpre"], d2["Vpre"], d2["Kpriv"], d2["Vpriv"], d2["priv_len"])
     assert len(t.ms) == 2 and min(t.ms) > 0.0
+    d3 = attn_to_dev(one, S.attention_inputs(one))
+    with lotts.kernel_timer(4) as t:
+        lotts.verify_attention(d3["Q"], d3["Kpre"], d3["Vpre"], d3["Kpriv"], d3["Vpriv"], d3["priv_len"])
+    assert len(t.ms) == 1
     assert torch.equal(O0, attn())                       # timer off again
 
 

@@ -26,7 +26,7 @@ def test_noalloc_entry_point_matches_the_workspace_one(oracle):
     from paper_2505_19634_amd import binding
     lib = binding.load()
     big = S.CONFIGS["C3"].with_(B=16, P=256, L=1200)                  # 2 partials per row, merged inside the launch
-    small = S.CONFIGS["C3"].with_(B=3, Hq=16, Hkv=2, k=2, P=64, L=700)  # fewer, longer rows of partials; separate merge launch
+    small = S.CONFIGS["C3"].with_(B=3, Hq=16, Hkv=2, k=2, P=64, L=700)  # fewer, longer rows of partials; merge workgroups
     for cfg, priv_len in ((big, None), (small, np.array([700, 3, 333], np.int32))):
         print("noalloc case", cfg, flush=True)
         a = S.attention_inputs(cfg, priv_len=priv_len)
