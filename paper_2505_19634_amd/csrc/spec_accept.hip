@@ -8,8 +8,7 @@
 //       into 2^-40 fixed-point weights -- all of the sub-chunk's loads are requested before the first
 //       is used -- and publishes the sub-chunk's integer sum as two 8-byte words, each carrying half
 //       of it and this call's 32-bit tag.  The workgroup of a branch's LAST
-//       slice then collects the branch's sums (it only ever waits for workgroups with smaller
-//       block indices, which were dispatched before it; the wait is bounded), locates the sub-chunk
+//       slice then collects the branch's sums (those that stay out for long it forms itself), locates the sub-chunk
 //       and the token where the integer CDF crosses T = floor(m * Z / 2^24), re-reading that one
 //       sub-chunk only, and clears the published words.  An empty residual (possible only after a
 //       draft of probability zero under both models) is resolved by that workgroup alone over the
@@ -280,7 +279,6 @@ __global__ __launch_bounds__(kAccThreads) void accept_pick_kernel(int B, int k, 
 constexpr int kFuMaxSub = 64;        // sub-chunks per branch (one wavefront each): one wavefront scans their sums
 constexpr int kFuMaxIter = 16;       // 16-byte loads per row and lane: sub-chunks of at most 4096 tokens
 constexpr int kFuMaxV = kFuMaxSub * kFuMaxIter * 256;
-constexpr int kFuSpinLimit = 1 << 18;  // polls of the collecting workgroup before it gives up (far beyond any real wait)
 
 struct FusedPlan {
     int wlen;    // tokens per sub-chunk, a multiple of 256
@@ -327,6 +325,9 @@ __device__ __forceinline__ unsigned long long tagged(unsigned half, unsigned tag
 __device__ __forceinline__ void publish(unsigned long long* slot, unsigned long long v) {
     __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// What a collecting workgroup that no longer waits leaves in a word that has not come.  Words are exchanged from both sides, so
+// a sub-chunk's wavefront that finds the mark knows that its word has no reader and takes it down again.
+__device__ __forceinline__ unsigned long long left_mark(unsigned tag) { return (unsigned long long)~tag << 32; }
 __device__ __forceinline__ unsigned long long peek(const unsigned long long* slot) {
     return __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -388,7 +389,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     __shared__ int sh_first[kAccWaves];
     __shared__ unsigned long long sh_scan[kAccWaves];
     __shared__ unsigned long long sh_base, sh_T;
-    __shared__ int sh_chunk, sh_bad;
+    __shared__ int sh_chunk;
+    __shared__ unsigned long long sh_missing, sh_sub[kFuMaxSub];
     const int b = blockIdx.x / pl.S, s = blockIdx.x - b * pl.S;
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
     const int n = accepted_length(b, k, V, p, q, draft, u, sh_first);
@@ -398,67 +400,59 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     const bool has_q = n < k;
     const float* qrow = has_q ? q + ((size_t)b * k + n) * V : prow;
     const int sub = s * kAccWaves + wave;          // this wavefront's sub-chunk of the row
-    const int lo = sub * pl.wlen;
-    // all of the sub-chunk is requested before any of it is used
-    float4 pv[MAXIT], qv[MAXIT];
+    // a wavefront's sum of the weights of a sub-chunk, in its last lane
+    auto sub_sum = [&](int sub) {
+        const int lo = sub * pl.wlen;
+        // all of the sub-chunk is requested before any of it is used
+        float4 pv[MAXIT], qv[MAXIT];
 #pragma unroll
-    for (int i = 0; i < MAXIT; ++i) {
-        const int idx = lo + (i * kWave + lane) * 4;
-        const bool in = i < pl.iters && idx < V;
-        pv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (in) pv[i] = load_row4(prow, idx, V);
-        if (in && has_q) qv[i] = load_row4(qrow, idx, V);
-    }
-    // per lane: at most 64 weights; their high parts (<= 2^16) and low parts (< 2^24) add up in 32 bits
-    unsigned w_hi = 0, w_lo = 0;
-#pragma unroll
-    for (int i = 0; i < MAXIT; ++i) {
-        const float pe[4] = {pv[i].x, pv[i].y, pv[i].z, pv[i].w};
-        const float qe[4] = {qv[i].x, qv[i].y, qv[i].z, qv[i].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            unsigned h, l;
-            fixed_weight_split(has_q ? residual(pe[e], qe[e]) : pe[e], h, l);
-            w_hi += h;
-            w_lo += l;
+        for (int i = 0; i < MAXIT; ++i) {
+            const int idx = lo + (i * kWave + lane) * 4;
+            const bool in = i < pl.iters && idx < V;
+            pv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (in) pv[i] = load_row4(prow, idx, V);
+            if (in && has_q) qv[i] = load_row4(qrow, idx, V);
         }
+        // per lane: at most 64 weights; their high parts (<= 2^16) and low parts (< 2^24) add up in 32 bits
+        unsigned w_hi = 0, w_lo = 0;
+#pragma unroll
+        for (int i = 0; i < MAXIT; ++i) {
+            const float pe[4] = {pv[i].x, pv[i].y, pv[i].z, pv[i].w};
+            const float qe[4] = {qv[i].x, qv[i].y, qv[i].z, qv[i].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                unsigned h, l;
+                fixed_weight_split(has_q ? residual(pe[e], qe[e]) : pe[e], h, l);
+                w_hi += h;
+                w_lo += l;
+            }
+        }
+        return wave_sum_split(w_hi, w_lo);
+    };
+    const unsigned long long s_sub = sub_sum(sub);
+    if (s != pl.S - 1) {  // uniform over the workgroup; all sub-chunks of these hold tokens
+        if (lane == kWave - 1) {
+            unsigned long long* mine = slots + ((size_t)b * kFuMaxSub + sub) * 2;
+            const unsigned long long old0 = atomicExch(mine + 0, tagged((unsigned)s_sub, tag));
+            const unsigned long long old1 = atomicExch(mine + 1, tagged((unsigned)(s_sub >> 32), tag));
+            if (old0 == left_mark(tag)) publish(mine + 0, 0ull);
+            if (old1 == left_mark(tag)) publish(mine + 1, 0ull);
+        }
+        return;
     }
-    const unsigned long long s_sub = wave_sum_split(w_hi, w_lo);
-    unsigned long long* mine = slots + ((size_t)b * kFuMaxSub + sub) * 2;
-    if (lane == kWave - 1 && sub < pl.nsub) {
-        publish(mine + 0, tagged((unsigned)s_sub, tag));
-        publish(mine + 1, tagged((unsigned)(s_sub >> 32), tag));
-    }
-    if (s != pl.S - 1) return;  // uniform over the workgroup
 
-    // ---- the branch's last slice collects: it waits only for workgroups dispatched before it ----
+    // ---- the branch's last slice collects ----
+    if (lane == kWave - 1) sh_sub[sub] = s_sub;
     if (tid == 0) {
         accept_len[b] = n;
-        sh_bad = 0;
+        sh_missing = 0;
     }
     __syncthreads();
     unsigned m = (unsigned)(u[(size_t)b * (k + 1) + k] * 16777216.0f);  // trunc(u * 2^24)
     m = m > 16777215u ? 16777215u : m;                                  // u must be < 1; keep T < Z regardless
-    if (wave == 0) {
-        unsigned long long v = 0;
-        if (lane < pl.nsub) {
-            unsigned long long* e = slots + ((size_t)b * kFuMaxSub + lane) * 2;
-            unsigned long long w0 = 0, w1 = 0;
-            bool ok = false;
-            for (int spin = 0; spin < kFuSpinLimit; ++spin) {
-                w0 = peek(e + 0);
-                w1 = peek(e + 1);
-                ok = (unsigned)(w0 >> 32) == tag && (unsigned)(w1 >> 32) == tag;
-                if (ok) break;
-                __builtin_amdgcn_s_sleep(1);
-            }
-            if (!ok) sh_bad = 1;  // never seen in practice: the producers were dispatched first and wait for nothing
-            v = ((w1 & 0xffffffffull) << 32) | (w0 & 0xffffffffull);
-            // the words are consumed: clear them, so that a captured launch (same tag) can be replayed
-            publish(e + 0, 0ull);
-            publish(e + 1, 0ull);
-        }
+    // first wavefront: where the threshold falls, from the sums of the sub-chunks, one per lane
+    auto locate = [&](unsigned long long v) {
         const unsigned long long incl = wave_incl_scan_limbs(v);
         const unsigned long long Z = shfl_u64(incl, kWave - 1);
         const unsigned long long T = (__umul64hi((unsigned long long)m, Z) << 40) | (((unsigned long long)m * Z) >> 24);
@@ -470,10 +464,54 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
             sh_chunk = lane;                        // after lane 0's store in the wavefront's program order
             sh_base = incl - v;
         }
+    };
+    unsigned long long v = 0;
+    bool missing = false;
+    if (wave == 0) {
+        const int own = s * kAccWaves;  // the sub-chunks from here on are this workgroup's
+        if (lane >= own && lane < pl.nsub) v = sh_sub[lane];
+        if (lane < own) {
+            unsigned long long* e = slots + ((size_t)b * kFuMaxSub + lane) * 2;
+            unsigned long long w0 = 0, w1 = 0;
+            auto came = [&](unsigned long long w) { return (unsigned)(w >> 32) == tag; };
+            bool ok = false;
+            for (int polls = 0; !ok && polls < kWaitPolls; ++polls) {
+                w0 = peek(e + 0);
+                w1 = peek(e + 1);
+                ok = came(w0) && came(w1);
+                if (!ok) __builtin_amdgcn_s_sleep(1);
+            }
+            // the words are consumed: clear them, so that a captured launch (same tag) can be replayed
+            if (ok) {
+                publish(e + 0, 0ull);
+                publish(e + 1, 0ull);
+            } else {  // the sums that have not come are formed here
+                w0 = atomicExch(e + 0, left_mark(tag));
+                w1 = atomicExch(e + 1, left_mark(tag));
+                if (came(w0)) publish(e + 0, 0ull);
+                if (came(w1)) publish(e + 1, 0ull);
+                missing = !(came(w0) && came(w1));
+            }
+            v = ((w1 & 0xffffffffull) << 32) | (w0 & 0xffffffffull);
+        }
+        const unsigned long long miss = __ballot(missing);
+        if (miss == 0) locate(v);
+        else if (lane == 0) sh_missing = miss;
     }
     __syncthreads();
-    int c = sh_chunk;
-    if (sh_bad) c = -3;
+    if (sh_missing) {  // uniform over the workgroup; the wavefronts in turn
+        int turn = 0;
+        for (unsigned long long left = sh_missing; left; left &= left - 1, ++turn) {
+            if (turn % kAccWaves != wave) continue;
+            const int j = __ffsll((long long)left) - 1;
+            const unsigned long long sum = sub_sum(j);
+            if (lane == kWave - 1) sh_sub[j] = sum;
+        }
+        __syncthreads();
+        if (wave == 0) locate(missing ? sh_sub[lane] : v);
+        __syncthreads();
+    }
+    const int c = sh_chunk;
     if (c == -1 && has_q) {  // empty residual: the row p_n itself is sampled (uniform over the workgroup)
         const int tok = pick_plain_row(prow, V, m, sh_scan);
         if (tid == 0) next_token[b] = tok;

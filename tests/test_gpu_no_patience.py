@@ -66,6 +66,47 @@ def test_logits_replayed(lotts, oracle):
             assert np.array_equal(n.cpu().numpy(), want[i][0]) and np.array_equal(t.cpu().numpy(), want[i][1]), i
 
 
+def accept_on_dev(s):
+    return [to_dev(s[n]) for n in ("p", "q", "draft", "u")]
+
+
+@pytest.mark.parametrize("B,k,V", [(3, 2, 1), (2, 1, 255), (6, 3, 1025), (4, 2, 16385), (5, 0, 50257), (32, 8, 30000), (3, 3, 151936),
+                                   (2, 2, 262143)])
+def test_accept(lotts, oracle, B, k, V):
+    cfg = S.CONFIGS["C2"].with_(B=B, V=V, k=k)
+    print("acceptance without patience", cfg, flush=True)
+    s = S.accept_inputs(cfg, salt=V)
+    for u_last in (None, 0.0, 1.0 - 2.0 ** -24):          # the first and the last token of the row among them
+        if u_last is not None:
+            s["u"][:, -1] = u_last
+        n_ref, t_ref = oracle.spec_accept(s["p"], s["q"], s["draft"], s["u"])
+        n, t = lotts.spec_accept(*accept_on_dev(s))
+        assert np.array_equal(n.cpu().numpy(), n_ref) and np.array_equal(t.cpu().numpy(), t_ref)
+
+
+def test_accept_replayed(lotts, oracle):
+    cfg = S.CONFIGS["C2"].with_(B=6, V=70001, k=3)
+    sets = [S.accept_inputs(cfg, salt=i) for i in range(3)]
+    want = [oracle.spec_accept(s["p"], s["q"], s["draft"], s["u"]) for s in sets]
+    buf = [x.clone() for x in accept_on_dev(sets[0])]
+    n, t = (torch.empty(cfg.B, dtype=torch.int32, device=DEV) for _ in range(2))
+    ws = torch.zeros(lotts.load().spec_accept_workspace_bytes(cfg.B, cfg.k, cfg.V), dtype=torch.uint8, device=DEV)
+    call = lambda: lotts.spec_accept(*buf, accept_len=n, next_token=t, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for i in (1, 2, 0, 1):
+        for dst, src in zip(buf, accept_on_dev(sets[i])):
+            dst.copy_(src)
+        for again in (graph.replay, call, graph.replay):
+            again()
+            torch.cuda.synchronize()
+            assert np.array_equal(n.cpu().numpy(), want[i][0]) and np.array_equal(t.cpu().numpy(), want[i][1]), i
+            assert int(ws.to(torch.int32).sum()) == 0     # every word is down again, taken or marked
+
+
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: "B%d_k%d_Hq%d_Hkv%d_D%d_P%d_L%d" % (c.B, c.k, c.Hq, c.Hkv, c.D, c.P, c.L))
 def test_attention(lotts, oracle, cfg):
     lens = np.linspace(cfg.k + 1, cfg.L, cfg.B).astype(np.int32) if cfg.B > 1 else None
