@@ -566,7 +566,9 @@ static inline LgLayout lg_layout(int B, int k, int V) {
     LgLayout l;
     l.nchunks = (V + kLgChunk - 1) / kLgChunk;
     const size_t rows = (size_t)B * (2 * k + 1);
-    l.iters = V <= 4 * kLgGroup * kLgMaxPieces && rows * kLgMaxPieces <= 0x7fffffff ? 4 : 8;
+    // four loads a thread up to 64 pieces to a row and while one grid (of fewer than 2^32 threads) holds all pieces; else eight
+    const size_t pieces4 = (V + 4 * kLgGroup - 1) / (4 * kLgGroup);
+    l.iters = pieces4 <= kLgMaxPieces && rows * pieces4 * kLgThreads <= 0xffffffffu ? 4 : 8;
     l.npieces = (V + l.iters * kLgGroup - 1) / (l.iters * kLgGroup);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     l.off_psum = up(rows * sizeof(float));

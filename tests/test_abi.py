@@ -162,3 +162,11 @@ def test_binding_refuses_cpu_tensors(lib):
         lotts.majority_vote(torch.zeros(4, dtype=torch.int32))
     with pytest.raises(ValueError):
         lotts.spec_accept(torch.zeros(1, 1, 8), None, None, torch.zeros(1, 1))
+
+
+def test_logits_rows_are_cut_so_that_one_grid_holds_them(lib):
+    """A grid holds fewer than 2^24 workgroups of 256 threads.  65535 x 127 rows of two pieces of 8192 logits fit; 65535 x 129 rows
+    do not, and are cut into single pieces of 16384, which fit -- fewer words between the workgroups, a smaller workspace."""
+    need = lib.spec_accept_logits_workspace_bytes
+    assert 2 * 65535 * 127 < 1 << 24 <= 2 * 65535 * 129
+    assert 0 < need(65535, 64, 16384) < need(65535, 63, 16384)
