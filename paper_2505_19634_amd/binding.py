@@ -100,12 +100,13 @@ def strerror(status: int) -> str:
 
 # The current stream's handle and the current device without the Python objects that torch.cuda.current_stream() makes: at
 # these call rates every microsecond of the host shows (a call of a few microseconds of GPU time waits for the next one).
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# Looked up when called: a torch built for the CPU lacks both, and greedy_search needs neither.
+def _raw_stream(index: int) -> int:
+    return torch._C._cuda_getCurrentRawStream(index)
 
 
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
-    return _raw_stream(_current_device()) if stream is None else int(stream.cuda_stream)
+    return _raw_stream(torch._C._cuda_getDevice()) if stream is None else int(stream.cuda_stream)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

@@ -170,3 +170,18 @@ def test_logits_rows_are_cut_so_that_one_grid_holds_them(lib):
     need = lib.spec_accept_logits_workspace_bytes
     assert 2 * 65535 * 127 < 1 << 24 <= 2 * 65535 * 129
     assert 0 < need(65535, 64, 16384) < need(65535, 63, 16384)
+
+
+def test_import_and_host_entry_points_need_no_gpu_build_of_torch():
+    """A torch built for the CPU lacks the bindings that hand out streams and devices; the package imports and searches all the same."""
+    import subprocess
+    import sys
+    code = ("import sys, torch\n"
+            "sys.path.insert(0, %r)\n"
+            "for n in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    if hasattr(torch._C, n): delattr(torch._C, n)\n"
+            "import paper_2505_19634_amd as lotts\n"
+            "B, gamma, acc, _, _ = lotts.greedy_search(lambda B, g, T: B + g, 1.0, 4, 2)\n"
+            "print('searched', B, gamma, acc)\n" % ROOT)
+    res = subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
+    assert res.returncode == 0 and "searched" in res.stdout, res.stdout
