@@ -568,10 +568,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
 
 extern "C" size_t spec_accept_workspace_bytes(int32_t B, int32_t k, int32_t V) {
     if (B < 1 || k < 0 || k > lotts::kAccMaxK || V < 1 || B > 65535) return 0;
-    const lotts::AcceptPlan pl = lotts::plan_accept(V);
-    const size_t two_launch = (size_t)2 * B * pl.nchunks * sizeof(unsigned long long);
-    const size_t one_launch = (size_t)B * lotts::kFuMaxSub * 2 * sizeof(unsigned long long);
-    return two_launch > one_launch ? two_launch : one_launch;  // the call picks the path from V and the pointers
+    if (V <= lotts::kFuMaxV) return (size_t)B * lotts::kFuMaxSub * 2 * sizeof(unsigned long long);  // one launch
+    return (size_t)2 * B * lotts::plan_accept(V).nchunks * sizeof(unsigned long long);
 }
 
 extern "C" int spec_accept(int32_t B, int32_t k, int32_t V, const float* p, const float* q, const int32_t* draft,
@@ -583,11 +581,8 @@ extern "C" int spec_accept(int32_t B, int32_t k, int32_t V, const float* p, cons
     if (k > 0 && (!q || !draft)) return LOTTS_ERR_NULL;
     if (workspace_bytes < spec_accept_workspace_bytes(B, k, V)) return LOTTS_ERR_WORKSPACE;
     if (((uintptr_t)workspace & 7) != 0) return LOTTS_ERR_SHAPE;
-    const AcceptPlan pl = plan_accept(V);
     unsigned long long* sums = static_cast<unsigned long long*>(workspace);
     hipStream_t s = (hipStream_t)stream;
-    // float4 loads need every row start 16-byte aligned
-    const bool vec = (V % 4 == 0) && (((uintptr_t)p & 15) == 0) && (k == 0 || ((uintptr_t)q & 15) == 0);
     if (V <= kFuMaxV) {  // one launch
         const FusedPlan fp = plan_fused(V);
         const unsigned tag = next_word_tag();
@@ -606,6 +601,9 @@ extern "C" int spec_accept(int32_t B, int32_t k, int32_t V, const float* p, cons
                          next_token, sums);
         return check_launch();
     }
+    const AcceptPlan pl = plan_accept(V);
+    // float4 loads need every row start 16-byte aligned
+    const bool vec = (V % 4 == 0) && (((uintptr_t)p & 15) == 0) && (k == 0 || ((uintptr_t)q & 15) == 0);
     const dim3 grid(pl.nchunks, B);
     if (vec)
         LOTTS_LAUNCH(accept_scan_kernel<true>, grid, dim3(kAccThreads), s, B, k, V, pl.chunk, pl.nchunks, p,

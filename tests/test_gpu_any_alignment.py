@@ -54,3 +54,17 @@ def test_fp32_attention_rows_anywhere(oracle, B, k, Hq, Hkv, D, P, L, pad):
     e_abs, e_fro, _ = attn_errors(O, Oref)
     assert e_abs <= TOL["f32"]["abs"] and e_fro <= TOL["f32"]["fro_band"]
     assert np.abs(lse.cpu().numpy().astype(np.float64) - lref).max() <= TOL["f32"]["lse"]
+
+
+@pytest.mark.parametrize("V", [1000, 262144, 262145, 600004])
+def test_accept_on_a_workspace_of_the_size_asked_for(oracle, V):
+    """One launch up to 2^18, two beyond: each within the bytes that the query names for that vocabulary."""
+    import paper_2505_19634_amd as lotts
+    cfg = S.CONFIGS["C2"].with_(B=3, V=V, k=2)
+    s = S.accept_inputs(cfg, salt=V)
+    n_ref, t_ref = oracle.spec_accept(s["p"], s["q"], s["draft"], s["u"])
+    need = lotts.load().spec_accept_workspace_bytes(cfg.B, cfg.k, V)
+    buf = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+    n, t = lotts.spec_accept(*(to_dev(s[x]) for x in ("p", "q", "draft", "u")), workspace=buf[:need])
+    assert np.array_equal(n.cpu().numpy(), n_ref) and np.array_equal(t.cpu().numpy(), t_ref)
+    assert bool((buf[need:] == 0x5a).all())
