@@ -161,12 +161,21 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
     //    1 x 2 heads x 8192 tokens, 64 shares, 10.6 us against 11.7 with a launch of its own (and 15.6 with 16 shares);
     //    8 x 8 heads x 4300 tokens, 4 shares, 27.4 us against 29.3 with the merge by the last arriver; short contexts too:
     //    2 x 2 heads x 4064 tokens 10.2 us against 11.0 with a launch of its own, 1 x 2 x 800 9.2 either way;
-    //  - a second launch where prefix items or several row groups add partials of their own;
-    //  - the last arriver, ONE workgroup at one unit's share of the bandwidth, where those shapes leave a few tens of KB.
+    //  - the last arriver, where one round of its loads is all (up to eight partials of a row) and there are few bytes of them: up
+    //    to 32 KB it is 2 .. 17 % ahead of merge workgroups (7 x 8 x 646 tokens 10.1 us against 11.0, 10 x 8 x 605, D = 64, 8.0
+    //    against 9.2), with more partials or bytes 3 .. 15 % behind (1 x 16 x 7834, D = 64, 12 KB in 16 partials 13.1 against 12.1;
+    //    8 x 8 x 1222, 60 KB, 15.0 against 13.7);
+    //  - a second launch where prefix items or several row groups add partials of their own -- an item then brings in rows of
+    //    several branches, and its last arriver would merge them one after the other: 3 x 8 heads x 1264 tokens behind 505, D = 64,
+    //    9.2 us against 15.1, 37 x 4 x 65 behind 300 10.1 against 23.5 -- but for the smallest batches (4 x 8 x 300 behind 200,
+    //    D = 64, 8.9 against 7.5).
+    const long long part_bytes = (long long)pl.nslots * GR * d.D * 4;  // of a (KV head, branch)
+    const bool last_arriver = pl.nslots <= 8 && (simple ? pl.nqt == 1 && part_bytes <= 32 * 1024
+                                                        : d.B * GR <= 2 * kRowTile && part_bytes <= 48 * 1024);
     if (pl.nslots == 1) pl.merge = kMergeNone;  // no prefix items, no key shares
     else if (simple && pl.nslots == 2 && pl.nqt == 1) pl.merge = kMergePair;
-    else if (simple) pl.merge = kMergeGroups;
-    else pl.merge = (long long)pl.nslots * GR * d.D * 4 <= 48 * 1024 ? kMergeLast : kMergeLaunch;
+    else if (last_arriver) pl.merge = kMergeLast;
+    else pl.merge = simple ? kMergeGroups : kMergeLaunch;
     // rows per merge workgroup: as few as leave at most one workgroup per unit in all
     auto rows_per_merger = [&](int threads) {
         pl.rpm = 1;
@@ -186,7 +195,13 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
         }
         if (cells(pl.nslots + 1) > kMaxCounters) pl.merge = kMergeLaunch;
     }
-    if (pl.merge == kMergeLaunch) rows_per_merger(kAttnThreads);
+    if (pl.merge == kMergeLaunch) {
+        rows_per_merger(kAttnThreads);
+        // a thread takes four partials of a row at least: more groups of threads only meet again in LDS (2 x 1 heads x 72 rows, 4
+        // partials, 12.9 -> 12.4 us)
+        while (pl.rpm * 2 * (d.D / 4) <= kAttnThreads && kAttnThreads / (pl.rpm * 2 * (d.D / 4)) * 4 >= pl.nslots) pl.rpm *= 2;
+        pl.mpp = ceil_div(GR, pl.rpm);
+    }
     pl.n_merge = pl.merge == kMergeGroups ? d.B * d.Hkv * pl.mpp : 0;
     pl.n_pre_items = d.Hkv * pl.n_rg_pre * pl.nsplit_pre;
     pl.n_priv_items = d.B * d.Hkv * pl.n_rg_priv * pl.nsplit_priv;

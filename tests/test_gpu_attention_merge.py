@@ -24,7 +24,15 @@ CASES = [
     BF.with_(B=12, Hq=16, Hkv=8, D=64, k=2, P=50, L=2100), BF.with_(B=7, Hq=8, Hkv=4, D=64, k=15, P=31, L=700),
     BF.with_(B=2, Hq=16, Hkv=2, k=7, P=60, L=9000),                    # as many cells as there are: two rows each instead of one
     BF.with_(B=1, Hq=8, Hkv=4, k=2, P=96, L=4000),                     # few pairs, up to 4096 tokens
+    # the last arriver: three to eight partials of few bytes; prefix items of the smallest batches
+    BF.with_(B=10, Hq=32, Hkv=8, D=64, k=2, P=95, L=510), BF.with_(B=7, Hq=32, Hkv=8, k=1, P=84, L=562),
+    BF.with_(B=5, Hq=16, Hkv=16, D=64, k=0, P=195, L=2021), BF.with_(B=15, Hq=16, Hkv=2, k=0, P=336, L=6487),
+    BF.with_(B=4, Hq=16, Hkv=8, D=64, k=1, P=200, L=300), BF.with_(B=1, Hq=16, Hkv=8, k=4, P=300, L=900),
+    # few branches and few tiles: one share, two
+    BF.with_(B=5, Hq=16, Hkv=8, D=64, k=2, P=0, L=150), BF.with_(B=6, Hq=32, Hkv=8, D=64, k=3, P=51, L=256),
     # a launch of its own: prefix items; several row groups
+    BF.with_(B=2, Hq=8, Hkv=1, k=8, P=0, L=539), BF.with_(B=24, Hq=32, Hkv=8, D=64, k=3, P=900, L=2000),
+    BF.with_(B=37, Hq=4, Hkv=4, k=1, P=300, L=65), BF.with_(B=16, Hq=40, Hkv=8, k=3, P=1100, L=1500),
     BF.with_(B=2, Hq=16, Hkv=2, k=4, P=1000, L=3000),
     BF.with_(B=3, Hq=24, Hkv=2, k=7, P=100, L=1400),
 ]

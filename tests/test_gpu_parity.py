@@ -642,7 +642,7 @@ def test_kernel_timer_counts_launches_and_changes_no_result(lotts, oracle):
     one, every duration is positive and shorter than the host-side bracket around it, outputs are untouched,
     and launches after the timer is full or stopped run untimed."""
     import time
-    cfg = BF.with_(B=16, P=128, L=500)                   # 128 (head, branch) pairs: two partials per row, merged in the launch
+    cfg = BF.with_(B=16, P=128, L=512)                   # 128 (head, branch) pairs, folded prefix: two partials per row, merged in the launch
     d = attn_to_dev(cfg, S.attention_inputs(cfg))
     s = S.accept_inputs(S.CONFIGS["C2"].with_(B=4, V=30000))
     sd = {n: to_dev(s[n]) for n in ("p", "q", "draft", "u")}
