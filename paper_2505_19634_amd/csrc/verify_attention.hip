@@ -119,39 +119,58 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
     // A prefix that is short next to the private caches is folded into the private items.
     pl.fold = (d.P > 0 && (long long)d.P * 4 <= d.Lmax) ? 1 : 0;
     const bool simple = pl.n_rg_priv == 1 && (d.P == 0 || pl.fold);  // an item's rows are one branch's rows
-    // A count just above one item per unit is the worst choice: a few units run two and everybody waits for them (48
-    // branches x 2 heads x 4300 tokens in 3 shares, 288 items, 48.6 us; in 2 shares, 192 items, 36.7).
-    // At D = 64 and one row tile an item has half the bytes in flight and two of them fit a unit with ease, so where one per
-    // unit leaves many units without an item, two per unit are dealt (12 branches x 8 heads x 2461 tokens, D = 64: 5 shares 15.9
-    // us, 2 shares 16.7; of different lengths 13.8 against 15.4).
-    auto shares = [&](int units) { return base < units ? units / base : 1; };
-    auto fills = [&](int units) { return shares(units) * base * 20 >= (long long)units * 17 && base <= units; };
-    long long want = shares(kNumCU);
-    if (simple && d.D == 64 && pl.nqt == 1 && !fills(kNumCU) && fills(2 * kNumCU)) want = shares(2 * kNumCU);
     // At least about one tile per wavefront.  Few branches: the folded prefix tiles count as well, and the last share may be
-    // ragged.  (With more, one share more would double the items and with them the partials; the built-in scratch of the
-    // allocation-free entry point has to hold what it held.)
+    // ragged -- from three shares on; below, a share more costs the merge more than it saves (5 x 8 heads x 96 tokens, D = 64:
+    // 5.0 us in one share, 5.8 in two; 6 x 8 x 307 6.3 in two, 7.0 in three).  (With more branches, one share more would double the
+    // items and with them the partials; the built-in scratch of the allocation-free entry point has to hold what it held.)
     const bool few = simple && base <= kNumCU / 2;
-    int max_split = few ? ceil_div(tiles_priv + (pl.fold ? tiles_pre : 0), kAttnWaves) : tiles_priv / kAttnWaves;
+    const int tiles_all = tiles_priv + (pl.fold ? tiles_pre : 0);
+    int max_split = !few ? tiles_priv / kAttnWaves : tiles_all < 3 * kAttnWaves ? tiles_all / kAttnWaves : ceil_div(tiles_all, kAttnWaves);
     const int cap_split = simple ? kMaxSplit : kMaxSplitStack;
     if (max_split > cap_split) max_split = cap_split;
     if (max_split < 1) max_split = 1;
-    pl.nsplit_priv = (int)(want > max_split ? max_split : want);
-    if (simple) {  // the fewest shares (partials) that leave the longest wavefront the same number of tiles
-        const int all = tiles_priv + (pl.fold ? tiles_pre : 0);
-        const int per_wave = ceil_div(all, kAttnWaves * pl.nsplit_priv);
-        pl.nsplit_priv = ceil_div(all, kAttnWaves * per_wave);
-    }
-    if (d.P > 0 && !pl.fold) {
-        const int tiles_per_item = ceil_div(tiles_priv, pl.nsplit_priv);
-        int s = (tiles_pre + tiles_per_item / 2) / tiles_per_item;
+    // Prefix shares beside s private ones (stacked plan): items of about the same length.
+    auto pre_shares = [&](int s) {
+        if (d.P == 0 || pl.fold) return 0;
+        const int tiles_per_item = ceil_div(tiles_priv, s);
+        int q = (tiles_pre + tiles_per_item / 2) / tiles_per_item;
         int cap = tiles_pre / kAttnWaves;
         if (cap > kMaxSplitStack) cap = kMaxSplitStack;
-        if (s > cap) s = cap;
-        pl.nsplit_pre = s < 1 ? 1 : s;
-    } else {
-        pl.nsplit_pre = 0;
+        if (q > cap) q = cap;
+        return q < 1 ? 1 : q;
+    };
+    // A count of items just above one per unit is the worst choice: a few units run two and everybody waits for them (48
+    // branches x 2 heads x 4300 tokens in 3 shares, 288 items, 48.6 us; in 2 shares, 192 items, 36.7).  Prefix items count (8 x 8
+    // heads x 512 tokens behind 2048: 26.7 us in 4 shares, 896 items with the prefix's, 15.2 in one, 224; 16 x 8 x 1500 behind 1100
+    // 33.5 us in 2, 336 items, 25.9 in one).  Branches of different lengths lose by it where few items are left for many units: 11 x 8 heads x 669 + 6418 / 4
+    // .. 6418 tokens 39.5 us in 3 shares, 44.1 in 2, at equal lengths 68.1 and 50.2.
+    // At D = 64 and one row tile an item has half the bytes in flight and two of them fit a unit with ease, so where one per
+    // unit leaves many units without an item, two per unit are dealt (12 branches x 8 heads x 2461 tokens, D = 64: 5 shares 15.9
+    // us, 2 shares 16.7; of different lengths 13.8 against 15.4; 24 x 8 x 2000 behind 900 21.5 against 24.2).  Where two do not
+    // fill the units either, branches of different lengths still need more items than units, from 40 tiles on (9 x 16 heads x 375
+    // .. 1500 tokens 12.1 us in two shares, 14.5 in one, at equal lengths 15.3 and 15.2; 12 x 16 x 1250 .. 5000 32.1 and 37.5).
+    auto items = [&](long long s) { return base * s + (long long)d.Hkv * pl.n_rg_pre * pre_shares((int)s); };
+    auto shares = [&](int units) {
+        long long s = base < units ? units / base : 1;
+        if (!simple && s > max_split) s = max_split;
+        while (s > 1 && items(s) > units) --s;
+        return s;
+    };
+    auto fills = [&](int units) {
+        const long long n = items(shares(units));
+        return n * 20 >= (long long)units * 17 && n <= units;
+    };
+    long long want = shares(kNumCU);
+    if (d.D == 64 && pl.nqt == 1 && !fills(kNumCU)) {
+        if (fills(2 * kNumCU)) want = shares(2 * kNumCU);
+        else if (simple && base < kNumCU && want == 1 && tiles_all >= 40) want = 2;
     }
+    pl.nsplit_priv = (int)(want > max_split ? max_split : want);
+    if (simple) {  // the fewest shares (partials) that leave the longest wavefront the same number of tiles
+        const int per_wave = ceil_div(tiles_all, kAttnWaves * pl.nsplit_priv);
+        pl.nsplit_priv = ceil_div(tiles_all, kAttnWaves * per_wave);
+    }
+    pl.nsplit_pre = pre_shares(pl.nsplit_priv);
     pl.nslots = pl.nsplit_pre + pl.nsplit_priv;
     // Who merges (measured with calls back to back, kernel + what merges):
     //  - an item that holds whole rows stores the output: 32 branches x 8 KV heads x 3168 tokens 57.3 -> 53.3 us;

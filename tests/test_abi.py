@@ -185,3 +185,17 @@ def test_import_and_host_entry_points_need_no_gpu_build_of_torch():
             "print('searched', B, gamma, acc)\n" % ROOT)
     res = subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert res.returncode == 0 and "searched" in res.stdout, res.stdout
+
+
+@pytest.mark.parametrize("B,k,Hq,Hkv,D,P,L,slots", [
+    # a share of the keys more is not worth a merge: few tiles
+    (5, 2, 16, 8, 64, 0, 150, 1), (6, 3, 32, 8, 64, 51, 256, 2),
+    # two items to a unit where branches of different lengths need more items than units
+    (23, 3, 32, 8, 64, 0, 3000, 2), (9, 1, 16, 16, 64, 0, 1500, 2),
+    # the prefix's items count: private and prefix items together leave no unit with two while others have none
+    (8, 3, 40, 8, 128, 2048, 512, 5), (16, 3, 40, 8, 128, 1100, 1500, 2), (24, 3, 32, 8, 64, 900, 2000, 3),
+])
+def test_partials_per_row(lib, B, k, Hq, Hkv, D, P, L, slots):
+    """How many partials a row has, from the bytes asked for: a block of 16384 cells, then D + 2 floats per partial."""
+    need = lib.verify_attention_workspace_bytes(ctypes.byref(make_desc(B=B, k=k, Hq=Hq, Hkv=Hkv, D=D, P=P, Lmax=L)))
+    assert (need - 16384 * 8) // (4 * (D + 2) * B * (k + 1) * Hq) == slots
