@@ -100,11 +100,13 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
 
 // Which form, and how it is cut.  Measured on 16 matrices between 1536 x 1536 and 152064 x 5120 at 1 .. 256 tokens, calls
 // back to back over rotated weights, reduce launch included.
-//   Direct: while everything a wavefront needs is in flight at once (K <= 4096) it takes 2.9 us + 0.022 us per KB of a
-//     workgroup's W and X (whole batches of loads) + 0.14 us per MB of W, against 7 us + 0.125 us per MB of W + 7e-6 us per token
-//     and (N + K) of the split stream forms: 2560 x 2048 at 1 / 40 / 192 tokens 5.2 / 7.8 / 13.5 us against 7.9 / 9.2 / 15.0; 4096 x
-//     4096 at 2 / 16 tokens 9.9 / 13.1 against 11.4 / 11.6; 6144 x 4096 at 2 tokens 17.7 against 13.9; 4096 x 2560 at 16 tokens 13.3
-//     against 10.0.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1 token 19.8 us against 14.2.
+//   Direct, up to K = 4096 and 8192 rows: 3.4 us + 0.022 us per KB of a workgroup's W and X (whole batches of loads) + 0.14 us per
+//     MB of W, against 7 us + 0.125 us per MB of W + 7e-6 us per token and (N + K) of the split stream forms; both fitted to 1188
+//     sizes (1536 .. 14336 rows, K 512 .. 4096, 1 .. 192 tokens), where the choice costs 0.3 % over the better form: 2560 x 2048 at
+//     1 / 40 / 192 tokens 5.2 / 7.8 / 13.5 us against 7.9 / 9.2 / 15.0; 4736 x 1280 at 24 tokens 12.4 against 9.7; 6144 x 4096 at 2
+//     tokens 17.7 against 13.9.  With more rows only the tile of 64 rows is left, four wavefronts with many small batches: 11904 x
+//     1280 at 48 tokens 16.5 us against 13.4.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1
+//     token 19.8 us against 14.2.
 //   256-row stream form: more than 256 blocks of 128 rows; an X chunk in LDS serves the most rows.  55296 x 5120 at 64
 //     tokens 92 us, 128-row form 104.
 //   128-row form below that, 64-row form when it would have to be split more than sevenfold (N <= 4608): the fewer splits,
@@ -118,9 +120,9 @@ static inline GemmPlan plan_gemm(int M, int N, int K) {
     // An even number of token tiles from 4 on: pairs of wavefronts own two row tiles together and half of the token tiles each.
     pl.rt = pl.mt >= 4 && pl.mt % 2 == 0 ? 2 : 1;
     pl.ksplit = 1;
-    if (K <= 4096) {
+    if (K <= 4096 && N <= 8192) {
         const double kb = plan_direct(M, N, K, &pl);
-        if (kb > 0.0 && 2.9 + 0.022 * kb + 0.14 * (2e-6 * N * K) < 7.0 + 0.125 * (2e-6 * N * K) + 7e-6 * M * (N + K)) {
+        if (kb > 0.0 && 3.4 + 0.022 * kb + 0.14 * (2e-6 * N * K) < 7.0 + 0.125 * (2e-6 * N * K) + 7e-6 * M * (N + K)) {
             pl.form = kDirect;
             return pl;
         }
@@ -471,8 +473,8 @@ __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const GemmParam
 
 // The direct form.  Small matrices are bound by fixed costs -- launch, first data, the exchange of partials -- so the whole K
 // range stays in one workgroup and both operands go straight from memory into fragment registers: with 16x16x32 MFMA a load
-// covers 64 contiguous bytes of 16 rows, and a wavefront's share of K is at most two batches of UB steps at K = 2048 (all of
-// it in flight at once).  The wavefronts' sums meet in LDS, added in wavefront order.  W is non-temporal when a single
+// covers 64 contiguous bytes of 16 rows, and a wavefront's share of K at K = 2048 is one or two batches of UB steps with tiles of
+// up to 32 rows (all of it in flight at once), eight batches with 64.  The wavefronts' sums meet in LDS, added in wavefront order.  W is non-temporal when a single
 // workgroup column reads it (NT); with several over the tokens the later ones find it in the L2.
 template <int RN, int TT, int WAVES, int UB, bool NT>
 __global__ __launch_bounds__(WAVES * kWave) void skinny_gemm_direct_kernel(const GemmParams p) {

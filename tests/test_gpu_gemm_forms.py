@@ -13,7 +13,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [
     # direct: one tile shape each (16 * RN weight rows x 16 * TT tokens), ragged in rows and tokens
     (1, 8, 128), (16, 2040, 256), (17, 2056, 384), (33, 1544, 1536), (64, 2560, 1920), (129, 2568, 640), (193, 2048, 128),
-    (192, 2504, 1152), (256, 2560, 1024), (1, 4096, 4096), (15, 3848, 4096),
+    (192, 2504, 1152), (256, 2560, 1024), (1, 4096, 4096), (15, 3848, 4096), (9, 5000, 2048), (39, 2568, 2048), (27, 4104, 896),
+    (60, 2568, 1024), (45, 5128, 1024), (192, 2048, 2048), (15, 3080, 2048), (30, 3912, 1024),
+    # either side of the direct form's lines: 8192 rows, K = 4096
+    (8, 8192, 512), (8, 8200, 512), (24, 4736, 1280), (2, 2048, 4096), (2, 2048, 4224),
     # 64-row blocks: split K, odd chunk counts, M in every token tile count
     (1, 2056, 8320), (31, 72, 4480), (40, 2048, 11008), (65, 520, 4352), (97, 4608, 4224), (129, 2056, 5248), (161, 64, 4224),
     (193, 264, 4480), (225, 136, 8192), (256, 4600, 4352),
