@@ -25,16 +25,16 @@
 //       and O^T += V^T P^T on 32x32x16 bf16 MFMA, flash-style running (max, sum, O).  The 4 states
 //       are combined through LDS after one barrier and the item's un-normalised partial goes to
 //       the workspace -- or, if the item holds whole rows (no key shares, no prefix items), straight to O.
-//       Who merges the partials of a row depends on how many there are: of two, the item that finishes later (arrivals are
-//       counted per (KV head, branch) in a cell that carries the call's tag: what an earlier call left there, complete
-//       or not, counts as zero arrivals); of more, merge workgroups at the end of the grid, which wait for a flag of
+//       Who merges the partials of a row depends on how many there are: of two, or of up to eight with few bytes, the item
+//       that finishes last (arrivals are counted per (KV head, branch) in a cell that carries the call's tag: what an earlier
+//       call left there, complete or not, counts as zero arrivals); of more, merge workgroups at the end of the grid, which wait for a flag of
 //       every partial they read and share the rows among them; one whose flags stay out for long leaves, and the item that
 //       delivers the last partial merges in its place.  Partials cross workgroups -- and XCDs,
 //       each with its own L2 -- inside one launch, so they are written and read with 16-byte
 //       buffer accesses that carry the device-scope cache policy (performed at the memory side of
 //       the L2s); nothing is ever flushed or invalidated cache-wide.
-//   attn_merge_kernel     second launch, where prefix items or several row groups add partials of their own and a row has many
-//       of them.
+//   attn_merge_kernel     second launch, where prefix items or several row groups add partials of their own (but for the
+//       smallest batches, where the last arriver merges).
 // fp32 path: attn_f32_kernel, plain fp32 VALU arithmetic, one workgroup per output row; it
 // exists for exactness checks on small fp32 problems.
 // Two entry points share all of this: verify_attention (the caller brings the workspace) and
@@ -71,7 +71,7 @@ struct AttnPlan {
     int nsplit_priv;    // key splits of a private segment
     int nsplit_pre;     // key splits of the prefix (stacked plan; 0 otherwise)
     int nslots;         // partials per output row
-    int merge;          // who merges a row's partials: one of the three below
+    int merge;          // who merges a row's partials: one of the five below
     int rpm, mpp;       // merge workgroups: rows each of them takes (a power of two), their number per (KV head, branch)
     int n_pre_items, n_priv_items, n_merge;
 };
@@ -120,7 +120,7 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
     pl.fold = (d.P > 0 && (long long)d.P * 4 <= d.Lmax) ? 1 : 0;
     const bool simple = pl.n_rg_priv == 1 && (d.P == 0 || pl.fold);  // an item's rows are one branch's rows
     // At least about one tile per wavefront.  Few branches: the folded prefix tiles count as well, and the last share may be
-    // ragged -- from three shares on; below, a share more costs the merge more than it saves (5 x 8 heads x 96 tokens, D = 64:
+    // ragged -- from three shares on; below, a share more costs the merge more than it saves (8 x 8 heads x 137 tokens, D = 64:
     // 5.0 us in one share, 5.8 in two; 6 x 8 x 307 6.3 in two, 7.0 in three).  (With more branches, one share more would double the
     // items and with them the partials; the built-in scratch of the allocation-free entry point has to hold what it held.)
     const bool few = simple && base <= kNumCU / 2;
@@ -146,7 +146,8 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
     // .. 6418 tokens 39.5 us in 3 shares, 44.1 in 2, at equal lengths 68.1 and 50.2.
     // At D = 64 and one row tile an item has half the bytes in flight and two of them fit a unit with ease, so where one per
     // unit leaves many units without an item, two per unit are dealt (12 branches x 8 heads x 2461 tokens, D = 64: 5 shares 15.9
-    // us, 2 shares 16.7; of different lengths 13.8 against 15.4; 24 x 8 x 2000 behind 900 21.5 against 24.2).  Where two do not
+    // us, 2 shares 16.7; of different lengths 13.8 against 15.4; 24 x 8 x 2000 behind 900, where one share a branch
+    // and the prefix's are more than one per unit already, 21.5 against 24.2).  Where two do not
     // fill the units either, branches of different lengths still need more items than units, from 40 tiles on (9 x 16 heads x 375
     // .. 1500 tokens 12.1 us in two shares, 14.5 in one, at equal lengths 15.3 and 15.2; 12 x 16 x 1250 .. 5000 32.1 and 37.5).
     auto items = [&](long long s) { return base * s + (long long)d.Hkv * pl.n_rg_pre * pre_shares((int)s); };
@@ -161,7 +162,7 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
         return n * 20 >= (long long)units * 17 && n <= units;
     };
     long long want = shares(kNumCU);
-    if (d.D == 64 && pl.nqt == 1 && !fills(kNumCU)) {
+    if (d.D == 64 && pl.nqt == 1 && (simple ? !fills(kNumCU) : items(want) > kNumCU)) {
         if (fills(2 * kNumCU)) want = shares(2 * kNumCU);
         else if (simple && base < kNumCU && want == 1 && tiles_all >= 40) want = 2;
     }
@@ -307,7 +308,7 @@ __device__ __forceinline__ void store_merged(const AttnParams& prm, int kvh, int
 // ---------------------------------------------------------------------------------------------
 // Merge of the partials of the G*R output rows of one (KV head, branch), run by the workgroup that
 // delivered the last of them:  O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, slots in index
-// order whoever merges.  4 floats per output quad; a thread takes two quads (256 apart) and eight
+// order (merge_rows below adds every SG-th slot and then the groups: its own fixed order).  4 floats per output quad; a thread takes two quads (256 apart) and eight
 // slots at a time, so that 16 sixteen-byte loads are in flight together, with device scope: the partials come from
 // the memory side of the L2s.
 // ---------------------------------------------------------------------------------------------
@@ -956,8 +957,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
 }
 
 // ---------------------------------------------------------------------------------------------
-// Separate merge launch, used when a row has many partials and items cover rows of several branches or branches have several
-// row groups: grid (row chunks of a (KV head, branch), KV head x branch).
+// Separate merge launch, used when items cover rows of several branches or branches have several row groups: grid (row chunks of a (KV head, branch), KV head x branch).
 // ---------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(const AttnParams prm) {
