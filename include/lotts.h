@@ -277,8 +277,9 @@ int skinny_gemm(int32_t M, int32_t N, int32_t K, const void *X, int64_t ldx, con
  *       *launches and, if ms is not NULL, each one's milliseconds to ms[0 .. *launches), in launch
  *       order (HOST array of at least max_launches floats).  Switches the timer off.
  * The order of launches inside one call: verify_attention 1 (2 -- attention, then merge -- when a row has
- * partials from prefix items (4 P > Lmax) or from several row groups, but for the smallest batches); spec_accept 1 (2 -- scan,
- * pick -- when V is beyond 2^18); spec_accept_logits 2 (row statistics, scan and pick); majority_vote 1; confidence_vote 1; skinny_gemm 1 (2 when K is split: GEMM, reduce).
+ * partials from prefix items (4 P > Lmax) or from several row groups, but for the smallest batches);
+ * spec_accept 1 (2 -- scan, pick -- when V is beyond 2^18); spec_accept_logits 2 (row statistics, scan and
+ * pick); majority_vote 1; confidence_vote 1; skinny_gemm 1 (2 when K is split: GEMM, reduce).
  */
 int lotts_timer_start(int32_t max_launches);
 int lotts_timer_pause(int32_t paused);

@@ -180,8 +180,8 @@ __device__ __forceinline__ unsigned long long lg_peek(const unsigned long long* 
 // for; that they come at all is not relied on (kWaitPolls).  The words are cleared by the next launch.
 // Bound by the vector unit: 17 instructions a logit that the integer definition fixes, 8 us of the chip's rate for 112 rows x
 // 152064 logits, behind the read that all workgroups start with.  Whole call, us, before (three launches: maxima, sums, scan) ->
-// now: 16 x 7 rows x 152064 bf16 30.9 -> 28.0, fp32 40.5 -> 30.7; 64 x 5 x 151936 63.9 -> 54.2; 5 x 15 rows x 50257 fp32 (rows off
-// a 16-byte boundary, element by element before) 48.1 -> 17.5.
+// now: 16 x 7 rows x 152064 bf16 30.8 -> 27.9, fp32 40.5 -> 30.7; 64 x 5 x 151936 63.9 -> 54.2; 5 x 15 rows x 50257 fp32 (rows off
+// a 16-byte boundary, element by element before) 48.0 -> 17.7.
 // IT = 4 up to 2^19 logits (a lane of the collecting wavefront per piece): 28.0 us against 28.9 with IT = 8 on the first of
 // these and 38.0 with IT = 2, whose workgroups come and go too often.
 template <bool BF16, int IT>

@@ -39,7 +39,7 @@ def run_attention(lotts, oracle, cfg, priv_len=None, Lmax=None, scale=0.0):
 
 BF = S.CONFIGS["C3"]
 SMALL_ATTN = [
-    S.CONFIGS["C1"],                                                 # tiny fp32, the configs[0] case
+    S.CONFIGS["C1"],                                                 # tiny fp32, the smallest case
     S.CONFIGS["C1"].with_(B=3, Hq=8, Hkv=2, D=128, P=50, L=77, k=2),  # fp32, GQA, D=128, ragged tiles
     BF.with_(B=3, P=96, L=200),                                      # several tiles + ragged tail, G*R = 20
     BF.with_(B=2, P=0, L=131),                                       # no prefix
