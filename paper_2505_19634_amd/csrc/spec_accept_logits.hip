@@ -297,8 +297,10 @@ __device__ __forceinline__ void lg_row_stats(int B, int b, int k, int npieces, i
         RowStat st;
         st.m = rmax[row];
         st.S = 0;
-        if (npieces <= (1 << lg)) {
-            if (sub < npieces) st.S = src[sub];
+        if (npieces <= (2 << lg)) {  // one or two pieces a lane: no load that is not needed
+            const int next = sub + (1 << lg);
+            const unsigned long long v0 = sub < npieces ? src[sub] : 0ull, v1 = next < npieces ? src[next] : 0ull;
+            st.S = v0 + v1;
         } else {
             for (int i0 = sub; i0 < npieces; i0 += 8 << lg) {  // eight loads in flight
                 unsigned long long v[8];
