@@ -51,6 +51,23 @@ inline int check_launch() {
     return hipGetLastError() == hipSuccess ? LOTTS_OK : LOTTS_ERR_LAUNCH;
 }
 
+// Division of 0 <= x < 2^31 by a divisor that the host knows: q = (2 x m) >> 32 >> l with l = ceil(log2 d), m = ceil(2^(31 + l) / d)
+// <= 2^32 - 1 (m = 2^31 for powers of two).  Exact: m d = 2^(31 + l) + e with 0 <= e < d <= 2^l, so x m / 2^(31 + l) = x / d + x e / (d
+// 2^(31 + l)) and the second term is below 1 / d.  Three instructions, scalar where x is; the compiler's own division by a
+// run-time value is about twenty vector instructions in one dependent chain, 0.1 us at one wavefront per SIMD.
+struct FastDiv {
+    unsigned m, l;
+};
+static inline FastDiv fast_div(unsigned d) {
+    FastDiv f = {0x80000000u, 0};
+    while ((1ull << f.l) < d) ++f.l;
+    f.m = (unsigned)(((1ull << (31 + f.l)) + d - 1) / d);
+    return f;
+}
+__host__ __device__ __forceinline__ int quot(int x, FastDiv f) {
+    return (int)((unsigned)(((unsigned long long)((unsigned)x << 1) * f.m) >> 32) >> f.l);
+}
+
 __device__ __forceinline__ float shfl_xor_f(float v, int mask) { return __shfl_xor(v, mask, kWave); }
 
 __device__ __forceinline__ unsigned long long shfl_down_u64(unsigned long long v, int delta) {

@@ -64,16 +64,17 @@ constexpr int kMaxSplitStack = 16;  // the same when prefix items or several row
 constexpr int kMaxCounters = 16384;  // 64-bit cells at the start of the workspace
 
 struct AttnPlan {
-    int nqt;            // row tiles per item: 1 or 2
+    int n_pre_items, n_priv_items;
     int fold;           // 1: private items also run their share of the prefix (no prefix items)
     int n_rg_priv;      // row groups per (branch, KV head)
-    int n_rg_pre;       // row groups per KV head over all branches' stacked rows (stacked plan)
     int nsplit_priv;    // key splits of a private segment
     int nsplit_pre;     // key splits of the prefix (stacked plan; 0 otherwise)
     int nslots;         // partials per output row
     int merge;          // who merges a row's partials: one of the five below
     int rpm, mpp;       // merge workgroups: rows each of them takes (a power of two), their number per (KV head, branch)
-    int n_pre_items, n_priv_items, n_merge;
+    int n_merge;
+    int nqt;            // row tiles per item: 1 or 2
+    int n_rg_pre;       // row groups per KV head over all branches' stacked rows (stacked plan)
 };
 constexpr int kMergeLast = 0;    // the last-arriving workgroup of a (KV head, branch), inside the attention launch
 constexpr int kMergeGroups = 1;  // merge workgroups at the end of the attention launch's grid
@@ -82,8 +83,20 @@ constexpr int kMergeNone = 3;    // an item holds whole rows: it stores the outp
 constexpr int kMergePair = 4;    // two items, one row tile: the later one reads the other's partial, its own is in registers
 
 struct AttnParams {
+    // first what every item needs before its first tile, together: few loads, few trips
     const void *Q, *Kpre, *Vpre, *Kpriv, *Vpriv;
     const int32_t* priv_len;
+    long long q_stride_b, q_stride_r, q_stride_h;
+    long long kpre_stride_h, kpre_stride_t;
+    long long kpriv_stride_b, kpriv_stride_h, kpriv_stride_t;
+    FastDiv d_hkv, d_nsp, d_rgp, d_wpriv, d_g;  // by Hkv, nsplit_priv, n_rg_priv, the wavefronts that share a private segment, G
+    int k, R, Hkv, G, GR, P, Lmax;
+    int near_rows;              // a tile's key rows lie within 2^31 bytes of its first one, prefix and private
+    int tiles_pre, first_wave;  // prefix tiles; folded plan: the wavefront of a segment that gets the first private tile
+    AttnPlan plan;
+    FastDiv d_npre, d_wpre, d_gr, d_mpp;  // by nsplit_pre, the wavefronts that share the prefix, GR, mpp
+    int B, Hq, D;
+    float scale_log2;  // scale * log2(e)
     void* ws;                  // workspace base; everything below lives in it
     unsigned ws_bytes;
     unsigned off_o, off_ml;    // byte offsets: partial O [Hkv][B*GR][nslots][D] fp32,
@@ -92,14 +105,7 @@ struct AttnParams {
     unsigned long long tag;        // this call's tag, shifted into place: larger than that of any earlier call
     void* O;
     float* lse;
-    int B, k, R, Hq, Hkv, G, GR, D, P, Lmax;
-    unsigned g_magic;  // ceil(2^32 / G): x / G == umulhi(x, g_magic) for x * G < 2^32
-    float scale_log2;  // scale * log2(e)
-    long long q_stride_b, q_stride_r, q_stride_h;
-    long long kpre_stride_h, kpre_stride_t;
-    long long kpriv_stride_b, kpriv_stride_h, kpriv_stride_t;
     long long o_stride_b, o_stride_r, o_stride_h;
-    AttnPlan plan;
 };
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -108,7 +114,7 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // and the launch agree.  The HBM stream runs best with one streaming workgroup per compute
 // unit, so the private caches are cut into just enough key shares to give every CU one item.
 static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
-    AttnPlan pl;
+    AttnPlan pl = {};
     const int GR = (d.Hq / d.Hkv) * (d.k + 1);
     pl.nqt = GR > kRowTile ? 2 : 1;
     const int rows_per_item = kRowTile * pl.nqt;
@@ -290,7 +296,7 @@ __device__ __forceinline__ float2 ws_load2(__amdgpu_buffer_rsrc_t r, unsigned by
 
 // Output quad c4 of row rl (0 .. G*R-1) of a (KV head, branch): normalise, convert, store; the first quad's thread stores LSE.
 __device__ __forceinline__ void store_merged(const AttnParams& prm, int kvh, int b, int rl, int c4, float4 o, float M, float Lsum) {
-    const int r = prm.G == 1 ? rl : (int)__umulhi((unsigned)rl, prm.g_magic), hg = rl - r * prm.G;
+    const int r = quot(rl, prm.d_g), hg = rl - r * prm.G;
     const int h = kvh * prm.G + hg;
     const float inv = 1.0f / Lsum;  // a row always sees itself: Lsum > 0
     __bf16* op = (__bf16*)prm.O + (long long)b * prm.o_stride_b + (long long)r * prm.o_stride_r +
@@ -377,29 +383,42 @@ __device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buf
 // A thread takes every SG-th slot, eight 16-byte loads in flight; the groups meet in LDS and are added in group order, so
 // the result does not depend on timing.  A row's slots are read by many threads at once: with one thread per quad the
 // reads of 64 slots were eight dependent rounds and the launch took 9 us more than at 16 slots.
-// DEV: inside the attention launch: device-scope loads.  keep = false: nothing is stored (known only late: see merger_stays).
+// DEV: inside the attention launch: device-scope loads.  wait() comes after everything that does not depend on the partials and
+// says whether the result is stored (see merger_stays).
 // ---------------------------------------------------------------------------------------------
-template <int D, bool DEV, int THREADS>
-__device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char* lds, int kvh, int b, int chunk, bool keep) {
+template <int D, bool DEV, int THREADS, typename Wait>
+__device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char* lds, int kvh, int b, int chunk, Wait wait) {
     constexpr int F4 = D / 4, CH = 8;
     const AttnPlan& pl = prm.plan;
     const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
     const int tid = threadIdx.x, ns = pl.nslots, rpm = pl.rpm;
-    const int c4 = tid % F4, r = (tid / F4) & (rpm - 1), sg = tid / (F4 * rpm), SG = THREADS / (F4 * rpm);
+    const int rshift = __builtin_ctz(rpm);
+    const int c4 = tid % F4, r = (tid / F4) & (rpm - 1), sg = (tid / F4) >> rshift, SG = (THREADS / F4) >> rshift;
     const int row = chunk * rpm + r;
     float M = -INFINITY, Lsum = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (row < prm.GR) {
-        const unsigned base = ((unsigned)kvh * prm.B * prm.GR + (unsigned)b * prm.GR + row) * ns;
-        for (int s0 = sg; s0 < ns; s0 += SG * CH) {
+    const unsigned first_slot = ((unsigned)kvh * prm.B * prm.GR + (unsigned)b * prm.GR + row) * ns + sg;
+    unsigned at_o = prm.off_o + (first_slot * D + c4 * 4) * 4u, at_ml = prm.off_ml + first_slot * 8u;
+    const unsigned step_o = SG * D * 4u, step_ml = SG * 8u;
+    int mine = row < prm.GR ? ns - sg : 0;  // slots from the own first one on
+    asm volatile("" : "+v"(at_o), "+v"(at_ml), "+v"(mine) : "s"(step_o), "s"(step_ml));  // computed before the wait
+    const bool keep = wait();
+    {
+        for (int first = 0; first < ns; first += SG * CH) {
             float2 mv[CH];
             float4 pv[CH];
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
-                const int sl = s0 + j * SG;
-                const bool in = sl < ns;
-                mv[j] = in ? ws_load2<DEV>(rs, prm.off_ml + (base + sl) * 8u) : make_float2(-INFINITY, 0.f);
-                pv[j] = in ? ws_load4<DEV>(rs, prm.off_o + ((base + sl) * D + c4 * 4) * 4u) : make_float4(0.f, 0.f, 0.f, 0.f);
+                mv[j] = make_float2(-INFINITY, 0.f);
+                pv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (first + j * SG < ns) {  // uniform; then whoever has such a slot
+                    if (first + j * SG < mine) {
+                        mv[j] = ws_load2<DEV>(rs, at_ml);
+                        pv[j] = ws_load4<DEV>(rs, at_o);
+                    }
+                    at_ml += step_ml;
+                    at_o += step_o;
+                }
             }
             float Mn = M;
 #pragma unroll
@@ -424,17 +443,34 @@ __device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char*
         sh_ml[tid] = make_float2(M, Lsum);
         __syncthreads();
         if (sg != 0) return;
-        float Mg = M;
-        for (int g = 1; g < SG; ++g) Mg = fmaxf(Mg, sh_ml[tid + g * F4 * rpm].x);
-        const float Mu = (Mg == -INFINITY) ? 0.f : Mg;
+        // eight groups' states requested together: one at a time is two LDS latencies a group, 1 us for eight
+        float2 ml[CH];
+        float4 v[CH];
+        auto request = [&](int g0) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const int at = tid + min(g0 + j, SG - 1) * F4 * rpm;
+                ml[j] = sh_ml[at];
+                v[j] = sh_o[at];
+            }
+        };
+        float Mg = -INFINITY, l = 0.f;
         float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-        float l = 0.f;
-        for (int g = 0; g < SG; ++g) {
-            const float2 ml = sh_ml[tid + g * F4 * rpm];
-            const float4 v = sh_o[tid + g * F4 * rpm];
-            const float w = __builtin_amdgcn_exp2f(ml.x - Mu);
-            l += ml.y * w;
-            t.x += v.x * w; t.y += v.y * w; t.z += v.z * w; t.w += v.w * w;
+        for (int g0 = SG - 1 & ~(CH - 1); g0 >= 0; g0 -= CH) {  // (the first eight last: they are added first)
+            request(g0);
+#pragma unroll
+            for (int j = 0; j < CH; ++j) Mg = fmaxf(Mg, ml[j].x);
+        }
+        const float Mu = (Mg == -INFINITY) ? 0.f : Mg;
+        for (int g0 = 0; g0 < SG; g0 += CH) {
+            if (g0 > 0) request(g0);
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                if (g0 + j >= SG) break;
+                const float w = __builtin_amdgcn_exp2f(ml[j].x - Mu);
+                l += ml[j].y * w;
+                t.x += v[j].x * w; t.y += v[j].y * w; t.z += v[j].z * w; t.w += v[j].w * w;
+            }
         }
         M = Mg; Lsum = l; o = t;
     }
@@ -494,12 +530,12 @@ __device__ __forceinline__ bf16x8 load_bf16x8(const __bf16* ptr) {
     return *reinterpret_cast<const bf16x8*>(ptr);
 }
 
-// One run of keys a wavefront streams: tiles of 32 keys starting at `lo`, `step` keys apart,
-// keys at or beyond `hi` do not belong to it.
+// One run of keys a wavefront streams: tiles of 32 keys starting at `lo`; keys at or beyond `hi` do not belong to it.  The same
+// in all lanes: bases, strides and counts stay in scalar registers.
 struct KeyRun {
-    const __bf16 *K, *V;
-    long long stride_t;
-    int lo, hi, step, ntiles;
+    const unsigned char *K, *V;
+    long long stride;  // bytes from key to key
+    int lo, hi;
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -522,12 +558,13 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     constexpr int OSTRIDE = D + 4;         // floats per row of a wavefront's merge buffer
     constexpr int OBUF = kRowTile * OSTRIDE * 4;
     static_assert(OBUF <= SLAB, "the merge buffer reuses the wavefront's slab");
+    static_assert(kRowTile * NQT * KSTRIDE <= kAttnWaves * GROUPS * SLAB, "Q passes through the slabs");
     __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnWaves * GROUPS * SLAB];
     __shared__ float sh_m[kAttnWaves * GROUPS][kRowTile];
     __shared__ __attribute__((aligned(8))) float sh_l[kAttnWaves * GROUPS][kRowTile];
     __shared__ int sh_pair[kAttnWaves];  // GROUPS = 2: half tiles stored by the pair of wavefronts w and w + 4
 
-    const int tid = threadIdx.x, wave_all = tid / kWave, lane = tid & (kWave - 1);
+    const int tid = threadIdx.x, wave_all = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
     const int grp = GROUPS == 1 ? 0 : wave_all / kAttnWaves;         // which row tile(s) this wavefront works on
     const int wave = GROUPS == 1 ? wave_all : wave_all % kAttnWaves;  // which of the item's four runs of key tiles it streams
     const int ln = lane & 31;   // MFMA column (query row) / A row (key or d) owned by this lane
@@ -541,54 +578,54 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     int id = blockIdx.x;
     if (id >= pl.n_priv_items + pl.n_pre_items) {  // a merge workgroup
         id -= pl.n_priv_items + pl.n_pre_items;
-        const int kvh = id % prm.Hkv, rest = id / prm.Hkv;
-        const int b = rest / pl.mpp, chunk = rest % pl.mpp;
-        const bool stays = merger_stays(prm, reinterpret_cast<int*>(sh_l), kvh, b, chunk);
-        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b, chunk, stays);
+        const int rest = quot(id, prm.d_hkv), kvh = id - rest * prm.Hkv;
+        const int b = quot(rest, prm.d_mpp), chunk = rest - b * pl.mpp;
+        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b, chunk,
+                                                   [&] { return merger_stays(prm, reinterpret_cast<int*>(sh_l), kvh, b, chunk); });
         return;
     }
     const bool is_private = id < pl.n_priv_items;
     int kvh, split, nsplit, rho0, rho_end, slot, b_item = 0;
-    KeyRun run[2];   // run[0]: folded prefix share (may be empty), run[1]: the item's own segment
-    run[0].ntiles = 0;
     if (is_private) {
-        kvh = id % prm.Hkv;
-        int rest = id / prm.Hkv;
-        split = rest % pl.nsplit_priv;
-        rest /= pl.nsplit_priv;
-        const int rg = rest % pl.n_rg_priv;
-        b_item = rest / pl.n_rg_priv;
+        int rest = quot(id, prm.d_hkv);
+        kvh = id - rest * prm.Hkv;
+        const int q = quot(rest, prm.d_nsp);
+        split = rest - q * pl.nsplit_priv;
+        b_item = quot(q, prm.d_rgp);
+        const int rg = q - b_item * pl.n_rg_priv;
         nsplit = pl.nsplit_priv;
         rho0 = b_item * GR + rg * kRowTile * NQT;
         rho_end = min((b_item + 1) * GR, rho0 + kRowTile * NQT);
         slot = pl.nsplit_pre + split;
     } else {
         id -= pl.n_priv_items;
-        kvh = id % prm.Hkv;
-        int rest = id / prm.Hkv;
-        split = rest % pl.nsplit_pre;
-        const int rg = rest / pl.nsplit_pre;
+        const int rest = quot(id, prm.d_hkv);
+        kvh = id - rest * prm.Hkv;
+        const int rg = quot(rest, prm.d_npre);
+        split = rest - rg * pl.nsplit_pre;
         nsplit = pl.nsplit_pre;
         rho0 = rg * kRowTile * NQT;
         rho_end = min(prm.B * GR, rho0 + kRowTile * NQT);
         slot = split;
     }
-    const int L_raw = is_private ? prm.priv_len[b_item] : 0;  // requested here, first used further down
+    // A scalar load: requested here, waited for where it is first used (a vector load was waited for at once, to be moved to a
+    // scalar register: 0.8 us in front of everything else).
+    const int L_raw = is_private ? *((const __attribute__((address_space(4))) int32_t*)prm.priv_len + b_item) : 0;
     // The 32-key tiles of a segment are dealt round-robin to all wavefronts working on it (the 4
     // wavefronts of each of its nsplit items): every wavefront streams the same number of tiles to
     // within one whatever the segment's length, and at any moment the wavefronts of a segment read
     // neighbouring tiles, which spreads each item's traffic over the memory channels.
     const int wave_of_seg = split * kAttnWaves + wave, waves_of_seg = nsplit * kAttnWaves;
-    if (is_private && pl.fold) {
-        run[0].K = (const __bf16*)prm.Kpre + (long long)kvh * prm.kpre_stride_h;
-        run[0].V = (const __bf16*)prm.Vpre + (long long)kvh * prm.kpre_stride_h;
-        run[0].stride_t = prm.kpre_stride_t;
-        run[0].lo = wave_of_seg * kTile;
-        run[0].hi = prm.P;
-        run[0].step = waves_of_seg * kTile;
-        run[0].ntiles = run[0].lo < run[0].hi ? (run[0].hi - run[0].lo + run[0].step - 1) / run[0].step : 0;
-    }
-    const int n_fold = run[0].ntiles;
+    // tiles of a segment of n tiles that wavefront i of those that share it gets
+    auto share_of = [&](int n, int i, FastDiv d) { return i < n ? quot(n - 1 - i, d) + 1 : 0; };
+    KeyRun pre, own;  // folded prefix share (may be empty); the item's own segment
+    pre.K = (const unsigned char*)prm.Kpre + kvh * prm.kpre_stride_h * 2;
+    pre.V = (const unsigned char*)prm.Vpre + kvh * prm.kpre_stride_h * 2;
+    pre.stride = prm.kpre_stride_t * 2;
+    pre.lo = wave_of_seg * kTile;
+    pre.hi = prm.P;
+    const int step = waves_of_seg * kTile;
+    const int n_fold = is_private && pl.fold ? share_of(prm.tiles_pre, wave_of_seg, prm.d_wpriv) : 0;
 
     unsigned char* kslab = lds + wave * SLAB;  // GROUPS = 2: re-pointed every tile
     unsigned char* vslab = kslab + KSLAB;
@@ -603,77 +640,115 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     const int tr_off = ((blk >> 1) * 4 + (i16 >> 2)) * VSTRIDE + ((blk & 1) * 16 + (i16 & 3) * 4) * 2;
 
     // The next tile is fetched into registers while the current one is being consumed from LDS.
-    // K and V are read exactly once, so the loads carry the non-temporal hint.
+    // K and V are read exactly once, so the loads carry the non-temporal hint.  A whole tile's addresses are a scalar base and
+    // one 32-bit offset of the lane.
     constexpr int NLD = NVL / GROUPS;      // load instructions per tile and operand issued by this wavefront
     u32x4 kst[NLD], vst[NLD];
-    auto fetch = [&](int it) {
-        const KeyRun& r = run[it < n_fold ? 0 : 1];
-        const int kb_ = r.lo + (it < n_fold ? it : it - n_fold) * r.step;
+    const int row0_ld = grp * RPI + v_row;
+    auto fetch = [&](const KeyRun& r, int kb_) {
+        const unsigned char *kp = r.K + kb_ * r.stride, *vp = r.V + kb_ * r.stride;
+        const long long pitch = r.stride * (GROUPS * RPI);
+        if (kb_ + kTile <= r.hi && prm.near_rows) {
+            const unsigned off = (unsigned)row0_ld * (unsigned)r.stride + v_chunk * 16;
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            int key = kb_ + (i * GROUPS + grp) * RPI + v_row;
-            key = key < r.hi ? key : r.hi - 1;  // a ragged last tile re-reads its last row; masked below
-            const long long off = (long long)key * r.stride_t + v_chunk * 8;
-            kst[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(r.K + off));
-            vst[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(r.V + off));
+            for (int i = 0; i < NLD; ++i) {
+                kst[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + i * pitch + off));
+                vst[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + i * pitch + off));
+            }
+            asm volatile("");  // keeps the compiler from merging these loads with the ones below, addresses per lane
+        } else {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) {
+                int key = i * GROUPS * RPI + row0_ld;
+                key = min(key, r.hi - 1 - kb_);  // a ragged last tile re-reads its last row; masked below
+                const long long off = key * r.stride + v_chunk * 16;
+                kst[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + off));
+                vst[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + off));
+            }
         }
     };
-    if (n_fold > 0) fetch(0);
-
     // ---- Q fragments (B operand of S^T = K Q^T: lane = query row ln, 8 contiguous d) ----
+    // Straight from memory they are 32-byte pieces of 32 rows an instruction, and come again for every wavefront: with two row
+    // tiles as many bytes as the item's keys and values.  Two row tiles: the whole workgroup requests the rows once, 16
+    // bytes a thread, and they pass through LDS further down (8 x 2 heads x 2560 tokens, 40 rows, 13.7 -> 13.1 us; with one
+    // row tile the passage costs more than it saves, 1 x 2 x 8192 9.4 -> 9.7).  Rows beyond the item's carry its first row again:
+    // nothing of theirs is ever stored.
+    constexpr bool QLDS = NQT > 1;
+    constexpr int QLD = kRowTile * NQT * LPR / (kAttnThreads * GROUPS);  // loads per thread
+    u32x4 qst[QLD];
     bf16x8 qf[TW][KS];
-    int q_r[TW];  // position (0..k) of this lane's query row
+    auto row_of = [&](int i, int& r, int& h, int& b) {  // row i of the item: position, query head, branch
+        const int rc = rho0 + i < rho_end ? rho0 + i : rho0;
+        b = is_private ? b_item : quot(rc, prm.d_gr);
+        const int rl = rc - b * GR;
+        r = quot(rl, prm.d_g);
+        h = kvh * prm.G + rl - r * prm.G;
+    };
+    if (!QLDS && n_fold > 0) fetch(pre, pre.lo);
 #pragma unroll
     for (int t = 0; t < TW; ++t) {
-        const int rho = rho0 + (grp * TW + t) * kRowTile + ln;
-        const bool valid = rho < rho_end;
-        const int rc = valid ? rho : rho0;
-        const int b = rc / GR, rl = rc - b * GR;
-        const int r = rl / prm.G, hg = rl - r * prm.G;
-        q_r[t] = r;
-        const __bf16* qp = (const __bf16*)prm.Q + (long long)b * prm.q_stride_b + (long long)r * prm.q_stride_r +
-                           (long long)(kvh * prm.G + hg) * prm.q_stride_h;
+        if (QLDS) break;
+        int r, h, b;
+        row_of((grp * TW + t) * kRowTile + ln, r, h, b);
+        const __bf16* qp = (const __bf16*)prm.Q + b * prm.q_stride_b + r * prm.q_stride_r + h * prm.q_stride_h;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            bf16x8 v = load_bf16x8(qp + (2 * s + hh) * 8);
-            if (!valid) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = (__bf16)0.0f;
-            }
-            qf[t][s] = v;
-        }
+        for (int s = 0; s < KS; ++s) qf[t][s] = load_bf16x8(qp + (2 * s + hh) * 8);
     }
+#pragma unroll
+    for (int i = 0; i < QLD; ++i) {
+        if (!QLDS) break;
+        int r, h, b;
+        row_of((tid + i * kAttnThreads * GROUPS) / LPR, r, h, b);
+        const __bf16* qp = (const __bf16*)prm.Q + b * prm.q_stride_b + r * prm.q_stride_r + h * prm.q_stride_h;
+        qst[i] = *reinterpret_cast<const u32x4*>(qp + tid % LPR * 8);
+    }
+    if (QLDS && n_fold > 0) fetch(pre, pre.lo);
 
     // ---- the item's own segment ----
-    int seg_len, causal_base;
+    int causal_base, n_own;
     if (is_private) {
         const int L = L_raw < prm.R ? prm.R : (L_raw > prm.Lmax ? prm.Lmax : L_raw);
-        seg_len = L;
+        own.hi = L;
         causal_base = L - prm.k;  // row at position r sees private keys [0, L - k + r)
-        const long long off = (long long)b_item * prm.kpriv_stride_b + (long long)kvh * prm.kpriv_stride_h;
-        run[1].K = (const __bf16*)prm.Kpriv + off;
-        run[1].V = (const __bf16*)prm.Vpriv + off;
-        run[1].stride_t = prm.kpriv_stride_t;
+        const long long off = (b_item * prm.kpriv_stride_b + kvh * prm.kpriv_stride_h) * 2;
+        own.K = (const unsigned char*)prm.Kpriv + off;
+        own.V = (const unsigned char*)prm.Vpriv + off;
+        own.stride = prm.kpriv_stride_t * 2;
+        // The dealing goes on where the folded prefix tiles stopped: prefix and private tiles form one
+        // sequence, so a wavefront that got one prefix tile more gets one private tile less.
+        int i = wave_of_seg - prm.first_wave;
+        i = i < 0 ? i + waves_of_seg : i;
+        own.lo = i * kTile;
+        n_own = share_of((L - 1) / kTile + 1, i, prm.d_wpriv);
     } else {
-        seg_len = prm.P;
+        own = pre;
         causal_base = prm.P;  // every row sees the whole prefix
-        run[1].K = (const __bf16*)prm.Kpre + (long long)kvh * prm.kpre_stride_h;
-        run[1].V = (const __bf16*)prm.Vpre + (long long)kvh * prm.kpre_stride_h;
-        run[1].stride_t = prm.kpre_stride_t;
+        n_own = share_of(prm.tiles_pre, wave_of_seg, prm.d_wpre);
     }
-    // The dealing goes on where the folded prefix tiles stopped: prefix and private tiles form one
-    // sequence, so a wavefront that got one prefix tile more gets one private tile less.
-    int first_wave = 0;
-    if (is_private && pl.fold) first_wave = ((prm.P + kTile - 1) / kTile) % waves_of_seg;
-    run[1].lo = ((wave_of_seg - first_wave + waves_of_seg) % waves_of_seg) * kTile;
-    run[1].hi = seg_len;
-    run[1].step = waves_of_seg * kTile;
-    run[1].ntiles = run[1].lo < seg_len ? (seg_len - run[1].lo + run[1].step - 1) / run[1].step : 0;
-    const int n_tiles = n_fold + run[1].ntiles;
-    if (n_fold == 0 && n_tiles > 0) fetch(0);
+    const int n_tiles = n_fold + n_own;
+    if (n_fold == 0 && n_tiles > 0) fetch(own, own.lo);
     int lim[TW];  // keys of this wavefront's own run visible to this lane's query row
 #pragma unroll
-    for (int t = 0; t < TW; ++t) lim[t] = min(is_private ? causal_base + q_r[t] : causal_base, run[1].hi);
+    for (int t = 0; t < TW; ++t) {
+        int r, h, b;
+        row_of((grp * TW + t) * kRowTile + ln, r, h, b);
+        lim[t] = min(is_private ? causal_base + r : causal_base, own.hi);
+    }
+    if (QLDS) {  // the slabs are free; the first tile is on its way
+#pragma unroll
+        for (int i = 0; i < QLD; ++i) {
+            const int e = tid + i * kAttnThreads * GROUPS;
+            *reinterpret_cast<u32x4*>(lds + e / LPR * KSTRIDE + e % LPR * 16) = qst[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < TW; ++t)
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                qf[t][s] = *reinterpret_cast<const bf16x8*>(lds + ((grp * TW + t) * kRowTile + ln) * KSTRIDE + (2 * s + hh) * 16);
+        if (GROUPS > 1 && tid < kAttnWaves) sh_pair[tid] = 0;
+        __syncthreads();
+    }
 
     // ---- running state ----
     f32x16 oacc[TW][DB];
@@ -688,13 +763,9 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             for (int i = 0; i < 16; ++i) oacc[t][db][i] = 0.f;
     }
 
-    if (GROUPS > 1) {  // the two wavefronts of a pair count their half tiles here
-        if (tid < kAttnWaves) sh_pair[tid] = 0;
-        __syncthreads();
-    }
     for (int it = 0; it < n_tiles; ++it) {
         const bool folded = it < n_fold;
-        const int kbase = folded ? run[0].lo + it * run[0].step : run[1].lo + (it - n_fold) * run[1].step;
+        const int kbase = folded ? pre.lo + it * step : own.lo + (it - n_fold) * step;
         if (GROUPS > 1) {
             kslab = lds + ((it & 1) * kAttnWaves + wave) * SLAB;
             vslab = kslab + KSLAB;
@@ -713,7 +784,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
                 __builtin_amdgcn_s_sleep(1);
             }
         }
-        if (it + 1 < n_tiles) fetch(it + 1);
+        if (it + 1 < n_fold) fetch(pre, kbase + step);
+        else if (it + 1 < n_tiles) fetch(own, own.lo + (it + 1 - n_fold) * step);
         // K fragments (A operand of S^T = K Q^T: lane = key row ln, 8 contiguous d)
         bf16x8 kf[KS];
 #pragma unroll
@@ -731,7 +803,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc, 0, 0, 0);
             // register i of this lane is key kbase + (i/4)*8 + hh*4 + i%4 for query row ln;
             // every row sees all of a prefix share, the causal limit applies to the own run only
-            const int vis = (folded ? run[0].hi : lim[t]) - kbase - hh * 4;  // key offsets below this are visible
+            const int vis = (folded ? pre.hi : lim[t]) - kbase - hh * 4;  // key offsets below this are visible
             float mx = -INFINITY;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -900,14 +972,14 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             const int c = __ffsll((long long)left) - 1;
             if (tid < pl.nslots) cell_clear(merger_flags(prm, kvh, b_item, c) + tid);
             if (tid == 0) cell_clear(merger_count(prm, kvh, b_item, c));
-            merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b_item, c, true);
+            merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b_item, c, [] { return true; });
             __syncthreads();
         }
         return;
     }
     int* sh_last = reinterpret_cast<int*>(sh_l);  // free again; kAttnWaves * kRowTile >= rows of an item
     const int rows_per_item = kRowTile * NQT;
-    const int b_first = rho0 / GR, b_last = (rho_end - 1) / GR;
+    const int b_first = quot(rho0, prm.d_gr), b_last = quot(rho_end - 1, prm.d_gr);
     const int nb = b_last - b_first + 1;  // <= rows_per_item
     if (tid < nb) {
         const int b = b_first + tid;
@@ -962,7 +1034,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
 template <int D>
 __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(const AttnParams prm) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnThreads * (sizeof(float4) + sizeof(float2))];
-    merge_rows<D, false, kAttnThreads>(prm, lds, blockIdx.y % prm.Hkv, blockIdx.y / prm.Hkv, blockIdx.x, true);
+    const int b = quot(blockIdx.y, prm.d_hkv);
+    merge_rows<D, false, kAttnThreads>(prm, lds, blockIdx.y - b * prm.Hkv, b, blockIdx.x, [] { return true; });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1132,7 +1205,7 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     prm.O = O; prm.lse = lse;
     prm.B = d.B; prm.k = d.k; prm.R = d.k + 1; prm.Hq = d.Hq; prm.Hkv = d.Hkv; prm.G = d.Hq / d.Hkv;
     prm.GR = prm.G * prm.R; prm.D = d.D; prm.P = d.P; prm.Lmax = d.Lmax;
-    prm.g_magic = (unsigned)((0x100000000ULL + (unsigned)prm.G - 1) / (unsigned)prm.G);  // G = 1 wraps to 0: handled where it is used
+    prm.d_g = fast_div(prm.G);
     const double scale = d.scale > 0.0f ? (double)d.scale : 1.0 / sqrt((double)d.D);
     prm.scale_log2 = (float)(scale * 1.4426950408889634074);
     prm.q_stride_b = d.q_stride_b; prm.q_stride_r = d.q_stride_r; prm.q_stride_h = d.q_stride_h;
@@ -1161,6 +1234,13 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     prm.off_o = (unsigned)off_o;
     prm.off_ml = (unsigned)off_ml;
     prm.counters = static_cast<unsigned long long*>(workspace);
+    prm.d_hkv = fast_div(d.Hkv); prm.d_nsp = fast_div(pl.nsplit_priv); prm.d_rgp = fast_div(pl.n_rg_priv);
+    prm.d_npre = fast_div(pl.nsplit_pre > 0 ? pl.nsplit_pre : 1); prm.d_mpp = fast_div(pl.mpp > 0 ? pl.mpp : 1); prm.d_gr = fast_div(prm.GR);
+    prm.d_wpriv = fast_div(kAttnWaves * pl.nsplit_priv); prm.d_wpre = fast_div(kAttnWaves * (pl.nsplit_pre > 0 ? pl.nsplit_pre : 1));
+    prm.tiles_pre = ceil_div(d.P, kTile);
+    prm.first_wave = pl.fold ? prm.tiles_pre % (kAttnWaves * pl.nsplit_priv) : 0;
+    const long long tile_span = (1LL << 31) / (2 * kTile);  // elements from key to key
+    prm.near_rows = d.kpriv_stride_t < tile_span && d.kpre_stride_t < tile_span;
     prm.tag = (g_call_tag.fetch_add(1, std::memory_order_relaxed) + 1) << kTagShift;
     const long long items = (long long)pl.n_pre_items + pl.n_priv_items + pl.n_merge;
     if (items > 0x7fffffffLL) return LOTTS_ERR_SHAPE;
