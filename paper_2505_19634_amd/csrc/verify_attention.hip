@@ -22,7 +22,9 @@
 //       wavefront streams its tiles with coalesced non-temporal 16-byte loads into registers one
 //       tile ahead, staged through a wavefront-private LDS slab
 //       (K read back row-wise as the MFMA A operand, V with the transposing LDS load), S^T = K Q^T
-//       and O^T += V^T P^T on 32x32x16 bf16 MFMA, flash-style running (max, sum, O).  The 4 states
+//       and O^T += V^T P^T on 32x32x16 bf16 MFMA, flash-style running (max, sum, O).  Where no wavefront gets more than
+//       one tile, a form of its own (ONE): the wavefronts publish their tiles' weights, and each forms a block of the item's output
+//       over all of them.  The 4 states
 //       are combined through LDS after one barrier and the item's un-normalised partial goes to
 //       the workspace -- or, if the item holds whole rows (no key shares, no prefix items), straight to O.
 //       Who merges the partials of a row depends on how many there are: of two, or of up to eight with few bytes, the item
@@ -75,6 +77,8 @@ struct AttnPlan {
     int n_merge;
     int nqt;            // row tiles per item: 1 or 2
     int n_rg_pre;       // row groups per KV head over all branches' stacked rows (stacked plan)
+    int one;            // 1: no wavefront of an item gets more than one key tile
+    int runs;           // runs of key tiles of an item
 };
 constexpr int kMergeLast = 0;    // the last-arriving workgroup of a (KV head, branch), inside the attention launch
 constexpr int kMergeGroups = 1;  // merge workgroups at the end of the attention launch's grid
@@ -178,6 +182,18 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
         pl.nsplit_priv = ceil_div(tiles_all, kAttnWaves * per_wave);
     }
     pl.nsplit_pre = pre_shares(pl.nsplit_priv);
+    // A form of its own where no wavefront gets more than one tile: four wavefronts to a row tile, eight to two (14 branches x 4
+    // heads x 448 tokens 9.9 -> 9.3 us, 12 x 1 x 736 9.7 -> 9.2, 8 x 2 heads x 2560 with 40 rows 12.8 -> 12.3).  Taking several tiles in
+    // rounds of it is level at two (20 x 4 .. 88 x 1: -2.5 .. +2.8 %) and loses from three on, and so do eight wavefronts that share four
+    // tiles (2 x 1 heads x 1888, 35 rows, 11.8 -> 12.6).  Not at D = 64, where the output has fewer blocks than there are
+    // wavefronts: level with one tile, 1 x 8 x 2600 behind 960 with two 9.7 -> 10.1.
+    int longest = ceil_div(tiles_all, kAttnWaves * pl.nsplit_priv);
+    if (pl.nsplit_pre > 0) {
+        const int longest_pre = ceil_div(tiles_pre, kAttnWaves * pl.nsplit_pre);
+        longest = longest > longest_pre ? longest : longest_pre;
+    }
+    pl.one = d.D == 128 && longest == pl.nqt;
+    pl.runs = pl.one ? kAttnWaves * pl.nqt : kAttnWaves;
     pl.nslots = pl.nsplit_pre + pl.nsplit_priv;
     // Who merges (measured with calls back to back, kernel + what merges):
     //  - an item that holds whole rows stores the output: 32 branches x 8 KV heads x 3168 tokens 57.3 -> 53.3 us;
@@ -541,14 +557,18 @@ struct KeyRun {
 // ---------------------------------------------------------------------------------------------
 // bf16 partial attention
 // ---------------------------------------------------------------------------------------------
-template <int D, int NQT, int GROUPS>
+template <int D, int NQT, int GROUPS, bool ONE>
 __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn_kernel(const AttnParams prm) {
     // GROUPS = 2: eight wavefronts, two per SIMD.  The second group of four takes the second row tile; wavefront w of
     // either group streams the same key tiles, so the two share them: each loads half of a tile into a slab both
     // read (two slabs per pair, taking turns; the pair meets once per tile at a counter in LDS, the four pairs stay
     // independent of each other).
     static_assert(GROUPS == 1 || (GROUPS == 2 && NQT == 2), "two groups split two row tiles");
-    constexpr int TW = NQT / GROUPS;       // row tiles per wavefront
+    static_assert(!ONE || (D == 128 && GROUPS == NQT), "every wavefront owns a block of the output");
+    // ONE: every wavefront has one key tile at most, its own, and works on all rows' scores.
+    constexpr int RUNS = ONE ? kAttnWaves * GROUPS : kAttnWaves;  // runs of key tiles of an item
+    constexpr int LG = ONE ? 1 : GROUPS;                          // wavefronts that load a tile together
+    constexpr int TW = ONE ? NQT : NQT / GROUPS;                  // row tiles per wavefront
     constexpr int KS = D / 16;             // MFMA k-steps of the QK^T contraction
     constexpr int DB = D / 32;             // 32-wide blocks of the head dimension
     constexpr int KSTRIDE = D * 2 + 16;    // bytes per key row of the K slab (pad: conflict-free 16-byte row reads)
@@ -560,13 +580,14 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     static_assert(OBUF <= SLAB, "the merge buffer reuses the wavefront's slab");
     static_assert(kRowTile * NQT * KSTRIDE <= kAttnWaves * GROUPS * SLAB, "Q passes through the slabs");
     __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnWaves * GROUPS * SLAB];
+    __shared__ float2 sh_ml[ONE ? RUNS * NQT : 1][kRowTile];  // ONE: (maximum, sum) of the rows of a tile
     __shared__ float sh_m[kAttnWaves * GROUPS][kRowTile];
     __shared__ __attribute__((aligned(8))) float sh_l[kAttnWaves * GROUPS][kRowTile];
     __shared__ int sh_pair[kAttnWaves];  // GROUPS = 2: half tiles stored by the pair of wavefronts w and w + 4
 
     const int tid = threadIdx.x, wave_all = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
-    const int grp = GROUPS == 1 ? 0 : wave_all / kAttnWaves;         // which row tile(s) this wavefront works on
-    const int wave = GROUPS == 1 ? wave_all : wave_all % kAttnWaves;  // which of the item's four runs of key tiles it streams
+    const int grp = LG == 1 ? 0 : wave_all / kAttnWaves;         // which row tile(s) this wavefront works on
+    const int wave = LG == 1 ? wave_all : wave_all % kAttnWaves;  // which of the item's runs of key tiles it streams
     const int ln = lane & 31;   // MFMA column (query row) / A row (key or d) owned by this lane
     const int hh = lane >> 5;   // which half of each 16-wide k block this lane holds
     const AttnPlan& pl = prm.plan;
@@ -615,7 +636,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     // wavefronts of each of its nsplit items): every wavefront streams the same number of tiles to
     // within one whatever the segment's length, and at any moment the wavefronts of a segment read
     // neighbouring tiles, which spreads each item's traffic over the memory channels.
-    const int wave_of_seg = split * kAttnWaves + wave, waves_of_seg = nsplit * kAttnWaves;
+    const int wave_of_seg = split * RUNS + wave, waves_of_seg = nsplit * RUNS;
     // tiles of a segment of n tiles that wavefront i of those that share it gets
     auto share_of = [&](int n, int i, FastDiv d) { return i < n ? quot(n - 1 - i, d) + 1 : 0; };
     KeyRun pre, own;  // folded prefix share (may be empty); the item's own segment
@@ -625,7 +646,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     pre.lo = wave_of_seg * kTile;
     pre.hi = prm.P;
     const int step = waves_of_seg * kTile;
-    const int n_fold = is_private && pl.fold ? share_of(prm.tiles_pre, wave_of_seg, prm.d_wpriv) : 0;
+    const int fold_tiles = is_private && pl.fold ? prm.tiles_pre : 0;
+    const int n_fold = share_of(fold_tiles, wave_of_seg, prm.d_wpriv);
 
     unsigned char* kslab = lds + wave * SLAB;  // GROUPS = 2: re-pointed every tile
     unsigned char* vslab = kslab + KSLAB;
@@ -642,12 +664,12 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     // The next tile is fetched into registers while the current one is being consumed from LDS.
     // K and V are read exactly once, so the loads carry the non-temporal hint.  A whole tile's addresses are a scalar base and
     // one 32-bit offset of the lane.
-    constexpr int NLD = NVL / GROUPS;      // load instructions per tile and operand issued by this wavefront
+    constexpr int NLD = NVL / LG;          // load instructions per tile and operand issued by this wavefront
     u32x4 kst[NLD], vst[NLD];
     const int row0_ld = grp * RPI + v_row;
     auto fetch = [&](const KeyRun& r, int kb_) {
         const unsigned char *kp = r.K + kb_ * r.stride, *vp = r.V + kb_ * r.stride;
-        const long long pitch = r.stride * (GROUPS * RPI);
+        const long long pitch = r.stride * (LG * RPI);
         if (kb_ + kTile <= r.hi && prm.near_rows) {
             const unsigned off = (unsigned)row0_ld * (unsigned)r.stride + v_chunk * 16;
 #pragma unroll
@@ -659,7 +681,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
         } else {
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
-                int key = i * GROUPS * RPI + row0_ld;
+                int key = i * LG * RPI + row0_ld;
                 key = min(key, r.hi - 1 - kb_);  // a ragged last tile re-reads its last row; masked below
                 const long long off = key * r.stride + v_chunk * 16;
                 kst[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + off));
@@ -705,7 +727,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     if (QLDS && n_fold > 0) fetch(pre, pre.lo);
 
     // ---- the item's own segment ----
-    int causal_base, n_own;
+    int causal_base, n_own, own_tiles;
     if (is_private) {
         const int L = L_raw < prm.R ? prm.R : (L_raw > prm.Lmax ? prm.Lmax : L_raw);
         own.hi = L;
@@ -719,11 +741,13 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
         int i = wave_of_seg - prm.first_wave;
         i = i < 0 ? i + waves_of_seg : i;
         own.lo = i * kTile;
-        n_own = share_of((L - 1) / kTile + 1, i, prm.d_wpriv);
+        own_tiles = (L - 1) / kTile + 1;
+        n_own = share_of(own_tiles, i, prm.d_wpriv);
     } else {
         own = pre;
         causal_base = prm.P;  // every row sees the whole prefix
-        n_own = share_of(prm.tiles_pre, wave_of_seg, prm.d_wpre);
+        own_tiles = prm.tiles_pre;
+        n_own = share_of(own_tiles, wave_of_seg, prm.d_wpre);
     }
     const int n_tiles = n_fold + n_own;
     if (n_fold == 0 && n_tiles > 0) fetch(own, own.lo);
@@ -746,204 +770,331 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 qf[t][s] = *reinterpret_cast<const bf16x8*>(lds + ((grp * TW + t) * kRowTile + ln) * KSTRIDE + (2 * s + hh) * 16);
-        if (GROUPS > 1 && tid < kAttnWaves) sh_pair[tid] = 0;
+        if (!ONE && GROUPS > 1 && tid < kAttnWaves) sh_pair[tid] = 0;
         __syncthreads();
     }
 
-    // ---- running state ----
-    f32x16 oacc[TW][DB];
-    float m_run[TW], l_run[TW];
+    // ---- results of the item: output quads (4 columns from c4 * 4 of rows row0 + q * RSTEP of a row tile) and their (max, sum) ----
+    constexpr int F4 = D / 4;
+    constexpr int QPT = kRowTile * F4 / kAttnThreads;  // per thread and row tile: 4 (D = 128) or 2 (D = 64)
+    constexpr int RSTEP = kAttnThreads / F4;
+    const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
+    const int tig = tid % kAttnThreads;  // thread within its group of four wavefronts
+    const int c4 = ONE ? (wave_all % DB) * 8 + (lane & 7) : tig % F4, row0 = ONE ? lane >> 3 : tig / F4;
+    float4 own_o[QPT];    // the combined quads, kept for a merge by this workgroup (kMergePair: one row tile)
+    float2 own_ml[QPT];
+    // Those of the first nrows rows go out: as the output itself, or as this item's partial.
+    auto put = [&](int tile, int nrows) {
+        const int rho = rho0 + tile * kRowTile + row0;
+        if (pl.merge == kMergeNone) {
 #pragma unroll
-    for (int t = 0; t < TW; ++t) {
-        m_run[t] = -INFINITY;
-        l_run[t] = 0.f;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[t][db][i] = 0.f;
-    }
-
-    for (int it = 0; it < n_tiles; ++it) {
-        const bool folded = it < n_fold;
-        const int kbase = folded ? pre.lo + it * step : own.lo + (it - n_fold) * step;
-        if (GROUPS > 1) {
-            kslab = lds + ((it & 1) * kAttnWaves + wave) * SLAB;
-            vslab = kslab + KSLAB;
+            for (int q = 0; q < QPT; ++q)
+                if (row0 + q * RSTEP < nrows) store_merged(prm, kvh, b_item, rho + q * RSTEP - b_item * GR, c4, own_o[q], own_ml[q].x, own_ml[q].y);
+            return;
         }
+        const unsigned pidx = ((unsigned)kvh * prm.B * GR + rho) * pl.nslots + slot, step_q = RSTEP * pl.nslots;
+        unsigned at_o = prm.off_o + (pidx * D + c4 * 4) * 4u, at_ml = prm.off_ml + pidx * 8u;
+        if (pl.merge != kMergeLaunch) {
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            *reinterpret_cast<u32x4*>(kslab + ((i * GROUPS + grp) * RPI + v_row) * KSTRIDE + v_chunk * 16) = kst[i];
-            *reinterpret_cast<u32x4*>(vslab + ((i * GROUPS + grp) * RPI + v_row) * VSTRIDE + v_chunk * 16) = vst[i];
-        }
-        if (GROUPS > 1) {
-            // both halves written: the pair's counter stands at 2 * (it + 1).  Whoever gets past this has also left
-            // the tile before behind (it counted this tile only after that), so the other slab is free.
-            if (lane == 0) __hip_atomic_fetch_add(&sh_pair[wave], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            for (int spin = 0; spin < (1 << 20); ++spin) {  // the partner runs the same tiles: the wait ends; bounded all the same
-                if (__hip_atomic_load(&sh_pair[wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= 2 * (it + 1)) break;
-                __builtin_amdgcn_s_sleep(1);
+            for (int q = 0; q < QPT; ++q) {
+                if (row0 + q * RSTEP < nrows) {
+                    ws_store4<true>(rs, at_o, own_o[q]);
+                    if (c4 == 0) ws_store2<true>(rs, at_ml, own_ml[q]);
+                }
+                at_o += step_q * D * 4u;
+                at_ml += step_q * 8u;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < QPT; ++q) {
+                if (row0 + q * RSTEP < nrows) {
+                    ws_store4<false>(rs, at_o, own_o[q]);
+                    if (c4 == 0) ws_store2<false>(rs, at_ml, own_ml[q]);
+                }
+                at_o += step_q * D * 4u;
+                at_ml += step_q * 8u;
             }
         }
-        if (it + 1 < n_fold) fetch(pre, kbase + step);
-        else if (it + 1 < n_tiles) fetch(own, own.lo + (it + 1 - n_fold) * step);
-        // K fragments (A operand of S^T = K Q^T: lane = key row ln, 8 contiguous d)
-        bf16x8 kf[KS];
+    };
+    if constexpr (ONE) {
+        // Nothing runs here: a wavefront publishes its tile's weights P with their maxima and sums per row, and after a barrier
+        // wavefront w multiplies block w of the output (32 columns of a row tile) over the keys of ALL the item's tiles, each tile's
+        // product weighted by its maximum.  (Parking every wavefront's whole output and adding the four up, as after the loop below,
+        // is 1.7 us of an item whose one tile takes 0.7; this way 1.1 us for both.)
+        const int nt = max(0, min(fold_tiles + own_tiles - split * RUNS, RUNS));  // tiles of the item: of wavefronts 0 .. nt - 1
+        const int db = wave_all % DB, t_own = wave_all / DB;
+        if (n_tiles > 0) {
+            const int kbase = n_fold > 0 ? pre.lo : own.lo;
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
-            kf[s] = *reinterpret_cast<const bf16x8*>(kslab + ln * KSTRIDE + (2 * s + hh) * 16);
-
-        bf16x8 pf[TW][2];
+            for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(kslab + (i * RPI + v_row) * KSTRIDE + v_chunk * 16) = kst[i];
 #pragma unroll
-        for (int t = 0; t < TW; ++t) {
-            // S^T[key][query] = sum_d K[key][d] Q[query][d]
+            for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(vslab + (i * RPI + v_row) * VSTRIDE + v_chunk * 16) = vst[i];
+            f32x16 acc[NQT];
+            bf16x8 kf[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(kslab + ln * KSTRIDE + (2 * s + hh) * 16);
+            __builtin_amdgcn_sched_barrier(0);  // all of them requested first
+#pragma unroll
+            for (int t = 0; t < NQT; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int t = 0; t < NQT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc[t], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < NQT; ++t) {
+                const int vis = (n_fold > 0 ? pre.hi : lim[t]) - kbase - hh * 4;
+                float mx = -INFINITY;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    float sc = acc[t][i] * prm.scale_log2;
+                    sc = (i >> 2) * 8 + (i & 3) < vis ? sc : -INFINITY;
+                    acc[t][i] = sc;
+                    mx = fmaxf(mx, sc);
+                }
+                mx = fmaxf(mx, shfl_xor_f(mx, 32));
+                const float m_use = (mx == -INFINITY) ? 0.f : mx;
+                bf16x8 pf[2];
+                float psum = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float pv = __builtin_amdgcn_exp2f(acc[t][i] - m_use);
+                    psum += pv;
+                    pf[i >> 3][i & 7] = (__bf16)pv;
+                }
+                psum += shfl_xor_f(psum, 32);
+                if (hh == 0) sh_ml[wave_all * NQT + t][ln] = make_float2(mx, psum);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)  // over the wavefront's own K tile, which nobody needs any more
+                    *reinterpret_cast<bf16x8*>(kslab + ((t * 2 + kb) * kWave + lane) * 16) = pf[kb];
+            }
+        }
+        __syncthreads();  // V tiles, P, maxima and sums are in LDS
+        float2 ml[RUNS];  // of row ln of the own row tile
+        f32x16 o;
+        float m_row = -INFINITY, l_row = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) ml[j] = sh_ml[j * NQT + t_own][ln];
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) ml[j].x = j < nt ? ml[j].x : -INFINITY;  // (beyond the last tile nobody has written)
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) m_row = fmaxf(m_row, ml[j].x);
+        const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
+#pragma unroll
+        for (int j = 0; j < RUNS; ++j) {
+            if (j >= nt) break;
+            const float w = __builtin_amdgcn_exp2f(ml[j].x - m_use);
+            l_row += ml[j].y * w;
             f32x16 acc;
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
-            for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc, 0, 0, 0);
-            // register i of this lane is key kbase + (i/4)*8 + hh*4 + i%4 for query row ln;
-            // every row sees all of a prefix share, the causal limit applies to the own run only
-            const int vis = (folded ? pre.hi : lim[t]) - kbase - hh * 4;  // key offsets below this are visible
-            float mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int koff = (i >> 2) * 8 + (i & 3);
-                float sc = acc[i] * prm.scale_log2;
-                sc = koff < vis ? sc : -INFINITY;
-                acc[i] = sc;
-                mx = fmaxf(mx, sc);
-            }
-            mx = fmaxf(mx, shfl_xor_f(mx, 32));
-            const float m_new = fmaxf(m_run[t], mx);
-            const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_use);
-            float psum = 0.f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float pv = __builtin_amdgcn_exp2f(acc[i] - m_use);
-                psum += pv;
-                pf[t][i >> 3][i & 7] = (__bf16)pv;
-            }
-            l_run[t] = l_run[t] * alpha + psum;
-            m_run[t] = m_new;
-            // Rescaling the accumulators is the largest block of vector work of a tile, and once a few hundred keys have
-            // gone by a tile rarely raises any row's maximum: alpha is exactly 1 for every lane then and the whole
-            // wavefront skips it (multiplying by 1 changes nothing, so the result is the same bit for bit).
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) oacc[t][db][i] *= alpha;
-            }
-        }
-        // O^T[d][query] += sum_key V[key][d] P^T[key][query]; V^T fragments by transposing LDS reads
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-#pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const unsigned char* ap = vslab + tr_off + (kb * 16) * VSTRIDE + db * 64;
-                const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) short4v*)(ap));
-                const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) short4v*)(ap + 8 * VSTRIDE));
+                const unsigned char* ap = lds + j * SLAB + KSLAB + tr_off + (kb * 16) * VSTRIDE + db * 64;
                 union {
                     short4v s[2];
                     bf16x8 v;
                 } vf;
-                vf.s[0] = lo;
-                vf.s[1] = hi;
-#pragma unroll
-                for (int t = 0; t < TW; ++t)
-                    oacc[t][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf[t][kb], oacc[t][db], 0, 0, 0);
+                vf.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap));
+                vf.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap + 8 * VSTRIDE));
+                const bf16x8 pf = *reinterpret_cast<const bf16x8*>(lds + j * SLAB + ((t_own * 2 + kb) * kWave + lane) * 16);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf, acc, 0, 0, 0);
             }
-        }
-    }
-
-    // ---- combine the 4 wavefronts' states of a row tile (fixed order) and store the item's partial ----
-    // Each wavefront parks its raw state in LDS (its slab is free now); after one barrier the 256 threads
-    // of a group of four wavefronts form sum_w 2^(m_w - m) O_w over their group and write the valid rows out,
-    // coalesced (two groups: both row tiles at the same time).  A thread owns QPT output quads of a row
-    // tile -- quad t + 256 q, t its number within the group: the same column of rows RSTEP apart -- and
-    // reads everything it needs for all of them before it uses any of it.
-    constexpr int F4 = D / 4;
-    constexpr int QPT = kRowTile * F4 / kAttnThreads;  // 4 (D = 128) or 2 (D = 64)
-    constexpr int RSTEP = kAttnThreads / F4;
-    if (GROUPS > 1) __syncthreads();  // nobody reads a key tile any more: the slabs become merge buffers
-    float* obuf = reinterpret_cast<float*>(lds + wave_all * SLAB);
-    const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
-    const int tig = tid % kAttnThreads;  // thread within its group of four wavefronts
-    const int c4 = tig % F4, row0 = tig / F4;
-    float4 own_o[QPT];    // the combined quads, kept for a merge by this workgroup (kMergePair: one row tile)
-    float2 own_ml[QPT];
 #pragma unroll
-    for (int t = 0; t < TW; ++t) {
-        if (t > 0) __syncthreads();  // the previous row tile has been read out
-        const int tile = grp * TW + t;  // row tile of the item
-        const float lsum = l_run[t] + shfl_xor_f(l_run[t], 32);
-        if (hh == 0) {
-            sh_m[wave_all][ln] = m_run[t];
-            sh_l[wave_all][ln] = lsum;
+            for (int i = 0; i < 16; ++i) o[i] += acc[i] * w;
         }
-        const int nrows = min(kRowTile, rho_end - (rho0 + tile * kRowTile));
-        if (ln < nrows) {  // rows beyond the item's are never read back
+        __syncthreads();  // the tiles and P have been read
+        {  // the block turns through LDS, wavefront-private, into 128-byte pieces of rows
+            constexpr int TSTRIDE = 36;  // floats per row of the block
+            float* ob = reinterpret_cast<float*>(lds + wave_all * SLAB);
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+                *reinterpret_cast<float4*>(ob + ln * TSTRIDE + q4 * 8 + hh * 4) = make_float4(o[q4 * 4 + 0], o[q4 * 4 + 1], o[q4 * 4 + 2], o[q4 * 4 + 3]);
+            if (hh == 0) *reinterpret_cast<float2*>(ob + ln * TSTRIDE + 32) = make_float2(m_row, l_row);
+#pragma unroll
+            for (int q = 0; q < QPT; ++q) {
+                const int row = row0 + q * RSTEP;
+                own_o[q] = *reinterpret_cast<const float4*>(ob + row * TSTRIDE + (lane & 7) * 4);
+                own_ml[q] = *reinterpret_cast<const float2*>(ob + row * TSTRIDE + 32);
+            }
+            put(t_own, min(kRowTile, rho_end - (rho0 + t_own * kRowTile)));
+        }
+    } else {
+        // ---- running state ----
+        f32x16 oacc[TW][DB];
+        float m_run[TW], l_run[TW];
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            m_run[t] = -INFINITY;
+            l_run[t] = 0.f;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-                    *reinterpret_cast<float4*>(obuf + ln * OSTRIDE + db * 32 + q4 * 8 + hh * 4) =
-                        make_float4(oacc[t][db][q4 * 4 + 0], oacc[t][db][q4 * 4 + 1], oacc[t][db][q4 * 4 + 2],
-                                    oacc[t][db][q4 * 4 + 3]);
+                for (int i = 0; i < 16; ++i) oacc[t][db][i] = 0.f;
         }
-        __syncthreads();
-        float mw[QPT][kAttnWaves], lw[QPT][kAttnWaves];
-        float4 ov[QPT][kAttnWaves];
-#pragma unroll
-        for (int q = 0; q < QPT; ++q)
-#pragma unroll
-            for (int w = 0; w < kAttnWaves; ++w) {
-                if (q * RSTEP >= nrows) continue;  // a whole group of rows beyond the item's (uniform)
-                const int row = min(row0 + q * RSTEP, nrows - 1);
-                mw[q][w] = sh_m[grp * kAttnWaves + w][row];
-                lw[q][w] = sh_l[grp * kAttnWaves + w][row];
-                ov[q][w] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds + (grp * kAttnWaves + w) * SLAB) +
-                                                            row * OSTRIDE + c4 * 4);
+
+        for (int it = 0; it < n_tiles; ++it) {
+            const bool folded = it < n_fold;
+            const int kbase = folded ? pre.lo + it * step : own.lo + (it - n_fold) * step;
+            if (GROUPS > 1) {
+                kslab = lds + ((it & 1) * kAttnWaves + wave) * SLAB;
+                vslab = kslab + KSLAB;
             }
 #pragma unroll
-        for (int q = 0; q < QPT; ++q) {
-            if (q * RSTEP >= nrows) continue;
-            const int row = row0 + q * RSTEP;
-            float mg = -INFINITY;
-#pragma unroll
-            for (int w = 0; w < kAttnWaves; ++w) mg = fmaxf(mg, mw[q][w]);
-            const float mg_use = (mg == -INFINITY) ? 0.f : mg;
-            float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-            float lg = 0.f;
-#pragma unroll
-            for (int w = 0; w < kAttnWaves; ++w) {
-                const float sc = __builtin_amdgcn_exp2f(mw[q][w] - mg_use);
-                o.x += ov[q][w].x * sc;
-                o.y += ov[q][w].y * sc;
-                o.z += ov[q][w].z * sc;
-                o.w += ov[q][w].w * sc;
-                lg += lw[q][w] * sc;
+            for (int i = 0; i < NLD; ++i) {
+                *reinterpret_cast<u32x4*>(kslab + ((i * GROUPS + grp) * RPI + v_row) * KSTRIDE + v_chunk * 16) = kst[i];
+                *reinterpret_cast<u32x4*>(vslab + ((i * GROUPS + grp) * RPI + v_row) * VSTRIDE + v_chunk * 16) = vst[i];
             }
-            own_o[q] = o;
-            own_ml[q] = make_float2(mg, lg);
-            if (row < nrows) {
-                const unsigned rho = rho0 + tile * kRowTile + row;
-                if (pl.merge == kMergeNone) {
-                    store_merged(prm, kvh, b_item, (int)rho - b_item * GR, c4, o, mg, lg);
-                    continue;
-                }
-                const unsigned pidx = ((unsigned)kvh * prm.B * GR + rho) * pl.nslots + slot;
-                if (pl.merge != kMergeLaunch) {
-                    ws_store4<true>(rs, prm.off_o + (pidx * D + c4 * 4) * 4u, o);
-                    if (c4 == 0) ws_store2<true>(rs, prm.off_ml + pidx * 8u, make_float2(mg, lg));
-                } else {
-                    ws_store4<false>(rs, prm.off_o + (pidx * D + c4 * 4) * 4u, o);
-                    if (c4 == 0) ws_store2<false>(rs, prm.off_ml + pidx * 8u, make_float2(mg, lg));
+            if (GROUPS > 1) {
+                // both halves written: the pair's counter stands at 2 * (it + 1).  Whoever gets past this has also left
+                // the tile before behind (it counted this tile only after that), so the other slab is free.
+                if (lane == 0) __hip_atomic_fetch_add(&sh_pair[wave], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                for (int spin = 0; spin < (1 << 20); ++spin) {  // the partner runs the same tiles: the wait ends; bounded all the same
+                    if (__hip_atomic_load(&sh_pair[wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= 2 * (it + 1)) break;
+                    __builtin_amdgcn_s_sleep(1);
                 }
             }
+            if (it + 1 < n_fold) fetch(pre, kbase + step);
+            else if (it + 1 < n_tiles) fetch(own, own.lo + (it + 1 - n_fold) * step);
+            // K fragments (A operand of S^T = K Q^T: lane = key row ln, 8 contiguous d)
+            bf16x8 kf[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                kf[s] = *reinterpret_cast<const bf16x8*>(kslab + ln * KSTRIDE + (2 * s + hh) * 16);
+
+            bf16x8 pf[TW][2];
+#pragma unroll
+            for (int t = 0; t < TW; ++t) {
+                // S^T[key][query] = sum_d K[key][d] Q[query][d]
+                f32x16 acc;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc, 0, 0, 0);
+                // register i of this lane is key kbase + (i/4)*8 + hh*4 + i%4 for query row ln;
+                // every row sees all of a prefix share, the causal limit applies to the own run only
+                const int vis = (folded ? pre.hi : lim[t]) - kbase - hh * 4;  // key offsets below this are visible
+                float mx = -INFINITY;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int koff = (i >> 2) * 8 + (i & 3);
+                    float sc = acc[i] * prm.scale_log2;
+                    sc = koff < vis ? sc : -INFINITY;
+                    acc[i] = sc;
+                    mx = fmaxf(mx, sc);
+                }
+                mx = fmaxf(mx, shfl_xor_f(mx, 32));
+                const float m_new = fmaxf(m_run[t], mx);
+                const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+                const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_use);
+                float psum = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const float pv = __builtin_amdgcn_exp2f(acc[i] - m_use);
+                    psum += pv;
+                    pf[t][i >> 3][i & 7] = (__bf16)pv;
+                }
+                l_run[t] = l_run[t] * alpha + psum;
+                m_run[t] = m_new;
+                // Rescaling the accumulators is the largest block of vector work of a tile, and once a few hundred keys have
+                // gone by a tile rarely raises any row's maximum: alpha is exactly 1 for every lane then and the whole
+                // wavefront skips it (multiplying by 1 changes nothing, so the result is the same bit for bit).
+                if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) oacc[t][db][i] *= alpha;
+                }
+            }
+            // O^T[d][query] += sum_key V[key][d] P^T[key][query]; V^T fragments by transposing LDS reads
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    const unsigned char* ap = vslab + tr_off + (kb * 16) * VSTRIDE + db * 64;
+                    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                        (__attribute__((address_space(3))) short4v*)(ap));
+                    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                        (__attribute__((address_space(3))) short4v*)(ap + 8 * VSTRIDE));
+                    union {
+                        short4v s[2];
+                        bf16x8 v;
+                    } vf;
+                    vf.s[0] = lo;
+                    vf.s[1] = hi;
+#pragma unroll
+                    for (int t = 0; t < TW; ++t)
+                        oacc[t][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf[t][kb], oacc[t][db], 0, 0, 0);
+                }
+            }
+        }
+
+        // ---- combine the 4 wavefronts' states of a row tile (fixed order) and store the item's partial ----
+        // Each wavefront parks its raw state in LDS (its slab is free now); after one barrier the 256 threads
+        // of a group of four wavefronts form sum_w 2^(m_w - m) O_w over their group and write the valid rows out,
+        // coalesced (two groups: both row tiles at the same time).  A thread owns QPT output quads of a row
+        // tile -- quad t + 256 q, t its number within the group: the same column of rows RSTEP apart -- and
+        // reads everything it needs for all of them before it uses any of it.
+        if (GROUPS > 1) __syncthreads();  // nobody reads a key tile any more: the slabs become merge buffers
+        float* obuf = reinterpret_cast<float*>(lds + wave_all * SLAB);
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            if (t > 0) __syncthreads();  // the previous row tile has been read out
+            const int tile = grp * TW + t;  // row tile of the item
+            const float lsum = l_run[t] + shfl_xor_f(l_run[t], 32);
+            if (hh == 0) {
+                sh_m[wave_all][ln] = m_run[t];
+                sh_l[wave_all][ln] = lsum;
+            }
+            const int nrows = min(kRowTile, rho_end - (rho0 + tile * kRowTile));
+            if (ln < nrows) {  // rows beyond the item's are never read back
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4)
+                        *reinterpret_cast<float4*>(obuf + ln * OSTRIDE + db * 32 + q4 * 8 + hh * 4) =
+                            make_float4(oacc[t][db][q4 * 4 + 0], oacc[t][db][q4 * 4 + 1], oacc[t][db][q4 * 4 + 2],
+                                        oacc[t][db][q4 * 4 + 3]);
+            }
+            __syncthreads();
+            float mw[QPT][kAttnWaves], lw[QPT][kAttnWaves];
+            float4 ov[QPT][kAttnWaves];
+#pragma unroll
+            for (int q = 0; q < QPT; ++q)
+#pragma unroll
+                for (int w = 0; w < kAttnWaves; ++w) {
+                    if (q * RSTEP >= nrows) continue;  // a whole group of rows beyond the item's (uniform)
+                    const int row = min(row0 + q * RSTEP, nrows - 1);
+                    mw[q][w] = sh_m[grp * kAttnWaves + w][row];
+                    lw[q][w] = sh_l[grp * kAttnWaves + w][row];
+                    ov[q][w] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds + (grp * kAttnWaves + w) * SLAB) +
+                                                                row * OSTRIDE + c4 * 4);
+                }
+#pragma unroll
+            for (int q = 0; q < QPT; ++q) {
+                if (q * RSTEP >= nrows) continue;
+                float mg = -INFINITY;
+#pragma unroll
+                for (int w = 0; w < kAttnWaves; ++w) mg = fmaxf(mg, mw[q][w]);
+                const float mg_use = (mg == -INFINITY) ? 0.f : mg;
+                float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+                float lg = 0.f;
+#pragma unroll
+                for (int w = 0; w < kAttnWaves; ++w) {
+                    const float sc = __builtin_amdgcn_exp2f(mw[q][w] - mg_use);
+                    o.x += ov[q][w].x * sc;
+                    o.y += ov[q][w].y * sc;
+                    o.z += ov[q][w].z * sc;
+                    o.w += ov[q][w].w * sc;
+                    lg += lw[q][w] * sc;
+                }
+                own_o[q] = o;
+                own_ml[q] = make_float2(mg, lg);
+            }
+            put(tile, nrows);
         }
     }
 
@@ -1236,9 +1387,9 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     prm.counters = static_cast<unsigned long long*>(workspace);
     prm.d_hkv = fast_div(d.Hkv); prm.d_nsp = fast_div(pl.nsplit_priv); prm.d_rgp = fast_div(pl.n_rg_priv);
     prm.d_npre = fast_div(pl.nsplit_pre > 0 ? pl.nsplit_pre : 1); prm.d_mpp = fast_div(pl.mpp > 0 ? pl.mpp : 1); prm.d_gr = fast_div(prm.GR);
-    prm.d_wpriv = fast_div(kAttnWaves * pl.nsplit_priv); prm.d_wpre = fast_div(kAttnWaves * (pl.nsplit_pre > 0 ? pl.nsplit_pre : 1));
+    prm.d_wpriv = fast_div(pl.runs * pl.nsplit_priv); prm.d_wpre = fast_div(pl.runs * (pl.nsplit_pre > 0 ? pl.nsplit_pre : 1));
     prm.tiles_pre = ceil_div(d.P, kTile);
-    prm.first_wave = pl.fold ? prm.tiles_pre % (kAttnWaves * pl.nsplit_priv) : 0;
+    prm.first_wave = pl.fold ? prm.tiles_pre % (pl.runs * pl.nsplit_priv) : 0;
     const long long tile_span = (1LL << 31) / (2 * kTile);  // elements from key to key
     prm.near_rows = d.kpriv_stride_t < tile_span && d.kpre_stride_t < tile_span;
     prm.tag = (g_call_tag.fetch_add(1, std::memory_order_relaxed) + 1) << kTagShift;
@@ -1246,10 +1397,15 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     if (items > 0x7fffffffLL) return LOTTS_ERR_SHAPE;
     const dim3 grid((unsigned)items), block(kAttnThreads);
     const dim3 block2(2 * kAttnThreads);
-    if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1>), grid, block, s, prm);
-    else if (d.D == 128) LOTTS_LAUNCH((attn_kernel<128, 2, 2>), grid, block2, s, prm);
-    else if (pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<64, 1, 1>), grid, block, s, prm);
-    else LOTTS_LAUNCH((attn_kernel<64, 2, 2>), grid, block2, s, prm);
+    if (pl.one) {
+        if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1, true>), grid, block, s, prm);
+        else LOTTS_LAUNCH((attn_kernel<128, 2, 2, true>), grid, block2, s, prm);
+    } else {
+        if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1, false>), grid, block, s, prm);
+        else if (d.D == 128) LOTTS_LAUNCH((attn_kernel<128, 2, 2, false>), grid, block2, s, prm);
+        else if (pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<64, 1, 1, false>), grid, block, s, prm);
+        else LOTTS_LAUNCH((attn_kernel<64, 2, 2, false>), grid, block2, s, prm);
+    }
     if (pl.merge == kMergeLaunch) {
         const int rc = check_launch();
         if (rc != LOTTS_OK) return rc;

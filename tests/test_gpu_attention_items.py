@@ -1,10 +1,11 @@
-"""verify_attention's work items at the edges of what they assume: key rows far apart."""
+"""verify_attention's work items at the edges of what they assume: key rows far apart, one tile for every wavefront."""
+import numpy as np
 import pytest
 import torch
 
 import synth_inputs as S
 from gpu_util import attn_to_dev
-from test_gpu_parity import BF
+from test_gpu_parity import BF, run_attention
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +28,24 @@ def test_key_rows_far_apart(far, stride):
     got = lotts.verify_attention(*(d[n] for n in ("Q", "Kpre", "Vpre", "Kpriv", "Vpriv", "priv_len")))
     torch.cuda.synchronize()
     assert torch.equal(got, want)
+
+
+ONE_TILE = [
+    # one row tile, at most four tiles an item: whole rows, pairs, last arriver, merge workgroups, a launch of its own
+    BF.with_(B=20, Hq=32, Hkv=8, k=3, P=0, L=128), BF.with_(B=20, Hq=32, Hkv=8, k=7, P=9, L=97), BF.with_(B=33, Hq=8, Hkv=8, k=0, P=0, L=1),
+    BF.with_(B=16, Hq=24, Hkv=8, k=3, P=31, L=225), BF.with_(B=9, Hq=16, Hkv=8, k=1, P=0, L=353), BF.with_(B=1, Hq=16, Hkv=2, k=2, P=225, L=961),
+    BF.with_(B=5, Hq=16, Hkv=2, k=3, P=300, L=120), BF.with_(B=6, Hq=16, Hkv=2, k=3, P=1500, L=320),
+    # two row tiles, five to eight tiles an item; 33, 40 and 64 rows
+    BF.with_(B=20, Hq=40, Hkv=8, k=7, P=0, L=256), BF.with_(B=17, Hq=24, Hkv=8, k=10, P=0, L=161), BF.with_(B=16, Hq=64, Hkv=8, k=7, P=60, L=449),
+    BF.with_(B=8, Hq=16, Hkv=2, k=4, P=511, L=2047), BF.with_(B=3, Hq=16, Hkv=2, k=4, P=900, L=801),
+]
+
+
+@pytest.mark.parametrize("cfg", ONE_TILE, ids=lambda c: "B%d_k%d_Hq%d_Hkv%d_P%d_L%d" % (c.B, c.k, c.Hq, c.Hkv, c.P, c.L))
+@pytest.mark.parametrize("ragged", [False, True])
+def test_one_tile_per_wavefront(oracle, cfg, ragged):
+    import paper_2505_19634_amd as lotts
+    lens = None
+    if ragged:  # wavefronts, and whole items, without a tile
+        lens = np.linspace(cfg.k + 1, cfg.L, cfg.B).astype(np.int32) if cfg.B > 1 else np.array([max(cfg.k + 1, cfg.L // 3)], np.int32)
+    run_attention(lotts, oracle, cfg, priv_len=lens)
