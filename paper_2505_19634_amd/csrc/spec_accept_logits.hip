@@ -75,19 +75,26 @@ __device__ __forceinline__ float pow2_neg_poly_2p30(float f) {
     return g;
 }
 
-// E = trunc(2^t * 2^30) through the definition's steps; every operation individually rounded
+// The conversions that truncate, with the instruction's results outside the integers' range (NaN: 0; beyond: the nearest end):
+// written out, because C++ leaves those results open.
+__device__ __forceinline__ int to_i32(float v) {
+    int r;
+    asm("v_cvt_i32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+__device__ __forceinline__ unsigned to_u32(float v) {
+    unsigned r;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+// E = trunc(2^t * 2^30) through the definition's steps; every operation individually rounded.  With n = floor(-t) = -trunc(t) the
+// definition's trunc(P * 2^(30 - n)) is one scaling by a power of two (exact: P * 2^30 >= 2^29, a result below the normal numbers
+// truncates to 0 as the definition's does) and one truncation.  From n = 31 on the result is 0 by itself; -inf logits
+// (n = the lowest integer) and NaN (rows that are -inf throughout, or hold +inf) truncate to 0 as well: no clamp, branch or select.
 __device__ __forceinline__ unsigned logit_weight(float y, float m) {
     const float t = mul_rn(sub_rn(y, m), 0x1.715476p+0f);
-    // -t clamped to 31 (also for -inf logits and NaN from a row that is -inf throughout: fminf returns
-    // the other operand): from 31 on the weight truncates to 0 by itself, P(0) * 2^-1 = 0.5, so the
-    // definition's "0 when floor(-t) >= 31" needs no branch and no select
-    const float a = fminf(-t, 31.0f);
-    // a - floor(a) in one instruction (exact for 0 <= a <= 31, as the subtraction is); floor(a) by truncation
-    const float f = __builtin_amdgcn_fractf(a);
-    const unsigned n = (unsigned)(int)a;
-    // trunc(P * 2^(30 - n)) = trunc(P * 2^30) >> n: P * 2^30 <= 2^30 is a non-negative number, and flooring
-    // it before the division by 2^n does not change the floor of the quotient
-    return __float2uint_rz(pow2_neg_poly_2p30(f)) >> n;
+    const float f = __builtin_amdgcn_fractf(-t);  // -t - floor(-t) in one instruction, exact
+    return to_u32(__builtin_ldexpf(pow2_neg_poly_2p30(f), to_i32(t)));
 }
 
 template <bool BF16>
@@ -189,12 +196,18 @@ __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V
                                                              const void* __restrict__ zt, const void* __restrict__ zd,
                                                              float inv_temp, unsigned long long* __restrict__ words,
                                                              float* __restrict__ rmax, unsigned long long* __restrict__ psum,
-                                                             unsigned long long* __restrict__ slots, long long nslots) {
+                                                             unsigned long long* __restrict__ slots, long long nslots,
+                                                             const int32_t* __restrict__ draft, unsigned* __restrict__ draft_e,
+                                                             FastDiv d_pieces, FastDiv d_targets) {
     __shared__ float sh_m[kLgWaves];
     __shared__ float sh_row;
     __shared__ unsigned long long sh_miss, sh_s[kLgWaves];
-    const int r = blockIdx.x / npieces, pc = blockIdx.x - r * npieces, tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int r = quot(blockIdx.x, d_pieces), pc = blockIdx.x - r * npieces, tid = threadIdx.x, lane = tid & (kWave - 1);
     const int nt = B * (k + 1);
+    // the token that was drafted where this row stands (a branch's last target row: none)
+    const int rb = quot(r, d_targets), rj = r - rb * (k + 1);
+    const int dx = r < nt ? (rj < k ? rb * k + rj : -1) : r - nt;
+    const int drafted = dx >= 0 ? ((const __attribute__((address_space(4))) int32_t*)draft)[dx] : -1;
     const void* z = r < nt ? zt : zd;
     const size_t base = (size_t)(r < nt ? r : r - nt) * V;
     const int lo = pc * (IT * kLgGroup);
@@ -206,6 +219,12 @@ __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V
     Raw8<BF16> raw[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) raw[it] = load_raw8<BF16>(z, base, lo + it * kLgGroup + tid * 8, V);
+    // Its weight is formed here, where the row's maximum is met anyway: the next launch's accept tests would reach its logit
+    // only behind the drafted token, two dependent trips through memory.
+    const int x = drafted < 0 ? 0 : (drafted >= V ? V - 1 : drafted);
+    const bool mine = dx >= 0 && x >= lo && x < lo + IT * kLgGroup;  // uniform
+    float yx = 0.f;
+    if (mine) yx = load_y<BF16>(z, base + x, inv_temp);
     float y[IT][8], m = -INFINITY;
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
@@ -269,8 +288,12 @@ __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V
 #pragma unroll
     for (int it = 0; it < IT; ++it)
 #pragma unroll
-        for (int e = 0; e < 8; e += 2)  // two weights (each at most 2^30) fit 32 bits together
-            s += logit_weight(y[it][e], m) + logit_weight(y[it][e + 1], m);
+        for (int e = 0; e < 8; e += 3) {  // three weights (each at most 2^30) fit 32 bits together
+            unsigned part = logit_weight(y[it][e], m);
+            if (e + 1 < 8) part += logit_weight(y[it][e + 1], m);
+            if (e + 2 < 8) part += logit_weight(y[it][e + 2], m);
+            s += part;
+        }
     // at most 64 weights a lane: s < 2^37; two limbs whose wavefront sums fit 32 bits
     const unsigned s0 = wave_incl_scan_u32((unsigned)s & 0xffffffu), s1 = wave_incl_scan_u32((unsigned)(s >> 24));
     if (lane == kWave - 1) sh_s[tid / kWave] = (unsigned long long)s0 + ((unsigned long long)s1 << 24);
@@ -281,6 +304,7 @@ __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V
         for (int w = 0; w < kLgWaves; ++w) tot += sh_s[w];
         psum[(size_t)r * npieces + pc] = tot;
         if (pc == 0) rmax[r] = m;
+        if (mine) draft_e[r] = logit_weight(yx, m);
     }
 }
 
@@ -325,26 +349,22 @@ __device__ __forceinline__ void lg_row_stats(int B, int b, int k, int npieces, i
 
 // Accepted length of branch b; every thread of the 256-thread workgroup gets it, and the statistics of the two rows at n (of
 // the target row alone when every draft was accepted) with it.
-template <bool BF16>
-__device__ __forceinline__ int lg_accepted_length(int B, int b, int k, int V, const void* zt, const void* zd,
-                                                  float inv_temp, const int32_t* draft, const float* u,
-                                                  const float* rmax, const unsigned long long* psum, int npieces,
-                                                  int lg, int* sh_first, RowStat* sh_stat, RowStat& sp, RowStat& sq) {
+__device__ __forceinline__ int lg_accepted_length(int B, int b, int k, const unsigned* draft_e, const float* u, const float* rmax,
+                                                  const unsigned long long* psum, int npieces, int lg, int* sh_first,
+                                                  RowStat* sh_stat, RowStat& sp, RowStat& sq) {
     const int tid = threadIdx.x;
-    float uv = 0.f, yp = 0.f, yq = 0.f;
-    if (tid < k) {  // on their way while the sums come
-        int x = draft[(size_t)b * k + tid];
+    float uv = 0.f;
+    unsigned Ep = 0, Eq = 0;
+    if (tid < k) {  // one trip together with the sums
         uv = u[(size_t)b * (k + 1) + tid];
-        x = x < 0 ? 0 : (x >= V ? V - 1 : x);
-        yp = load_y<BF16>(zt, (size_t)trow(b, tid, k) * V + x, inv_temp);
-        yq = load_y<BF16>(zd, ((size_t)b * k + tid) * V + x, inv_temp);
+        Ep = draft_e[trow(b, tid, k)];
+        Eq = draft_e[drow(B, b, tid, k)];
     }
     lg_row_stats(B, b, k, npieces, lg, rmax, psum, sh_stat);
     __syncthreads();
     bool rejected = false;
     if (tid < k) {
         const RowStat p = sh_stat[tid], q = sh_stat[k + 1 + tid];
-        const unsigned long long Ep = logit_weight(yp, p.m), Eq = logit_weight(yq, q.m);
         const u128 U = (u128)(unsigned)(uv * 16777216.0f);
         rejected = !(U * Eq * p.S < ((u128)1 << 24) * Ep * q.S);
     }
@@ -359,11 +379,42 @@ __device__ __forceinline__ int lg_accepted_length(int B, int b, int k, int V, co
     return n;
 }
 
+// Sampling weights are below 2^80 and a thread's sum of eight below 2^83: three 32-bit limbs and their carries, not the four of
+// 128 bits with a comparison and a selection of their own.
+struct U96 {
+    unsigned v[3];
+};
+__device__ __forceinline__ u128 widen(U96 a) { return (u128)a.v[0] | ((u128)a.v[1] << 32) | ((u128)a.v[2] << 64); }
+// a weight (at most 2^30) times a row's sum (below 2^50): two products
+__device__ __forceinline__ U96 mul_e_s(unsigned e, unsigned long long s) {
+    const unsigned long long lo = (unsigned long long)e * (unsigned)s;
+    const unsigned long long hi = (unsigned long long)e * (unsigned)(s >> 32) + (lo >> 32);
+    return U96{{(unsigned)lo, (unsigned)hi, (unsigned)(hi >> 32)}};
+}
+__device__ __forceinline__ U96 add_96(U96 a, U96 b) {
+    unsigned c;
+    U96 r;
+    r.v[0] = __builtin_addc(a.v[0], b.v[0], 0u, &c);
+    r.v[1] = __builtin_addc(a.v[1], b.v[1], c, &c);
+    r.v[2] = __builtin_addc(a.v[2], b.v[2], c, &c);
+    return r;
+}
+// max(0, a - b)
+__device__ __forceinline__ U96 sub_sat_96(U96 a, U96 b) {
+    unsigned c;
+    U96 r;
+    r.v[0] = __builtin_subc(a.v[0], b.v[0], 0u, &c);
+    r.v[1] = __builtin_subc(a.v[1], b.v[1], c, &c);
+    r.v[2] = __builtin_subc(a.v[2], b.v[2], c, &c);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) r.v[i] = c ? 0u : r.v[i];
+    return r;
+}
+
 // the 8 weights a thread owns in a chunk (tokens lo .. lo+7, clipped to V): residual or plain
 template <bool BF16>
 __device__ __forceinline__ void lg_weights8(const void* zt_row, const void* zd_row, int lo, int V, float inv_temp,
-                                            bool residual, RowStat sp, RowStat sq, u128 (&W)[8],
-                                            unsigned long long (&Ep)[8]) {
+                                            bool residual, RowStat sp, RowStat sq, U96 (&W)[8], unsigned (&Ep)[8]) {
     float yp[8], yq[8];
     const Raw8<BF16> rp = load_raw8<BF16>(zt_row, 0, lo, V);
     if (residual) {
@@ -372,15 +423,13 @@ __device__ __forceinline__ void lg_weights8(const void* zt_row, const void* zd_r
     }
     scale8<BF16>(rp, inv_temp, yp);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const bool in = lo + e < V;
-        Ep[e] = in ? logit_weight(yp[e], sp.m) : 0ull;
+    for (int e = 0; e < 8; ++e) {  // (beyond V the logits are -inf and weigh 0: a branch for each cost more than the weights)
+        Ep[e] = logit_weight(yp[e], sp.m);
         if (residual) {
-            const unsigned long long Eq = in ? logit_weight(yq[e], sq.m) : 0ull;
-            const u128 a = (u128)Ep[e] * sq.S, c = (u128)Eq * sp.S;
-            W[e] = a > c ? a - c : (u128)0;
+            const unsigned Eq = logit_weight(yq[e], sq.m);
+            W[e] = sub_sat_96(mul_e_s(Ep[e], sq.S), mul_e_s(Eq, sp.S));
         } else {
-            W[e] = Ep[e];
+            W[e] = U96{{Ep[e], 0u, 0u}};
         }
     }
 }
@@ -388,7 +437,7 @@ __device__ __forceinline__ void lg_weights8(const void* zt_row, const void* zd_r
 template <bool BF16>
 __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, int V, int nchunks, int npieces, int lg, unsigned tag,
                                                                   const void* __restrict__ zt, const void* __restrict__ zd,
-                                                                  float inv_temp, const int32_t* __restrict__ draft,
+                                                                  float inv_temp, const unsigned* __restrict__ draft_e,
                                                                   const float* __restrict__ u,
                                                                   const float* __restrict__ rmax,
                                                                   const unsigned long long* __restrict__ psum,  // [rows][npieces]
@@ -406,31 +455,26 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
     const int b = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
     __shared__ RowStat sh_stat[2 * kLgMaxK + 1];
     const float u_last = u[(size_t)b * (k + 1) + k];
-    // the words of the launch before are consumed: cleared, so that a captured call (same tags) can be replayed
-    for (int i = c * kLgThreads + tid; i < (2 * k + 1) * npieces * 2; i += nchunks * kLgThreads) {
-        const int j = i / (npieces * 2);
-        const int row = j <= k ? trow(b, j, k) : drow(B, b, j - k - 1, k);
-        words[(size_t)row * npieces * 2 + (i - j * npieces * 2)] = 0ull;
-    }
     RowStat sp, sq;
-    const int n = lg_accepted_length<BF16>(B, b, k, V, zt, zd, inv_temp, draft, u, rmax, psum, npieces, lg, sh_first, sh_stat, sp, sq);
+    const int n = lg_accepted_length(B, b, k, draft_e, u, rmax, psum, npieces, lg, sh_first, sh_stat, sp, sq);
     bool residual = n < k;
     const size_t es = BF16 ? 2 : 4;
     const void* zt_row = static_cast<const char*>(zt) + (size_t)trow(b, n, k) * V * es;
     const void* zd_row = residual ? static_cast<const char*>(zd) + ((size_t)b * k + n) * V * es : zt_row;
-    u128 W[8];
-    unsigned long long Ep[8];
+    U96 W[8];
+    unsigned Ep[8];
     __shared__ unsigned long long sh_e[kLgWaves];
     // sums of a chunk's weights (residual after a rejection) and of its plain ones; complete in thread 0 only
     auto chunk_sums = [&](int chunk, u128& w, unsigned long long& e) {
         lg_weights8<BF16>(zt_row, zd_row, chunk * kLgChunk + tid * 8, V, inv_temp, n < k, sp, sq, W, Ep);
-        w = 0;
-        e = 0;
+        U96 sum = W[0];
+        e = Ep[0];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            w += W[i];
+        for (int i = 1; i < 8; ++i) {
+            sum = add_96(sum, W[i]);
             e += Ep[i];
         }
+        w = widen(sum);
         // both sums over the workgroup at once: the totals stand in lane 63 of every wavefront
         w = wave_incl_scan_u128(w);
         const unsigned e0 = wave_incl_scan_u32((unsigned)e & 0xffffffu), e1 = wave_incl_scan_u32((unsigned)(e >> 24));
@@ -460,6 +504,12 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
         lg_publish(mine + 3, (unsigned)(w >> 96), tag);
         lg_publish(mine + 4, (unsigned)e, tag);
         lg_publish(mine + 5, (unsigned)(e >> 32), tag);   // the plain sum of a chunk is below 2^41
+    }
+    // the words of the launch before are consumed: cleared, so that a captured call (same tags) can be replayed
+    for (int i = c * kLgThreads + tid; i < (2 * k + 1) * npieces * 2; i += nchunks * kLgThreads) {
+        const int j = i / (npieces * 2);
+        const int row = j <= k ? trow(b, j, k) : drow(B, b, j - k - 1, k);
+        words[(size_t)row * npieces * 2 + (i - j * npieces * 2)] = 0ull;
     }
     if (c != nchunks - 1) return;  // uniform over the workgroup
 
@@ -540,43 +590,63 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
     const RowStat sq2 = residual ? sq : sp;
     const int lo = cc * kLgChunk + tid * 8;
     lg_weights8<BF16>(zt_row, zd_row2, lo, V, inv_temp, residual, sp, sq2, W, Ep);
-    u128 local = 0;
+    U96 sum = W[0];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) local += W[i];
+    for (int i = 1; i < 8; ++i) sum = add_96(sum, W[i]);
+    const u128 local = widen(sum);
     u128 total;
     const u128 run = base + block_excl_scan_u128(local, sh_w, total);
-    if (run <= T && T < run + local) {
-        int tok = lo;
+    if (run <= T && T < run + local) {  // exactly one thread
+        // its first token whose inclusive prefix exceeds T
+        const u128 rest = T - run;  // below local
+        const U96 t = {{(unsigned)rest, (unsigned)(rest >> 32), (unsigned)(rest >> 64)}};
+        U96 pre = W[0];
+        int passed = 0;
 #pragma unroll
-        for (int i = 7; i >= 0; --i) {  // the first i whose inclusive prefix exceeds T
-            u128 pre = run;
-#pragma unroll
-            for (int j = 0; j <= i; ++j) pre += W[j];
-            if (pre > T) tok = lo + i;
+        for (int i = 0; i < 8; ++i) {
+            if (i > 0) pre = add_96(pre, W[i]);
+            passed += widen(pre) > widen(t) ? 0 : 1;
         }
+        const int tok = lo + passed;
         next_token[b] = tok;
     }
 }
 
 
 struct LgLayout {
-    size_t off_psum, off_chunks, off_words, total;
+    size_t off_psum, off_chunks, off_words, off_draft, total;
     int nchunks, npieces, iters;
 };
 // [row maxima][sums of the pieces][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces: 2 per (row, piece)]
+// [weights of the drafted tokens: one per row]
 static inline LgLayout lg_layout(int B, int k, int V) {
     LgLayout l;
     l.nchunks = (V + kLgChunk - 1) / kLgChunk;
     const size_t rows = (size_t)B * (2 * k + 1);
-    // four loads a thread up to 64 pieces to a row and while one grid (of fewer than 2^32 threads) holds all pieces; else eight
-    const size_t pieces4 = (V + 4 * kLgGroup - 1) / (4 * kLgGroup);
-    l.iters = pieces4 <= kLgMaxPieces && rows * pieces4 * kLgThreads <= 0xffffffffu ? 4 : 8;
+    // Loads a thread (a piece is that many times 2048 logits): of four, five and six what leaves the least to read to the fullest
+    // unit, with a workgroup's fixed part counted as one load; eight where a row would have more than 64 pieces, or one grid (of
+    // fewer than 2^32 threads) could not hold them.  With four throughout, the 2128 pieces of 112 rows x 152064 were 80 more than
+    // are resident at once, and those ended 2.8 us after the others: 26.4 us, 25.2 with five.  544 x 151936 64.2 -> 58.9, 72 x 151936
+    // 20.2 -> 19.5 (six), 75 x 50257 fp32 15.8 -> 15.3, 72 x 65537 17.0 -> 16.3; four stays where it is 55 x 72936 (15.1, five 15.7), 63 x
+    // 49153 (15.5, 16.1).  Eight for one workgroup to a unit instead of two of four loses: 63 x 49153 17.2.
+    size_t best = 0;
+    l.iters = 8;
+    for (int it = 4; it <= 6; ++it) {
+        const size_t pieces = (V + it * kLgGroup - 1) / (it * kLgGroup);
+        if (pieces > kLgMaxPieces || rows * pieces * kLgThreads > 0xffffffffu) continue;
+        const size_t cost = (rows * pieces + kNumCU - 1) / kNumCU * (it + 1);
+        if (best == 0 || cost < best) {
+            best = cost;
+            l.iters = it;
+        }
+    }
     l.npieces = (V + l.iters * kLgGroup - 1) / (l.iters * kLgGroup);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     l.off_psum = up(rows * sizeof(float));
     l.off_chunks = l.off_psum + up(rows * l.npieces * sizeof(unsigned long long));
     l.off_words = l.off_chunks + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
-    l.total = l.off_words + up(rows * l.npieces * 2 * sizeof(unsigned long long));
+    l.off_draft = l.off_words + up(rows * l.npieces * 2 * sizeof(unsigned long long));
+    l.total = l.off_draft + up(rows * sizeof(unsigned));
     return l;
 }
 static inline bool lg_sizes_ok(int B, int k, int V) {
@@ -596,21 +666,27 @@ static int lg_launch(int B, int k, int V, const void* zt, const void* zd, float 
     unsigned long long* psum = reinterpret_cast<unsigned long long*>(ws + l.off_psum);
     unsigned long long* chunks = reinterpret_cast<unsigned long long*>(ws + l.off_chunks);
     unsigned long long* words = reinterpret_cast<unsigned long long*>(ws + l.off_words);
+    unsigned* draft_e = reinterpret_cast<unsigned*>(ws + l.off_draft);
     const unsigned tag_s = next_word_tag(), tag_c = next_word_tag();
     const long long nslots = (long long)B * l.nchunks * 6;
     const dim3 sgrid((unsigned)((long long)l.npieces * B * (2 * k + 1)));  // (piece, row) pairs, row-major
-    if (l.iters == 4)
-        LOTTS_LAUNCH((lg_stat_kernel<BF16, 4>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, tag_s, zt, zd, inv_temp, words,
-                     rmax, psum, chunks, nslots);
-    else
-        LOTTS_LAUNCH((lg_stat_kernel<BF16, 8>), sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, tag_s, zt, zd, inv_temp, words,
-                     rmax, psum, chunks, nslots);
+    const FastDiv d_pieces = fast_div(l.npieces), d_targets = fast_div(k + 1);
+    auto stat = [&](auto kernel) {
+        LOTTS_LAUNCH(kernel, sgrid, dim3(kLgThreads), s, B, k, V, l.npieces, tag_s, zt, zd, inv_temp, words, rmax, psum, chunks, nslots, draft,
+                     draft_e, d_pieces, d_targets);
+    };
+    switch (l.iters) {
+        case 4: stat(lg_stat_kernel<BF16, 4>); break;
+        case 5: stat(lg_stat_kernel<BF16, 5>); break;
+        case 6: stat(lg_stat_kernel<BF16, 6>); break;
+        default: stat(lg_stat_kernel<BF16, 8>); break;
+    }
     const int rc = check_launch();
     if (rc != LOTTS_OK) return rc;
     int lg = 6;  // lanes that add up a row's pieces: not more than there are pieces, all rows at once if they fit
     while (lg > 0 && (((2 * k + 1) << lg) > kLgThreads || (1 << lg) >= 2 * l.npieces)) --lg;
     LOTTS_LAUNCH((lg_scan_pick_kernel<BF16>), dim3(l.nchunks, B), dim3(kLgThreads), s, B, k, V, l.nchunks, l.npieces, lg, tag_c, zt,
-                 zd, inv_temp, draft, u, rmax, psum, accept_len, words, chunks, next_token, priv_len);
+                 zd, inv_temp, draft_e, u, rmax, psum, accept_len, words, chunks, next_token, priv_len);
     return check_launch();
 }
 
