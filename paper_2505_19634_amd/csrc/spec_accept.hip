@@ -2,7 +2,8 @@
 // the paper cites for speculative decoding in Section 2 / Section 3.2).
 //
 // One launch when the vocabulary fits (accept_fused_kernel), two otherwise:
-//   accept_fused_kernel  grid (S slices x B branches), 4 wavefronts per workgroup.  Every workgroup
+//   accept_fused_kernel  grid (S slices x B branches), 4 wavefronts per workgroup, 1, 2 or 4 of them to a
+//       sub-chunk.  Every workgroup
 //       re-derives the branch's accepted length n from the 2k gathered probabilities; each of its
 //       wavefronts turns one sub-chunk of the row to be sampled (residual max(0, p_n - q_n), or p_k)
 //       into 2^-40 fixed-point weights -- all of the sub-chunk's loads are requested before the first
@@ -284,14 +285,21 @@ struct FusedPlan {
     int wlen;    // tokens per sub-chunk, a multiple of 256
     int iters;   // wlen / 256: 16-byte loads per row and lane, and tokens per thread in the pick
     int nsub;    // sub-chunks that hold tokens, <= kFuMaxSub
-    int S;       // workgroups (slices of 4 sub-chunks) per branch
+    int parts;   // wavefronts that share a sub-chunk: 1, 2 or 4
+    int S;       // workgroups (slices of 4 / parts sub-chunks) per branch
 };
-static inline FusedPlan plan_fused(int V) {
+static inline FusedPlan plan_fused(int B, int V) {
     FusedPlan pl;
     pl.wlen = ((V + kFuMaxSub - 1) / kFuMaxSub + 255) / 256 * 256;
     pl.iters = pl.wlen / 256;
     pl.nsub = (V + pl.wlen - 1) / pl.wlen;
-    pl.S = (pl.nsub + kAccWaves - 1) / kAccWaves;
+    // Few branches: a unit takes in about 50 KB a microsecond, and with a wavefront to a sub-chunk most units have none (8 branches
+    // x 152k tokens are 120 workgroups of up to 80 KB); so wavefronts share sub-chunks while there are at most two workgroups to a
+    // unit.  Kernels in a captured graph, parts 1 -> 2 or 4: 8 x 151936 6.8 -> 5.7 us, 1 x 151936 6.6 -> 5.5, 16 x 152064 7.1 -> 6.2, 3 x
+    // 256000 7.9 -> 6.0, 16 x 40000 5.1 -> 4.9; up to one workgroup a unit only, 16 x 152064 stays at 7.0.
+    pl.parts = 1;
+    while (pl.parts < kAccWaves && (long long)B * ((pl.nsub * pl.parts * 2 + kAccWaves - 1) / kAccWaves) <= 2 * kNumCU) pl.parts *= 2;
+    pl.S = (pl.nsub * pl.parts + kAccWaves - 1) / kAccWaves;
     return pl;
 }
 
@@ -377,7 +385,7 @@ __device__ __forceinline__ float4 load_row4(const float* row, int idx, int V) {
     return make_float4(row[idx], idx + 1 < V ? row[idx + 1] : 0.f, idx + 2 < V ? row[idx + 2] : 0.f, 0.f);
 }
 
-template <int MAXIT>
+template <int MAXIT, int PARTS>
 __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k, int V, FusedPlan pl, unsigned tag,
                                                                    const float* __restrict__ p,
                                                                    const float* __restrict__ q,
@@ -399,16 +407,18 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     const float* prow = p + ((size_t)b * (k + 1) + n) * V;
     const bool has_q = n < k;
     const float* qrow = has_q ? q + ((size_t)b * k + n) * V : prow;
-    const int sub = s * kAccWaves + wave;          // this wavefront's sub-chunk of the row
-    // a wavefront's sum of the weights of a sub-chunk, in its last lane
-    auto sub_sum = [&](int sub) {
+    const int sub = (s * kAccWaves + wave) / PARTS;  // this wavefront's sub-chunk of the row
+    const int part = wave % PARTS;                   // and the part of it: every PARTS-th of its groups of 256 tokens
+    constexpr int PIT = MAXIT / PARTS;
+    // a wavefront's sum of the weights of a part of a sub-chunk, in its last lane
+    auto part_sum = [&](int sub, int part) {
         const int lo = sub * pl.wlen;
-        // all of the sub-chunk is requested before any of it is used
-        float4 pv[MAXIT], qv[MAXIT];
+        // all of the part is requested before any of it is used
+        float4 pv[PIT], qv[PIT];
 #pragma unroll
-        for (int i = 0; i < MAXIT; ++i) {
-            const int idx = lo + (i * kWave + lane) * 4;
-            const bool in = i < pl.iters && idx < V;
+        for (int i = 0; i < PIT; ++i) {
+            const int it = i * PARTS + part, idx = lo + (it * kWave + lane) * 4;
+            const bool in = it < pl.iters && idx < V;
             pv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
             qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
             if (in) pv[i] = load_row4(prow, idx, V);
@@ -417,7 +427,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
         // per lane: at most 64 weights; their high parts (<= 2^16) and low parts (< 2^24) add up in 32 bits
         unsigned w_hi = 0, w_lo = 0;
 #pragma unroll
-        for (int i = 0; i < MAXIT; ++i) {
+        for (int i = 0; i < PIT; ++i) {
             const float pe[4] = {pv[i].x, pv[i].y, pv[i].z, pv[i].w};
             const float qe[4] = {qv[i].x, qv[i].y, qv[i].z, qv[i].w};
 #pragma unroll
@@ -430,9 +440,16 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
         }
         return wave_sum_split(w_hi, w_lo);
     };
-    const unsigned long long s_sub = sub_sum(sub);
+    unsigned long long s_sub = part_sum(sub, part);
+    if (PARTS > 1) {  // the parts meet in LDS; the sum stands in the last lane of the first part's wavefront
+        if (lane == kWave - 1) sh_scan[wave] = s_sub;
+        __syncthreads();
+        s_sub = 0;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) s_sub += sh_scan[wave - part + i];
+    }
     if (s != pl.S - 1) {  // uniform over the workgroup; all sub-chunks of these hold tokens
-        if (lane == kWave - 1) {
+        if (lane == kWave - 1 && part == 0) {
             unsigned long long* mine = slots + ((size_t)b * kFuMaxSub + sub) * 2;
             const unsigned long long old0 = atomicExch(mine + 0, tagged((unsigned)s_sub, tag));
             const unsigned long long old1 = atomicExch(mine + 1, tagged((unsigned)(s_sub >> 32), tag));
@@ -443,7 +460,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     }
 
     // ---- the branch's last slice collects ----
-    if (lane == kWave - 1) sh_sub[sub] = s_sub;
+    if (lane == kWave - 1 && part == 0) sh_sub[sub] = s_sub;
     if (tid == 0) {
         accept_len[b] = n;
         sh_missing = 0;
@@ -468,7 +485,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     unsigned long long v = 0;
     bool missing = false;
     if (wave == 0) {
-        const int own = s * kAccWaves;  // the sub-chunks from here on are this workgroup's
+        const int own = s * kAccWaves / PARTS;  // the sub-chunks from here on are this workgroup's
         if (lane >= own && lane < pl.nsub) v = sh_sub[lane];
         if (lane < own) {
             unsigned long long* e = slots + ((size_t)b * kFuMaxSub + lane) * 2;
@@ -504,7 +521,8 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
         for (unsigned long long left = sh_missing; left; left &= left - 1, ++turn) {
             if (turn % kAccWaves != wave) continue;
             const int j = __ffsll((long long)left) - 1;
-            const unsigned long long sum = sub_sum(j);
+            unsigned long long sum = 0;
+            for (int i = 0; i < PARTS; ++i) sum += part_sum(j, i);
             if (lane == kWave - 1) sh_sub[j] = sum;
         }
         __syncthreads();
@@ -527,10 +545,16 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     const int lo2 = c * pl.wlen + tid * pl.iters;
     float pw[MAXIT], qw[MAXIT];
 #pragma unroll
-    for (int i = 0; i < MAXIT; ++i) {
-        const bool in = i < pl.iters && lo2 + i < V;
-        pw[i] = in ? prow[lo2 + i] : 0.f;
-        qw[i] = (in && has_q) ? qrow[lo2 + i] : 0.f;
+    for (int g = 0; g < MAXIT; g += 4) {  // 16 bytes at a time: one by one the loads were 0.4 us more
+        const bool in = g < pl.iters && lo2 + g < V;
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 pg = in ? load_row4(prow, lo2 + g, V) : zero, qg = in && has_q ? load_row4(qrow, lo2 + g, V) : zero;
+        const float pe[4] = {pg.x, pg.y, pg.z, pg.w}, qe[4] = {qg.x, qg.y, qg.z, qg.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {  // (the next thread's tokens weigh nothing here)
+            pw[g + e] = g + e < pl.iters ? pe[e] : 0.f;
+            qw[g + e] = g + e < pl.iters ? qe[e] : 0.f;
+        }
     }
     unsigned long long w[MAXIT], local = 0;
 #pragma unroll
@@ -584,21 +608,17 @@ extern "C" int spec_accept(int32_t B, int32_t k, int32_t V, const float* p, cons
     unsigned long long* sums = static_cast<unsigned long long*>(workspace);
     hipStream_t s = (hipStream_t)stream;
     if (V <= kFuMaxV) {  // one launch
-        const FusedPlan fp = plan_fused(V);
+        const FusedPlan fp = plan_fused(B, V);
         const unsigned tag = next_word_tag();
         const dim3 fgrid((unsigned)((long long)B * fp.S));
-        if (fp.iters <= 4)
-            LOTTS_LAUNCH(accept_fused_kernel<4>, fgrid, dim3(kAccThreads), s, B, k, V, fp, tag, p, q, draft, u, accept_len,
-                         next_token, sums);
-        else if (fp.iters <= 8)
-            LOTTS_LAUNCH(accept_fused_kernel<8>, fgrid, dim3(kAccThreads), s, B, k, V, fp, tag, p, q, draft, u, accept_len,
-                         next_token, sums);
-        else if (fp.iters <= 12)
-            LOTTS_LAUNCH(accept_fused_kernel<12>, fgrid, dim3(kAccThreads), s, B, k, V, fp, tag, p, q, draft, u, accept_len,
-                         next_token, sums);
-        else
-            LOTTS_LAUNCH(accept_fused_kernel<16>, fgrid, dim3(kAccThreads), s, B, k, V, fp, tag, p, q, draft, u, accept_len,
-                         next_token, sums);
+        auto fused = [&](auto kernel) {
+            LOTTS_LAUNCH(kernel, fgrid, dim3(kAccThreads), s, B, k, V, fp, tag, p, q, draft, u, accept_len, next_token, sums);
+        };
+        auto with_parts = [&](auto one, auto two, auto four) { fp.parts == 1 ? fused(one) : fp.parts == 2 ? fused(two) : fused(four); };
+        if (fp.iters <= 4) with_parts(accept_fused_kernel<4, 1>, accept_fused_kernel<4, 2>, accept_fused_kernel<4, 4>);
+        else if (fp.iters <= 8) with_parts(accept_fused_kernel<8, 1>, accept_fused_kernel<8, 2>, accept_fused_kernel<8, 4>);
+        else if (fp.iters <= 12) with_parts(accept_fused_kernel<12, 1>, accept_fused_kernel<12, 2>, accept_fused_kernel<12, 4>);
+        else with_parts(accept_fused_kernel<16, 1>, accept_fused_kernel<16, 2>, accept_fused_kernel<16, 4>);
         return check_launch();
     }
     const AcceptPlan pl = plan_accept(V);
