@@ -1,4 +1,5 @@
-"""Thin Python binding of liblotts.so: argument marshalling only.
+"""Thin Python binding of liblotts.so: argument marshalling only.  The calls that are shorter on the GPU than in Python
+(verify_attention, spec_accept, majority_vote, skinny_gemm) go through the extension _calls, the others through ctypes.
 
 torch supplies device memory and the current stream; every step of the verify path runs in
 the library's HIP kernels.  There is no fallback: if the library is missing the import fails.
@@ -10,6 +11,8 @@ import os
 from typing import Dict, Optional, Tuple
 
 import torch
+
+from . import _calls
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblotts.so")
@@ -90,6 +93,9 @@ def load() -> ctypes.CDLL:
         lib.lotts_timer_stop.argtypes = [ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_float)]
         lib.confidence_vote.restype = ctypes.c_int
         lib.confidence_vote.argtypes = [i32, i32, i32, vp, vp, vp, i32, i32, vp, vp, vp]
+        lib.calls = _calls.Calls(*(ctypes.cast(f, vp).value for f in (
+            lib.verify_attention_workspace_bytes, lib.verify_attention, lib.spec_accept_workspace_bytes, lib.spec_accept,
+            lib.majority_vote, lib.skinny_gemm_workspace_bytes, lib.skinny_gemm)))
         _lib = lib
     return _lib
 
@@ -128,11 +134,23 @@ def _remember(key: tuple, value):
     return value
 
 
+def _workspace_key(kind: str, index: int, stream: Optional[torch.cuda.Stream]) -> Tuple[str, int, int]:
+    return kind, index, _raw_stream(index) if stream is None else int(stream.cuda_stream)
+
+
+def _finish(rc: int, kind: str, index: int, stream: Optional[torch.cuda.Stream], again, name: str) -> None:
+    """What a native call answered, other than 0: an error, or the bytes of workspace that it needs to be made again."""
+    if rc > 0:
+        rc = again(_workspace(kind, index, rc, stream))
+    if rc != 0:
+        raise LottsError(rc, name)
+
+
 def _workspace(kind: str, index: int, nbytes: int, stream: Optional[torch.cuda.Stream]) -> torch.Tensor:
     """One cached scratch tensor per entry point, device and stream, grown on demand.  Calls on different streams
     may overlap in time, so they never share one.  The tensor is allocated and zero-filled on the stream that will
     use it (verify_attention wants its arrival cells zero at first use), so the fill is ordered before the kernel."""
-    key = (kind, index, _raw_stream(index) if stream is None else int(stream.cuda_stream))
+    key = _workspace_key(kind, index, stream)
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < nbytes:
         if ws is not None:
@@ -202,16 +220,13 @@ def verify_attention(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Vpre: Option
         out = torch.empty(Q.shape, dtype=Q.dtype, device=Q.device)
     if return_lse and lse is None:
         lse = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
-    desc, need, Kpre, Vpre = _attn_call(lib, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, out, scale)
-    if need == 0:
-        raise LottsError(-2, "verify_attention_workspace_bytes")
-    if workspace is None:
-        workspace = _workspace("attn", Q.get_device(), need, stream)
-    rc = lib.verify_attention(desc, Q.data_ptr(), _ptr(Kpre), _ptr(Vpre), Kpriv.data_ptr(), Vpriv.data_ptr(),
-                              priv_len.data_ptr(), out.data_ptr(), _ptr(lse), workspace.data_ptr(), workspace.nbytes,
-                              _stream_handle(stream))
+    index, handle = Q.get_device(), _stream_handle(stream)
+    cached = None if workspace is not None else _workspaces.get(_workspace_key("attn", index, stream))
+    call = lib.calls.verify_attention
+    rc = call(Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, scale, out, lse, workspace, cached, handle)
     if rc != 0:
-        raise LottsError(rc, "verify_attention")
+        _finish(rc, "attn", index, stream, lambda ws: call(Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, scale, out, lse, None, ws, handle),
+                "verify_attention")
     return (out, lse) if return_lse else out
 
 
@@ -240,33 +255,16 @@ def spec_accept(p: torch.Tensor, q: Optional[torch.Tensor], draft: Optional[torc
     lib = load()
     if not p.is_cuda:
         raise ValueError("spec_accept runs on the GPU only")
-    B, R, V = p.shape
-    k = R - 1
-    if p.dtype != torch.float32 or u.dtype != torch.float32 or not p.is_contiguous() or not u.is_contiguous():
-        raise TypeError("p and u must be contiguous float32")
-    if u.shape != (B, R):
-        raise ValueError("u must be [B][k+1]")
-    if k > 0:
-        if q is None or draft is None or q.shape != (B, k, V) or draft.shape != (B, k):
-            raise ValueError("q must be [B][k][V] and draft [B][k]")
-        if q.dtype != torch.float32 or draft.dtype != torch.int32 or not q.is_contiguous() or not draft.is_contiguous():
-            raise TypeError("q must be contiguous float32 and draft contiguous int32")
-    else:
-        q, draft = None, None
     if accept_len is None:
-        accept_len = torch.empty((B,), dtype=torch.int32, device=p.device)
+        accept_len = torch.empty((p.shape[0],), dtype=torch.int32, device=p.device)
     if next_token is None:
-        next_token = torch.empty((B,), dtype=torch.int32, device=p.device)
-    need = _sized.get(("accept", B, k, V))
-    if need is None:
-        need = _remember(("accept", B, k, V), lib.spec_accept_workspace_bytes(B, k, V))
-    if need == 0:
-        raise LottsError(-2, "spec_accept_workspace_bytes")
-    ws = _workspace("accept", p.get_device(), need, stream) if workspace is None else workspace
-    rc = lib.spec_accept(B, k, V, p.data_ptr(), _ptr(q), _ptr(draft), u.data_ptr(), accept_len.data_ptr(),
-                         next_token.data_ptr(), ws.data_ptr(), ws.nbytes, _stream_handle(stream))
+        next_token = torch.empty((p.shape[0],), dtype=torch.int32, device=p.device)
+    index, handle = p.get_device(), _stream_handle(stream)
+    cached = None if workspace is not None else _workspaces.get(_workspace_key("accept", index, stream))
+    call = lib.calls.spec_accept
+    rc = call(p, q, draft, u, accept_len, next_token, workspace, cached, handle)
     if rc != 0:
-        raise LottsError(rc, "spec_accept")
+        _finish(rc, "accept", index, stream, lambda ws: call(p, q, draft, u, accept_len, next_token, None, ws, handle), "spec_accept")
     return accept_len, next_token
 
 
@@ -278,14 +276,11 @@ def majority_vote(answers: torch.Tensor, *, winner: Optional[torch.Tensor] = Non
         raise ValueError("majority_vote runs on the GPU only")
     if answers.dim() == 1:
         answers = answers[None, :]
-    if answers.dtype != torch.int32 or not answers.is_contiguous():
-        raise TypeError("answers must be contiguous int32")
-    N, B = answers.shape
     if winner is None:
-        winner = torch.empty((N,), dtype=torch.int32, device=answers.device)
+        winner = torch.empty((answers.shape[0],), dtype=torch.int32, device=answers.device)
     if winner_count is None:
-        winner_count = torch.empty((N,), dtype=torch.int32, device=answers.device)
-    rc = lib.majority_vote(N, B, answers.data_ptr(), winner.data_ptr(), winner_count.data_ptr(), _stream_handle(stream))
+        winner_count = torch.empty((answers.shape[0],), dtype=torch.int32, device=answers.device)
+    rc = lib.calls.majority_vote(answers, winner, winner_count, _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "majority_vote")
     return winner, winner_count
@@ -384,22 +379,14 @@ def skinny_gemm(X: torch.Tensor, W: torch.Tensor, *, out: Optional[torch.Tensor]
     lib = load()
     if not X.is_cuda or X.dtype != torch.bfloat16 or W.dtype != torch.bfloat16:
         raise TypeError("skinny_gemm takes bfloat16 tensors on the GPU")
-    M, K = X.shape
-    N, K2 = W.shape
-    if K2 != K or X.stride(1) != 1 or W.stride(1) != 1:
-        raise ValueError("X [M][K] and W [N][K] must share K and have contiguous rows")
     if out is None:
-        out = torch.empty((M, N), dtype=torch.bfloat16, device=X.device)
-    need = _sized.get(("gemm", M, N, K))
-    if need is None:
-        need = _remember(("gemm", M, N, K), lib.skinny_gemm_workspace_bytes(M, N, K))
-    if need == 0:
-        raise LottsError(-2, "skinny_gemm_workspace_bytes")
-    ws = _workspace("gemm", X.get_device(), need, stream) if workspace is None else workspace
-    rc = lib.skinny_gemm(M, N, K, X.data_ptr(), X.stride(0), W.data_ptr(), W.stride(0), out.data_ptr(), out.stride(0),
-                         ws.data_ptr(), ws.nbytes, _stream_handle(stream))
+        out = torch.empty((X.shape[0], W.shape[0]), dtype=torch.bfloat16, device=X.device)
+    index, handle = X.get_device(), _stream_handle(stream)
+    cached = None if workspace is not None else _workspaces.get(_workspace_key("gemm", index, stream))
+    call = lib.calls.skinny_gemm
+    rc = call(X, W, out, workspace, cached, handle)
     if rc != 0:
-        raise LottsError(rc, "skinny_gemm")
+        _finish(rc, "gemm", index, stream, lambda ws: call(X, W, out, None, ws, handle), "skinny_gemm")
     return out
 
 
