@@ -34,15 +34,20 @@ constexpr int kGemmTileFloats = 32 * 32;  // one accumulator tile: 32 weight row
 constexpr int kStaggerStride = 2048;
 constexpr int kGemmOutRow = 80;           // bytes per token row of a 32 x 32 bf16 tile on its way out through LDS (64 + pad)
 
-struct GemmParams {
+struct GemmParams {  // (in the order in which the kernels come to need it)
     const __bf16 *X, *W;
-    __bf16* Y;
-    float* part;  // fp32 partials when ksplit > 1: [ksplit][block of weight rows][row wavefront][tile][quad][lane] float4
-    int M, N, K, ksplit;
+    long long ldx, ldw;
+    int M, N, K;
+    int tokens;  // direct: tokens a workgroup owns
+    int ksplit;
     int rows;     // weight rows a wavefront owns: 32, or fewer (a multiple of 4) when that fills the chip better
-    int nblocks, roww, rt, tt;  // launch geometry, for the reduce kernel: blocks, row wavefronts, row / token tiles per wavefront
+    FastDiv d_ksplit;           // by ksplit
+    FastDiv d_steps[2];         // by the half-chunk steps of a K split: all splits have one of two numbers of them, 2 apart
     int stagger;                // stream forms: blocks start their K loop at different steps
-    long long ldx, ldw, ldy;
+    int nblocks, roww, rt, tt;  // launch geometry, for the reduce kernel: blocks, row wavefronts, row / token tiles per wavefront
+    __bf16* Y;
+    long long ldy;
+    float* part;  // fp32 partials when ksplit > 1: [ksplit][block of weight rows][row wavefront][tile][quad][lane] float4
 };
 
 enum GemmForm { kStream256, kStream128, kStream64, kDirect };
@@ -80,7 +85,7 @@ static inline int plan_rows(int N, int roww, int mt) {
 static inline int direct_waves(int rn) { return rn == 4 ? 4 : 8; }
 static inline int direct_batch(int rn, int tt) { return rn == 4 ? 2 : (tt == 1 ? 8 : 4); }
 
-// Direct form: the tile that leaves the fewest bytes (its weight rows plus its tokens, over the whole K) to a workgroup with
+// Direct form: the tile -- the tokens in even shares: 40 tokens in two workgroups are 20 and 20, not 32 and 8 -- that leaves the fewest bytes (its weight rows plus its tokens, over the whole K) to a workgroup with
 // at most one workgroup per unit.  Returns those KB, with a wavefront's share of K in whole batches, or 0 if no tile fits.
 static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
     static const int tiles[][2] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 3}, {4, 2}, {4, 3}};
@@ -89,7 +94,7 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
         const long long nx = (N + 16 * t[0] - 1) / (16 * t[0]), ny = (M + 16 * t[1] - 1) / (16 * t[1]);
         if (nx * ny > kNumCU) continue;
         const int unit = direct_waves(t[0]) * direct_batch(t[0], t[1]) * 32;
-        const double kb = (16.0 * t[0] + (16 * t[1] < M ? 16 * t[1] : M)) * ((K + unit - 1) / unit * unit) * 2.0 / 1024.0;
+        const double kb = (16.0 * t[0] + (double)((M + ny - 1) / ny)) * ((K + unit - 1) / unit * unit) * 2.0 / 1024.0;
         if (best == 0.0 || kb < best) {
             best = kb;
             pl->rn = t[0]; pl->tt = t[1]; pl->nblocks = (int)nx; pl->nby = (int)ny;
@@ -217,13 +222,18 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
     const int grp = RT == 1 ? wr : wr >> 1, th = RT == 1 ? 0 : wr & 1;
     const int n0 = blockIdx.x * (p.rows * ROWW) + grp * (p.rows * RT);  // pairs always own 2 x 32 rows
     const int chunks = p.K / kGemmChunk;
-    const int c_lo = (int)((long long)blockIdx.y * chunks / p.ksplit);
-    const int c_hi = (int)((long long)(blockIdx.y + 1) * chunks / p.ksplit);
+    // (Through host-made divisors: the run-time divisions here, two of them of 64 bits, stood 0.5 us in front of the first load.)
+    const int c_lo = quot(blockIdx.y * chunks, p.d_ksplit);
+    const int c_hi = quot((blockIdx.y + 1) * chunks, p.d_ksplit);
     const int G = 2 * (c_hi - c_lo);  // half-chunk steps
     // Staggered start: block x begins 5 x steps into its K range and wraps around; the pointers go back once, at that step.  (A
     // select of the offset in every transfer instead cost 2 % of 55296 x 5120.)
-    const int turn = (int)blockIdx.x * 5;
-    const int first = p.stagger && G > 0 ? (turn + turn / G) % G : 0;
+    int first = 0;
+    if (p.stagger && G > 0) {
+        const FastDiv d = G == 2 * quot(chunks, p.d_ksplit) ? p.d_steps[0] : p.d_steps[1];
+        const int turn = (int)blockIdx.x * 5, at = turn + quot(turn, d);
+        first = at - quot(at, d) * G;
+    }
     const int wrap = first > 0 ? G - first : -1;  // the step that is back at the start of the range
     unsigned char* xs = lds;
     unsigned char* wsl = lds + XS * XSTAGE + grp * (WS * RT * WSTAGE);
@@ -325,6 +335,9 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
         if (i < G) fetch_x(i);
         if (i + 1 < G) fetch_w(i + 1);
     }
+    // Arguments that are still on their way share the LDS reads' counter and come in any order: with one outstanding, every wait of
+    // the loop for a fragment would be a wait for all of them (192 tokens x 22016 x 2048 29.4 -> 30.1 us, 256 36.5 -> 38.2).
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) alone
     for (int g = 0; g < G; ++g) {
         // issued after step g's X: W of the steps up to g + XS - 1 and X of those up to g + XS - 2, as far as there are any
         if (g + XS - 1 < G)
@@ -482,14 +495,14 @@ __global__ __launch_bounds__(WAVES * kWave) void skinny_gemm_direct_kernel(const
     __shared__ __attribute__((aligned(16))) float4 red[WAVES][TILES][kWave];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
     const int lr = lane & 15, kg = lane >> 4;
-    const int n0 = blockIdx.x * (16 * RN), m0 = blockIdx.y * (16 * TT);
+    const int n0 = blockIdx.x * (16 * RN), m0 = blockIdx.y * p.tokens, m_end = min(m0 + p.tokens, p.M);
     const int S = p.K / 32;
     const int s_lo = (int)((long long)wave * S / WAVES), s_hi = (int)((long long)(wave + 1) * S / WAVES);
     const __bf16 *wp[RN], *xp[TT];
 #pragma unroll
     for (int i = 0; i < RN; ++i) wp[i] = p.W + (long long)min(n0 + i * 16 + lr, p.N - 1) * p.ldw + kg * 8;
 #pragma unroll
-    for (int t = 0; t < TT; ++t) xp[t] = p.X + (long long)min(m0 + t * 16 + lr, p.M - 1) * p.ldx + kg * 8;
+    for (int t = 0; t < TT; ++t) xp[t] = p.X + (long long)min(m0 + t * 16 + lr, m_end - 1) * p.ldx + kg * 8;
     g_f32x4 acc[RN][TT];
 #pragma unroll
     for (int i = 0; i < RN; ++i)
@@ -549,7 +562,7 @@ __global__ __launch_bounds__(WAVES * kWave) void skinny_gemm_direct_kernel(const
         }
         const int i = tile / TT, t = tile % TT;
         const int m = m0 + t * 16 + (l & 15), n = n0 + i * 16 + (l >> 4) * 4;
-        if (m < p.M && n < p.N) {
+        if (m < m_end && n < p.N) {
             g_bf16x4 o;
             o[0] = (__bf16)s.x; o[1] = (__bf16)s.y; o[2] = (__bf16)s.z; o[3] = (__bf16)s.w;
             *reinterpret_cast<g_bf16x4*>(p.Y + (long long)m * p.ldy + n) = o;
@@ -611,6 +624,11 @@ extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64
     p.M = M; p.N = N; p.K = K; p.ksplit = pl.ksplit; p.rows = pl.rows;
     p.nblocks = pl.nblocks; p.roww = pl.roww; p.rt = pl.rt; p.tt = pl.mt / pl.rt;
     p.stagger = ldw % kStaggerStride == 0;
+    p.tokens = pl.form == kDirect ? (M + pl.nby - 1) / pl.nby : 0;
+    p.d_ksplit = fast_div(pl.ksplit);
+    const int steps = 2 * (K / kGemmChunk / pl.ksplit);  // of the shorter splits
+    p.d_steps[0] = fast_div(steps > 0 ? steps : 1);
+    p.d_steps[1] = fast_div(steps + 2);
     p.ldx = ldx; p.ldw = ldw; p.ldy = ldy;
     hipStream_t s = (hipStream_t)stream;
     const dim3 grid(pl.nblocks, pl.form == kDirect ? pl.nby : pl.ksplit);
