@@ -13,10 +13,11 @@
 // token = first v whose prefix sum exceeds floor(U_k * sum W / 2^24).  128-bit integers.
 //
 // Two launches:
-//   lg_stat_kernel      grid (pieces of 8192 or 16384 logits, B * (2k + 1) rows, the pieces of a row next to each other): a
+//   lg_stat_kernel      grid (pieces of 8192 to 16384 logits, B * (2k + 1) rows, the pieces of a row next to each other): a
 //                       workgroup reads its piece ONCE into registers, publishes the piece's maximum under this call's tag (two words),
 //                       collects the maxima of the row's other pieces (one that stays out for long it forms itself, from
-//                       the logits), and stores the piece's integer weight sum, formed from the registers.
+//                       the logits), and stores the piece's integer weight sum, formed from the registers; the piece that
+//                       holds the row's drafted token stores its weight too.
 //   lg_scan_pick_kernel grid (chunks, B): accept tests -> n; 128-bit chunk sums of the weights of row n, published as
 //                       six 8-byte words that each carry 32 bits of a sum and this call's tag.  The workgroup of a
 //                       branch's LAST chunk then collects the branch's sums (one that stays out for long it forms itself)
@@ -185,12 +186,12 @@ __device__ __forceinline__ unsigned long long lg_peek(const unsigned long long* 
 // launch while their logits stay in registers; what a launch boundary and a second read of all logits cost before is one trip
 // through memory now.  A row's pieces are neighbours in the grid, so the others' words are mostly there when they are looked
 // for; that they come at all is not relied on (kWaitPolls).  The words are cleared by the next launch.
-// Bound by the vector unit: 17 instructions a logit that the integer definition fixes, 8 us of the chip's rate for 112 rows x
-// 152064 logits, behind the read that all workgroups start with.  Whole call, us, before (three launches: maxima, sums, scan) ->
-// now: 16 x 7 rows x 152064 bf16 30.8 -> 27.9, fp32 40.5 -> 30.7; 64 x 5 x 151936 63.9 -> 54.2; 5 x 15 rows x 50257 fp32 (rows off
-// a 16-byte boundary, element by element before) 48.0 -> 17.7.
-// IT = 4 up to 2^19 logits (a lane of the collecting wavefront per piece): 28.0 us against 28.9 with IT = 8 on the first of
-// these and 38.0 with IT = 2, whose workgroups come and go too often.
+// Bound by the vector unit: 16 instructions a logit that the integer definition fixes (12 for the weight, the rest unpacking, scaling,
+// maximum and sum), 7 us of the chip's rate for 112 rows x 152064 logits, behind the read that all workgroups start with: a unit returns
+// loads in order, so the words of the exchange wait behind the logits that the unit's other workgroups have asked for (fewer
+// workgroups at a time are no way out: 28.7 us with five to a unit, 30.4 with four, against 27.4).  Whole call, us, as three launches
+// (maxima, sums, scan) -> two -> now: 16 x 7 rows x 152064 bf16 30.8 -> 27.5 -> 23.1, fp32 40.5 -> 31.3 -> 27.7; 5 x 15 rows x 50257 fp32
+// (rows off a 16-byte boundary) 48.0 -> 15.7 -> 13.5; 32 x 17 x 151936 bf16 68.3 -> 55.6.
 template <bool BF16, int IT>
 __global__ __launch_bounds__(kLgThreads) void lg_stat_kernel(int B, int k, int V, int npieces, unsigned tag,
                                                              const void* __restrict__ zt, const void* __restrict__ zd,
