@@ -2,10 +2,9 @@
 // the paper cites for speculative decoding in Section 2 / Section 3.2).
 //
 // One launch when the vocabulary fits (accept_fused_kernel), two otherwise:
-//   accept_fused_kernel  grid (S slices x B branches), 4 wavefronts per workgroup, 1, 2 or 4 of them to a
-//       sub-chunk.  Every workgroup
-//       re-derives the branch's accepted length n from the 2k gathered probabilities; each of its
-//       wavefronts turns one sub-chunk of the row to be sampled (residual max(0, p_n - q_n), or p_k)
+//   accept_fused_kernel  grid (S slices x B branches), 4 wavefronts per workgroup, 1, 2 or 4 of them to a sub-chunk.
+//       Every workgroup re-derives the branch's accepted length n from the 2k gathered probabilities; its
+//       wavefronts turn its sub-chunks of the row to be sampled (residual max(0, p_n - q_n), or p_k)
 //       into 2^-40 fixed-point weights -- all of the sub-chunk's loads are requested before the first
 //       is used -- and publishes the sub-chunk's integer sum as two 8-byte words, each carrying half
 //       of it and this call's 32-bit tag.  The workgroup of a branch's LAST
