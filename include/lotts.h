@@ -153,7 +153,8 @@ int spec_accept(int32_t B, int32_t k, int32_t V, const float *p, const float *q,
                 const float *u, int32_t *accept_len, int32_t *next_token, void *workspace,
                 size_t workspace_bytes, void *stream);
 
-/* Bytes of workspace spec_accept_logits needs (0 if the sizes are invalid). */
+/* Bytes of workspace spec_accept_logits needs (0 if the sizes are invalid).  Never fewer for more branches, drafts or tokens
+ * (while one grid holds all pieces of 8192 logits, 2^24 - 1 of them), so a workspace for the largest batch serves the smaller ones. */
 size_t spec_accept_logits_workspace_bytes(int32_t B, int32_t k, int32_t V);
 
 /*

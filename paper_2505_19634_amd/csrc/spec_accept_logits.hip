@@ -616,6 +616,7 @@ __global__ __launch_bounds__(kLgThreads) void lg_scan_pick_kernel(int B, int k, 
 
 struct LgLayout {
     size_t off_psum, off_chunks, off_words, off_draft, total;
+    size_t asked;  // what the workspace query answers, >= total
     int nchunks, npieces, iters;
 };
 // [row maxima][sums of the pieces][tagged words of the chunks: 6 per (branch, chunk)][tagged words of the pieces: 2 per (row, piece)]
@@ -642,12 +643,20 @@ static inline LgLayout lg_layout(int B, int k, int V) {
         }
     }
     l.npieces = (V + l.iters * kLgGroup - 1) / (l.iters * kLgGroup);
+    // The query asks for the smallest pieces' words whichever are taken: by the pieces' number alone 14 branches would ask for less
+    // than 13, and a workspace sized for the larger batch would be too small for the smaller one.
+    const size_t smallest = (V + 4 * kLgGroup - 1) / (4 * kLgGroup);
+    const size_t most = rows * smallest * kLgThreads > 0xffffffffu ? (size_t)l.npieces : smallest;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    l.off_psum = up(rows * sizeof(float));
-    l.off_chunks = l.off_psum + up(rows * l.npieces * sizeof(unsigned long long));
-    l.off_words = l.off_chunks + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
-    l.off_draft = l.off_words + up(rows * l.npieces * 2 * sizeof(unsigned long long));
-    l.total = l.off_draft + up(rows * sizeof(unsigned));
+    auto bytes = [&](size_t pieces) {
+        l.off_psum = up(rows * sizeof(float));
+        l.off_chunks = l.off_psum + up(rows * pieces * sizeof(unsigned long long));
+        l.off_words = l.off_chunks + up((size_t)B * l.nchunks * 6 * sizeof(unsigned long long));
+        l.off_draft = l.off_words + up(rows * pieces * 2 * sizeof(unsigned long long));
+        return l.off_draft + up(rows * sizeof(unsigned));
+    };
+    l.asked = bytes(most);
+    l.total = bytes(l.npieces);
     return l;
 }
 static inline bool lg_sizes_ok(int B, int k, int V) {
@@ -695,7 +704,7 @@ static int lg_launch(int B, int k, int V, const void* zt, const void* zd, float 
 
 extern "C" size_t spec_accept_logits_workspace_bytes(int32_t B, int32_t k, int32_t V) {
     if (!lotts::lg_sizes_ok(B, k, V)) return 0;
-    return lotts::lg_layout(B, k, V).total;
+    return lotts::lg_layout(B, k, V).asked;
 }
 
 extern "C" int spec_accept_logits(int32_t B, int32_t k, int32_t V, const void* target_logits, const void* draft_logits,
@@ -708,7 +717,7 @@ extern "C" int spec_accept_logits(int32_t B, int32_t k, int32_t V, const void* t
     if (!(inv_temperature > 0.0f) || inv_temperature > 3.0e38f) return LOTTS_ERR_SHAPE;
     if (!target_logits || !u || !accept_len || !next_token || !workspace) return LOTTS_ERR_NULL;
     if (k > 0 && (!draft_logits || !draft)) return LOTTS_ERR_NULL;
-    if (workspace_bytes < spec_accept_logits_workspace_bytes(B, k, V)) return LOTTS_ERR_WORKSPACE;
+    if (workspace_bytes < lg_layout(B, k, V).total) return LOTTS_ERR_WORKSPACE;
     if (((uintptr_t)workspace & 15) != 0) return LOTTS_ERR_SHAPE;
     const bool bf16 = logit_dtype == LOTTS_BF16;
     const uintptr_t es = bf16 ? 2 : 4;

@@ -199,3 +199,20 @@ def test_partials_per_row(lib, B, k, Hq, Hkv, D, P, L, slots):
     """How many partials a row has, from the bytes asked for: a block of 16384 cells, then D + 2 floats per partial."""
     need = lib.verify_attention_workspace_bytes(ctypes.byref(make_desc(B=B, k=k, Hq=Hq, Hkv=Hkv, D=D, P=P, Lmax=L)))
     assert (need - 16384 * 8) // (4 * (D + 2) * B * (k + 1) * Hq) == slots
+
+
+def test_logits_workspace_grows_with_every_size(lib):
+    """A workspace that was sized for the largest batch serves the smaller ones: the bytes asked for never shrink as branches, drafts or
+    tokens become more, whatever pieces the rows are cut into."""
+    need = lib.spec_accept_logits_workspace_bytes
+    for V in (1, 8193, 32000, 50257, 128256, 151936, 152064, 262144, 524288, 524289, 786433, 1 << 20):
+        for k in (0, 1, 3, 7, 15):
+            sizes = [need(B, k, V) for B in range(1, 130)]
+            assert sizes == sorted(sizes), (k, V)
+    for V in (50257, 152064):
+        for B in (1, 13, 14, 64):
+            sizes = [need(B, k, V) for k in range(0, 40)]
+            assert sizes == sorted(sizes), (B, V)
+    for B, k in ((1, 0), (13, 3), (64, 7)):
+        sizes = [need(B, k, V) for V in range(1, (1 << 20) + 1, 1021)]
+        assert sizes == sorted(sizes), (B, k)
