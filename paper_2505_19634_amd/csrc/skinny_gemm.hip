@@ -85,16 +85,22 @@ static inline int plan_rows(int N, int roww, int mt) {
 static inline int direct_waves(int rn) { return rn == 4 ? 4 : 8; }
 static inline int direct_batch(int rn, int tt) { return rn == 4 ? 2 : (tt == 1 ? 8 : 4); }
 
-// Direct form: the tile -- the tokens in even shares: 40 tokens in two workgroups are 20 and 20, not 32 and 8 -- that leaves the fewest bytes (its weight rows plus its tokens, over the whole K) to a workgroup with
-// at most one workgroup per unit.  Returns those KB, with a wavefront's share of K in whole batches, or 0 if no tile fits.
-static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
+// Direct form: the tile that leaves the fewest bytes (its weight rows plus its tokens, over the whole K) to a workgroup with at most one
+// workgroup per unit.  Tokens are dealt in even shares: 40 tokens in two workgroups are 20 and 20, not 32 and 8 (60 sizes whose tile
+// or shares that changes: 5 % faster; but 6784 .. 7424 x 768 at 33 .. 36 tokens, in tiles of 64 rows then, 7.5 -> 8.0 us).  Returns those
+// KB, with a wavefront's share of K in whole batches, or 0 if no tile fits; `filled`: the fewest KB with tiles full of tokens.
+static inline double plan_direct(int M, int N, int K, GemmPlan* pl, double* filled) {
     static const int tiles[][2] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 3}, {4, 2}, {4, 3}};
     double best = 0.0;
+    *filled = 0.0;
     for (const auto& t : tiles) {
         const long long nx = (N + 16 * t[0] - 1) / (16 * t[0]), ny = (M + 16 * t[1] - 1) / (16 * t[1]);
         if (nx * ny > kNumCU) continue;
         const int unit = direct_waves(t[0]) * direct_batch(t[0], t[1]) * 32;
-        const double kb = (16.0 * t[0] + (double)((M + ny - 1) / ny)) * ((K + unit - 1) / unit * unit) * 2.0 / 1024.0;
+        const double row_kb = ((K + unit - 1) / unit * unit) * 2.0 / 1024.0;
+        const double kb = (16.0 * t[0] + (double)((M + ny - 1) / ny)) * row_kb;
+        const double kb_filled = (16.0 * t[0] + (16 * t[1] < M ? 16 * t[1] : M)) * row_kb;
+        if (*filled == 0.0 || kb_filled < *filled) *filled = kb_filled;
         if (best == 0.0 || kb < best) {
             best = kb;
             pl->rn = t[0]; pl->tt = t[1]; pl->nblocks = (int)nx; pl->nby = (int)ny;
@@ -107,11 +113,14 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl) {
 // back to back over rotated weights, reduce launch included.
 //   Direct, up to K = 4096 and 8192 rows: 3.4 us + 0.022 us per KB of a workgroup's W and X (whole batches of loads) + 0.14 us per
 //     MB of W, against 7 us + 0.125 us per MB of W + 7e-6 us per token and (N + K) of the split stream forms; both fitted to 1188
-//     sizes (1536 .. 14336 rows, K 512 .. 4096, 1 .. 192 tokens), where the choice costs 0.3 % over the better form: 2560 x 2048 at
-//     1 / 40 / 192 tokens 5.2 / 7.8 / 13.5 us against 7.9 / 9.2 / 15.0; 4736 x 1280 at 24 tokens 12.4 against 9.7; 6144 x 4096 at 2
-//     tokens 17.7 against 13.9.  With more rows only the tile of 64 rows is left, four wavefronts with many small batches: 11904 x
-//     1280 at 48 tokens 16.5 us against 13.4.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1
-//     token 19.8 us against 14.2.
+//     sizes (1536 .. 14336 rows, K 512 .. 4096, 1 .. 192 tokens) with tiles full of tokens, where the choice costs 0.4 % over the better
+//     form: 2560 x 2048 at 1 / 40 / 192 tokens 5.1 / 7.6 / 13.4 us against 7.9 / 9.2 / 15.0; 4736 x 1280 at 24 tokens 12.4 against 9.7; 6144
+//     x 4096 at 2 tokens 17.7 against 13.2.  Even shares are fewer KB, but not all of what is counted less is time saved: where only they
+//     put the direct form ahead, 0.034 us per KB + 0.15 us per MB of W have to stay below 6.5 us + 10e-6 us per token and (N + K),
+//     fitted to 492 such sizes: always direct is 5.3 % over the better form there (3968 x 2176 at 168 tokens 20.0 us, streamed
+//     17.3), never direct 2.5 % (2176 x 1408 at 66 tokens 8.7 us, streamed 10.1), so 0.4 %, as on 270 sizes beside them.
+//     With more rows only the tile of 64 rows is left, four wavefronts with many small batches: 11904 x 1280 at 48 tokens 16.5 us
+//     against 13.2.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1 token 19.8 us against 13.8.
 //   256-row stream form: more than 256 blocks of 128 rows; an X chunk in LDS serves the most rows.  55296 x 5120 at 64
 //     tokens 92 us, 128-row form 104.
 //   128-row form below that, 64-row form when it would have to be split more than sevenfold (N <= 4608): the fewer splits,
@@ -126,8 +135,10 @@ static inline GemmPlan plan_gemm(int M, int N, int K) {
     pl.rt = pl.mt >= 4 && pl.mt % 2 == 0 ? 2 : 1;
     pl.ksplit = 1;
     if (K <= 4096 && N <= 8192) {
-        const double kb = plan_direct(M, N, K, &pl);
-        if (kb > 0.0 && 3.4 + 0.022 * kb + 0.14 * (2e-6 * N * K) < 7.0 + 0.125 * (2e-6 * N * K) + 7e-6 * M * (N + K)) {
+        double filled;
+        const double kb = plan_direct(M, N, K, &pl, &filled), mb = 2e-6 * N * K, tokens = 1e-6 * M * (N + K);
+        auto ahead = [&](double k) { return 3.4 + 0.022 * k + 0.14 * mb < 7.0 + 0.125 * mb + 7.0 * tokens; };
+        if (kb > 0.0 && (ahead(filled) || (ahead(kb) && 0.034 * kb + 0.15 * mb < 6.5 + 10.0 * tokens))) {
             pl.form = kDirect;
             return pl;
         }

@@ -1,0 +1,43 @@
+// The launch plans of the library, answered on the host: a line "gemm M N K", "logits B k V" or "attention B k Hq Hkv D P Lmax" in, the
+// plan's numbers out.  Host code only; nothing here launches, so the few runtime calls that the sources make have empty bodies.
+#ifdef PLANS_RUNTIME
+extern "C" {
+void* __hipRegisterFatBinary(void*) { return nullptr; }
+void __hipRegisterFunction() {}
+void __hipRegisterVar() {}
+void __hipUnregisterFatBinary() {}
+}
+#else
+#include "skinny_gemm.hip"
+#include "spec_accept_logits.hip"
+#include "verify_attention.hip"
+#include <cstdio>
+#include <cstring>
+
+int main() {
+    char kind[16];
+    while (scanf("%15s", kind) == 1) {
+        if (!strcmp(kind, "gemm")) {
+            int M, N, K;
+            if (scanf("%d %d %d", &M, &N, &K) != 3) return 1;
+            const lotts::GemmPlan p = lotts::plan_gemm(M, N, K);
+            static const char* const forms[] = {"stream256", "stream128", "stream64", "direct"};
+            printf("form %s rn %d tt %d nby %d ksplit %d\n", forms[p.form], p.rn, p.tt, p.nby, p.ksplit);
+        } else if (!strcmp(kind, "logits")) {
+            int B, k, V;
+            if (scanf("%d %d %d", &B, &k, &V) != 3) return 1;
+            const lotts::LgLayout l = lotts::lg_layout(B, k, V);
+            printf("loads %d pieces %d\n", l.iters, l.npieces);
+        } else if (!strcmp(kind, "attention")) {
+            lotts_attn_desc d = {};
+            d.dtype = LOTTS_BF16;
+            if (scanf("%d %d %d %d %d %d %d", &d.B, &d.k, &d.Hq, &d.Hkv, &d.D, &d.P, &d.Lmax) != 7) return 1;
+            const lotts::AttnPlan p = lotts::plan_attention(d);
+            printf("one %d nqt %d fold %d shares %d prefix_shares %d merge %d\n", p.one, p.nqt, p.fold, p.nsplit_priv, p.nsplit_pre, p.merge);
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}
+#endif
