@@ -244,7 +244,7 @@ int kv_append(int32_t B, int32_t k, int32_t Hkv, int32_t D, lotts_dtype dtype, c
               int64_t priv_stride_b, int64_t priv_stride_h, int64_t priv_stride_t, int32_t Lmax,
               const int32_t *priv_len, void *stream);
 
-/* Bytes of workspace skinny_gemm needs (0 if the sizes are invalid). */
+/* Bytes of workspace skinny_gemm needs (0 if the sizes are invalid); never fewer for more tokens of the same matrix. */
 size_t skinny_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K);
 
 /*

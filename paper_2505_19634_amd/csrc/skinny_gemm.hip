@@ -127,14 +127,14 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl, double* fill
 //     the fewer fp32 partials, but the more often a unit reads X.  2048 x 11008 at 40 / 192 tokens in 64-row blocks x 8
 //     splits 14.8 / 24.3 us, 128 x 16 17.1 / 26.5; 5120 x 5120 at 64 / 192 tokens 128 x 6 17.9 / 26.0, 64 x 3 17.4 / 28.6; 6144 x 6144
 //     21.5 / 31.0 against 23.4 / 38.1.
-static inline GemmPlan plan_gemm(int M, int N, int K) {
+static inline GemmPlan plan_gemm(int M, int N, int K, bool may_be_direct = true) {
     GemmPlan pl = {};
     const int chunks = K / kGemmChunk;
     pl.mt = (M + 31) / 32;
     // An even number of token tiles from 4 on: pairs of wavefronts own two row tiles together and half of the token tiles each.
     pl.rt = pl.mt >= 4 && pl.mt % 2 == 0 ? 2 : 1;
     pl.ksplit = 1;
-    if (K <= 4096 && N <= 8192) {
+    if (may_be_direct && K <= 4096 && N <= 8192) {
         double filled;
         const double kb = plan_direct(M, N, K, &pl, &filled), mb = 2e-6 * N * K, tokens = 1e-6 * M * (N + K);
         auto ahead = [&](double k) { return 3.4 + 0.022 * k + 0.14 * mb < 7.0 + 0.125 * mb + 7.0 * tokens; };
@@ -167,8 +167,11 @@ static inline GemmPlan plan_gemm(int M, int N, int K) {
     return pl;
 }
 
-// fp32 partials of one K split
-static inline size_t split_floats(const GemmPlan& pl) { return (size_t)pl.nblocks * pl.roww * pl.mt * kGemmTileFloats; }
+// Workspace of a plan: the fp32 partials of its K splits, 256 bytes at least.
+static inline size_t plan_bytes(const GemmPlan& pl) {
+    const size_t bytes = pl.ksplit > 1 ? sizeof(float) * pl.ksplit * pl.nblocks * pl.roww * pl.mt * kGemmTileFloats : 0;
+    return bytes < 256 ? 256 : bytes;
+}
 
 // The streaming kernel.  WAVES = ROWW * KG wavefronts, 32 * ROWW weight rows per workgroup: a row wavefront owns one MFMA row
 // tile of 32 weight rows and all M tokens -- or, for an even number of token tiles from 4 on (97..128, 161..192,
@@ -610,11 +613,11 @@ static void launch_direct(dim3 grid, hipStream_t s, const GemmParams& p) {
 
 }  // namespace lotts
 
+// The query asks for the K splits of the stream form also where the direct form is taken: which one is faster changes back and forth with
+// the tokens, and a workspace sized for the most of them would be too small for fewer.
 extern "C" size_t skinny_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
     if (!lotts::gemm_sizes_ok(M, N, K)) return 0;
-    const lotts::GemmPlan pl = lotts::plan_gemm(M, N, K);
-    const size_t bytes = pl.ksplit > 1 ? pl.ksplit * lotts::split_floats(pl) * sizeof(float) : 0;
-    return bytes < 256 ? 256 : bytes;
+    return lotts::plan_bytes(lotts::plan_gemm(M, N, K, false));
 }
 
 extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,
@@ -624,8 +627,8 @@ extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64
     if (!X || !W || !Y || !workspace) return LOTTS_ERR_NULL;
     if (ldx < K || ldw < K || ldy < N || (ldx % 8) || (ldw % 8) || (ldy % 4)) return LOTTS_ERR_SHAPE;
     if ((((uintptr_t)X | (uintptr_t)W | (uintptr_t)workspace) & 15) || ((uintptr_t)Y & 7)) return LOTTS_ERR_SHAPE;
-    if (workspace_bytes < skinny_gemm_workspace_bytes(M, N, K)) return LOTTS_ERR_WORKSPACE;
     const GemmPlan pl = plan_gemm(M, N, K);
+    if (workspace_bytes < plan_bytes(pl)) return LOTTS_ERR_WORKSPACE;
     GemmParams p;
 
     p.X = static_cast<const __bf16*>(X);

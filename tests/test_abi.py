@@ -216,3 +216,12 @@ def test_logits_workspace_grows_with_every_size(lib):
     for B, k in ((1, 0), (13, 3), (64, 7)):
         sizes = [need(B, k, V) for V in range(1, (1 << 20) + 1, 1021)]
         assert sizes == sorted(sizes), (B, k)
+
+
+def test_gemm_workspace_grows_with_the_tokens(lib):
+    """A workspace that was sized for the most tokens serves fewer, whichever form each number of tokens takes."""
+    need = lib.skinny_gemm_workspace_bytes
+    for N in (64, 512, 1024, 1536, 2048, 2560, 4608, 5120, 8192, 8200, 22016, 40000):
+        for K in (128, 1152, 2048, 2176, 2816, 3584, 4096, 4224, 5120, 11008):
+            sizes = [need(M, N, K) for M in range(1, 257)]
+            assert sizes == sorted(sizes), (N, K)
