@@ -7,12 +7,11 @@ the library's HIP kernels.  There is no fallback: if the library is missing the 
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from typing import Dict, Optional, Tuple
 
 import torch
-
-from . import _calls
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblotts.so")
@@ -49,12 +48,19 @@ class LottsError(RuntimeError):
 _lib = None
 
 
+def _unbuilt(what: str) -> ImportError:
+    return ImportError(what + " is not built: run paper_2505_19634_amd/build.py (or __graft_entry__.build())")
+
+
 def load() -> ctypes.CDLL:
     global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
-            raise ImportError("liblotts.so is not built: run paper_2505_19634_amd/build.py "
-                              "(or __graft_entry__.build())")
+            raise _unbuilt("liblotts.so")
+        try:   # here and not on top: an unbuilt tree gets the message above
+            _calls = importlib.import_module("._calls", __package__)
+        except ModuleNotFoundError:
+            raise _unbuilt("the extension _calls") from None
         lib = ctypes.CDLL(LIB_PATH)
         vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
         lib.lotts_strerror.restype = ctypes.c_char_p

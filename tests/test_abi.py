@@ -225,3 +225,18 @@ def test_gemm_workspace_grows_with_the_tokens(lib):
         for K in (128, 1152, 2048, 2176, 2816, 3584, 4096, 4224, 5120, 11008):
             sizes = [need(M, N, K) for M in range(1, 257)]
             assert sizes == sorted(sizes), (N, K)
+
+
+@pytest.mark.parametrize("built", [(), ("liblotts.so",)])
+def test_an_unbuilt_tree_says_so(tmp_path, built):
+    """Without the library, or with the library alone, the import names what to run."""
+    import shutil
+    import subprocess
+    import sys
+    package = tmp_path / "paper_2505_19634_amd"
+    shutil.copytree(os.path.join(ROOT, "paper_2505_19634_amd"), package, ignore=shutil.ignore_patterns("*.so", "__pycache__", "csrc"))
+    for name in built:
+        shutil.copy(os.path.join(ROOT, "paper_2505_19634_amd", name), package)
+    res = subprocess.run([sys.executable, "-c", "import paper_2505_19634_amd"], cwd=tmp_path, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                         text=True, timeout=300, env={**os.environ, "PYTHONPATH": str(tmp_path)})
+    assert res.returncode != 0 and "is not built: run paper_2505_19634_amd/build.py" in res.stdout, res.stdout
