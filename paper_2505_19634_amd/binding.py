@@ -61,6 +61,10 @@ def load() -> ctypes.CDLL:
             _calls = importlib.import_module("._calls", __package__)
         except ModuleNotFoundError:
             raise _unbuilt("the extension _calls") from None
+        built_for = getattr(_calls, "built_for_torch", None)
+        if built_for != torch.__version__:
+            raise ImportError("the extension _calls was built for torch %s, this is %s: run paper_2505_19634_amd/build.py" %
+                              (built_for, torch.__version__))
         lib = ctypes.CDLL(LIB_PATH)
         vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
         lib.lotts_strerror.restype = ctypes.c_char_p

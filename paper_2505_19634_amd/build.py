@@ -1,7 +1,6 @@
-"""Build liblotts.so (HIP kernels + C ABI) for gfx950 with hipcc, and _calls.so (the binding's host side) with g++, in-tree."""
+"""Build liblotts.so (HIP kernels + C ABI) for gfx950 with hipcc, and the extension _calls (the binding's host side) with g++, in-tree."""
 from __future__ import annotations
 
-import importlib.util
 import os
 import subprocess
 import sysconfig
@@ -13,7 +12,7 @@ LIB = os.path.join(_HERE, "liblotts.so")
 LIB_NO_POLLS = os.path.join(_HERE, "liblotts_no_polls.so")
 CALIB = os.path.join(_HERE, "calib_copy")
 PROBE = os.path.join(_HERE, "libread_probe.so")
-CALLS = os.path.join(_HERE, "_calls.so")
+CALLS = os.path.join(_HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["verify_attention.hip", "spec_accept.hip", "spec_accept_logits.hip", "majority_vote.hip",
            "confidence_vote.hip", "skinny_gemm.hip", "kv_append.hip", "kernel_timer.hip", "greedy_search.cpp"]
 
@@ -26,7 +25,8 @@ def build(verbose: bool = False) -> str:
     off for all device code."""
     lib = FLAGS + ["-fPIC", "-shared", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
     sources = [os.path.join(CSRC, s) for s in SOURCES]
-    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    import torch   # its version, its headers and its C++ ABI; no GPU is looked for
+    torch_dir = os.path.dirname(torch.__file__)
     jobs = [
         lib + sources + ["-o", LIB],
         # the same library without patience, for the tests: whatever waits for another workgroup gives up at once
@@ -36,7 +36,8 @@ def build(verbose: bool = False) -> str:
         # the read-only streaming probe bench.py puts next to the attention kernel (measurement aid, its own library)
         FLAGS + ["-fPIC", "-shared", os.path.join(CSRC, "read_probe.hip"), "-o", PROBE],
         # the Python extension that makes the shortest calls (host code only; torch is loaded before it)
-        ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(torch_dir, "include"),
+        ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+         '-DLOTTS_TORCH="%s"' % torch.__version__, "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(torch_dir, "include"),
          "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-L" + os.path.join(torch_dir, "lib"), "-ltorch_python",
          "-ltorch_cpu", "-lc10", "-o", CALLS],
     ]

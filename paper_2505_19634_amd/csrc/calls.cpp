@@ -265,5 +265,9 @@ PyMODINIT_FUNC PyInit__calls(void) {
         Py_DECREF(m);
         return nullptr;
     }
+    if (PyModule_AddStringConstant(m, "built_for_torch", LOTTS_TORCH) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
     return m;
 }

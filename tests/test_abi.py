@@ -240,3 +240,15 @@ def test_an_unbuilt_tree_says_so(tmp_path, built):
     res = subprocess.run([sys.executable, "-c", "import paper_2505_19634_amd"], cwd=tmp_path, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
                          text=True, timeout=300, env={**os.environ, "PYTHONPATH": str(tmp_path)})
     assert res.returncode != 0 and "is not built: run paper_2505_19634_amd/build.py" in res.stdout, res.stdout
+
+
+def test_the_extension_is_for_this_interpreter_and_this_torch(lib, monkeypatch):
+    """It is C++ on torch's and Python's insides: named by the interpreter, refused under another torch than it was built for."""
+    import sysconfig
+    import torch
+    from paper_2505_19634_amd import binding
+    assert os.path.exists(os.path.join(ROOT, "paper_2505_19634_amd", "_calls" + sysconfig.get_config_var("EXT_SUFFIX")))
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(torch, "__version__", "0.0.1")
+    with pytest.raises(ImportError, match="built for torch .*, this is 0.0.1: run paper_2505_19634_amd/build.py"):
+        binding.load()
