@@ -1,5 +1,6 @@
 """Thin Python binding of liblotts.so: argument marshalling only.  The calls that are shorter on the GPU than in Python
-(verify_attention, spec_accept, majority_vote, skinny_gemm) go through the extension _calls, the others through ctypes.
+(verify_attention, verify_attention_noalloc, spec_accept, majority_vote, skinny_gemm) go through the extension _calls, the others
+through ctypes.
 
 torch supplies device memory and the current stream; every step of the verify path runs in
 the library's HIP kernels.  There is no fallback: if the library is missing the import fails.
@@ -105,7 +106,7 @@ def load() -> ctypes.CDLL:
         lib.confidence_vote.argtypes = [i32, i32, i32, vp, vp, vp, i32, i32, vp, vp, vp]
         lib.calls = _calls.Calls(*(ctypes.cast(f, vp).value for f in (
             lib.verify_attention_workspace_bytes, lib.verify_attention, lib.spec_accept_workspace_bytes, lib.spec_accept,
-            lib.majority_vote, lib.skinny_gemm_workspace_bytes, lib.skinny_gemm)))
+            lib.majority_vote, lib.skinny_gemm_workspace_bytes, lib.skinny_gemm, lib.verify_attention_noalloc)))
         _lib = lib
     return _lib
 
@@ -132,7 +133,7 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 _workspaces: Dict[Tuple[str, int, int], torch.Tensor] = {}
 _retired = []   # grown-out workspaces: kept alive, a kernel enqueued earlier may still be using them
 
-# What depends on sizes, strides and types alone -- a checked descriptor, a workspace size -- keyed by those values; bounded.
+# Workspace sizes, keyed by the sizes that they depend on; bounded.
 _sized: Dict[tuple, object] = {}
 _SIZED_MAX = 4096
 
@@ -197,25 +198,6 @@ def make_attn_desc(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Kpriv: torch.T
     return d
 
 
-def _attn_call(lib, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, out, scale):
-    """(pointer to the descriptor, workspace bytes, Kpre, Vpre) of a call, checked: everything that the checks and the
-    descriptor look at is in the key, so a call of sizes, strides and types seen before is only looked up."""
-    if Kpre is not None and Kpre.shape[1] == 0:
-        Kpre, Vpre = None, None
-    scale = float(scale)
-    key = (Q.shape, Q.stride(), Q.dtype, Kpriv.shape, Kpriv.stride(), Vpriv.stride(), out.stride(), priv_len.dtype, scale,
-           None if Kpre is None else (Kpre.shape, Kpre.stride(), Vpre.stride()))
-    hit = _sized.get(key)
-    if hit is None:
-        if Vpriv.stride() != Kpriv.stride() or (Kpre is not None and Vpre.stride() != Kpre.stride()):
-            raise ValueError("K and V of a segment must share strides")
-        if priv_len.dtype != torch.int32:
-            raise TypeError("priv_len must be int32")
-        desc = ctypes.pointer(make_attn_desc(Q, Kpre, Kpriv, out, scale))   # read only from here on, also by other threads
-        hit = _remember(key, (desc, lib.verify_attention_workspace_bytes(desc)))
-    return hit[0], hit[1], Kpre, Vpre
-
-
 def verify_attention(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Vpre: Optional[torch.Tensor],
                      Kpriv: torch.Tensor, Vpriv: torch.Tensor, priv_len: torch.Tensor, *, scale: float = 0.0,
                      out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None,
@@ -249,9 +231,7 @@ def verify_attention_noalloc(Q: torch.Tensor, Kpre: Optional[torch.Tensor], Vpre
     lib = load()
     if not Q.is_cuda:
         raise ValueError("verify_attention_noalloc runs on the GPU only")
-    desc, _, Kpre, Vpre = _attn_call(lib, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, out, scale)
-    rc = lib.verify_attention_noalloc(desc, Q.data_ptr(), _ptr(Kpre), _ptr(Vpre), Kpriv.data_ptr(), Vpriv.data_ptr(),
-                                      priv_len.data_ptr(), out.data_ptr(), _ptr(lse), _stream_handle(stream))
+    rc = lib.calls.verify_attention_noalloc(Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, scale, out, lse, _stream_handle(stream))
     if rc != 0:
         raise LottsError(rc, "verify_attention_noalloc")
     return out
@@ -327,6 +307,9 @@ def spec_accept_logits(target_logits: torch.Tensor, draft_logits: Optional[torch
         accept_len = torch.empty((B,), dtype=torch.int32, device=u.device)
     if next_token is None:
         next_token = torch.empty((B,), dtype=torch.int32, device=u.device)
+    for t in (accept_len, next_token):
+        if t.dtype != torch.int32 or t.numel() < B or not t.is_contiguous():
+            raise TypeError("accept_len and next_token must be contiguous int32 [B]")
     if priv_len is not None and (priv_len.dtype != torch.int32 or tuple(priv_len.shape) != (B,) or
                                  not priv_len.is_contiguous() or priv_len.device != u.device):
         raise TypeError("priv_len must be a contiguous int32 [B] tensor on the same GPU")
