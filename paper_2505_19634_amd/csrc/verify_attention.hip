@@ -579,7 +579,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     constexpr int OSTRIDE = D + 4;         // floats per row of a wavefront's merge buffer
     constexpr int OBUF = kRowTile * OSTRIDE * 4;
     static_assert(OBUF <= SLAB, "the merge buffer reuses the wavefront's slab");
-    static_assert(kRowTile * NQT * KSTRIDE <= kAttnWaves * GROUPS * SLAB, "Q passes through the slabs");
+    static_assert(kRowTile * NQT * KSTRIDE <= kAttnWaves * GROUPS * SLAB, "Q may pass through the slabs");
     __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnWaves * GROUPS * SLAB];
     __shared__ float2 sh_ml[ONE ? RUNS * NQT : 1][kRowTile];  // ONE: (maximum, sum) of the rows of a tile
     __shared__ float sh_m[kAttnWaves * GROUPS][kRowTile];
@@ -692,11 +692,12 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     };
     // ---- Q fragments (B operand of S^T = K Q^T: lane = query row ln, 8 contiguous d) ----
     // Straight from memory they are 32-byte pieces of 32 rows an instruction, and come again for every wavefront: with two row
-    // tiles as many bytes as the item's keys and values.  Two row tiles: the whole workgroup requests the rows once, 16
-    // bytes a thread, and they pass through LDS further down (8 x 2 heads x 2560 tokens, 40 rows, 13.7 -> 13.1 us; with one
-    // row tile the passage costs more than it saves, 1 x 2 x 8192 9.4 -> 9.7).  Rows beyond the item's carry its first row again:
-    // nothing of theirs is ever stored.
-    constexpr bool QLDS = NQT > 1;
+    // tiles at D = 128 as many bytes as the item's keys and values.  There the whole workgroup requests the rows once, 16
+    // bytes a thread, and they pass through LDS further down (8 x 2 heads x 2560 tokens, 40 rows, 13.7 -> 13.1 us).  Elsewhere the
+    // passage, a barrier behind the Q rows in front of the first scores, costs more than it saves: one row tile, 1 x 2 x 8192 9.4 -> 9.7;
+    // D = 64 with half the bytes, 4 x 8 x 5643, 36 rows, 16.3 -> 16.9, 7 x 8 x 1828, 40 rows, 12.5 -> 13.1, 22 of 23 sizes 1 .. 6 %.  Rows
+    // beyond the item's carry its first row again: nothing of theirs is ever stored.
+    constexpr bool QLDS = NQT > 1 && D == 128;
     constexpr int QLD = kRowTile * NQT * LPR / (kAttnThreads * GROUPS);  // loads per thread
     u32x4 qst[QLD];
     bf16x8 qf[TW][KS];
@@ -771,7 +772,9 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 qf[t][s] = *reinterpret_cast<const bf16x8*>(lds + ((grp * TW + t) * kRowTile + ln) * KSTRIDE + (2 * s + hh) * 16);
-        if (!ONE && GROUPS > 1 && tid < kAttnWaves) sh_pair[tid] = 0;
+    }
+    if (GROUPS > 1) {  // Q has been read from the slabs; the two wavefronts of a pair count their half tiles from here
+        if (!ONE && tid < kAttnWaves) sh_pair[tid] = 0;
         __syncthreads();
     }
 
