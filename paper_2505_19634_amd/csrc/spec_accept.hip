@@ -6,7 +6,7 @@
 //       Every workgroup re-derives the branch's accepted length n from the 2k gathered probabilities; its
 //       wavefronts turn its sub-chunks of the row to be sampled (residual max(0, p_n - q_n), or p_k)
 //       into 2^-40 fixed-point weights -- all of the sub-chunk's loads are requested before the first
-//       is used -- and publishes the sub-chunk's integer sum as two 8-byte words, each carrying half
+//       is used -- and publish the sub-chunk's integer sum as two 8-byte words, each carrying half
 //       of it and this call's 32-bit tag.  The workgroup of a branch's LAST
 //       slice then collects the branch's sums (those that stay out for long it forms itself), locates the sub-chunk
 //       and the token where the integer CDF crosses T = floor(m * Z / 2^24), re-reading that one
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_pick_kernel(int B, int k, 
 // ---------------------------------------------------------------------------------------------
 // single-launch path
 // ---------------------------------------------------------------------------------------------
-constexpr int kFuMaxSub = 64;        // sub-chunks per branch (one wavefront each): one wavefront scans their sums
+constexpr int kFuMaxSub = 64;        // sub-chunks per branch: one wavefront scans their sums
 constexpr int kFuMaxIter = 16;       // 16-byte loads per row and lane: sub-chunks of at most 4096 tokens
 constexpr int kFuMaxV = kFuMaxSub * kFuMaxIter * 256;
 
@@ -294,10 +294,13 @@ static inline FusedPlan plan_fused(int B, int V) {
     pl.nsub = (V + pl.wlen - 1) / pl.wlen;
     // Few branches: a unit takes in about 50 KB a microsecond, and with a wavefront to a sub-chunk most units have none (8 branches
     // x 152k tokens are 120 workgroups of up to 80 KB); so wavefronts share sub-chunks while there are at most two workgroups to a
-    // unit.  Kernels in a captured graph, parts 1 -> 2 or 4: 8 x 151936 6.8 -> 5.7 us, 1 x 151936 6.6 -> 5.5, 16 x 152064 7.1 -> 6.2, 3 x
-    // 256000 7.9 -> 6.0, 16 x 40000 5.1 -> 4.9; up to one workgroup a unit only, 16 x 152064 stays at 7.0.
+    // unit, one where a sub-chunk is one or two groups of 256 tokens (16 x 32768 tokens 4.8 us, with two 4.9).  Kernels in a captured
+    // graph, parts 1 -> 2 or 4: 8 x 151936 6.8 -> 5.7 us, 1 x 151936 6.6 -> 5.5, 16 x 152064 7.1 -> 6.2, 3 x 256000 7.9 -> 6.0, 16 x 40000
+    // 5.1 -> 4.9; up to one workgroup a unit only, 16 x 152064 stays at 7.0.  Not where one workgroup holds the whole row: nobody has
+    // anything to exchange then (1 x 1000 4.0 us, shared 4.2; 128 x 1000 4.4 and 4.7).
     pl.parts = 1;
-    while (pl.parts < kAccWaves && (long long)B * ((pl.nsub * pl.parts * 2 + kAccWaves - 1) / kAccWaves) <= 2 * kNumCU) pl.parts *= 2;
+    const int units = pl.iters <= 2 ? kNumCU : 2 * kNumCU;
+    while (pl.nsub > kAccWaves && pl.parts < kAccWaves && (long long)B * ((pl.nsub * pl.parts * 2 + kAccWaves - 1) / kAccWaves) <= units) pl.parts *= 2;
     pl.S = (pl.nsub * pl.parts + kAccWaves - 1) / kAccWaves;
     return pl;
 }
@@ -408,7 +411,7 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     const float* qrow = has_q ? q + ((size_t)b * k + n) * V : prow;
     const int sub = (s * kAccWaves + wave) / PARTS;  // this wavefront's sub-chunk of the row
     const int part = wave % PARTS;                   // and the part of it: every PARTS-th of its groups of 256 tokens
-    constexpr int PIT = MAXIT / PARTS;
+    constexpr int PIT = (MAXIT + PARTS - 1) / PARTS;
     // a wavefront's sum of the weights of a part of a sub-chunk, in its last lane
     auto part_sum = [&](int sub, int part) {
         const int lo = sub * pl.wlen;
@@ -543,16 +546,25 @@ __global__ __launch_bounds__(kAccThreads) void accept_fused_kernel(int B, int k,
     // inside the sub-chunk: thread t owns pl.iters consecutive tokens (served by the caches: just streamed)
     const int lo2 = c * pl.wlen + tid * pl.iters;
     float pw[MAXIT], qw[MAXIT];
+    if constexpr (MAXIT < 4) {
 #pragma unroll
-    for (int g = 0; g < MAXIT; g += 4) {  // 16 bytes at a time: one by one the loads were 0.4 us more
-        const bool in = g < pl.iters && lo2 + g < V;
-        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 pg = in ? load_row4(prow, lo2 + g, V) : zero, qg = in && has_q ? load_row4(qrow, lo2 + g, V) : zero;
-        const float pe[4] = {pg.x, pg.y, pg.z, pg.w}, qe[4] = {qg.x, qg.y, qg.z, qg.w};
+        for (int i = 0; i < MAXIT; ++i) {
+            const bool in = i < pl.iters && lo2 + i < V;
+            pw[i] = in ? prow[lo2 + i] : 0.f;
+            qw[i] = in && has_q ? qrow[lo2 + i] : 0.f;
+        }
+    } else {  // 16 bytes at a time: one by one the loads were 0.4 us more (with one or two of them, 0.1 .. 0.2 us less)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {  // (the next thread's tokens weigh nothing here)
-            pw[g + e] = g + e < pl.iters ? pe[e] : 0.f;
-            qw[g + e] = g + e < pl.iters ? qe[e] : 0.f;
+        for (int g = 0; g < MAXIT; g += 4) {
+            const bool in = g < pl.iters && lo2 + g < V;
+            const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 pg = in ? load_row4(prow, lo2 + g, V) : zero, qg = in && has_q ? load_row4(qrow, lo2 + g, V) : zero;
+            const float pe[4] = {pg.x, pg.y, pg.z, pg.w}, qe[4] = {qg.x, qg.y, qg.z, qg.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {  // (the next thread's tokens weigh nothing here)
+                pw[g + e] = g + e < pl.iters ? pe[e] : 0.f;
+                qw[g + e] = g + e < pl.iters ? qe[e] : 0.f;
+            }
         }
     }
     unsigned long long w[MAXIT], local = 0;
@@ -614,7 +626,9 @@ extern "C" int spec_accept(int32_t B, int32_t k, int32_t V, const float* p, cons
             LOTTS_LAUNCH(kernel, fgrid, dim3(kAccThreads), s, B, k, V, fp, tag, p, q, draft, u, accept_len, next_token, sums);
         };
         auto with_parts = [&](auto one, auto two, auto four) { fp.parts == 1 ? fused(one) : fp.parts == 2 ? fused(two) : fused(four); };
-        if (fp.iters <= 4) with_parts(accept_fused_kernel<4, 1>, accept_fused_kernel<4, 2>, accept_fused_kernel<4, 4>);
+        // (two: rows of up to 32768 tokens; in the form for four, 128 x 16384 are 8.1 us instead of 6.8, 128 x 1000 4.4 instead of 4.0)
+        if (fp.iters <= 2) with_parts(accept_fused_kernel<2, 1>, accept_fused_kernel<2, 2>, accept_fused_kernel<2, 4>);
+        else if (fp.iters <= 4) with_parts(accept_fused_kernel<4, 1>, accept_fused_kernel<4, 2>, accept_fused_kernel<4, 4>);
         else if (fp.iters <= 8) with_parts(accept_fused_kernel<8, 1>, accept_fused_kernel<8, 2>, accept_fused_kernel<8, 4>);
         else if (fp.iters <= 12) with_parts(accept_fused_kernel<12, 1>, accept_fused_kernel<12, 2>, accept_fused_kernel<12, 4>);
         else with_parts(accept_fused_kernel<16, 1>, accept_fused_kernel<16, 2>, accept_fused_kernel<16, 4>);

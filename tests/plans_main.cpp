@@ -1,4 +1,4 @@
-// The launch plans of the library, answered on the host: a line "gemm M N K", "logits B k V" or "attention B k Hq Hkv D P Lmax" in, the
+// The launch plans of the library, answered on the host: a line "gemm M N K", "accept B V", "logits B k V" or "attention B k Hq Hkv D P Lmax" in, the
 // plan's numbers out.  Host code only; nothing here launches, so the few runtime calls that the sources make have empty bodies.
 #ifdef PLANS_RUNTIME
 extern "C" {
@@ -9,6 +9,7 @@ void __hipUnregisterFatBinary() {}
 }
 #else
 #include "skinny_gemm.hip"
+#include "spec_accept.hip"
 #include "spec_accept_logits.hip"
 #include "verify_attention.hip"
 #include <cstdio>
@@ -23,6 +24,11 @@ int main() {
             const lotts::GemmPlan p = lotts::plan_gemm(M, N, K);
             static const char* const forms[] = {"stream256", "stream128", "stream64", "direct"};
             printf("form %s rn %d tt %d nby %d ksplit %d\n", forms[p.form], p.rn, p.tt, p.nby, p.ksplit);
+        } else if (!strcmp(kind, "accept")) {
+            int B, V;
+            if (scanf("%d %d", &B, &V) != 2) return 1;
+            const lotts::FusedPlan p = lotts::plan_fused(B, V);
+            printf("groups %d subs %d parts %d\n", p.iters, p.nsub, p.parts);
         } else if (!strcmp(kind, "logits")) {
             int B, k, V;
             if (scanf("%d %d %d", &B, &k, &V) != 3) return 1;

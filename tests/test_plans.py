@@ -9,3 +9,11 @@ def test_gemm_forms_on_either_side_of_the_line():
     direct = [(1, 2560, 2048), (40, 2560, 2048), (192, 2560, 2048), (192, 2048, 2048), (34, 1408, 1152), (66, 2176, 1408), (108, 1024, 2176)]
     plans = ask(["gemm %d %d %d" % s for s in streamed + direct])
     assert [p["form"] == "direct" for p in plans] == [False] * len(streamed) + [True] * len(direct), plans
+
+
+def test_short_sub_chunks_of_the_acceptance():
+    from test_gpu_accept_parts import SHORT
+    for (groups, parts, B, V), plan in zip(SHORT, ask(["accept %d %d" % c[2:] for c in SHORT])):
+        assert (plan["groups"], plan["parts"]) == (groups, parts), (B, V, plan)
+    # a row that one workgroup holds is not shared: there would be sums to exchange
+    assert all(p["parts"] == 1 for p in ask(["accept %d %d" % (B, V) for B in (1, 4, 128) for V in (1, 257, 1000, 1024)]))
