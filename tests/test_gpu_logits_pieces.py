@@ -9,8 +9,9 @@ from test_gpu_parity import logit_inputs
 
 pytestmark = pytest.mark.gpu
 
-# pieces of 4, 5, 6 and 8 x 2048 logits, by the sizes
-CASES = [(4, 8, 3, 16385), (4, 1, 0, 8193), (5, 5, 4, 40961), (5, 5, 4, 51200), (6, 7, 4, 49152), (6, 17, 3, 24576), (8, 2, 1, 600001)]
+# pieces of 4, 5, 6 and 8 x 2048 logits, by the sizes (checked on the host, test_plans.py)
+CASES = [(4, 8, 3, 16385), (4, 1, 0, 8193), (5, 5, 4, 40961), (5, 5, 4, 51200), (6, 7, 4, 49152), (6, 17, 3, 24576), (5, 2, 1, 600001),
+         (8, 2, 1, 786433), (8, 1, 0, 1048575)]
 
 
 @pytest.mark.parametrize("loads,B,k,V", CASES, ids=lambda x: str(x))

@@ -31,9 +31,12 @@ def lotts():
     assert m.load() is usual and binding._workspaces is workspaces
 
 
+LOGITS = [(3, 2, 1), (4, 3, 8193), (5, 0, 50257), (1, 8, 16385), (16, 3, 152064), (2, 1, 524288), (2, 1, 600001),
+          (1, 256, 9000), (1, 40, 152064), (2, 100, 60001), (2, 1, 786433)]   # pieces of every size
+
+
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("B,k,V", [(3, 2, 1), (4, 3, 8193), (5, 0, 50257), (1, 8, 16385), (16, 3, 152064), (2, 1, 524288), (2, 1, 600001),
-                                   (1, 256, 9000), (1, 40, 152064), (2, 100, 60001)])
+@pytest.mark.parametrize("B,k,V", LOGITS)
 def test_logits(lotts, oracle, B, k, V, bf16):
     cfg = S.CONFIGS["C1"].with_(B=B, V=V, k=k)
     print("logits without patience", cfg, bf16, flush=True)

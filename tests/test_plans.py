@@ -17,3 +17,11 @@ def test_short_sub_chunks_of_the_acceptance():
         assert (plan["groups"], plan["parts"]) == (groups, parts), (B, V, plan)
     # a row that one workgroup holds is not shared: there would be sums to exchange
     assert all(p["parts"] == 1 for p in ask(["accept %d %d" % (B, V) for B in (1, 4, 128) for V in (1, 257, 1000, 1024)]))
+
+
+def test_logits_lists_reach_every_size_of_piece():
+    from test_gpu_logits_pieces import CASES
+    from test_gpu_no_patience import LOGITS
+    for case, p in zip(CASES, ask(["logits %d %d %d" % c[1:] for c in CASES])):
+        assert p["loads"] == case[0], (case, p)
+    assert {p["loads"] for p in ask(["logits %d %d %d" % c for c in LOGITS])} == {4, 5, 6, 8}
