@@ -19,6 +19,22 @@ def test_short_sub_chunks_of_the_acceptance():
     assert all(p["parts"] == 1 for p in ask(["accept %d %d" % (B, V) for B in (1, 4, 128) for V in (1, 257, 1000, 1024)]))
 
 
+def attention(cfg):
+    return "attention %d %d %d %d %d %d %d" % (cfg.B, cfg.k, cfg.Hq, cfg.Hkv, cfg.D, cfg.P, cfg.L)
+
+
+def test_attention_lists_reach_the_one_tile_form_and_its_merges():
+    from test_gpu_attention_items import ONE_TILE, ONE_TILE_MERGES, SEVERAL_TILES, TWO_ROW_TILES_D64
+    plans = ask([attention(c) for c in ONE_TILE])
+    for cfg, p in zip(ONE_TILE, plans):
+        assert p["one"] == 1, (cfg, p)
+    for nqt, merges in ONE_TILE_MERGES.items():
+        assert {p["merge"] for p in plans if p["nqt"] == nqt} == merges, nqt
+    assert any(p["fold"] for p in plans if p["merge"] == 4) and any(p["prefix_shares"] for p in plans if p["merge"] == 0)
+    assert all(p["one"] == 0 for p in ask([attention(c) for c in SEVERAL_TILES]))
+    assert all(p["nqt"] == 2 for p in ask([attention(c) for c in TWO_ROW_TILES_D64]))
+
+
 def test_logits_lists_reach_every_size_of_piece():
     from test_gpu_logits_pieces import CASES
     from test_gpu_no_patience import LOGITS
