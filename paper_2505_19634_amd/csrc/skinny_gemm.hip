@@ -116,9 +116,11 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl, double* fill
 //     sizes (1536 .. 14336 rows, K 512 .. 4096, 1 .. 192 tokens) with tiles full of tokens, where the choice costs 0.4 % over the better
 //     form: 2560 x 2048 at 1 / 40 / 192 tokens 5.1 / 7.6 / 13.4 us against 7.9 / 9.2 / 15.0; 4736 x 1280 at 24 tokens 12.4 against 9.7; 6144
 //     x 4096 at 2 tokens 17.7 against 13.2.  Even shares are fewer KB, but not all of what is counted less is time saved: where only they
-//     put the direct form ahead, 0.034 us per KB + 0.15 us per MB of W have to stay below 6.5 us + 10e-6 us per token and (N + K),
-//     fitted to 492 such sizes: always direct is 5.3 % over the better form there (3968 x 2176 at 168 tokens 20.0 us, streamed
-//     17.3), never direct 2.5 % (2176 x 1408 at 66 tokens 8.7 us, streamed 10.1), so 0.4 %, as on 270 sizes beside them.
+//     put the direct form ahead, 0.034 us per KB + 0.15 us per MB of W have to stay below 6.7 us (6.3 with 64 weight rows to a
+//     workgroup) + 10e-6 us per token and (N + K), fitted to 492 such sizes: always direct is 5.3 % over the better form there (3968 x
+//     2176 at 168 tokens 20.0 us, streamed 17.3), never direct 2.5 % (2176 x 1408 at 66 tokens 8.7 us, streamed 10.1), so 0.2 %, and 0.2 ..
+//     0.5 % on 430 sizes beside them.  (Calls that are not captured have one launch less to make by it, too: 3328 x 1536 and 1536 x 3072
+//     at 36 tokens, level in a graph.)
 //     With more rows only the tile of 64 rows is left, four wavefronts with many small batches: 11904 x 1280 at 48 tokens 16.5 us
 //     against 13.2.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1 token 19.8 us against 13.8.
 //   256-row stream form: more than 256 blocks of 128 rows; an X chunk in LDS serves the most rows.  55296 x 5120 at 64
@@ -138,7 +140,7 @@ static inline GemmPlan plan_gemm(int M, int N, int K, bool may_be_direct = true)
         double filled;
         const double kb = plan_direct(M, N, K, &pl, &filled), mb = 2e-6 * N * K, tokens = 1e-6 * M * (N + K);
         auto ahead = [&](double k) { return 3.4 + 0.022 * k + 0.14 * mb < 7.0 + 0.125 * mb + 7.0 * tokens; };
-        if (kb > 0.0 && (ahead(filled) || (ahead(kb) && 0.034 * kb + 0.15 * mb < 6.5 + 10.0 * tokens))) {
+        if (kb > 0.0 && (ahead(filled) || (ahead(kb) && 0.034 * kb + 0.15 * mb < (pl.rn == 4 ? 6.3 : 6.7) + 10.0 * tokens))) {
             pl.form = kDirect;
             return pl;
         }

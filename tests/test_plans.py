@@ -6,7 +6,7 @@ def test_gemm_forms_on_either_side_of_the_line():
     """Sizes measured in both forms, us.  Counting even shares of the tokens alone, the direct form was taken where it is the slower
     one: 64 weight rows to a workgroup, or X the smaller part of what it takes in."""
     streamed = [(168, 3968, 2176), (36, 8064, 1536), (100, 4352, 1792), (46, 3968, 1920), (184, 3072, 1920), (255, 2688, 2688)]
-    direct = [(1, 2560, 2048), (40, 2560, 2048), (192, 2560, 2048), (192, 2048, 2048), (34, 1408, 1152), (66, 2176, 1408), (108, 1024, 2176)]
+    direct = [(1, 2560, 2048), (40, 2560, 2048), (192, 2560, 2048), (192, 2048, 2048), (34, 1408, 1152), (66, 2176, 1408), (108, 1024, 2176), (36, 3328, 1536)]
     plans = ask(["gemm %d %d %d" % s for s in streamed + direct])
     assert [p["form"] == "direct" for p in plans] == [False] * len(streamed) + [True] * len(direct), plans
 
