@@ -189,7 +189,7 @@ __device__ __forceinline__ unsigned long long lg_peek(const unsigned long long* 
 // Bound by the vector unit: 16 instructions a logit that the integer definition fixes (12 for the weight, the rest unpacking, scaling,
 // maximum and sum), 7 us of the chip's rate for 112 rows x 152064 logits, behind the read that all workgroups start with: a unit returns
 // loads in order, so the words of the exchange wait behind the logits that the unit's other workgroups have asked for (fewer
-// workgroups at a time are no way out: 28.7 us with five to a unit, 30.4 with four, against 27.4).  Whole call, us, as three launches
+// workgroups at a time are no way out: 28.7 us with five to a unit, 30.4 with four, against 27.4).  In a captured graph, us, as three launches
 // (maxima, sums, scan) -> two -> now: 16 x 7 rows x 152064 bf16 30.8 -> 27.5 -> 23.1, fp32 40.5 -> 31.3 -> 27.7; 5 x 15 rows x 50257 fp32
 // (rows off a 16-byte boundary) 48.0 -> 15.7 -> 13.5; 32 x 17 x 151936 bf16 68.3 -> 55.6.
 template <bool BF16, int IT>

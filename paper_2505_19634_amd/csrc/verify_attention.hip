@@ -219,7 +219,8 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
     else if (simple && pl.nslots == 2 && pl.nqt == 1) pl.merge = kMergePair;
     else if (last_arriver) pl.merge = kMergeLast;
     else pl.merge = simple ? kMergeGroups : kMergeLaunch;
-    // rows per merge workgroup: as few as leave at most one workgroup per unit in all
+    // rows per merge workgroup: as few as leave at most one merge workgroup per unit (items are not counted, so with two row tiles,
+    // whose items leave no room for another workgroup, some mergers start when an item ends)
     auto rows_per_merger = [&](int threads) {
         pl.rpm = 1;
         while (pl.rpm * 2 * (d.D / 4) <= threads && (long long)d.B * d.Hkv * ceil_div(GR, pl.rpm) > kNumCU) pl.rpm *= 2;
