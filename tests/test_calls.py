@@ -17,7 +17,12 @@ class Library:
         (ctypes.c_int, [VP] * 10)]
 
     def __init__(self):
-        from paper_2505_19634_amd import binding
+        try:
+            from paper_2505_19634_amd import binding
+        except ImportError:
+            import __graft_entry__
+            __graft_entry__.build()
+            from paper_2505_19634_amd import binding
         self.made, self.answer = [], 0
 
         def query(*args):
