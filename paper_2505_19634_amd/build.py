@@ -10,6 +10,7 @@ ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "liblotts.so")
 LIB_NO_POLLS = os.path.join(_HERE, "liblotts_no_polls.so")
+LIB_FLAT = os.path.join(_HERE, "liblotts_flat.so")
 CALIB = os.path.join(_HERE, "calib_copy")
 PROBE = os.path.join(_HERE, "libread_probe.so")
 CALLS = os.path.join(_HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
@@ -31,6 +32,8 @@ def build(verbose: bool = False) -> str:
         lib + sources + ["-o", LIB],
         # the same library without patience, for the tests: whatever waits for another workgroup gives up at once
         lib + ["-DLOTTS_WAIT_POLLS=0"] + sources + ["-o", LIB_NO_POLLS],
+        # and with attention's flat plan for calls of any length, for the tests
+        lib + ["-DLOTTS_FLAT_STEPS=0"] + sources + ["-o", LIB_FLAT],
         # the counter-calibration copy program (profiling aid, not part of the library)
         FLAGS + [os.path.join(CSRC, "calib_copy.hip"), "-o", CALIB],
         # the read-only streaming probe bench.py puts next to the attention kernel (measurement aid, its own library)

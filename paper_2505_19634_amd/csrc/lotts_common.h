@@ -120,4 +120,19 @@ __device__ __forceinline__ unsigned wave_incl_scan_u32(unsigned v) {
     return dpp_add<0x143, 0xc>(v);  // row_bcast 31: rows 2 and 3 take lane 31
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_max(unsigned v) {
+    return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false));
+}
+// maximum over the wavefront
+__device__ __forceinline__ unsigned wave_max_u31(unsigned v) {
+    v = dpp_max<0x111, 0xf>(v);
+    v = dpp_max<0x112, 0xf>(v);
+    v = dpp_max<0x114, 0xf>(v);
+    v = dpp_max<0x118, 0xf>(v);
+    v = dpp_max<0x142, 0xa>(v);
+    v = dpp_max<0x143, 0xc>(v);
+    return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
 }  // namespace lotts

@@ -35,12 +35,15 @@
 //       each with its own L2 -- inside one launch, so they are written and read with 16-byte
 //       buffer accesses that carry the device-scope cache policy (performed at the memory side of
 //       the L2s); nothing is ever flushed or invalidated cache-wide.
+//       For long calls the shares of a branch follow its length (the "flat" plan, see FlatCuts): every item takes an equal piece of
+//       its KV head's tiles, branch after branch, and starts with the cuts, from all branches' lengths, on the device.
 //   attn_merge_kernel     second launch, where prefix items or several row groups add partials of their own (but for the
 //       smallest batches, where the last arriver merges).
 // fp32 path: attn_f32_kernel, plain fp32 VALU arithmetic, one workgroup per output row; it
 // exists for exactness checks on small fp32 problems.
 // Two entry points share all of this: verify_attention (the caller brings the workspace) and
 // verify_attention_noalloc (arrival cells and partials in a static device array of this file).
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 
@@ -64,6 +67,14 @@ constexpr int kMaxSplit = 64;       // key shares of a segment whose partials ar
 constexpr int kMaxSplitStack = 16;  // the same when prefix items or several row groups add partials of their own
 
 constexpr int kMaxCounters = 16384;  // 64-bit cells at the start of the workspace
+// Flat plan (below): places of a head's sequence that stand for what starting on a branch costs an item (its states meet, its rows go
+// out, Q and a first tile come in: about two tiles of each wavefront; 6 is level, without any 44 x 2 heads x 1310 .. 5243 tokens
+// took 2 % more).
+constexpr int kStartTiles = 8;
+// Flat plan: from this many tiles of each wavefront on (a build of the tests sets 0).
+#ifndef LOTTS_FLAT_STEPS
+#define LOTTS_FLAT_STEPS 17
+#endif
 
 struct AttnPlan {
     int n_pre_items, n_priv_items;
@@ -79,6 +90,10 @@ struct AttnPlan {
     int n_rg_pre;       // row groups per KV head over all branches' stacked rows (stacked plan)
     int one;            // 1: no wavefront of an item gets more than one key tile
     int runs;           // runs of key tiles of an item
+};
+struct AttnPlans : AttnPlan {
+    int flat;     // 0: shares of fixed number; 1: the items deal the tiles by the branches' lengths where those differ; 2: always
+    int workers;  // flat: items per KV head
 };
 constexpr int kMergeLast = 0;    // the last-arriving workgroup of a (KV head, branch), inside the attention launch
 constexpr int kMergeGroups = 1;  // merge workgroups at the end of the attention launch's grid
@@ -110,6 +125,9 @@ struct AttnParams {
     void* O;
     float* lse;
     long long o_stride_b, o_stride_r, o_stride_h;
+    // flat plans only (behind everything else: a call that is not captured reads its arguments from far away, 0.2 us for every line more)
+    int flat, workers;
+    FastDiv d_workers;  // by workers
 };
 
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -117,8 +135,8 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // Launch plan.  Depends on the descriptor only (never on device data), so the workspace query
 // and the launch agree.  The HBM stream runs best with one streaming workgroup per compute
 // unit, so the private caches are cut into just enough key shares to give every CU one item.
-static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
-    AttnPlan pl = {};
+static inline AttnPlans plan_attention(const lotts_attn_desc& d) {
+    AttnPlans pl = {};
     const int GR = (d.Hq / d.Hkv) * (d.k + 1);
     pl.nqt = GR > kRowTile ? 2 : 1;
     const int rows_per_item = kRowTile * pl.nqt;
@@ -246,17 +264,46 @@ static inline AttnPlan plan_attention(const lotts_attn_desc& d) {
         while (pl.rpm * 2 * (d.D / 4) <= kAttnThreads && kAttnThreads / (pl.rpm * 2 * (d.D / 4)) * 4 >= pl.nslots) pl.rpm *= 2;
         pl.mpp = ceil_div(GR, pl.rpm);
     }
+    // Branches of different lengths.  Fixed shares leave the longest branches' items behind: the host does not know the lengths, so the
+    // number of shares cannot follow them.  In the flat plan the items deal a head's tiles among themselves on the device (see FlatCuts),
+    // unless the lengths turn out to be alike, and then the same kernel runs the fixed shares.  Finding that out and being able to do either
+    // costs an item about 0.7 us, so it is for long calls only: from 17 tiles a wavefront on, 26 x 2 heads x 1086 + 2399 .. 9596 tokens 43.2 ->
+    // 39.0 us, 19 x 4 x 1051 + 2722 .. 10890 67.1 -> 59.8, 64 x 2 x 1003 + 1792 .. 7168 65.9 -> 59.0; equal lengths lose 0 .. 2 % (16 x 8 x 572 +
+    // 5318 63.4 -> 64.0, 56 x 2 x 1030 + 5994 73.2 -> 73.0), at D = 64 up to 4 %.  (Of 14 .. 17 tiles a wavefront the different
+    // lengths gain as much, but calls there are short enough for equal ones to lose 1 %.)  At D = 64 with a third more items of whole rows than
+    // units the few units with two of them hold up everybody, whatever the lengths: always dealt (17 x 16 heads x 897 + 4635
+    // tokens 78.5 -> 64.0, 42 x 8 x 390 + 5137 86.8 -> 83.6; with more items than that fixed shares even out).
+    const int units = d.D == 64 && pl.nqt == 1 ? 2 * kNumCU : kNumCU;  // (two items to a unit there)
+    const int workers = units / d.Hkv;
+    const long long farthest = std::max((d.Lmax + 32LL) * d.kpriv_stride_t, (d.P + 32LL) * d.kpre_stride_t) * 2;  // bytes
+    const long long flat_bytes = (long long)d.Hkv * (workers + d.B) * GR * (d.D * 4 + 8) + kMaxCounters * 8 + 512;
+    if (simple && !pl.one && d.B > 1 && d.B <= kWave && workers > 0 && (pl.nsplit_priv == 1 || d.B * pl.nsplit_priv <= workers) &&
+        (long long)d.B * tiles_all >= (long long)LOTTS_FLAT_STEPS * kAttnWaves * workers &&
+        (long long)d.B * (tiles_all + kStartTiles) * workers < (1LL << 31) && farthest < (1LL << 31) && flat_bytes <= (16 << 20)) {
+        pl.flat = d.D == 64 && pl.nqt == 1 && base * pl.nsplit_priv > kNumCU && base * pl.nsplit_priv * 3 <= 4 * kNumCU ? 2 : 1;
+        pl.workers = workers;
+        // Where an item has whole branches of its own, the last arriver merges the few that are cut; where branches have several items each,
+        // merge workgroups (44 x 2 x 1310 .. 5243 40.7 -> 35.0 us, with the last arriver 38.7).
+        pl.merge = kMergeLast;
+        if (workers > d.B) {
+            rows_per_merger(kAttnThreads * pl.nqt);
+            if ((long long)d.Hkv * (workers + 2 * d.B) * pl.mpp <= kMaxCounters) pl.merge = kMergeGroups;
+        }
+    }
     pl.n_merge = pl.merge == kMergeGroups ? d.B * d.Hkv * pl.mpp : 0;
     pl.n_pre_items = d.Hkv * pl.n_rg_pre * pl.nsplit_pre;
-    pl.n_priv_items = d.B * d.Hkv * pl.n_rg_priv * pl.nsplit_priv;
+    pl.n_priv_items = pl.flat ? d.Hkv * std::max(pl.workers, d.B * pl.nsplit_priv) : d.B * d.Hkv * pl.n_rg_priv * pl.nsplit_priv;
     return pl;
 }
 
-static inline size_t part_o_elems(const lotts_attn_desc& d, const AttnPlan& pl) {
-    return (size_t)d.Hkv * d.B * (d.Hq / d.Hkv) * (d.k + 1) * pl.nslots * d.D;
+static inline size_t part_rows(const lotts_attn_desc& d, const AttnPlans& pl) {
+    return (size_t)(d.Hq / d.Hkv) * (d.k + 1) * d.Hkv * (pl.flat ? pl.workers + d.B : d.B * pl.nslots);
 }
-static inline size_t part_ml_elems(const lotts_attn_desc& d, const AttnPlan& pl) {
-    return (size_t)d.Hkv * d.B * (d.Hq / d.Hkv) * (d.k + 1) * pl.nslots * 2;
+static inline size_t part_o_elems(const lotts_attn_desc& d, const AttnPlans& pl) {
+    return part_rows(d, pl) * d.D;
+}
+static inline size_t part_ml_elems(const lotts_attn_desc& d, const AttnPlans& pl) {
+    return part_rows(d, pl) * 2;
 }
 
 // Workspace: [arrival cells][partial O][partial (max, sum)], each part 256-byte aligned.  The
@@ -268,12 +315,12 @@ static inline size_t part_ml_elems(const lotts_attn_desc& d, const AttnPlan& pl)
 // then adds one.  A cell left at zero (a fresh zero-filled buffer, or the reset the last arriver
 // does) and a cell left behind by an earlier call that never completed both start the new call
 // at zero arrivals, so no call can poison the buffer for the next one.  With merge workgroups the same cells are, for
-// every merge workgroup of a (KV head, branch), one flag per key share and one arrival cell.  An item sets its flag of every
+// every merge workgroup of a (KV head, branch), one flag per key share (flat plan: per partial) and one arrival cell.  An item sets its flag of every
 // merge workgroup that reads its partial to (tag << 16) | 1; a merge workgroup that leaves sets its flags to (tag << 16) | 2;
 // whoever merges puts the zeros back.  Any other content counts as not arrived.
 constexpr int kTagShift = 16;            // arrivals per cell < 2^16, checked on the host
 static std::atomic<unsigned long long> g_call_tag{0};
-static inline size_t workspace_layout(const lotts_attn_desc& d, const AttnPlan& pl, size_t* off_o, size_t* off_ml) {
+static inline size_t workspace_layout(const lotts_attn_desc& d, const AttnPlans& pl, size_t* off_o, size_t* off_ml) {
     size_t bytes = (size_t)kMaxCounters * sizeof(unsigned long long);
     if (off_o) *off_o = bytes;
     bytes += part_o_elems(d, pl) * sizeof(float);
@@ -327,6 +374,75 @@ __device__ __forceinline__ void store_merged(const AttnParams& prm, int kvh, int
     *reinterpret_cast<bf16x4*>(op) = ov;
     if (prm.lse && c4 == 0)
         prm.lse[((long long)b * prm.R + r) * prm.Hq + h] = (M + log2f(Lsum)) * 0.69314718055994530942f;
+}
+
+// Where the partials of a (KV head, branch) lie, in rows of partials (D floats, or 8 bytes of (max, sum)), and their number; the cells of
+// its merge workgroups follow the same numbering.
+struct Partials {
+    unsigned first, row_step, step;  // row 0 of the first partial; from row to row; from partial to partial
+    int n;
+    int cell;                        // flat: number of the first partial among all
+};
+
+// Flat plan.  A KV head's tiles -- branch after branch, a branch's folded prefix tiles and then its private ones -- form one sequence,
+// and item i of the head's `workers` takes the i-th of equal pieces of it, whatever the branches' lengths: where a piece ends inside a branch,
+// that branch has a partial from either side; where it covers several branches, the item works on one after the other.  kStartTiles
+// places of the sequence in front of every branch stand for what starting on a branch costs an item.  A partial's number is its item's
+// plus its branch's: strictly rising along the sequence, at most workers + B of them per head.
+struct FlatCuts {
+    unsigned end;    // of branch `lane`, in the head's sequence
+    unsigned total;
+    int len;         // of branch `lane`
+    int workers;     // items with anything to do
+    bool dealt;      // by the lengths; or the fixed number of shares to every branch
+};
+__device__ __forceinline__ FlatCuts flat_cuts(const AttnParams& prm, int fold_tiles, int lane, int L) {
+    FlatCuts c;
+    L = L < prm.R ? prm.R : (L > prm.Lmax ? prm.Lmax : L);
+    c.len = L;
+    const int tiles = fold_tiles + (L - 1) / kTile + 1;
+    c.end = wave_incl_scan_u32(lane < prm.B ? kStartTiles + tiles : 0);
+    c.total = __builtin_amdgcn_readlane(c.end, kWave - 1);
+    c.workers = min(prm.workers, (int)c.total);  // (at least one place each)
+    // Steps (a tile for every wavefront of an item) of a branch's fixed shares, and how long they take, in steps of a full chip: all
+    // items together are bound by the memory, whose rate they share, until so few are left that each is bound by what a unit takes in,
+    // about twice as much.  At whatever length L that happens, sum of min(steps, L) / items + (longest - L) / 2 is no
+    // more than the whole time.
+    const int steps = lane < prm.B ? quot(tiles - 1, prm.d_wpriv) + 1 : 0;
+    const int longest = wave_max_u31(steps);
+    auto until = [&](int L) {  // (in half steps of all the head's items)
+        const int sum = __builtin_amdgcn_readlane(wave_incl_scan_u32(min(steps, L)), kWave - 1);
+        return 2 * sum * prm.plan.nsplit_priv + (longest - L) * prm.workers;
+    };
+    const int fixed = max(max(until(longest), until(longest * 3 / 4)), max(until(longest / 2), longest * prm.workers));
+    c.dealt = prm.flat > 1 || fixed * kAttnWaves > (int)(2 * c.total) + 2 * kAttnWaves * prm.workers;
+    return c;
+}
+__device__ __forceinline__ unsigned flat_cut(const AttnParams& prm, const FlatCuts& c, int i) {
+    return c.workers == prm.workers ? quot(i * c.total, prm.d_workers) : i * c.total / c.workers;
+}
+// the item that has place `at`: the last one whose piece starts at or before it
+__device__ __forceinline__ int flat_worker(const FlatCuts& c, unsigned at) { return ((at + 1) * c.workers - 1) / c.total; }
+// a branch's tiles are places first .. last of the sequence
+__device__ __forceinline__ void flat_branch(const FlatCuts& c, int b, unsigned* first, unsigned* last) {
+    *first = (b > 0 ? __builtin_amdgcn_readlane(c.end, b - 1) : 0) + kStartTiles;
+    *last = __builtin_amdgcn_readlane(c.end, b) - 1;
+}
+__device__ __forceinline__ Partials flat_partials(const AttnParams& prm, const FlatCuts& c, int kvh, int b) {
+    int number = b * prm.plan.nsplit_priv, n = prm.plan.nsplit_priv;
+    if (c.dealt) {
+        unsigned first, last;
+        flat_branch(c, b, &first, &last);
+        const int w0 = flat_worker(c, first);
+        n = flat_worker(c, last) - w0 + 1;
+        number = w0 + b;
+    }
+    number += kvh * (prm.workers + prm.B);
+    return {(unsigned)number * prm.GR, 1u, (unsigned)prm.GR, n, number};
+}
+__device__ __forceinline__ Partials fixed_partials(const AttnParams& prm, int kvh, int b) {
+    const unsigned n = prm.plan.nslots;
+    return {((unsigned)kvh * prm.B + b) * prm.GR * n, n, 1u, (int)n, 0};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -405,19 +521,19 @@ __device__ __forceinline__ void merge_branch(const AttnParams& prm, __amdgpu_buf
 // says whether the result is stored (see merger_stays).
 // ---------------------------------------------------------------------------------------------
 template <int D, bool DEV, int THREADS, typename Wait>
-__device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char* lds, int kvh, int b, int chunk, Wait wait) {
+__device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char* lds, int kvh, int b, int chunk, const Partials& parts, Wait wait) {
     constexpr int F4 = D / 4, CH = 8;
     const AttnPlan& pl = prm.plan;
     const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
-    const int tid = threadIdx.x, ns = pl.nslots, rpm = pl.rpm;
+    const int tid = threadIdx.x, ns = parts.n, rpm = pl.rpm;
     const int rshift = __builtin_ctz(rpm);
     const int c4 = tid % F4, r = (tid / F4) & (rpm - 1), sg = (tid / F4) >> rshift, SG = (THREADS / F4) >> rshift;
     const int row = chunk * rpm + r;
     float M = -INFINITY, Lsum = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    const unsigned first_slot = ((unsigned)kvh * prm.B * prm.GR + (unsigned)b * prm.GR + row) * ns + sg;
+    const unsigned first_slot = parts.first + row * parts.row_step + sg * parts.step;
     unsigned at_o = prm.off_o + (first_slot * D + c4 * 4) * 4u, at_ml = prm.off_ml + first_slot * 8u;
-    const unsigned step_o = SG * D * 4u, step_ml = SG * 8u;
+    const unsigned step_o = SG * parts.step * D * 4u, step_ml = SG * parts.step * 8u;
     int mine = row < prm.GR ? ns - sg : 0;  // slots from the own first one on
     asm volatile("" : "+v"(at_o), "+v"(at_ml), "+v"(mine) : "s"(step_o), "s"(step_ml));  // computed before the wait
     const bool keep = wait();
@@ -495,12 +611,16 @@ __device__ __forceinline__ void merge_rows(const AttnParams& prm, unsigned char*
     if (row < prm.GR && keep) store_merged(prm, kvh, b, row, c4, o, M, Lsum);
 }
 
-// Cells of a merge workgroup: a flag per key share, and, behind all flags, the count that is used once it has left.
-__device__ __forceinline__ unsigned long long* merger_flags(const AttnParams& prm, int kvh, int b, int chunk) {
-    return prm.counters + ((kvh * prm.B + b) * prm.plan.mpp + chunk) * prm.plan.nslots;
+// Cells of a merge workgroup: a flag per partial, and, behind all flags, the count that is used once it has left.
+template <bool FLAT>
+__device__ __forceinline__ unsigned long long* merger_flag(const AttnParams& prm, const Partials& parts, int kvh, int b, int chunk, int slot) {
+    const int mpp = prm.plan.mpp;
+    return prm.counters + (FLAT ? (parts.cell + slot) * mpp + chunk : ((kvh * prm.B + b) * mpp + chunk) * parts.n + slot);
 }
+template <bool FLAT>
 __device__ __forceinline__ unsigned long long* merger_count(const AttnParams& prm, int kvh, int b, int chunk) {
-    return prm.counters + prm.plan.n_merge * prm.plan.nslots + (kvh * prm.B + b) * prm.plan.mpp + chunk;
+    const int flags = FLAT ? prm.Hkv * (prm.workers + prm.B) * prm.plan.mpp : prm.plan.n_merge * prm.plan.nslots;
+    return prm.counters + flags + (kvh * prm.B + b) * prm.plan.mpp + chunk;
 }
 // whoever merges takes the cells down: a captured launch is replayed with the same tag
 __device__ __forceinline__ void cell_clear(unsigned long long* cell) {
@@ -508,37 +628,47 @@ __device__ __forceinline__ void cell_clear(unsigned long long* cell) {
 }
 // Counts n partials of a merge workgroup that has left; true for whoever counts the last one.  (Raised to this call's tag first, as
 // the arrival cells are.)
-__device__ __forceinline__ bool count_partials(const AttnParams& prm, unsigned long long* count, int n) {
+__device__ __forceinline__ bool count_partials(const AttnParams& prm, const Partials& parts, unsigned long long* count, int n) {
     atomicMax(count, prm.tag);
-    return atomicAdd(count, (unsigned long long)n) + n == prm.tag + prm.plan.nslots;
+    return atomicAdd(count, (unsigned long long)n) + n == prm.tag + parts.n;
 }
 // A merge workgroup: all its flags have come (true), or it leaves and takes its marks with it: it exchanges every flag for one, and
 // so does every item that raises a flag, so each side knows from what it finds there which of the two came first.  The
 // partials that were there it counts, the others are counted by the items that find a mark; who counts the last one merges.
 // The answer is in LDS, so that the first loads of the merge need not wait for it.
-__device__ __forceinline__ bool merger_stays(const AttnParams& prm, int* sh, int kvh, int b, int chunk) {
-    const int tid = threadIdx.x, ns = prm.plan.nslots;
-    if (tid < kWave) {  // ns <= kMaxSplit: a lane per flag
-        unsigned long long* flags = merger_flags(prm, kvh, b, chunk);
-        bool missing = tid < ns;
-        // (eight times the patience: with two to a unit these workgroups start together with the items)
-        for (int polls = 0; missing && polls < 8 * kWaitPolls; ++polls) {
-            missing = __hip_atomic_load(flags + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != prm.tag + 1;
-            if (missing) __builtin_amdgcn_s_sleep(4);
-        }
-        bool all = __ballot(missing) == 0;
+template <bool FLAT>
+__device__ __forceinline__ bool merger_stays(const AttnParams& prm, const Partials& parts, int* sh, int kvh, int b, int chunk) {
+    const int tid = threadIdx.x, ns = parts.n;
+    if (tid < kWave) {  // a lane per flag (flat plan: kWave at a time; otherwise ns <= kMaxSplit)
+        bool all = true;
+        int s0 = 0;
+        do {
+            unsigned long long* flag = merger_flag<FLAT>(prm, parts, kvh, b, chunk, s0 + tid);
+            bool missing = s0 + tid < ns;
+            // (eight times the patience: with two to a unit these workgroups start together with the items)
+            for (int polls = 0; missing && polls < 8 * kWaitPolls; ++polls) {
+                missing = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != prm.tag + 1;
+                if (missing) __builtin_amdgcn_s_sleep(4);
+            }
+            all = all && __ballot(missing) == 0;
+            s0 += kWave;
+        } while (FLAT && s0 < ns);
         if (!all) {
-            const bool there = tid < ns && atomicExch(flags + tid, prm.tag + 2) == prm.tag + 1;
-            const int n = __popcll(__ballot(there));
+            int n = 0;
+            for (s0 = 0; s0 < ns; s0 += kWave) {
+                const bool there = s0 + tid < ns && atomicExch(merger_flag<FLAT>(prm, parts, kvh, b, chunk, s0 + tid), prm.tag + 2) == prm.tag + 1;
+                n += __popcll(__ballot(there));
+            }
             if (tid == 0 && n > 0) {
-                unsigned long long* count = merger_count(prm, kvh, b, chunk);
-                all = count_partials(prm, count, n);
+                unsigned long long* count = merger_count<FLAT>(prm, kvh, b, chunk);
+                all = count_partials(prm, parts, count, n);
                 if (all) cell_clear(count);
             }
             all = __ballot(all) != 0;
         }
         if (tid == 0) *sh = all;
-        if (all && tid < ns) cell_clear(flags + tid);
+        if (all)
+            for (s0 = tid; s0 < ns; s0 += kWave) cell_clear(merger_flag<FLAT>(prm, parts, kvh, b, chunk, s0));
     }
     __syncthreads();
     return *sh != 0;
@@ -559,14 +689,29 @@ struct KeyRun {
 // ---------------------------------------------------------------------------------------------
 // bf16 partial attention
 // ---------------------------------------------------------------------------------------------
-template <int D, int NQT, int GROUPS, bool ONE>
-__global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn_kernel(const AttnParams prm) {
+// FLAT: the arguments, read again where they are needed.  What is used in every segment would otherwise stay in scalar registers
+// through all of them, 150 more than there are, each moved to a lane of a vector register and back.
+template <bool FLAT>
+__device__ __forceinline__ const AttnParams& reread(const AttnParams& prm) {
+    if constexpr (FLAT) {
+        auto at = __builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(at));
+        return *(const AttnParams*)at;
+    } else {
+        return prm;
+    }
+}
+
+template <int D, int NQT, int GROUPS, bool ONE, bool FLAT>
+__global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn_kernel(const AttnParams prm_) {
+    const AttnParams& prm = prm_;
     // GROUPS = 2: eight wavefronts, two per SIMD.  The second group of four takes the second row tile; wavefront w of
     // either group streams the same key tiles, so the two share them: each loads half of a tile into a slab both
     // read (two slabs per pair, taking turns; the pair meets once per tile at a counter in LDS, the four pairs stay
     // independent of each other).
     static_assert(GROUPS == 1 || (GROUPS == 2 && NQT == 2), "two groups split two row tiles");
     static_assert(!ONE || (D == 128 && GROUPS == NQT), "every wavefront owns a block of the output");
+    static_assert(!FLAT || (!ONE && GROUPS == NQT), "a row tile per group of four wavefronts");
     // ONE: every wavefront has one key tile at most, its own, and works on all rows' scores.
     constexpr int RUNS = ONE ? kAttnWaves * GROUPS : kAttnWaves;  // runs of key tiles of an item
     constexpr int LG = ONE ? 1 : GROUPS;                          // wavefronts that load a tile together
@@ -586,6 +731,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     __shared__ float sh_m[kAttnWaves * GROUPS][kRowTile];
     __shared__ __attribute__((aligned(8))) float sh_l[kAttnWaves * GROUPS][kRowTile];
     __shared__ int sh_pair[kAttnWaves];  // GROUPS = 2: half tiles stored by the pair of wavefronts w and w + 4
+    __shared__ unsigned long long sh_flat[2];  // FLAT: what one wavefront has found out about the partials of the item's last and first branch
 
     const int tid = threadIdx.x, wave_all = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
     const int grp = LG == 1 ? 0 : wave_all / kAttnWaves;         // which row tile(s) this wavefront works on
@@ -603,13 +749,49 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
         id -= pl.n_priv_items + pl.n_pre_items;
         const int rest = quot(id, prm.d_hkv), kvh = id - rest * prm.Hkv;
         const int b = quot(rest, prm.d_mpp), chunk = rest - b * pl.mpp;
-        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b, chunk,
-                                                   [&] { return merger_stays(prm, reinterpret_cast<int*>(sh_l), kvh, b, chunk); });
+        Partials parts;
+        if constexpr (FLAT) {
+            parts = flat_partials(prm, flat_cuts(prm, pl.fold ? prm.tiles_pre : 0, lane, prm.priv_len[min(lane, prm.B - 1)]), kvh, b);
+            if (parts.n == 1) return;  // whole rows of one item
+        } else {
+            parts = fixed_partials(prm, kvh, b);
+        }
+        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b, chunk, parts,
+                                                   [&] { return merger_stays<FLAT>(prm, parts, reinterpret_cast<int*>(sh_l), kvh, b, chunk); });
         return;
     }
-    const bool is_private = id < pl.n_priv_items;
+    const bool is_private = FLAT || id < pl.n_priv_items;
     int kvh, split, nsplit, rho0, rho_end, slot, b_item = 0;
-    if (is_private) {
+    FlatCuts cuts;
+    unsigned piece_end = 0;  // FLAT: where the item's piece of the head's sequence ends
+    // FLAT: tiles [lo, hi) of branch b_item are the item's, now and next (b beyond the last branch: nothing more)
+    struct Seg {
+        int b, lo, hi;
+    } seg = {0, 0, 0};
+    auto seg_at = [&](int b, unsigned from) {
+        const AttnParams& prm = reread<FLAT>(prm_);  // the first branch from b on of which the piece has tiles
+        for (; b < prm.B; ++b) {
+            unsigned first, last;
+            flat_branch(cuts, b, &first, &last);
+            if (first >= piece_end) break;
+            const unsigned lo = max(first, from), hi = min(last + 1, piece_end);
+            if (lo < hi) return Seg{b, (int)(lo - first), (int)(hi - first)};
+        }
+        return Seg{prm.B, 0, 0};
+    };
+    int piece_of = 0;  // FLAT: which of the head's items this is
+    // FLAT: requested in front of everything else, as loads return in order
+    const int len_lane = FLAT ? prm.priv_len[min(lane, prm.B - 1)] : 0;
+    if constexpr (FLAT) {  // the fixed shares' item; what its prefix share and its Q rows are does not depend on the lengths
+        piece_of = quot(id, prm.d_hkv);
+        kvh = id - piece_of * prm.Hkv;
+        b_item = quot(piece_of, prm.d_nsp);
+        nsplit = pl.nsplit_priv;
+        split = piece_of - b_item * nsplit;
+        b_item = min(b_item, prm.B - 1);
+        rho0 = b_item * GR;
+        rho_end = rho0 + GR;
+    } else if (is_private) {
         int rest = quot(id, prm.d_hkv);
         kvh = id - rest * prm.Hkv;
         const int q = quot(rest, prm.d_nsp);
@@ -633,7 +815,7 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     }
     // A scalar load: requested here, waited for where it is first used (a vector load was waited for at once, to be moved to a
     // scalar register: 0.8 us in front of everything else).
-    const int L_raw = is_private ? *((const __attribute__((address_space(4))) int32_t*)prm.priv_len + b_item) : 0;
+    const int L_raw = is_private && !FLAT ? *((const __attribute__((address_space(4))) int32_t*)prm.priv_len + b_item) : 0;
     // The 32-key tiles of a segment are dealt round-robin to all wavefronts working on it (the 4
     // wavefronts of each of its nsplit items): every wavefront streams the same number of tiles to
     // within one whatever the segment's length, and at any moment the wavefronts of a segment read
@@ -647,9 +829,10 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     pre.stride = prm.kpre_stride_t * 2;
     pre.lo = wave_of_seg * kTile;
     pre.hi = prm.P;
-    const int step = waves_of_seg * kTile;
+    int step = waves_of_seg * kTile;
     const int fold_tiles = is_private && pl.fold ? prm.tiles_pre : 0;
-    const int n_fold = share_of(fold_tiles, wave_of_seg, prm.d_wpriv);
+    int n_fold = 0, n_own = 0, causal_base = 0, own_tiles = 0;
+    n_fold = share_of(fold_tiles, wave_of_seg, prm.d_wpriv);
 
     unsigned char* kslab = lds + wave * SLAB;  // GROUPS = 2: re-pointed every tile
     unsigned char* vslab = kslab + KSLAB;
@@ -670,6 +853,19 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     u32x4 kst[NLD], vst[NLD];
     const int row0_ld = grp * RPI + v_row;
     auto fetch = [&](const KeyRun& r, int kb_) {
+        if constexpr (FLAT) {
+            // rows at or beyond r.hi are out of the buffer's range: they read as zeros, and are masked below
+            const unsigned stride = (unsigned)r.stride, bytes = (unsigned)(r.hi - 1) * stride + D * 2;
+            const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void*)r.K, 0, (int)bytes, 0x00020000);
+            const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void*)r.V, 0, (int)bytes, 0x00020000);
+            const unsigned off = ((unsigned)kb_ + row0_ld) * stride + v_chunk * 16, pitch = stride * (LG * RPI);
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) {
+                kst[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, (int)(off + i * pitch), 0, 2);
+                vst[i] = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)(off + i * pitch), 0, 2);
+            }
+            return;
+        }
         const unsigned char *kp = r.K + kb_ * r.stride, *vp = r.V + kb_ * r.stride;
         const long long pitch = r.stride * (LG * RPI);
         if (kb_ + kTile <= r.hi && prm.near_rows) {
@@ -691,6 +887,30 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             }
         }
     };
+    auto private_run = [&](int b, int len, KeyRun& r) {
+        const AttnParams& prm = reread<FLAT>(prm_);
+        const long long off = (b * prm.kpriv_stride_b + kvh * prm.kpriv_stride_h) * 2;
+        r.K = (const unsigned char*)prm.Kpriv + off;
+        r.V = (const unsigned char*)prm.Vpriv + off;
+        r.stride = prm.kpriv_stride_t * 2;
+        r.hi = len;
+    };
+    // FLAT: the wavefront's tiles of a segment.  Place t of a branch goes to wavefront t % kAttnWaves, so what one gets more in one
+    // segment it gets less in the next.
+    auto deal = [&] {
+        private_run(seg.b, __builtin_amdgcn_readlane(cuts.len, seg.b), own);
+        const int t = seg.lo + ((wave - seg.lo) & (kAttnWaves - 1));
+        const int n = t < seg.hi ? (seg.hi - 1 - t) / kAttnWaves + 1 : 0;
+        n_fold = t < fold_tiles ? min(n, (fold_tiles - 1 - t) / kAttnWaves + 1) : 0;
+        n_own = n - n_fold;
+        pre.lo = t * kTile;
+        own.lo = (t + n_fold * kAttnWaves - fold_tiles) * kTile;
+        if (n > 0) {  // (one copy of the loads for either kind)
+            KeyRun r = own;
+            if (n_fold > 0) r = pre;
+            fetch(r, r.lo);
+        }
+    };
     // ---- Q fragments (B operand of S^T = K Q^T: lane = query row ln, 8 contiguous d) ----
     // Straight from memory they are 32-byte pieces of 32 rows an instruction, and come again for every wavefront: with two row
     // tiles at D = 128 as many bytes as the item's keys and values.  There the whole workgroup requests the rows once, 16
@@ -702,486 +922,682 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
     constexpr int QLD = kRowTile * NQT * LPR / (kAttnThreads * GROUPS);  // loads per thread
     u32x4 qst[QLD];
     bf16x8 qf[TW][KS];
-    auto row_of = [&](int i, int& r, int& h, int& b) {  // row i of the item: position, query head, branch
+    auto row_of = [&](const AttnParams& prm, int i, int& r, int& h, int& b) {  // row i of the item: position, query head, branch
         const int rc = rho0 + i < rho_end ? rho0 + i : rho0;
         b = is_private ? b_item : quot(rc, prm.d_gr);
         const int rl = rc - b * GR;
         r = quot(rl, prm.d_g);
         h = kvh * prm.G + rl - r * prm.G;
     };
-    if (!QLDS && n_fold > 0) fetch(pre, pre.lo);
-#pragma unroll
-    for (int t = 0; t < TW; ++t) {
-        if (QLDS) break;
-        int r, h, b;
-        row_of((grp * TW + t) * kRowTile + ln, r, h, b);
-        const __bf16* qp = (const __bf16*)prm.Q + b * prm.q_stride_b + r * prm.q_stride_r + h * prm.q_stride_h;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qf[t][s] = load_bf16x8(qp + (2 * s + hh) * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < QLD; ++i) {
-        if (!QLDS) break;
-        int r, h, b;
-        row_of((tid + i * kAttnThreads * GROUPS) / LPR, r, h, b);
-        const __bf16* qp = (const __bf16*)prm.Q + b * prm.q_stride_b + r * prm.q_stride_r + h * prm.q_stride_h;
-        qst[i] = *reinterpret_cast<const u32x4*>(qp + tid % LPR * 8);
-    }
-    if (QLDS && n_fold > 0) fetch(pre, pre.lo);
-
-    // ---- the item's own segment ----
-    int causal_base, n_own, own_tiles;
-    if (is_private) {
-        const int L = L_raw < prm.R ? prm.R : (L_raw > prm.Lmax ? prm.Lmax : L_raw);
-        own.hi = L;
-        causal_base = L - prm.k;  // row at position r sees private keys [0, L - k + r)
-        const long long off = (b_item * prm.kpriv_stride_b + kvh * prm.kpriv_stride_h) * 2;
-        own.K = (const unsigned char*)prm.Kpriv + off;
-        own.V = (const unsigned char*)prm.Vpriv + off;
-        own.stride = prm.kpriv_stride_t * 2;
-        // The dealing goes on where the folded prefix tiles stopped: prefix and private tiles form one
-        // sequence, so a wavefront that got one prefix tile more gets one private tile less.
-        int i = wave_of_seg - prm.first_wave;
-        i = i < 0 ? i + waves_of_seg : i;
-        own.lo = i * kTile;
-        own_tiles = (L - 1) / kTile + 1;
-        n_own = share_of(own_tiles, i, prm.d_wpriv);
-    } else {
-        own = pre;
-        causal_base = prm.P;  // every row sees the whole prefix
-        own_tiles = prm.tiles_pre;
-        n_own = share_of(own_tiles, wave_of_seg, prm.d_wpre);
-    }
-    const int n_tiles = n_fold + n_own;
-    if (n_fold == 0 && n_tiles > 0) fetch(own, own.lo);
-    int lim[TW];  // keys of this wavefront's own run visible to this lane's query row
-#pragma unroll
-    for (int t = 0; t < TW; ++t) {
-        int r, h, b;
-        row_of((grp * TW + t) * kRowTile + ln, r, h, b);
-        lim[t] = min(is_private ? causal_base + r : causal_base, own.hi);
-    }
-    if (QLDS) {  // the slabs are free; the first tile is on its way
-#pragma unroll
-        for (int i = 0; i < QLD; ++i) {
-            const int e = tid + i * kAttnThreads * GROUPS;
-            *reinterpret_cast<u32x4*>(lds + e / LPR * KSTRIDE + e % LPR * 16) = qst[i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < TW; ++t)
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-                qf[t][s] = *reinterpret_cast<const bf16x8*>(lds + ((grp * TW + t) * kRowTile + ln) * KSTRIDE + (2 * s + hh) * 16);
-    }
-    if (GROUPS > 1) {  // Q has been read from the slabs; the two wavefronts of a pair count their half tiles from here
-        if (!ONE && tid < kAttnWaves) sh_pair[tid] = 0;
-        __syncthreads();
-    }
-
-    // ---- results of the item: output quads (4 columns from c4 * 4 of rows row0 + q * RSTEP of a row tile) and their (max, sum) ----
-    constexpr int F4 = D / 4;
-    constexpr int QPT = kRowTile * F4 / kAttnThreads;  // per thread and row tile: 4 (D = 128) or 2 (D = 64)
-    constexpr int RSTEP = kAttnThreads / F4;
-    const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
-    const int tig = tid % kAttnThreads;  // thread within its group of four wavefronts
-    const int c4 = ONE ? (wave_all % DB) * 8 + (lane & 7) : tig % F4, row0 = ONE ? lane >> 3 : tig / F4;
-    float4 own_o[QPT];    // the combined quads, kept for a merge by this workgroup (kMergePair: one row tile)
-    float2 own_ml[QPT];
-    // Those of the first nrows rows go out: as the output itself, or as this item's partial.
-    auto put = [&](int tile, int nrows) {
-        const int rho = rho0 + tile * kRowTile + row0;
-        if (pl.merge == kMergeNone) {
-#pragma unroll
-            for (int q = 0; q < QPT; ++q)
-                if (row0 + q * RSTEP < nrows) store_merged(prm, kvh, b_item, rho + q * RSTEP - b_item * GR, c4, own_o[q], own_ml[q].x, own_ml[q].y);
-            return;
-        }
-        const unsigned pidx = ((unsigned)kvh * prm.B * GR + rho) * pl.nslots + slot, step_q = RSTEP * pl.nslots;
-        unsigned at_o = prm.off_o + (pidx * D + c4 * 4) * 4u, at_ml = prm.off_ml + pidx * 8u;
-        if (pl.merge != kMergeLaunch) {
-#pragma unroll
-            for (int q = 0; q < QPT; ++q) {
-                if (row0 + q * RSTEP < nrows) {
-                    ws_store4<true>(rs, at_o, own_o[q]);
-                    if (c4 == 0) ws_store2<true>(rs, at_ml, own_ml[q]);
-                }
-                at_o += step_q * D * 4u;
-                at_ml += step_q * 8u;
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < QPT; ++q) {
-                if (row0 + q * RSTEP < nrows) {
-                    ws_store4<false>(rs, at_o, own_o[q]);
-                    if (c4 == 0) ws_store2<false>(rs, at_ml, own_ml[q]);
-                }
-                at_o += step_q * D * 4u;
-                at_ml += step_q * 8u;
-            }
-        }
-    };
-    if constexpr (ONE) {
-        // Nothing runs here: a wavefront publishes its tile's weights P with their maxima and sums per row, and after a barrier
-        // wavefront w multiplies block w of the output (32 columns of a row tile) over the keys of ALL the item's tiles, each tile's
-        // product weighted by its maximum.  (Parking every wavefront's whole output and adding the four up, as after the loop below,
-        // is 1.7 us of an item whose one tile takes 0.7; this way 1.1 us for both.)
-        const int nt = max(0, min(fold_tiles + own_tiles - split * RUNS, RUNS));  // tiles of the item: of wavefronts 0 .. nt - 1
-        const int db = wave_all % DB, t_own = wave_all / DB;
-        if (n_tiles > 0) {
-            const int kbase = n_fold > 0 ? pre.lo : own.lo;
-#pragma unroll
-            for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(kslab + (i * RPI + v_row) * KSTRIDE + v_chunk * 16) = kst[i];
-#pragma unroll
-            for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(vslab + (i * RPI + v_row) * VSTRIDE + v_chunk * 16) = vst[i];
-            f32x16 acc[NQT];
-            bf16x8 kf[KS];
-#pragma unroll
-            for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(kslab + ln * KSTRIDE + (2 * s + hh) * 16);
-            __builtin_amdgcn_sched_barrier(0);  // all of them requested first
-#pragma unroll
-            for (int t = 0; t < NQT; ++t)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-#pragma unroll
-                for (int t = 0; t < NQT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc[t], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < NQT; ++t) {
-                const int vis = (n_fold > 0 ? pre.hi : lim[t]) - kbase - hh * 4;
-                float mx = -INFINITY;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    float sc = acc[t][i] * prm.scale_log2;
-                    sc = (i >> 2) * 8 + (i & 3) < vis ? sc : -INFINITY;
-                    acc[t][i] = sc;
-                    mx = fmaxf(mx, sc);
-                }
-                mx = fmaxf(mx, shfl_xor_f(mx, 32));
-                const float m_use = (mx == -INFINITY) ? 0.f : mx;
-                bf16x8 pf[2];
-                float psum = 0.f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float pv = __builtin_amdgcn_exp2f(acc[t][i] - m_use);
-                    psum += pv;
-                    pf[i >> 3][i & 7] = (__bf16)pv;
-                }
-                psum += shfl_xor_f(psum, 32);
-                if (hh == 0) sh_ml[wave_all * NQT + t][ln] = make_float2(mx, psum);
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)  // over the wavefront's own K tile, which nobody needs any more
-                    *reinterpret_cast<bf16x8*>(kslab + ((t * 2 + kb) * kWave + lane) * 16) = pf[kb];
-            }
-        }
-        __syncthreads();  // V tiles, P, maxima and sums are in LDS
-        float2 ml[RUNS];  // of row ln of the own row tile
-        f32x16 o;
-        float m_row = -INFINITY, l_row = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[i] = 0.f;
-#pragma unroll
-        for (int j = 0; j < RUNS; ++j) ml[j] = sh_ml[j * NQT + t_own][ln];
-#pragma unroll
-        for (int j = 0; j < RUNS; ++j) ml[j].x = j < nt ? ml[j].x : -INFINITY;  // (beyond the last tile nobody has written)
-#pragma unroll
-        for (int j = 0; j < RUNS; ++j) m_row = fmaxf(m_row, ml[j].x);
-        const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
-#pragma unroll
-        for (int j = 0; j < RUNS; ++j) {
-            if (j >= nt) break;
-            const float w = __builtin_amdgcn_exp2f(ml[j].x - m_use);
-            l_row += ml[j].y * w;
-            f32x16 acc;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const unsigned char* ap = lds + j * SLAB + KSLAB + tr_off + (kb * 16) * VSTRIDE + db * 64;
-                union {
-                    short4v s[2];
-                    bf16x8 v;
-                } vf;
-                vf.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap));
-                vf.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap + 8 * VSTRIDE));
-                const bf16x8 pf = *reinterpret_cast<const bf16x8*>(lds + j * SLAB + ((t_own * 2 + kb) * kWave + lane) * 16);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf, acc, 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) o[i] += acc[i] * w;
-        }
-        __syncthreads();  // the tiles and P have been read
-        {  // the block turns through LDS, wavefront-private, into 128-byte pieces of rows
-            constexpr int TSTRIDE = 36;  // floats per row of the block
-            float* ob = reinterpret_cast<float*>(lds + wave_all * SLAB);
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                *reinterpret_cast<float4*>(ob + ln * TSTRIDE + q4 * 8 + hh * 4) = make_float4(o[q4 * 4 + 0], o[q4 * 4 + 1], o[q4 * 4 + 2], o[q4 * 4 + 3]);
-            if (hh == 0) *reinterpret_cast<float2*>(ob + ln * TSTRIDE + 32) = make_float2(m_row, l_row);
-#pragma unroll
-            for (int q = 0; q < QPT; ++q) {
-                const int row = row0 + q * RSTEP;
-                own_o[q] = *reinterpret_cast<const float4*>(ob + row * TSTRIDE + (lane & 7) * 4);
-                own_ml[q] = *reinterpret_cast<const float2*>(ob + row * TSTRIDE + 32);
-            }
-            put(t_own, min(kRowTile, rho_end - (rho0 + t_own * kRowTile)));
-        }
-    } else {
-        // ---- running state ----
-        f32x16 oacc[TW][DB];
-        float m_run[TW], l_run[TW];
+    auto load_q = [&](int tid) {
+        const AttnParams& prm = reread<FLAT>(prm_);
+        const int lane = tid & (kWave - 1), ln = lane & 31, hh = lane >> 5;
 #pragma unroll
         for (int t = 0; t < TW; ++t) {
-            m_run[t] = -INFINITY;
-            l_run[t] = 0.f;
+            if (QLDS) break;
+            int r, h, b;
+            row_of(prm, (grp * TW + t) * kRowTile + ln, r, h, b);
+            const __bf16* qp = (const __bf16*)prm.Q + b * prm.q_stride_b + r * prm.q_stride_r + h * prm.q_stride_h;
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+            for (int s = 0; s < KS; ++s) qf[t][s] = load_bf16x8(qp + (2 * s + hh) * 8);
+        }
 #pragma unroll
-                for (int i = 0; i < 16; ++i) oacc[t][db][i] = 0.f;
+        for (int i = 0; i < QLD; ++i) {
+            if (!QLDS) break;
+            int r, h, b;
+            row_of(prm, (tid + i * kAttnThreads * GROUPS) / LPR, r, h, b);
+            const __bf16* qp = (const __bf16*)prm.Q + b * prm.q_stride_b + r * prm.q_stride_r + h * prm.q_stride_h;
+            qst[i] = *reinterpret_cast<const u32x4*>(qp + tid % LPR * 8);
+        }
+    };
+    auto request_first = [&] {
+        if (!QLDS && n_fold > 0) fetch(pre, pre.lo);
+        load_q(tid);
+        if (QLDS && n_fold > 0) fetch(pre, pre.lo);
+    };
+    if (!FLAT) request_first();
+    bool cut_first = false;  // FLAT: the first segment's partial waits to be counted
+    Partials parts_first = {};
+    int b_first_seg = 0, slot_first = 0;
+    if constexpr (FLAT) {
+        cuts = flat_cuts(prm, fold_tiles, lane, len_lane);
+        if (cuts.dealt) {
+            if (piece_of >= cuts.workers) return;
+            const unsigned piece = flat_cut(prm, cuts, piece_of);
+            piece_end = flat_cut(prm, cuts, piece_of + 1);
+            seg = seg_at(__builtin_ctzll(__ballot(cuts.end > piece)), piece);
+            if (seg.b >= prm.B) return;  // nothing but a branch's start
+            step = kAttnWaves * kTile;
+            b_item = seg.b;
+            rho0 = b_item * GR;
+            rho_end = rho0 + GR;
+            deal();
+            load_q(tid);
+        } else {  // (a request in front of the decision gains nothing for these and costs dealt items up to 3 %)
+            if (piece_of >= prm.B * nsplit) return;
+            request_first();
+        }
+    }
+    for (;;) {  // once, but in a flat plan's item: once per branch it has tiles of
+        const int tid_all = tid;
+        int tid_seg = tid;
+        if constexpr (FLAT) asm volatile("" : "+v"(tid_seg));  // lane addresses are formed anew for every segment, not kept in registers
+        const int tid = tid_seg, lane = tid & (kWave - 1), ln = lane & 31, hh = lane >> 5;
+        const AttnParams& prm = reread<FLAT>(prm_);
+
+        // ---- the item's own segment ----
+        if (FLAT && cuts.dealt) {
+            causal_base = own.hi - prm.k;
+        } else if (is_private) {
+            int L;
+            if constexpr (FLAT) L = __builtin_amdgcn_readlane(cuts.len, b_item);
+            else L = L_raw < prm.R ? prm.R : (L_raw > prm.Lmax ? prm.Lmax : L_raw);
+            causal_base = L - prm.k;  // row at position r sees private keys [0, L - k + r)
+            private_run(b_item, L, own);
+            // The dealing goes on where the folded prefix tiles stopped: prefix and private tiles form one
+            // sequence, so a wavefront that got one prefix tile more gets one private tile less.
+            int i = wave_of_seg - prm.first_wave;
+            i = i < 0 ? i + waves_of_seg : i;
+            own.lo = i * kTile;
+            own_tiles = (L - 1) / kTile + 1;
+            n_own = share_of(own_tiles, i, prm.d_wpriv);
+        } else {
+            own = pre;
+            causal_base = prm.P;  // every row sees the whole prefix
+            own_tiles = prm.tiles_pre;
+            n_own = share_of(own_tiles, wave_of_seg, prm.d_wpre);
+        }
+        const int n_tiles = n_fold + n_own;
+        if (!(FLAT && cuts.dealt) && n_fold == 0 && n_tiles > 0) fetch(own, own.lo);
+        int lim[TW];  // keys of this wavefront's own run visible to this lane's query row
+#pragma unroll
+        for (int t = 0; t < TW; ++t) {
+            int r, h, b;
+            row_of(prm, (grp * TW + t) * kRowTile + ln, r, h, b);
+            lim[t] = min(is_private ? causal_base + r : causal_base, own.hi);
+        }
+        if (QLDS) {  // the slabs are free; the first tile is on its way
+#pragma unroll
+            for (int i = 0; i < QLD; ++i) {
+                const int e = tid + i * kAttnThreads * GROUPS;
+                *reinterpret_cast<u32x4*>(lds + e / LPR * KSTRIDE + e % LPR * 16) = qst[i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < TW; ++t)
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    qf[t][s] = *reinterpret_cast<const bf16x8*>(lds + ((grp * TW + t) * kRowTile + ln) * KSTRIDE + (2 * s + hh) * 16);
+        }
+        if (GROUPS > 1) {  // Q has been read from the slabs; the two wavefronts of a pair count their half tiles from here
+            if (!ONE && tid < kAttnWaves) sh_pair[tid] = 0;
+            __syncthreads();
         }
 
-        for (int it = 0; it < n_tiles; ++it) {
-            const bool folded = it < n_fold;
-            const int kbase = folded ? pre.lo + it * step : own.lo + (it - n_fold) * step;
-            if (GROUPS > 1) {
-                kslab = lds + ((it & 1) * kAttnWaves + wave) * SLAB;
-                vslab = kslab + KSLAB;
-            }
+        // ---- results of the item: output quads (4 columns from c4 * 4 of rows row0 + q * RSTEP of a row tile) and their (max, sum) ----
+        constexpr int F4 = D / 4;
+        constexpr int QPT = kRowTile * F4 / kAttnThreads;  // per thread and row tile: 4 (D = 128) or 2 (D = 64)
+        constexpr int RSTEP = kAttnThreads / F4;
+        const __amdgpu_buffer_rsrc_t rs = ws_rsrc(prm);
+        const int tig = tid % kAttnThreads;  // thread within its group of four wavefronts
+        int c4 = ONE ? (wave_all % DB) * 8 + (lane & 7) : tig % F4, row0 = ONE ? lane >> 3 : tig / F4;
+        float4 own_o[QPT];    // the combined quads, kept for a merge by this workgroup (kMergePair: one row tile)
+        float2 own_ml[QPT];
+        // Those of the first nrows rows go out: as the output itself, or as this item's partial.
+        Partials parts;
+        if constexpr (FLAT) {
+            parts = flat_partials(prm, cuts, kvh, b_item);
+            slot = cuts.dealt ? piece_of + b_item - (parts.cell - kvh * (prm.workers + prm.B)) : split;
+        } else {
+            parts = fixed_partials(prm, kvh, b_item);
+        }
+        const int b_put = b_item, rho_put = rho0, end_put = rho_end;  // (the next segment's are set before this one's rows go out)
+        auto put = [&](int tile, int nrows) {
+            const AttnParams& prm = reread<FLAT>(prm_);
+            const AttnPlan& pl = prm.plan;
+            const int rho = rho_put + tile * kRowTile + row0;
+            if (FLAT ? parts.n == 1 : pl.merge == kMergeNone) {
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) {
-                *reinterpret_cast<u32x4*>(kslab + ((i * GROUPS + grp) * RPI + v_row) * KSTRIDE + v_chunk * 16) = kst[i];
-                *reinterpret_cast<u32x4*>(vslab + ((i * GROUPS + grp) * RPI + v_row) * VSTRIDE + v_chunk * 16) = vst[i];
+                for (int q = 0; q < QPT; ++q)
+                    if (row0 + q * RSTEP < nrows) store_merged(prm, kvh, b_put, rho + q * RSTEP - b_put * GR, c4, own_o[q], own_ml[q].x, own_ml[q].y);
+                return;
             }
-            if (GROUPS > 1) {
-                // both halves written: the pair's counter stands at 2 * (it + 1).  Whoever gets past this has also left
-                // the tile before behind (it counted this tile only after that), so the other slab is free.
-                if (lane == 0) __hip_atomic_fetch_add(&sh_pair[wave], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                for (int spin = 0; spin < (1 << 20); ++spin) {  // the partner runs the same tiles: the wait ends; bounded all the same
-                    if (__hip_atomic_load(&sh_pair[wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= 2 * (it + 1)) break;
-                    __builtin_amdgcn_s_sleep(1);
+            const unsigned pidx = FLAT ? parts.first + slot * parts.step + (rho - b_put * GR) : ((unsigned)kvh * prm.B * GR + rho) * pl.nslots + slot;
+            const unsigned step_q = RSTEP * (FLAT ? 1 : pl.nslots);
+            unsigned at_o = prm.off_o + (pidx * D + c4 * 4) * 4u, at_ml = prm.off_ml + pidx * 8u;
+            if (pl.merge != kMergeLaunch) {
+#pragma unroll
+                for (int q = 0; q < QPT; ++q) {
+                    if (row0 + q * RSTEP < nrows) {
+                        ws_store4<true>(rs, at_o, own_o[q]);
+                        if (c4 == 0) ws_store2<true>(rs, at_ml, own_ml[q]);
+                    }
+                    at_o += step_q * D * 4u;
+                    at_ml += step_q * 8u;
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < QPT; ++q) {
+                    if (row0 + q * RSTEP < nrows) {
+                        ws_store4<false>(rs, at_o, own_o[q]);
+                        if (c4 == 0) ws_store2<false>(rs, at_ml, own_ml[q]);
+                    }
+                    at_o += step_q * D * 4u;
+                    at_ml += step_q * 8u;
                 }
             }
-            if (it + 1 < n_fold) fetch(pre, kbase + step);
-            else if (it + 1 < n_tiles) fetch(own, own.lo + (it + 1 - n_fold) * step);
-            // K fragments (A operand of S^T = K Q^T: lane = key row ln, 8 contiguous d)
-            bf16x8 kf[KS];
+        };
+        if constexpr (ONE) {
+            // Nothing runs here: a wavefront publishes its tile's weights P with their maxima and sums per row, and after a barrier
+            // wavefront w multiplies block w of the output (32 columns of a row tile) over the keys of ALL the item's tiles, each tile's
+            // product weighted by its maximum.  (Parking every wavefront's whole output and adding the four up, as after the loop below,
+            // is 1.7 us of an item whose one tile takes 0.7; this way 1.1 us for both.)
+            const int nt = max(0, min(fold_tiles + own_tiles - split * RUNS, RUNS));  // tiles of the item: of wavefronts 0 .. nt - 1
+            const int db = wave_all % DB, t_own = wave_all / DB;
+            if (n_tiles > 0) {
+                const int kbase = n_fold > 0 ? pre.lo : own.lo;
 #pragma unroll
-            for (int s = 0; s < KS; ++s)
-                kf[s] = *reinterpret_cast<const bf16x8*>(kslab + ln * KSTRIDE + (2 * s + hh) * 16);
-
-            bf16x8 pf[TW][2];
+                for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(kslab + (i * RPI + v_row) * KSTRIDE + v_chunk * 16) = kst[i];
 #pragma unroll
-            for (int t = 0; t < TW; ++t) {
-                // S^T[key][query] = sum_d K[key][d] Q[query][d]
+                for (int i = 0; i < NLD; ++i) *reinterpret_cast<u32x4*>(vslab + (i * RPI + v_row) * VSTRIDE + v_chunk * 16) = vst[i];
+                f32x16 acc[NQT];
+                bf16x8 kf[KS];
+#pragma unroll
+                for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(kslab + ln * KSTRIDE + (2 * s + hh) * 16);
+                __builtin_amdgcn_sched_barrier(0);  // all of them requested first
+#pragma unroll
+                for (int t = 0; t < NQT; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+#pragma unroll
+                    for (int t = 0; t < NQT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc[t], 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < NQT; ++t) {
+                    const int vis = (n_fold > 0 ? pre.hi : lim[t]) - kbase - hh * 4;
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        float sc = acc[t][i] * prm.scale_log2;
+                        sc = (i >> 2) * 8 + (i & 3) < vis ? sc : -INFINITY;
+                        acc[t][i] = sc;
+                        mx = fmaxf(mx, sc);
+                    }
+                    mx = fmaxf(mx, shfl_xor_f(mx, 32));
+                    const float m_use = (mx == -INFINITY) ? 0.f : mx;
+                    bf16x8 pf[2];
+                    float psum = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float pv = __builtin_amdgcn_exp2f(acc[t][i] - m_use);
+                        psum += pv;
+                        pf[i >> 3][i & 7] = (__bf16)pv;
+                    }
+                    psum += shfl_xor_f(psum, 32);
+                    if (hh == 0) sh_ml[wave_all * NQT + t][ln] = make_float2(mx, psum);
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)  // over the wavefront's own K tile, which nobody needs any more
+                        *reinterpret_cast<bf16x8*>(kslab + ((t * 2 + kb) * kWave + lane) * 16) = pf[kb];
+                }
+            }
+            __syncthreads();  // V tiles, P, maxima and sums are in LDS
+            float2 ml[RUNS];  // of row ln of the own row tile
+            f32x16 o;
+            float m_row = -INFINITY, l_row = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[i] = 0.f;
+#pragma unroll
+            for (int j = 0; j < RUNS; ++j) ml[j] = sh_ml[j * NQT + t_own][ln];
+#pragma unroll
+            for (int j = 0; j < RUNS; ++j) ml[j].x = j < nt ? ml[j].x : -INFINITY;  // (beyond the last tile nobody has written)
+#pragma unroll
+            for (int j = 0; j < RUNS; ++j) m_row = fmaxf(m_row, ml[j].x);
+            const float m_use = (m_row == -INFINITY) ? 0.f : m_row;
+#pragma unroll
+            for (int j = 0; j < RUNS; ++j) {
+                if (j >= nt) break;
+                const float w = __builtin_amdgcn_exp2f(ml[j].x - m_use);
+                l_row += ml[j].y * w;
                 f32x16 acc;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 #pragma unroll
-                for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc, 0, 0, 0);
-                // register i of this lane is key kbase + (i/4)*8 + hh*4 + i%4 for query row ln;
-                // every row sees all of a prefix share, the causal limit applies to the own run only
-                const int vis = (folded ? pre.hi : lim[t]) - kbase - hh * 4;  // key offsets below this are visible
-                float mx = -INFINITY;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int koff = (i >> 2) * 8 + (i & 3);
-                    float sc = acc[i] * prm.scale_log2;
-                    sc = koff < vis ? sc : -INFINITY;
-                    acc[i] = sc;
-                    mx = fmaxf(mx, sc);
-                }
-                mx = fmaxf(mx, shfl_xor_f(mx, 32));
-                const float m_new = fmaxf(m_run[t], mx);
-                const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-                const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_use);
-                float psum = 0.f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float pv = __builtin_amdgcn_exp2f(acc[i] - m_use);
-                    psum += pv;
-                    pf[t][i >> 3][i & 7] = (__bf16)pv;
-                }
-                l_run[t] = l_run[t] * alpha + psum;
-                m_run[t] = m_new;
-                // Rescaling the accumulators is the largest block of vector work of a tile, and once a few hundred keys have
-                // gone by a tile rarely raises any row's maximum: alpha is exactly 1 for every lane then and the whole
-                // wavefront skips it (multiplying by 1 changes nothing, so the result is the same bit for bit).
-                if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) oacc[t][db][i] *= alpha;
-                }
-            }
-            // O^T[d][query] += sum_key V[key][d] P^T[key][query]; V^T fragments by transposing LDS reads
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-#pragma unroll
                 for (int kb = 0; kb < 2; ++kb) {
-                    const unsigned char* ap = vslab + tr_off + (kb * 16) * VSTRIDE + db * 64;
-                    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (__attribute__((address_space(3))) short4v*)(ap));
-                    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (__attribute__((address_space(3))) short4v*)(ap + 8 * VSTRIDE));
+                    const unsigned char* ap = lds + j * SLAB + KSLAB + tr_off + (kb * 16) * VSTRIDE + db * 64;
                     union {
                         short4v s[2];
                         bf16x8 v;
                     } vf;
-                    vf.s[0] = lo;
-                    vf.s[1] = hi;
-#pragma unroll
-                    for (int t = 0; t < TW; ++t)
-                        oacc[t][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf[t][kb], oacc[t][db], 0, 0, 0);
+                    vf.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap));
+                    vf.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap + 8 * VSTRIDE));
+                    const bf16x8 pf = *reinterpret_cast<const bf16x8*>(lds + j * SLAB + ((t_own * 2 + kb) * kWave + lane) * 16);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.v, pf, acc, 0, 0, 0);
                 }
-            }
-        }
-
-        // ---- combine the 4 wavefronts' states of a row tile (fixed order) and store the item's partial ----
-        // Each wavefront parks its raw state in LDS (its slab is free now); after one barrier the 256 threads
-        // of a group of four wavefronts form sum_w 2^(m_w - m) O_w over their group and write the valid rows out,
-        // coalesced (two groups: both row tiles at the same time).  A thread owns QPT output quads of a row
-        // tile -- quad t + 256 q, t its number within the group: the same column of rows RSTEP apart -- and
-        // reads everything it needs for all of them before it uses any of it.
-        if (GROUPS > 1) __syncthreads();  // nobody reads a key tile any more: the slabs become merge buffers
-        float* obuf = reinterpret_cast<float*>(lds + wave_all * SLAB);
 #pragma unroll
-        for (int t = 0; t < TW; ++t) {
-            if (t > 0) __syncthreads();  // the previous row tile has been read out
-            const int tile = grp * TW + t;  // row tile of the item
-            const float lsum = l_run[t] + shfl_xor_f(l_run[t], 32);
-            if (hh == 0) {
-                sh_m[wave_all][ln] = m_run[t];
-                sh_l[wave_all][ln] = lsum;
+                for (int i = 0; i < 16; ++i) o[i] += acc[i] * w;
             }
-            const int nrows = min(kRowTile, rho_end - (rho0 + tile * kRowTile));
-            if (ln < nrows) {  // rows beyond the item's are never read back
+            __syncthreads();  // the tiles and P have been read
+            {  // the block turns through LDS, wavefront-private, into 128-byte pieces of rows
+                constexpr int TSTRIDE = 36;  // floats per row of the block
+                float* ob = reinterpret_cast<float*>(lds + wave_all * SLAB);
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *reinterpret_cast<float4*>(ob + ln * TSTRIDE + q4 * 8 + hh * 4) = make_float4(o[q4 * 4 + 0], o[q4 * 4 + 1], o[q4 * 4 + 2], o[q4 * 4 + 3]);
+                if (hh == 0) *reinterpret_cast<float2*>(ob + ln * TSTRIDE + 32) = make_float2(m_row, l_row);
+#pragma unroll
+                for (int q = 0; q < QPT; ++q) {
+                    const int row = row0 + q * RSTEP;
+                    own_o[q] = *reinterpret_cast<const float4*>(ob + row * TSTRIDE + (lane & 7) * 4);
+                    own_ml[q] = *reinterpret_cast<const float2*>(ob + row * TSTRIDE + 32);
+                }
+                put(t_own, min(kRowTile, rho_end - (rho0 + t_own * kRowTile)));
+            }
+        } else {
+            // ---- running state ----
+            f32x16 oacc[TW][DB];
+            float m_run[TW], l_run[TW];
+#pragma unroll
+            for (int t = 0; t < TW; ++t) {
+                m_run[t] = -INFINITY;
+                l_run[t] = 0.f;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4)
-                        *reinterpret_cast<float4*>(obuf + ln * OSTRIDE + db * 32 + q4 * 8 + hh * 4) =
-                            make_float4(oacc[t][db][q4 * 4 + 0], oacc[t][db][q4 * 4 + 1], oacc[t][db][q4 * 4 + 2],
-                                        oacc[t][db][q4 * 4 + 3]);
+                    for (int i = 0; i < 16; ++i) oacc[t][db][i] = 0.f;
+            }
+
+            for (int it = 0; it < n_tiles; ++it) {
+                const bool folded = it < n_fold;
+                const int kbase = folded ? pre.lo + it * step : own.lo + (it - n_fold) * step;
+                if (GROUPS > 1) {
+                    kslab = lds + ((it & 1) * kAttnWaves + wave) * SLAB;
+                    vslab = kslab + KSLAB;
+                }
+#pragma unroll
+                for (int i = 0; i < NLD; ++i) {
+                    *reinterpret_cast<u32x4*>(kslab + ((i * GROUPS + grp) * RPI + v_row) * KSTRIDE + v_chunk * 16) = kst[i];
+                    *reinterpret_cast<u32x4*>(vslab + ((i * GROUPS + grp) * RPI + v_row) * VSTRIDE + v_chunk * 16) = vst[i];
+                }
+                if (GROUPS > 1) {
+                    // both halves written: the pair's counter stands at 2 * (it + 1).  Whoever gets past this has also left
+                    // the tile before behind (it counted this tile only after that), so the other slab is free.
+                    if (lane == 0) __hip_atomic_fetch_add(&sh_pair[wave], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    for (int spin = 0; spin < (1 << 20); ++spin) {  // the partner runs the same tiles: the wait ends; bounded all the same
+                        if (__hip_atomic_load(&sh_pair[wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) >= 2 * (it + 1)) break;
+                        __builtin_amdgcn_s_sleep(1);
+                    }
+                }
+                if constexpr (FLAT) {
+                    if (it + 1 < n_tiles) {
+                        KeyRun r = own;
+                        if (it + 1 < n_fold) r = pre;
+                        fetch(r, it + 1 < n_fold ? kbase + step : own.lo + (it + 1 - n_fold) * step);
+                    }
+                } else {
+                    if (it + 1 < n_fold) fetch(pre, kbase + step);
+                    else if (it + 1 < n_tiles) fetch(own, own.lo + (it + 1 - n_fold) * step);
+                }
+                // K fragments (A operand of S^T = K Q^T: lane = key row ln, 8 contiguous d)
+                bf16x8 kf[KS];
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    kf[s] = *reinterpret_cast<const bf16x8*>(kslab + ln * KSTRIDE + (2 * s + hh) * 16);
+                __builtin_amdgcn_sched_barrier(0);
+
+                bf16x8 pf[TW][2];
+#pragma unroll
+                for (int t = 0; t < TW; ++t) {
+                    // S^T[key][query] = sum_d K[key][d] Q[query][d]
+                    f32x16 acc;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[t][s], acc, 0, 0, 0);
+                    // register i of this lane is key kbase + (i/4)*8 + hh*4 + i%4 for query row ln;
+                    // every row sees all of a prefix share, the causal limit applies to the own run only
+                    const int vis = (folded ? pre.hi : lim[t]) - kbase - hh * 4;  // key offsets below this are visible
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int koff = (i >> 2) * 8 + (i & 3);
+                        float sc = acc[i] * prm.scale_log2;
+                        sc = koff < vis ? sc : -INFINITY;
+                        acc[i] = sc;
+                        mx = fmaxf(mx, sc);
+                    }
+                    mx = fmaxf(mx, shfl_xor_f(mx, 32));
+                    const float m_new = fmaxf(m_run[t], mx);
+                    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+                    const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_use);
+                    float psum = 0.f;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float pv = __builtin_amdgcn_exp2f(acc[i] - m_use);
+                        psum += pv;
+                        pf[t][i >> 3][i & 7] = (__bf16)pv;
+                    }
+                    l_run[t] = l_run[t] * alpha + psum;
+                    m_run[t] = m_new;
+                    // Rescaling the accumulators is the largest block of vector work of a tile, and once a few hundred keys have
+                    // gone by a tile rarely raises any row's maximum: alpha is exactly 1 for every lane then and the whole
+                    // wavefront skips it (multiplying by 1 changes nothing, so the result is the same bit for bit).
+                    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+                        for (int db = 0; db < DB; ++db)
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) oacc[t][db][i] *= alpha;
+                    }
+                }
+                union {
+                    short4v s[2];
+                    bf16x8 v;
+                } vf[DB][2];
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb) {
+                        const unsigned char* ap = vslab + tr_off + (kb * 16) * VSTRIDE + db * 64;
+                        vf[db][kb].s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap));
+                        vf[db][kb].s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(ap + 8 * VSTRIDE));
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int t = 0; t < TW; ++t)
+                            oacc[t][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][kb].v, pf[t][kb], oacc[t][db], 0, 0, 0);
+            }
+
+            // ---- combine the 4 wavefronts' states of a row tile (fixed order) and store the item's partial ----
+            // Each wavefront parks its raw state in LDS (its slab is free now); after one barrier the 256 threads
+            // of a group of four wavefronts form sum_w 2^(m_w - m) O_w over their group and write the valid rows out,
+            // coalesced (two groups: both row tiles at the same time).  A thread owns QPT output quads of a row
+            // tile -- quad t + 256 q, t its number within the group: the same column of rows RSTEP apart -- and
+            // reads everything it needs for all of them before it uses any of it.
+            if (GROUPS > 1) __syncthreads();  // nobody reads a key tile any more: the slabs become merge buffers
+            int tid_end = tid_all;
+            if constexpr (FLAT) {  // (formed here, not kept through the tiles)
+                asm volatile("" : "+v"(tid_end));
+                c4 = tid_end % kAttnThreads % F4;
+                row0 = tid_end % kAttnThreads / F4;
+            }
+            const int ln = tid_end & 31, hh = (tid_end & (kWave - 1)) >> 5;
+            float* obuf = reinterpret_cast<float*>(lds + wave_all * SLAB);
+#pragma unroll
+            for (int t = 0; t < TW; ++t) {
+                if (t > 0) __syncthreads();  // the previous row tile has been read out
+                const int tile = grp * TW + t;  // row tile of the item
+                const float lsum = l_run[t] + shfl_xor_f(l_run[t], 32);
+                if (hh == 0) {
+                    sh_m[wave_all][ln] = m_run[t];
+                    sh_l[wave_all][ln] = lsum;
+                }
+                const int nrows = min(kRowTile, end_put - (rho_put + tile * kRowTile));
+                if (ln < nrows) {  // rows beyond the item's are never read back
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4)
+                            *reinterpret_cast<float4*>(obuf + ln * OSTRIDE + db * 32 + q4 * 8 + hh * 4) =
+                                make_float4(oacc[t][db][q4 * 4 + 0], oacc[t][db][q4 * 4 + 1], oacc[t][db][q4 * 4 + 2],
+                                            oacc[t][db][q4 * 4 + 3]);
+                }
+                if constexpr (FLAT) {  // the next segment's first tile and Q rows are on their way while this one's states meet
+                    if (cuts.dealt) seg = seg_at(seg.b + 1, 0);
+                    else seg.b = prm.B;
+                    if (seg.b < prm.B) {
+                        b_item = seg.b;
+                        rho0 = b_item * GR;
+                        rho_end = rho0 + GR;
+                        deal();
+                    }
+                }
+                __syncthreads();
+                constexpr int QB = FLAT ? QPT / 2 : QPT;  // quads at a time (FLAT: the next segment's tile and Q rows hold registers)
+#pragma unroll
+                for (int q0 = 0; q0 < QPT; q0 += QB) {
+                    float mw[QB][kAttnWaves], lw[QB][kAttnWaves];
+                    float4 ov[QB][kAttnWaves];
+#pragma unroll
+                    for (int q = 0; q < QB; ++q)
+#pragma unroll
+                        for (int w = 0; w < kAttnWaves; ++w) {
+                            if (!FLAT && (q0 + q) * RSTEP >= nrows) continue;  // a whole group of rows beyond the item's (uniform)
+                            const int row = min(row0 + (q0 + q) * RSTEP, nrows - 1);
+                            mw[q][w] = sh_m[grp * kAttnWaves + w][row];
+                            lw[q][w] = sh_l[grp * kAttnWaves + w][row];
+                            ov[q][w] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds + (grp * kAttnWaves + w) * SLAB) +
+                                                                        row * OSTRIDE + c4 * 4);
+                        }
+#pragma unroll
+                    for (int q = 0; q < QB; ++q) {
+                        if (!FLAT && (q0 + q) * RSTEP >= nrows) continue;
+                        float mg = -INFINITY;
+#pragma unroll
+                        for (int w = 0; w < kAttnWaves; ++w) mg = fmaxf(mg, mw[q][w]);
+                        const float mg_use = (mg == -INFINITY) ? 0.f : mg;
+                        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+                        float lg = 0.f;
+#pragma unroll
+                        for (int w = 0; w < kAttnWaves; ++w) {
+                            const float sc = __builtin_amdgcn_exp2f(mw[q][w] - mg_use);
+                            o.x += ov[q][w].x * sc;
+                            o.y += ov[q][w].y * sc;
+                            o.z += ov[q][w].z * sc;
+                            o.w += ov[q][w].w * sc;
+                            lg += lw[q][w] * sc;
+                        }
+                        own_o[q0 + q] = o;
+                        own_ml[q0 + q] = make_float2(mg, lg);
+                    }
+                }
+                if (FLAT && seg.b < prm.B) load_q(tid);
+                put(tile, nrows);
+            }
+        }
+
+        if constexpr (FLAT) {
+            const AttnParams& prm = reread<FLAT>(prm_);
+            const AttnPlan& pl = prm.plan;
+            // Only the first and the last segment of an item can be cut; both are counted at the end, so that nothing waits for a
+            // partial's way to memory in between.
+            if (seg.b < prm.B) {
+                if (parts.n > 1) {
+                    cut_first = true;
+                    parts_first = parts;
+                    b_first_seg = b_put;
+                    slot_first = slot;
+                }
+                __syncthreads();  // the states of the wavefronts have been read
+                continue;
+            }
+            const bool cut_last = parts.n > 1;
+            if (!cut_first && !cut_last) return;
+            __builtin_amdgcn_s_waitcnt(0);  // the partials are in memory
+            __syncthreads();
+            if (pl.merge == kMergeGroups) {
+                if (tid < kWave) {
+                    bool mine = false;
+                    if (cut_last && tid < pl.mpp && atomicExch(merger_flag<FLAT>(prm, parts, kvh, b_put, tid, slot), prm.tag + 1) == prm.tag + 2)
+                        mine = count_partials(prm, parts, merger_count<FLAT>(prm, kvh, b_put, tid), 1);
+                    const unsigned long long found = __ballot(mine);
+                    mine = false;
+                    if (cut_first && tid < pl.mpp && atomicExch(merger_flag<FLAT>(prm, parts_first, kvh, b_first_seg, tid, slot_first), prm.tag + 1) == prm.tag + 2)
+                        mine = count_partials(prm, parts_first, merger_count<FLAT>(prm, kvh, b_first_seg, tid), 1);
+                    const unsigned long long found_first = __ballot(mine);
+                    if (tid == 0) {
+                        sh_flat[0] = found;
+                        sh_flat[1] = found_first;
+                    }
+                }
+                __syncthreads();
+                for (int e = 0; e < 2; ++e) {
+                    const Partials pe = e == 0 ? parts : parts_first;
+                    const int be = e == 0 ? b_put : b_first_seg;
+                    for (unsigned long long left = sh_flat[e]; left; left &= left - 1) {  // uniform over the workgroup
+                        const int c = __ffsll((long long)left) - 1;
+                        for (int j = tid; j < pe.n; j += kAttnThreads * GROUPS) cell_clear(merger_flag<FLAT>(prm, pe, kvh, be, c, j));
+                        if (tid == 0) cell_clear(merger_count<FLAT>(prm, kvh, be, c));
+                        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, be, c, pe, [] { return true; });
+                        __syncthreads();
+                    }
+                }
+                return;
+            }
+            if (tid < 2) {
+                bool last = false;
+                if (tid == 0 ? cut_last : cut_first) {
+                    unsigned long long* cnt = prm.counters + kvh * prm.B + (tid == 0 ? b_put : b_first_seg);
+                    atomicMax(cnt, prm.tag);
+                    last = atomicAdd(cnt, 1ull) == prm.tag + (unsigned long long)((tid == 0 ? parts.n : parts_first.n) - 1);
+                    if (last) cell_clear(cnt);
+                }
+                sh_flat[tid] = last;
             }
             __syncthreads();
-            float mw[QPT][kAttnWaves], lw[QPT][kAttnWaves];
-            float4 ov[QPT][kAttnWaves];
+            // partials in the order of the sequence; the last segment's own is still in registers
+            const int tile0 = grp * kRowTile, nrows = min(kRowTile, GR - tile0);
+            for (int e = 0; e < 2; ++e) {
+                if (!sh_flat[e]) continue;  // uniform
+                int row1 = row0;
+                asm volatile("" : "+v"(row1));
+                const Partials pe = e == 0 ? parts : parts_first;
+                const int mine = e == 0 ? slot : -1;
+                float2 ml[QPT];
+                float4 o[QPT];
 #pragma unroll
-            for (int q = 0; q < QPT; ++q)
+                for (int q = 0; q < QPT; ++q) {
+                    ml[q] = make_float2(-INFINITY, 0.f);
+                    o[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+                constexpr int CH = 2;
+                for (int j0 = 0; j0 < pe.n; j0 += CH) {
+                    float2 mv[CH][QPT];
+                    float4 pv[CH][QPT];
 #pragma unroll
-                for (int w = 0; w < kAttnWaves; ++w) {
-                    if (q * RSTEP >= nrows) continue;  // a whole group of rows beyond the item's (uniform)
-                    const int row = min(row0 + q * RSTEP, nrows - 1);
-                    mw[q][w] = sh_m[grp * kAttnWaves + w][row];
-                    lw[q][w] = sh_l[grp * kAttnWaves + w][row];
-                    ov[q][w] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lds + (grp * kAttnWaves + w) * SLAB) +
-                                                                row * OSTRIDE + c4 * 4);
+                    for (int j = 0; j < CH; ++j)
+#pragma unroll
+                        for (int q = 0; q < QPT; ++q) {
+                            mv[j][q] = make_float2(-INFINITY, 0.f);
+                            pv[j][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                            if (j0 + j == mine) {
+                                mv[j][q] = own_ml[q];
+                                pv[j][q] = own_o[q];
+                            }
+                            if (j0 + j == mine || j0 + j >= pe.n || q * RSTEP >= nrows) continue;
+                            const unsigned pidx = pe.first + (j0 + j) * pe.step + tile0 + min(row1 + q * RSTEP, nrows - 1);
+                            mv[j][q] = ws_load2<true>(rs, prm.off_ml + pidx * 8u);
+                            pv[j][q] = ws_load4<true>(rs, prm.off_o + (pidx * D + c4 * 4) * 4u);
+                        }
+#pragma unroll
+                    for (int q = 0; q < QPT; ++q) {
+                        float M = ml[q].x;
+#pragma unroll
+                        for (int j = 0; j < CH; ++j) M = fmaxf(M, mv[j][q].x);
+                        const float Mu = (M == -INFINITY) ? 0.f : M;
+                        const float a = __builtin_amdgcn_exp2f(ml[q].x - Mu);
+                        ml[q].y *= a;
+                        o[q].x *= a; o[q].y *= a; o[q].z *= a; o[q].w *= a;
+#pragma unroll
+                        for (int j = 0; j < CH; ++j) {
+                            const float w = __builtin_amdgcn_exp2f(mv[j][q].x - Mu);
+                            ml[q].y += mv[j][q].y * w;
+                            o[q].x += pv[j][q].x * w; o[q].y += pv[j][q].y * w; o[q].z += pv[j][q].z * w; o[q].w += pv[j][q].w * w;
+                        }
+                        ml[q].x = M;
+                    }
                 }
 #pragma unroll
-            for (int q = 0; q < QPT; ++q) {
-                if (q * RSTEP >= nrows) continue;
-                float mg = -INFINITY;
-#pragma unroll
-                for (int w = 0; w < kAttnWaves; ++w) mg = fmaxf(mg, mw[q][w]);
-                const float mg_use = (mg == -INFINITY) ? 0.f : mg;
-                float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-                float lg = 0.f;
-#pragma unroll
-                for (int w = 0; w < kAttnWaves; ++w) {
-                    const float sc = __builtin_amdgcn_exp2f(mw[q][w] - mg_use);
-                    o.x += ov[q][w].x * sc;
-                    o.y += ov[q][w].y * sc;
-                    o.z += ov[q][w].z * sc;
-                    o.w += ov[q][w].w * sc;
-                    lg += lw[q][w] * sc;
-                }
-                own_o[q] = o;
-                own_ml[q] = make_float2(mg, lg);
+                for (int q = 0; q < QPT; ++q)
+                    if (row1 + q * RSTEP < nrows)
+                        store_merged(prm, kvh, e == 0 ? b_put : b_first_seg, tile0 + row1 + q * RSTEP, c4, o[q], ml[q].x, ml[q].y);
             }
-            put(tile, nrows);
+            return;
         }
-    }
-
-    if (pl.merge == kMergeLaunch || pl.merge == kMergeNone) return;
-    // ---- arrival: whoever completes the set of partials of a (KV head, branch) merges it ----
-    // Every thread waits until its partial stores are acknowledged; then one thread per covered
-    // branch counts the arrival in that branch's cell: raise it to (this call's tag, 0) if it holds
-    // anything older, add one.  The two atomics go to one address from one thread, so they take
-    // effect in program order.  The last arrival puts a zero back, which lets a captured launch
-    // (same tag every time) be replayed.
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (pl.merge == kMergeGroups) {  // the item's partial is in memory: raise its flag for each of the branch's merge workgroups
-        unsigned long long* sh_mine = reinterpret_cast<unsigned long long*>(sh_l);  // free again
-        if (tid < kWave) {  // mpp <= rows of an item <= 64
-            bool mine = false;
-            if (tid < pl.mpp) {
-                if (atomicExch(merger_flags(prm, kvh, b_item, tid) + slot, prm.tag + 1) == prm.tag + 2)  // that workgroup has left
-                    mine = count_partials(prm, merger_count(prm, kvh, b_item, tid), 1);
+        if (pl.merge == kMergeLaunch || pl.merge == kMergeNone) return;
+        // ---- arrival: whoever completes the set of partials of a (KV head, branch) merges it ----
+        // Every thread waits until its partial stores are acknowledged; then one thread per covered
+        // branch counts the arrival in that branch's cell: raise it to (this call's tag, 0) if it holds
+        // anything older, add one.  The two atomics go to one address from one thread, so they take
+        // effect in program order.  The last arrival puts a zero back, which lets a captured launch
+        // (same tag every time) be replayed.
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (pl.merge == kMergeGroups) {  // the item's partial is in memory: raise its flag for each of the branch's merge workgroups
+            unsigned long long* sh_mine = reinterpret_cast<unsigned long long*>(sh_l);  // free again
+            if (tid < kWave) {  // mpp <= rows of an item <= 64
+                bool mine = false;
+                if (tid < pl.mpp) {
+                    if (atomicExch(merger_flag<FLAT>(prm, parts, kvh, b_item, tid, slot), prm.tag + 1) == prm.tag + 2)  // that workgroup has left
+                        mine = count_partials(prm, parts, merger_count<FLAT>(prm, kvh, b_item, tid), 1);
+                }
+                const unsigned long long all = __ballot(mine);
+                if (tid == 0) *sh_mine = all;
             }
-            const unsigned long long all = __ballot(mine);
-            if (tid == 0) *sh_mine = all;
+            __syncthreads();
+            for (unsigned long long left = *sh_mine; left; left &= left - 1) {  // uniform over the workgroup
+                const int c = __ffsll((long long)left) - 1;
+                if (tid < pl.nslots) cell_clear(merger_flag<FLAT>(prm, parts, kvh, b_item, c, tid));
+                if (tid == 0) cell_clear(merger_count<FLAT>(prm, kvh, b_item, c));
+                merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b_item, c, parts, [] { return true; });
+                __syncthreads();
+            }
+            return;
+        }
+        int* sh_last = reinterpret_cast<int*>(sh_l);  // free again; kAttnWaves * kRowTile >= rows of an item
+        const int rows_per_item = kRowTile * NQT;
+        const int b_first = quot(rho0, prm.d_gr), b_last = quot(rho_end - 1, prm.d_gr);
+        const int nb = b_last - b_first + 1;  // <= rows_per_item
+        if (tid < nb) {
+            const int b = b_first + tid;
+            int expected = pl.n_rg_priv * pl.nsplit_priv;
+            if (pl.nsplit_pre > 0) {
+                const int rg_lo = (b * GR) / rows_per_item, rg_hi = ((b + 1) * GR - 1) / rows_per_item;
+                expected += pl.nsplit_pre * (rg_hi - rg_lo + 1);
+            }
+            unsigned long long* cnt = prm.counters + kvh * prm.B + b;
+            atomicMax(cnt, prm.tag);
+            const unsigned long long seen = atomicAdd(cnt, 1ull);
+            const int last = (seen == prm.tag + (unsigned long long)(expected - 1));
+            if (last) atomicExch(cnt, 0ull);
+            sh_last[tid] = last;
         }
         __syncthreads();
-        for (unsigned long long left = *sh_mine; left; left &= left - 1) {  // uniform over the workgroup
-            const int c = __ffsll((long long)left) - 1;
-            if (tid < pl.nslots) cell_clear(merger_flags(prm, kvh, b_item, c) + tid);
-            if (tid == 0) cell_clear(merger_count(prm, kvh, b_item, c));
-            merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b_item, c, [] { return true; });
-            __syncthreads();
+        if (NQT == 1 && pl.merge == kMergePair) {  // the item's rows are the branch's rows; slot order, as everywhere
+            if (!sh_last[0]) return;
+            float2 mv[QPT];
+            float4 pv[QPT];
+            const int n_rows = rho_end - rho0;
+#pragma unroll
+            for (int q = 0; q < QPT; ++q) {
+                if (q * RSTEP >= n_rows) continue;
+                const unsigned pidx = ((unsigned)kvh * prm.B * GR + rho0 + min(row0 + q * RSTEP, n_rows - 1)) * 2 + (1 - slot);
+                mv[q] = ws_load2<true>(rs, prm.off_ml + pidx * 8u);
+                pv[q] = ws_load4<true>(rs, prm.off_o + (pidx * D + c4 * 4) * 4u);
+            }
+#pragma unroll
+            for (int q = 0; q < QPT; ++q) {
+                const int row = row0 + q * RSTEP;
+                if (row >= n_rows) continue;
+                const float2 ma = slot == 0 ? own_ml[q] : mv[q], mb = slot == 0 ? mv[q] : own_ml[q];
+                const float4 oa = slot == 0 ? own_o[q] : pv[q], ob = slot == 0 ? pv[q] : own_o[q];
+                const float M = fmaxf(ma.x, mb.x), Mu = (M == -INFINITY) ? 0.f : M;
+                const float wa = __builtin_amdgcn_exp2f(ma.x - Mu), wb = __builtin_amdgcn_exp2f(mb.x - Mu);
+                store_merged(prm, kvh, b_item, row, c4,
+                             make_float4(oa.x * wa + ob.x * wb, oa.y * wa + ob.y * wb, oa.z * wa + ob.z * wb, oa.w * wa + ob.w * wb),
+                             M, ma.y * wa + mb.y * wb);
+            }
+            return;
         }
+        if (GROUPS == 1 || tid < kAttnThreads)  // the merge is written for 256 threads
+            for (int j = 0; j < nb; ++j)
+                if (sh_last[j]) merge_branch<D>(prm, rs, kvh, b_first + j, tid);  // uniform over the workgroup
+        __builtin_amdgcn_s_waitcnt(0);
         return;
     }
-    int* sh_last = reinterpret_cast<int*>(sh_l);  // free again; kAttnWaves * kRowTile >= rows of an item
-    const int rows_per_item = kRowTile * NQT;
-    const int b_first = quot(rho0, prm.d_gr), b_last = quot(rho_end - 1, prm.d_gr);
-    const int nb = b_last - b_first + 1;  // <= rows_per_item
-    if (tid < nb) {
-        const int b = b_first + tid;
-        int expected = pl.n_rg_priv * pl.nsplit_priv;
-        if (pl.nsplit_pre > 0) {
-            const int rg_lo = (b * GR) / rows_per_item, rg_hi = ((b + 1) * GR - 1) / rows_per_item;
-            expected += pl.nsplit_pre * (rg_hi - rg_lo + 1);
-        }
-        unsigned long long* cnt = prm.counters + kvh * prm.B + b;
-        atomicMax(cnt, prm.tag);
-        const unsigned long long seen = atomicAdd(cnt, 1ull);
-        const int last = (seen == prm.tag + (unsigned long long)(expected - 1));
-        if (last) atomicExch(cnt, 0ull);
-        sh_last[tid] = last;
-    }
-    __syncthreads();
-    if (NQT == 1 && pl.merge == kMergePair) {  // the item's rows are the branch's rows; slot order, as everywhere
-        if (!sh_last[0]) return;
-        float2 mv[QPT];
-        float4 pv[QPT];
-        const int n_rows = rho_end - rho0;
-#pragma unroll
-        for (int q = 0; q < QPT; ++q) {
-            if (q * RSTEP >= n_rows) continue;
-            const unsigned pidx = ((unsigned)kvh * prm.B * GR + rho0 + min(row0 + q * RSTEP, n_rows - 1)) * 2 + (1 - slot);
-            mv[q] = ws_load2<true>(rs, prm.off_ml + pidx * 8u);
-            pv[q] = ws_load4<true>(rs, prm.off_o + (pidx * D + c4 * 4) * 4u);
-        }
-#pragma unroll
-        for (int q = 0; q < QPT; ++q) {
-            const int row = row0 + q * RSTEP;
-            if (row >= n_rows) continue;
-            const float2 ma = slot == 0 ? own_ml[q] : mv[q], mb = slot == 0 ? mv[q] : own_ml[q];
-            const float4 oa = slot == 0 ? own_o[q] : pv[q], ob = slot == 0 ? pv[q] : own_o[q];
-            const float M = fmaxf(ma.x, mb.x), Mu = (M == -INFINITY) ? 0.f : M;
-            const float wa = __builtin_amdgcn_exp2f(ma.x - Mu), wb = __builtin_amdgcn_exp2f(mb.x - Mu);
-            store_merged(prm, kvh, b_item, row, c4,
-                         make_float4(oa.x * wa + ob.x * wb, oa.y * wa + ob.y * wb, oa.z * wa + ob.z * wb, oa.w * wa + ob.w * wb),
-                         M, ma.y * wa + mb.y * wb);
-        }
-        return;
-    }
-    if (GROUPS == 1 || tid < kAttnThreads)  // the merge is written for 256 threads
-        for (int j = 0; j < nb; ++j)
-            if (sh_last[j]) merge_branch<D>(prm, rs, kvh, b_first + j, tid);  // uniform over the workgroup
-    __builtin_amdgcn_s_waitcnt(0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1191,7 +1607,8 @@ template <int D>
 __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(const AttnParams prm) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kAttnThreads * (sizeof(float4) + sizeof(float2))];
     const int b = quot(blockIdx.y, prm.d_hkv);
-    merge_rows<D, false, kAttnThreads>(prm, lds, blockIdx.y - b * prm.Hkv, b, blockIdx.x, [] { return true; });
+    const int kvh = blockIdx.y - b * prm.Hkv;
+    merge_rows<D, false, kAttnThreads>(prm, lds, kvh, b, blockIdx.x, fixed_partials(prm, kvh, b), [] { return true; });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1343,8 +1760,8 @@ static int fill_desc(const lotts_attn_desc* in, lotts_attn_desc* d) {
 // addressed with 32-bit byte offsets, arrivals per cell are counted in 16 bits).
 static size_t workspace_need(const lotts_attn_desc& d) {
     if (d.dtype == LOTTS_F32) return 256;  // the fp32 path needs none; keep the pointer non-NULL
-    const AttnPlan pl = plan_attention(d);
-    const long long arrivals = (long long)pl.n_rg_priv * pl.nsplit_priv + (long long)pl.nsplit_pre * (pl.n_rg_priv + 1);
+    const AttnPlans pl = plan_attention(d);
+    const long long arrivals = pl.flat ? pl.workers : (long long)pl.n_rg_priv * pl.nsplit_priv + (long long)pl.nsplit_pre * (pl.n_rg_priv + 1);
     if (arrivals >= (1 << kTagShift)) return 0;
     const size_t bytes = workspace_layout(d, pl, nullptr, nullptr);
     return bytes < 0x7fffffffULL ? bytes : 0;
@@ -1381,8 +1798,8 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
         return check_launch();
     }
 
-    prm.plan = plan_attention(d);
-    const AttnPlan& pl = prm.plan;
+    const AttnPlans pl = plan_attention(d);
+    prm.plan = pl;
     size_t off_o, off_ml;
     const size_t total = workspace_layout(d, pl, &off_o, &off_ml);
     prm.ws = workspace;
@@ -1398,18 +1815,25 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     const long long tile_span = (1LL << 31) / (2 * kTile);  // elements from key to key
     prm.near_rows = d.kpriv_stride_t < tile_span && d.kpre_stride_t < tile_span;
     prm.tag = (g_call_tag.fetch_add(1, std::memory_order_relaxed) + 1) << kTagShift;
+    prm.flat = pl.flat; prm.workers = pl.workers;
+    prm.d_workers = fast_div(pl.workers > 0 ? pl.workers : 1);
     const long long items = (long long)pl.n_pre_items + pl.n_priv_items + pl.n_merge;
     if (items > 0x7fffffffLL) return LOTTS_ERR_SHAPE;
     const dim3 grid((unsigned)items), block(kAttnThreads);
     const dim3 block2(2 * kAttnThreads);
     if (pl.one) {
-        if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1, true>), grid, block, s, prm);
-        else LOTTS_LAUNCH((attn_kernel<128, 2, 2, true>), grid, block2, s, prm);
+        if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1, true, false>), grid, block, s, prm);
+        else LOTTS_LAUNCH((attn_kernel<128, 2, 2, true, false>), grid, block2, s, prm);
+    } else if (pl.flat) {
+        if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1, false, true>), grid, block, s, prm);
+        else if (d.D == 128) LOTTS_LAUNCH((attn_kernel<128, 2, 2, false, true>), grid, block2, s, prm);
+        else if (pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<64, 1, 1, false, true>), grid, block, s, prm);
+        else LOTTS_LAUNCH((attn_kernel<64, 2, 2, false, true>), grid, block2, s, prm);
     } else {
-        if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1, false>), grid, block, s, prm);
-        else if (d.D == 128) LOTTS_LAUNCH((attn_kernel<128, 2, 2, false>), grid, block2, s, prm);
-        else if (pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<64, 1, 1, false>), grid, block, s, prm);
-        else LOTTS_LAUNCH((attn_kernel<64, 2, 2, false>), grid, block2, s, prm);
+        if (d.D == 128 && pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<128, 1, 1, false, false>), grid, block, s, prm);
+        else if (d.D == 128) LOTTS_LAUNCH((attn_kernel<128, 2, 2, false, false>), grid, block2, s, prm);
+        else if (pl.nqt == 1) LOTTS_LAUNCH((attn_kernel<64, 1, 1, false, false>), grid, block, s, prm);
+        else LOTTS_LAUNCH((attn_kernel<64, 2, 2, false, false>), grid, block2, s, prm);
     }
     if (pl.merge == kMergeLaunch) {
         const int rc = check_launch();

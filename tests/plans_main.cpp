@@ -1,4 +1,4 @@
-// The launch plans of the library, answered on the host: a line "gemm M N K", "accept B V", "logits B k V" or "attention B k Hq Hkv D P Lmax" in, the
+// The launch plans of the library, answered on the host: a line "gemm M N K", "accept B V", "logits B k V" or "attention B k Hq Hkv D P Lmax" or "lengths ..." in, the
 // plan's numbers out.  Host code only; nothing here launches, so the few runtime calls that the sources make have empty bodies.
 #ifdef PLANS_RUNTIME
 extern "C" {
@@ -40,6 +40,12 @@ int main() {
             if (scanf("%d %d %d %d %d %d %d", &d.B, &d.k, &d.Hq, &d.Hkv, &d.D, &d.P, &d.Lmax) != 7) return 1;
             const lotts::AttnPlan p = lotts::plan_attention(d);
             printf("one %d nqt %d fold %d shares %d prefix_shares %d merge %d\n", p.one, p.nqt, p.fold, p.nsplit_priv, p.nsplit_pre, p.merge);
+        } else if (!strcmp(kind, "lengths")) {
+            lotts_attn_desc d = {};
+            d.dtype = LOTTS_BF16;
+            if (scanf("%d %d %d %d %d %d %d", &d.B, &d.k, &d.Hq, &d.Hkv, &d.D, &d.P, &d.Lmax) != 7) return 1;
+            const lotts::AttnPlans p = lotts::plan_attention(d);
+            printf("flat %d workers %d merge %d nqt %d fold %d\n", p.flat, p.workers, p.merge, p.nqt, p.fold);
         } else {
             return 1;
         }

@@ -1,0 +1,179 @@
+"""verify_attention where the items deal a KV head's tiles by the branches' lengths, on the device.  A build of the library that does so for
+calls of any length (liblotts_flat.so) runs small geometries against the CPU oracle; which plans they reach is checked on the host
+(test_plans.py)."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as S
+from gpu_util import DEV, attn_to_dev
+from test_gpu_no_patience import lotts as no_polls  # noqa: F401  (a fixture)
+from test_gpu_parity import BF, run_attention
+
+pytestmark = pytest.mark.gpu
+NAMES = ("Q", "Kpre", "Vpre", "Kpriv", "Vpriv", "priv_len")
+
+CASES = [
+    # branches with several items each (merge workgroups): one row tile and two, both head dims, a prefix and none
+    BF.with_(B=20, Hq=32, Hkv=8, k=3, P=30, L=400), BF.with_(B=17, Hq=40, Hkv=8, k=8, P=60, L=500), BF.with_(B=12, Hq=80, Hkv=16, k=6, D=64, P=31, L=333),
+    BF.with_(B=9, Hq=16, Hkv=2, k=1, D=64, P=100, L=900),
+    BF.with_(B=2, Hq=2, Hkv=1, k=1, D=64, P=0, L=9000),     # up to 512 items for two branches: partials beyond a wavefront's lanes
+    BF.with_(B=33, Hq=9, Hkv=3, k=2, D=64, P=0, L=700),     # heads that do not divide the units
+    # items with several branches each (the last arriver)
+    BF.with_(B=40, Hq=8, Hkv=8, k=0, P=0, L=300), BF.with_(B=64, Hq=40, Hkv=8, k=7, P=33, L=260),
+    BF.with_(B=35, Hq=16, Hkv=16, k=2, D=64, P=40, L=200), BF.with_(B=34, Hq=80, Hkv=16, k=7, D=64, P=0, L=130),
+    BF.with_(B=18, Hq=16, Hkv=16, k=0, D=64, P=20, L=230),  # a few more items of whole rows than units
+]
+LONG = [BF.with_(B=64, Hq=2, Hkv=2, k=1, P=70, L=4352), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2200)]
+
+
+def lengths(cfg, pattern):
+    lo, B = cfg.k + 1, cfg.B
+    if pattern == "equal":
+        return np.full(B, cfg.L, np.int32)
+    if pattern == "ragged":
+        return np.linspace(lo, cfg.L, B).astype(np.int32)
+    if pattern == "shuffled":
+        return np.random.default_rng(B).permutation(np.linspace(lo, cfg.L, B)).astype(np.int32)
+    out = np.full(B, lo, np.int32)  # all but one hold the new tokens only
+    out[{"first": 0, "last": B - 1, "one": B // 2}[pattern]] = cfg.L
+    return out if pattern != "none" else np.full(B, lo, np.int32)
+
+
+@pytest.fixture(scope="module")
+def flat():
+    """The package on top of that build, with workspaces of its own, for the tests of this file."""
+    import paper_2505_19634_amd as m
+    from paper_2505_19634_amd import binding
+    usual, workspaces = m.load(), binding._workspaces
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setattr(binding, "LIB_PATH", os.path.join(os.path.dirname(binding.LIB_PATH), "liblotts_flat.so"))
+        mp.setattr(binding, "_lib", None)
+        mp.setattr(binding, "_workspaces", {})
+        mp.setattr(binding, "_sized", {})
+        assert m.load() is not usual
+        yield m
+        torch.cuda.synchronize()
+    assert m.load() is usual and binding._workspaces is workspaces
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=lambda c: "B%d_k%d_Hq%d_Hkv%d_D%d_P%d_L%d" % (c.B, c.k, c.Hq, c.Hkv, c.D, c.P, c.L))
+@pytest.mark.parametrize("pattern", ["equal", "ragged", "shuffled", "first", "last", "one"])
+def test_lengths(flat, oracle, cfg, pattern):
+    run_attention(flat, oracle, cfg, priv_len=lengths(cfg, pattern))
+
+
+@pytest.mark.parametrize("cfg", [CASES[0], CASES[1], CASES[6]], ids=["groups", "two_row_tiles", "last_arriver"])
+def test_replays_with_other_lengths(flat, cfg):
+    """What a captured call deals follows the lengths it finds, and every cell is down again when it ends."""
+    sets = [attn_to_dev(cfg, S.attention_inputs(cfg, salt=i, priv_len=lengths(cfg, p))) for i, p in enumerate(("equal", "shuffled", "one"))]
+    want = [flat.verify_attention(*(d[n] for n in NAMES)).clone() for d in sets]
+    buf = {n: sets[0][n].clone() for n in NAMES}
+    out = torch.empty_like(buf["Q"])
+    ws = torch.zeros(16 << 20, dtype=torch.uint8, device=DEV)
+    call = lambda: flat.verify_attention(*(buf[n] for n in NAMES), out=out, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for i in (1, 2, 0, 1):
+        for n in NAMES:
+            buf[n].copy_(sets[i][n])
+        for again in (graph.replay, call, graph.replay):
+            out.zero_()
+            again()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want[i]), i
+            assert int(ws[:131072].to(torch.int32).sum()) == 0
+
+
+@pytest.mark.parametrize("cfg", [CASES[0], CASES[1], CASES[3]], ids=["D128", "two_row_tiles", "D64"])
+def test_strided_operands(flat, cfg):
+    """Caches [B][L][Hkv][D], padded prefix rows, Q as columns of a wider projection: the same result, bit for bit."""
+    d = attn_to_dev(cfg, S.attention_inputs(cfg, priv_len=lengths(cfg, "shuffled")))
+    want = flat.verify_attention(*(d[n] for n in NAMES)).clone()
+    for n in ("Kpriv", "Vpriv"):
+        d[n] = d[n].transpose(1, 2).contiguous().transpose(1, 2)
+    for n in ("Kpre", "Vpre"):
+        wide = torch.full((cfg.Hkv, cfg.P, cfg.D + 24), float("nan"), dtype=torch.bfloat16, device=DEV)
+        wide[..., :cfg.D].copy_(d[n])
+        d[n] = wide[..., :cfg.D]
+    wide = torch.full((cfg.B, cfg.k + 1, cfg.Hq + 3, cfg.D), float("nan"), dtype=torch.bfloat16, device=DEV)
+    wide[:, :, :cfg.Hq].copy_(d["Q"])
+    d["Q"] = wide[:, :, :cfg.Hq]
+    assert torch.equal(flat.verify_attention(*(d[n] for n in NAMES)), want)
+
+
+def test_rows_behind_the_lengths_do_not_count(flat):
+    """NaN in every cache row at or beyond a branch's length: those rows are read as zeros or not at all."""
+    cfg = CASES[0]
+    d = attn_to_dev(cfg, S.attention_inputs(cfg, priv_len=lengths(cfg, "shuffled")))
+    want = flat.verify_attention(*(d[n] for n in NAMES)).clone()
+    for b, L in enumerate(d["priv_len"].tolist()):
+        for n in ("Kpriv", "Vpriv"):
+            d[n][b, :, L:] = float("nan")
+    assert torch.equal(flat.verify_attention(*(d[n] for n in NAMES)), want)
+
+
+def test_calls_side_by_side(flat):
+    cfgs = [CASES[0], CASES[1], CASES[6]]
+    sets = [attn_to_dev(c, S.attention_inputs(c, priv_len=lengths(c, "shuffled"))) for c in cfgs]
+    for d, c in zip(sets, cfgs):
+        if c.P == 0:
+            d["Kpre"] = d["Vpre"] = None
+    want = [flat.verify_attention(*(d[n] for n in NAMES)).clone() for d in sets]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in sets]
+    got = [[flat.verify_attention(*(d[n] for n in NAMES), stream=s) for d, s in zip(sets, streams)] for _ in range(20)]
+    torch.cuda.synchronize()
+    for round_ in got:
+        assert all(torch.equal(o, w) for o, w in zip(round_, want))
+
+
+def long_inputs(cfg):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(cfg.B)
+    t = lambda *shape: (torch.randn(shape, generator=g, device=DEV) * 0.5).to(torch.bfloat16)
+    d = {"Q": t(cfg.B, cfg.k + 1, cfg.Hq, cfg.D), "Kpriv": t(cfg.B, cfg.Hkv, cfg.L, cfg.D), "Vpriv": t(cfg.B, cfg.Hkv, cfg.L, cfg.D)}
+    for n in ("Kpre", "Vpre"):
+        d[n] = t(cfg.Hkv, cfg.P, cfg.D) if cfg.P else None
+    d["priv_len"] = torch.from_numpy(lengths(cfg, "shuffled")).to(DEV)
+    return d
+
+
+@pytest.mark.parametrize("cfg", LONG, ids=["groups", "last_arriver"])
+def test_long_calls(cfg):
+    """The library itself, against plain fp32 attention of some branches."""
+    import paper_2505_19634_amd as lotts
+    d = long_inputs(cfg)
+    O = lotts.verify_attention(*(d[n] for n in NAMES))
+    G = cfg.Hq // cfg.Hkv
+    for b in range(0, cfg.B, 7):
+        L = int(d["priv_len"][b])
+        K, V = (torch.cat(([d[p].float()] if cfg.P else []) + [d[n][b, :, :L].float()], 1) for p, n in (("Kpre", "Kpriv"), ("Vpre", "Vpriv")))
+        for r in range(cfg.k + 1):
+            q = d["Q"][b, r].float().view(cfg.Hkv, G, cfg.D)
+            n = cfg.P + L - cfg.k + r
+            z = torch.matmul(q, K[:, :n].transpose(1, 2).contiguous()) / cfg.D ** 0.5
+            ref = torch.matmul(torch.softmax(z, -1), V[:, :n]).view(cfg.Hq, cfg.D)
+            err = ((O[b, r].float() - ref).norm() / ref.norm()).item()
+            assert err <= 8e-3, (b, r, err)  # one row of few: twice the band of whole outputs (4e-3)
+
+
+@pytest.mark.parametrize("cfg", LONG, ids=["groups", "last_arriver"])
+def test_long_calls_without_patience(no_polls, cfg):  # noqa: F811
+    """Merge workgroups that leave at once: the items merge in their place, in the same order."""
+    from paper_2505_19634_amd import binding
+    d = long_inputs(cfg)
+    got = [no_polls.verify_attention(*(d[n] for n in NAMES)).clone() for _ in range(3)]
+    torch.cuda.synchronize()
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setattr(binding, "LIB_PATH", os.path.join(os.path.dirname(binding.LIB_PATH), "liblotts.so"))
+        mp.setattr(binding, "_lib", None)
+        mp.setattr(binding, "_workspaces", {})
+        want = no_polls.verify_attention(*(d[n] for n in NAMES))
+        torch.cuda.synchronize()
+    assert all(torch.equal(o, want) for o in got)

@@ -41,3 +41,18 @@ def test_logits_lists_reach_every_size_of_piece():
     for case, p in zip(CASES, ask(["logits %d %d %d" % c[1:] for c in CASES])):
         assert p["loads"] == case[0], (case, p)
     assert {p["loads"] for p in ask(["logits %d %d %d" % c for c in LOGITS])} == {4, 5, 6, 8}
+
+
+def test_lengths_lists_reach_the_flat_plan():
+    """Small calls in the tests' build, long ones in the library itself: both merges, one row tile and two, with and without a prefix."""
+    from test_gpu_attention_lengths import CASES, LONG
+    line = lambda c: attention(c).replace("attention", "lengths")
+    plans = ask([line(c) for c in CASES], ("-DLOTTS_FLAT_STEPS=0",))
+    assert all(p["flat"] for p in plans), list(zip(CASES, plans))
+    assert {(c.D, p["nqt"], p["merge"]) for c, p in zip(CASES, plans)} == {(D, nqt, m) for D in (64, 128) for nqt in (1, 2) for m in (0, 1)}
+    assert {p["fold"] for p in plans} == {0, 1} and 2 in {p["flat"] for p in plans}
+    assert not any(p["flat"] for p in ask([line(c) for c in CASES]))
+    assert all(p["flat"] == 1 for p in ask([line(c) for c in LONG]))
+    # one branch more than a wavefront has lanes, rows of several row groups, a prefix in items of its own: not these
+    other = [LONG[0].with_(B=65), LONG[0].with_(k=70), LONG[0].with_(P=LONG[0].L)]
+    assert not any(p["flat"] for p in ask([line(c) for c in other]))
