@@ -264,6 +264,20 @@ int skinny_gemm(int32_t M, int32_t N, int32_t K, const void *X, int64_t ldx, con
                 int64_t ldy, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * skinny_gemm_append -- the QKV projection of the B * (k + 1) new tokens with the append of its K and V columns: skinny_gemm into Y
+ * and kv_append of Y's last 2 * Hkv * D columns (the K heads, then the V heads) to the tails of the private caches, in
+ * skinny_gemm's launches.  Y and the caches get the bits that the two calls give them.
+ *   X [B * (k + 1)][K], W [N][K], Y [B * (k + 1)][N]: as for skinny_gemm, row b * (k + 1) + r = new token r of branch b;
+ *       B * (k + 1) <= 256, 2 * Hkv * D <= N, D a multiple of 8, ldy a multiple of 8, Y 16-byte aligned
+ *   Kpriv, Vpriv, their strides, Lmax, priv_len: as for kv_append (bf16); the caches overlap no other operand
+ *   workspace: >= skinny_gemm_workspace_bytes(B * (k + 1), N, K), any contents
+ */
+int skinny_gemm_append(int32_t B, int32_t k, int32_t Hkv, int32_t D, int32_t N, int32_t K, const void *X, int64_t ldx, const void *W,
+                       int64_t ldw, void *Y, int64_t ldy, void *Kpriv, void *Vpriv, int64_t priv_stride_b, int64_t priv_stride_h,
+                       int64_t priv_stride_t, int32_t Lmax, const int32_t *priv_len, void *workspace, size_t workspace_bytes,
+                       void *stream);
+
+/*
  * Kernel timer -- device execution time of the kernels the entry points launch, for callers that
  * have no profiler at hand (not an operation of the paper; a measurement aid).
  * Between lotts_timer_start and lotts_timer_stop every kernel launched by the CALLING HOST THREAD
@@ -280,7 +294,8 @@ int skinny_gemm(int32_t M, int32_t N, int32_t K, const void *X, int64_t ldx, con
  * The order of launches inside one call: verify_attention 1 (2 -- attention, then merge -- when a row has
  * partials from prefix items (4 P > Lmax) or from several row groups, but for the smallest batches);
  * spec_accept 1 (2 -- scan, pick -- when V is beyond 2^18); spec_accept_logits 2 (row statistics, scan and
- * pick); majority_vote 1; confidence_vote 1; skinny_gemm 1 (2 when K is split: GEMM, reduce).
+ * pick); majority_vote 1; confidence_vote 1; skinny_gemm 1 (2 when K is split: GEMM, reduce),
+ * skinny_gemm_append the same (and kv_append where a product that streams W has K unsplit).
  */
 int lotts_timer_start(int32_t max_launches);
 int lotts_timer_pause(int32_t paused);

@@ -21,7 +21,8 @@ LOTTS_F32, LOTTS_BF16 = 0, 1
 
 EXPORTS = ("lotts_strerror", "verify_attention_workspace_bytes", "verify_attention", "verify_attention_noalloc",
            "spec_accept_workspace_bytes", "spec_accept", "spec_accept_logits_workspace_bytes", "spec_accept_logits",
-           "majority_vote", "confidence_vote", "skinny_gemm_workspace_bytes", "skinny_gemm", "kv_append", "greedy_search",
+           "majority_vote", "confidence_vote", "skinny_gemm_workspace_bytes", "skinny_gemm", "skinny_gemm_append", "kv_append",
+           "greedy_search",
            "lotts_timer_start", "lotts_timer_pause", "lotts_timer_stop")
 
 
@@ -90,6 +91,8 @@ def load() -> ctypes.CDLL:
         lib.skinny_gemm_workspace_bytes.argtypes = [i32, i32, i32]
         lib.skinny_gemm.restype = ctypes.c_int
         lib.skinny_gemm.argtypes = [i32, i32, i32, vp, ctypes.c_int64, vp, ctypes.c_int64, vp, ctypes.c_int64, vp, sz, vp]
+        lib.skinny_gemm_append.restype = ctypes.c_int
+        lib.skinny_gemm_append.argtypes = [i32] * 6 + [vp, ctypes.c_int64] * 3 + [vp, vp] + [ctypes.c_int64] * 3 + [i32, vp, vp, sz, vp]
         lib.kv_append.restype = ctypes.c_int
         lib.kv_append.argtypes = [i32, i32, i32, i32, i32, vp, vp] + [ctypes.c_int64] * 3 + [vp, vp] + [ctypes.c_int64] * 3 + [i32, vp, vp]
         lib.greedy_search.restype = ctypes.c_int
@@ -380,6 +383,42 @@ def skinny_gemm(X: torch.Tensor, W: torch.Tensor, *, out: Optional[torch.Tensor]
     rc = call(X, W, out, workspace, cached, handle)
     if rc != 0:
         _finish(rc, "gemm", index, stream, lambda ws: call(X, W, out, None, ws, handle), "skinny_gemm")
+    return out
+
+
+def skinny_gemm_append(X: torch.Tensor, W: torch.Tensor, Kpriv: torch.Tensor, Vpriv: torch.Tensor, priv_len: torch.Tensor, *,
+                       out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
+                       stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
+    """The QKV projection Y = X @ W.T of the new tokens, X [B * (k+1)][K], W [(Hq + 2 Hkv) * D][K], with kv_append of its K and V
+    columns (the last 2 Hkv heads) to Kpriv/Vpriv [B][Hkv][Lmax][D], in one call.  All bf16 on one GPU; returns Y."""
+    lib = load()
+    for t in (X, W, Kpriv, Vpriv):
+        if t.dtype != torch.bfloat16 or t.device != X.device or not t.is_cuda or t.stride(-1) != 1:
+            raise TypeError("skinny_gemm_append takes bfloat16 tensors on one GPU, their last dimension contiguous")
+    if X.dim() != 2 or W.dim() != 2 or Kpriv.dim() != 4 or X.shape[1] != W.shape[1]:
+        raise ValueError("X must be [M][K], W [N][K] and Kpriv [B][Hkv][Lmax][D]")
+    (M, K), N, (B, Hkv, Lmax, D) = X.shape, W.shape[0], Kpriv.shape
+    if B == 0 or M % B or Vpriv.shape != Kpriv.shape or Vpriv.stride() != Kpriv.stride():
+        raise ValueError("X holds the same number of tokens of each of Kpriv's branches, Vpriv shares Kpriv's shape and strides")
+    if any(n > 1 and s == 0 for t in (X, W, Kpriv) for n, s in zip(t.shape, t.stride())):
+        raise ValueError("expanded tensors are not supported")
+    if priv_len.dtype != torch.int32 or tuple(priv_len.shape) != (B,) or not priv_len.is_contiguous() or priv_len.device != X.device:
+        raise TypeError("priv_len must be a contiguous int32 [B] tensor on the same GPU")
+    if out is None:
+        out = torch.empty((M, N), dtype=torch.bfloat16, device=X.device)
+    elif out.dtype != torch.bfloat16 or out.device != X.device or tuple(out.shape) != (M, N) or out.stride(1) != 1:
+        raise TypeError("out must be bfloat16 [M][N] on the same GPU, its rows contiguous")
+    need = _sized.get(("gemm", M, N, K))
+    if need is None:
+        need = _remember(("gemm", M, N, K), lib.skinny_gemm_workspace_bytes(M, N, K))
+    if need == 0:
+        raise LottsError(-2, "skinny_gemm_workspace_bytes")
+    ws = _workspace("gemm", X.get_device(), need, stream) if workspace is None else workspace
+    rc = lib.skinny_gemm_append(B, M // B - 1, Hkv, D, N, K, _ptr(X), X.stride(0), _ptr(W), W.stride(0), _ptr(out), out.stride(0),
+                                _ptr(Kpriv), _ptr(Vpriv), Kpriv.stride(0), Kpriv.stride(1), Kpriv.stride(2), Lmax, _ptr(priv_len),
+                                _ptr(ws), ws.nbytes, _stream_handle(stream))
+    if rc != 0:
+        raise LottsError(rc, "skinny_gemm_append")
     return out
 
 

@@ -16,7 +16,8 @@ struct AppendParams {
     int B, R, Hkv, pieces, Lmax;                            // pieces: 16-byte pieces of a row of D elements
 };
 
-// I: 32 bits while the number of pieces allows.  Bound by latency (launch, one load, one store): the three divisions of a
+// Where the rows come straight from the projection, skinny_gemm_append saves this launch; rows that something has worked on in between
+// (a rotary embedding) are appended here.  I: 32 bits while the number of pieces allows.  Bound by latency (launch, one load, one store): the three divisions of a
 // 64-bit index were most of the instructions (a 36-layer step of 8 branches 2641 -> 2631 us).
 template <typename I>
 __global__ __launch_bounds__(256) void kv_append_kernel(const AppendParams p) {

@@ -12,6 +12,8 @@
 //       partials in a fixed order and converts.
 //   skinny_gemm_direct_kernel<RN, TT, WAVES, UB>  small matrices: a workgroup owns 16 * RN weight rows and 16 * TT tokens for
 //       the WHOLE K range, its wavefronts a share of K each; no partials, no second launch.
+// skinny_gemm_append, for the QKV projection, also puts its K and V columns into the branches' caches: the kernel that writes Y (the
+// direct or the reduce kernel) stores them twice.
 #include "lotts_common.h"
 
 namespace lotts {
@@ -49,6 +51,37 @@ struct GemmParams {  // (in the order in which the kernels come to need it)
     long long ldy;
     float* part;  // fp32 partials when ksplit > 1: [ksplit][block of weight rows][row wavefront][tile][quad][lane] float4
 };
+
+// Where the K and V columns of a QKV projection go beside Y: token m = b * R + r of branch b to position len[b] - R + r of its caches.
+// A launch of its own for these few KB is all fixed cost (4.3 us between two launches of a graph); the threads that hold the columns
+// store them a second time for next to nothing: a 36-layer step of 8 branches x 5 tokens 2534 -> 2426 us, 3 us a layer.
+struct GemmAppend {
+    __bf16 *Kpriv, *Vpriv;
+    const int32_t* len;
+    long long sb, sh, st;  // strides in elements
+    int n_new, D, Hkv, R, Lmax;  // the first of the K columns
+    FastDiv d_R, d_D;
+};
+
+struct GemmAppendParams : GemmParams {
+    GemmAppend a;
+};
+template <typename P>
+constexpr bool kAppends = std::is_same<P, GemmAppendParams>::value;
+
+// The position of token m in its branch's caches, negative if there is none.  The epilogues read it ahead of the sums that they wait for.
+__device__ __forceinline__ int append_position(const GemmAppend& a, int m) {
+    const int b = quot(m, a.d_R), t = a.len[b] - a.R + (m - b * a.R);
+    return t < a.Lmax ? t : -1;
+}
+// Columns n .. n + 3 of token m; D a multiple of 8 keeps them in one head.
+__device__ __forceinline__ void append_store(const GemmAppend& a, int m, int t, int n, g_bf16x4 v) {
+    if (n < a.n_new || t < 0) return;
+    const int head = quot(n - a.n_new, a.d_D), d = n - a.n_new - head * a.D;
+    const bool k = head < a.Hkv;
+    __bf16* row = (k ? a.Kpriv : a.Vpriv) + quot(m, a.d_R) * a.sb + (k ? head : head - a.Hkv) * a.sh + t * a.st + d;
+    *reinterpret_cast<g_bf16x4*>(row) = v;
+}
 
 enum GemmForm { kStream256, kStream128, kStream64, kDirect };
 
@@ -457,7 +490,8 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
 
 // One workgroup per accumulator tile of 32 tokens x 32 weight rows: thread (quad, lane) adds up the tile's partials as the stream
 // kernel's lanes left them, in split order (deterministic), and the bf16 tile turns through LDS into 64-byte row pieces of Y.
-__global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const GemmParams p) {
+template <typename P>
+__global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const P p) {
     __shared__ __attribute__((aligned(16))) unsigned char tr[32 * kGemmOutRow];
     const int tiles = p.rt * p.tt;
     const int j = blockIdx.x % tiles, wb = blockIdx.x / tiles;
@@ -468,6 +502,10 @@ __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const GemmParam
     if (m_base >= p.M || n_base >= p.N) return;  // uniform over the workgroup
     const int q4 = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1), ln = lane & 31, hh = lane >> 5;
     const bool in = m_base + ln < p.M && (p.rt > 1 || q4 * 8 < p.rows);  // what the stream kernel has stored
+    const int ml = threadIdx.x >> 3, nc = (threadIdx.x & 7) * 4, m = m_base + ml, n = n_base + nc;
+    int t = -1;
+    if constexpr (kAppends<P>)
+        if (n_base + 32 > p.a.n_new) t = append_position(p.a, min(m, p.M - 1));
     const long long stride = (long long)p.nblocks * p.roww * tiles * (kGemmTileFloats / 4);
     const float4* src = reinterpret_cast<const float4*>(p.part) + (long long)blockIdx.x * (kGemmTileFloats / 4) + threadIdx.x;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -494,10 +532,11 @@ __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const GemmParam
     o[3] = (__bf16)s.w;
     *reinterpret_cast<g_bf16x4*>(tr + ln * kGemmOutRow + (q4 * 8 + hh * 4) * 2) = o;
     __syncthreads();
-    const int ml = threadIdx.x >> 3, nc = (threadIdx.x & 7) * 4;
-    if (m_base + ml < p.M && n_base + nc < p.N && (p.rt > 1 || nc < p.rows))
-        *reinterpret_cast<g_bf16x4*>(p.Y + (long long)(m_base + ml) * p.ldy + n_base + nc) =
-            *reinterpret_cast<const g_bf16x4*>(tr + ml * kGemmOutRow + nc * 2);
+    if (m < p.M && n < p.N && (p.rt > 1 || nc < p.rows)) {
+        const g_bf16x4 y = *reinterpret_cast<const g_bf16x4*>(tr + ml * kGemmOutRow + nc * 2);
+        *reinterpret_cast<g_bf16x4*>(p.Y + (long long)m * p.ldy + n) = y;
+        if constexpr (kAppends<P>) append_store(p.a, m, t, n, y);
+    }
 }
 
 // The direct form.  Small matrices are bound by fixed costs -- launch, first data, the exchange of partials -- so the whole K
@@ -505,13 +544,22 @@ __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const GemmParam
 // covers 64 contiguous bytes of 16 rows, and a wavefront's share of K at K = 2048 is one or two batches of UB steps with tiles of
 // up to 32 rows (all of it in flight at once), eight batches with 64.  The wavefronts' sums meet in LDS, added in wavefront order.  W is non-temporal when a single
 // workgroup column reads it (NT); with several over the tokens the later ones find it in the L2.
-template <int RN, int TT, int WAVES, int UB, bool NT>
-__global__ __launch_bounds__(WAVES * kWave) void skinny_gemm_direct_kernel(const GemmParams p) {
-    constexpr int TILES = RN * TT;
+template <int RN, int TT, int WAVES, int UB, bool NT, typename P>
+__global__ __launch_bounds__(WAVES * kWave) void skinny_gemm_direct_kernel(const P p) {
+    constexpr int TILES = RN * TT, TURNS = (TILES + WAVES - 1) / WAVES;  // of the last loop
     __shared__ __attribute__((aligned(16))) float4 red[WAVES][TILES][kWave];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid & (kWave - 1);
     const int lr = lane & 15, kg = lane >> 4;
     const int n0 = blockIdx.x * (16 * RN), m0 = blockIdx.y * p.tokens, m_end = min(m0 + p.tokens, p.M);
+    int to[TURNS];
+    if constexpr (kAppends<P>) {
+#pragma unroll
+        for (int e = 0; e < TURNS; ++e) to[e] = -1;
+        if (n0 + 16 * RN > p.a.n_new) {
+#pragma unroll
+            for (int e = 0; e < TURNS; ++e) to[e] = append_position(p.a, min(m0 + (wave + e * WAVES) % TT * 16 + lr, p.M - 1));
+        }
+    }
     const int S = p.K / 32;
     const int s_lo = (int)((long long)wave * S / WAVES), s_hi = (int)((long long)(wave + 1) * S / WAVES);
     const __bf16 *wp[RN], *xp[TT];
@@ -568,20 +616,23 @@ __global__ __launch_bounds__(WAVES * kWave) void skinny_gemm_direct_kernel(const
 #pragma unroll
         for (int t = 0; t < TT; ++t) red[wave][i * TT + t][lane] = make_float4(acc[i][t][0], acc[i][t][1], acc[i][t][2], acc[i][t][3]);
     __syncthreads();
-    for (int e = tid; e < TILES * kWave; e += WAVES * kWave) {
-        const int tile = e / kWave, l = e % kWave;
-        float4 s = red[0][tile][l];
+#pragma unroll
+    for (int e = 0; e < TURNS; ++e) {
+        const int tile = wave + e * WAVES;
+        if (tile >= TILES) break;
+        float4 s = red[0][tile][lane];
 #pragma unroll
         for (int w = 1; w < WAVES; ++w) {
-            const float4 v = red[w][tile][l];
+            const float4 v = red[w][tile][lane];
             s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
         }
         const int i = tile / TT, t = tile % TT;
-        const int m = m0 + t * 16 + (l & 15), n = n0 + i * 16 + (l >> 4) * 4;
+        const int m = m0 + t * 16 + lr, n = n0 + i * 16 + kg * 4;
         if (m < m_end && n < p.N) {
             g_bf16x4 o;
             o[0] = (__bf16)s.x; o[1] = (__bf16)s.y; o[2] = (__bf16)s.z; o[3] = (__bf16)s.w;
             *reinterpret_cast<g_bf16x4*>(p.Y + (long long)m * p.ldy + n) = o;
+            if constexpr (kAppends<P>) append_store(p.a, m, to[e], n, o);
         }
     }
 }
@@ -606,33 +657,23 @@ static void launch_stream(int mt, dim3 grid, hipStream_t s, const GemmParams& p)
     }
 }
 
-template <int RN, int TT, int WAVES, int UB>
-static void launch_direct(dim3 grid, hipStream_t s, const GemmParams& p) {
+template <int RN, int TT, int WAVES, int UB, typename P>
+static void launch_direct(dim3 grid, hipStream_t s, const P& p) {
     const dim3 block(WAVES * kWave);
-    if (grid.y == 1) LOTTS_LAUNCH((skinny_gemm_direct_kernel<RN, TT, WAVES, UB, true>), grid, block, s, p);
-    else LOTTS_LAUNCH((skinny_gemm_direct_kernel<RN, TT, WAVES, UB, false>), grid, block, s, p);
+    if (grid.y == 1) LOTTS_LAUNCH((skinny_gemm_direct_kernel<RN, TT, WAVES, UB, true, P>), grid, block, s, p);
+    else LOTTS_LAUNCH((skinny_gemm_direct_kernel<RN, TT, WAVES, UB, false, P>), grid, block, s, p);
 }
 
-}  // namespace lotts
-
-// The query asks for the K splits of the stream form also where the direct form is taken: which one is faster changes back and forth with
-// the tokens, and a workspace sized for the most of them would be too small for fewer.
-extern "C" size_t skinny_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
-    if (!lotts::gemm_sizes_ok(M, N, K)) return 0;
-    return lotts::plan_bytes(lotts::plan_gemm(M, N, K, false));
-}
-
-extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,
-                           void* Y, int64_t ldy, void* workspace, size_t workspace_bytes, void* stream) {
-    using namespace lotts;
+// What both entry points check and prepare.
+static int prepare(int M, int N, int K, const void* X, int64_t ldx, const void* W, int64_t ldw, void* Y, int64_t ldy, void* workspace,
+                   size_t workspace_bytes, GemmPlan* plan, GemmParams* params) {
     if (!gemm_sizes_ok(M, N, K)) return LOTTS_ERR_SHAPE;
     if (!X || !W || !Y || !workspace) return LOTTS_ERR_NULL;
     if (ldx < K || ldw < K || ldy < N || (ldx % 8) || (ldw % 8) || (ldy % 4)) return LOTTS_ERR_SHAPE;
     if ((((uintptr_t)X | (uintptr_t)W | (uintptr_t)workspace) & 15) || ((uintptr_t)Y & 7)) return LOTTS_ERR_SHAPE;
-    const GemmPlan pl = plan_gemm(M, N, K);
+    const GemmPlan pl = *plan = plan_gemm(M, N, K);
     if (workspace_bytes < plan_bytes(pl)) return LOTTS_ERR_WORKSPACE;
-    GemmParams p;
-
+    GemmParams& p = *params;
     p.X = static_cast<const __bf16*>(X);
     p.W = static_cast<const __bf16*>(W);
     p.Y = static_cast<__bf16*>(Y);
@@ -646,7 +687,12 @@ extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64
     p.d_steps[0] = fast_div(steps > 0 ? steps : 1);
     p.d_steps[1] = fast_div(steps + 2);
     p.ldx = ldx; p.ldw = ldw; p.ldy = ldy;
-    hipStream_t s = (hipStream_t)stream;
+    return LOTTS_OK;
+}
+
+// The launches of a plan: the one that writes Y gets p as it is.
+template <typename P>
+static int launch_plan(const GemmPlan& pl, hipStream_t s, const P& p) {
     const dim3 grid(pl.nblocks, pl.form == kDirect ? pl.nby : pl.ksplit);
     switch (pl.form) {
         case kStream256: launch_stream<8, 1, 2, 2>(pl.mt, grid, s, p); break;
@@ -664,8 +710,55 @@ extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64
             }
             break;
     }
-    int rc = check_launch();
+    const int rc = check_launch();
     if (rc != LOTTS_OK || pl.ksplit == 1) return rc;
-    LOTTS_LAUNCH(skinny_gemm_reduce_kernel, dim3((unsigned)(pl.nblocks * pl.roww * pl.mt)), dim3(256), s, p);
+    LOTTS_LAUNCH(skinny_gemm_reduce_kernel<P>, dim3((unsigned)(pl.nblocks * pl.roww * pl.mt)), dim3(256), s, p);
     return check_launch();
+}
+
+}  // namespace lotts
+
+// The query asks for the K splits of the stream form also where the direct form is taken: which one is faster changes back and forth with
+// the tokens, and a workspace sized for the most of them would be too small for fewer.
+extern "C" size_t skinny_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
+    if (!lotts::gemm_sizes_ok(M, N, K)) return 0;
+    return lotts::plan_bytes(lotts::plan_gemm(M, N, K, false));
+}
+
+extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,
+                           void* Y, int64_t ldy, void* workspace, size_t workspace_bytes, void* stream) {
+    using namespace lotts;
+    GemmPlan pl;
+    GemmParams p;
+    const int rc = prepare(M, N, K, X, ldx, W, ldw, Y, ldy, workspace, workspace_bytes, &pl, &p);
+    return rc != LOTTS_OK ? rc : launch_plan(pl, (hipStream_t)stream, p);
+}
+
+extern "C" int skinny_gemm_append(int32_t B, int32_t k, int32_t Hkv, int32_t D, int32_t N, int32_t K, const void* X, int64_t ldx,
+                                  const void* W, int64_t ldw, void* Y, int64_t ldy, void* Kpriv, void* Vpriv, int64_t priv_stride_b,
+                                  int64_t priv_stride_h, int64_t priv_stride_t, int32_t Lmax, const int32_t* priv_len, void* workspace,
+                                  size_t workspace_bytes, void* stream) {
+    using namespace lotts;
+    if (B < 1 || B > kGemmMaxM || k < 0 || k > 255 || Hkv < 1 || D < 8 || (D % 8) || 2LL * Hkv * D > N || Lmax < k + 1) return LOTTS_ERR_SHAPE;
+    if (!Kpriv || !Vpriv || !priv_len) return LOTTS_ERR_NULL;
+    for (int64_t s : {priv_stride_b, priv_stride_h, priv_stride_t})
+        if (s < 0 || (s % 8)) return LOTTS_ERR_SHAPE;
+    if (priv_stride_t < D || (ldy % 8) || (((uintptr_t)Y | (uintptr_t)Kpriv | (uintptr_t)Vpriv) & 15)) return LOTTS_ERR_SHAPE;
+    GemmPlan pl;
+    GemmAppendParams p;
+    int rc = prepare(B * (k + 1), N, K, X, ldx, W, ldw, Y, ldy, workspace, workspace_bytes, &pl, &p);
+    if (rc != LOTTS_OK) return rc;
+    const int n_new = N - 2 * Hkv * D;
+    // The stream kernel writes Y itself only where K is not split: matrices beyond the direct form with 129 blocks of rows or more, or
+    // short in K.  There the append stays its own launch, 4 us behind a product of 25 and more, and the kernel without a twin.
+    if (pl.form != kDirect && pl.ksplit == 1) {
+        rc = launch_plan<GemmParams>(pl, (hipStream_t)stream, p);
+        if (rc != LOTTS_OK) return rc;
+        const __bf16* fresh = static_cast<const __bf16*>(Y) + n_new;
+        return kv_append(B, k, Hkv, D, LOTTS_BF16, fresh, fresh + (long long)Hkv * D, (k + 1) * ldy, ldy, D, Kpriv, Vpriv, priv_stride_b,
+                         priv_stride_h, priv_stride_t, Lmax, priv_len, stream);
+    }
+    p.a = {static_cast<__bf16*>(Kpriv), static_cast<__bf16*>(Vpriv), priv_len, priv_stride_b, priv_stride_h, priv_stride_t,
+           n_new, D, Hkv, k + 1, Lmax, fast_div(k + 1), fast_div(D)};
+    return launch_plan(pl, (hipStream_t)stream, p);
 }

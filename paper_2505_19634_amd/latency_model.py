@@ -9,8 +9,8 @@ search is exercised end to end on real MI355X latencies.  Nothing here is one of
 experiments.
 
 Verify step of the target model for B branches and gamma drafts (M = B * (gamma + 1) new tokens):
-per layer QKV projection, append of the new K and V rows to the caches, attention, O projection, gate+up
-and down projections (skinny_gemm, kv_append and verify_attention, one layer's buffers timed and
+per layer QKV projection with the append of the new K and V rows to the caches, attention, O projection, gate+up
+and down projections (skinny_gemm_append, skinny_gemm and verify_attention, one layer's buffers timed and
 multiplied by the layer count), then the LM head and the acceptance from logits.  Norms, rotary
 embedding and activation are not modelled (they are outside this library); the draft model's gamma sequential steps cost `draft_ratio` times a
 one-token step of the target each (an assumption: a draft model a tenth of the target's size).
@@ -96,14 +96,16 @@ class StepTimer:
         s, R = self.s, gamma + 1
         assert 1 <= B <= self.max_B and 0 <= gamma <= self.max_gamma and private + R <= self.Lmax
         M = B * R
-        layer = sum(self._gemm_ms(M, self.W[n]) for n in ("qkv", "o", "gate_up", "down"))
+        layer = sum(self._gemm_ms(M, self.W[n]) for n in ("o", "gate_up", "down"))
         Q = torch.zeros((B, R, s.Hq, s.D), dtype=torch.bfloat16, device=self.dev)
         pl = torch.full((B,), private + R, dtype=torch.int32, device=self.dev)
         args = (Q, self.Kpre, self.Vpre, self.Kpriv[:B], self.Vpriv[:B], pl)
         layer += self._timed(lambda: binding.verify_attention(*args))
-        heads = torch.zeros((B, R, s.Hq + 2 * s.Hkv, s.D), dtype=torch.bfloat16, device=self.dev)
-        layer += self._timed(lambda: binding.kv_append(heads[:, :, s.Hq:s.Hq + s.Hkv], heads[:, :, s.Hq + s.Hkv:],
-                                                       self.Kpriv[:B], self.Vpriv[:B], pl))
+        X = torch.zeros((M, s.hidden), dtype=torch.bfloat16, device=self.dev)
+        for b0 in range(0, B, 256 // R):  # whole branches, at most 256 tokens a call
+            b1 = min(B, b0 + 256 // R)
+            layer += self._timed(lambda: binding.skinny_gemm_append(X[b0 * R:b1 * R], self.W["qkv"], self.Kpriv[b0:b1],
+                                                                    self.Vpriv[b0:b1], pl[b0:b1]))
         head = self._gemm_ms(M, self.W["lm_head"])
         zt = torch.zeros((B, R, s.V), dtype=torch.bfloat16, device=self.dev)
         zd = torch.zeros((B, gamma, s.V), dtype=torch.bfloat16, device=self.dev) if gamma else None
@@ -118,9 +120,8 @@ class StepTimer:
 class FullModel:
     """Every layer of a decoder shape resident on one GPU -- its bf16 weights (62 GB for the 32B shape) and the KV
     caches of B branches, each layer its own memory -- and one verify step of the whole stack as one captured graph:
-    per layer the QKV projection, kv_append of its K and V columns to the caches, verify_attention on its Q columns, the
-    O projection, gate+up, and
-    down on the first half of gate+up's output (norms, rotary embedding and activation are outside this
+    per layer the QKV projection, which appends its K and V columns to the caches, verify_attention on its Q columns, the
+    O projection, gate+up, and down on the first half of gate+up's output (norms, rotary embedding and activation are outside this
     library, so the values that flow are not a language model's; the shapes, the memory traffic and the launch
     sequence are), then the LM head and the acceptance from logits.  Replaying the graph gives the step's device
     time with the gaps between launches and with nothing left in a cache by an earlier use of the same weights:
@@ -170,8 +171,7 @@ class FullModel:
         s, M = self.s, self.B * self.R
         h = self.h
         for L in self.layers:
-            binding.skinny_gemm(h, L["qkv"], out=self.qkv, workspace=self.ws_gemm)
-            binding.kv_append(self.k_view, self.v_view, L["Kpriv"], L["Vpriv"], self.priv_len)
+            binding.skinny_gemm_append(h, L["qkv"], L["Kpriv"], L["Vpriv"], self.priv_len, out=self.qkv, workspace=self.ws_gemm)
             binding.verify_attention(self.q_view, L["Kpre"], L["Vpre"], L["Kpriv"], L["Vpriv"], self.priv_len,
                                      out=self.attn, workspace=self.ws_attn)
             binding.skinny_gemm(self.attn.view(M, s.Hq * s.D), L["o"], out=self.o, workspace=self.ws_gemm)

@@ -252,3 +252,19 @@ def test_the_extension_is_for_this_interpreter_and_this_torch(lib, monkeypatch):
     monkeypatch.setattr(torch, "__version__", "0.0.1")
     with pytest.raises(ImportError, match="built for torch .*, this is 0.0.1: run paper_2505_19634_amd/build.py"):
         binding.load()
+
+
+def test_append_in_the_projection_is_rejected_before_any_launch(lib):
+    one, big = ctypes.c_void_p(4096), 1 << 30
+    names = ("B", "k", "H", "D", "N", "K", "X", "ldx", "W", "ldw", "Y", "ldy", "kp", "vp", "pb", "ph", "pt", "Lmax", "pl", "ws", "wsb")
+    ok = (4, 3, 2, 128, 2560, 2048, one, 2048, one, 2048, one, 2560, one, one, 2 * 512 * 128, 512 * 128, 128, 512, one, one, big)
+    bad = lambda **kw: lib.skinny_gemm_append(*[kw.get(n, v) for n, v in zip(names, ok)], None)
+    for n in ("X", "W", "Y", "kp", "vp", "pl", "ws"):
+        assert bad(**{n: None}) == -1, n
+    for kw in (dict(B=0), dict(B=257, k=0), dict(B=64, k=4), dict(k=-1), dict(k=256, B=1), dict(H=0), dict(D=4), dict(D=12), dict(H=11),
+               dict(Lmax=3), dict(N=2556), dict(K=2000), dict(ldx=2040), dict(ldw=2052), dict(ldy=2564), dict(ldy=2552), dict(pb=-8),
+               dict(ph=100), dict(pt=120), dict(pt=132)):
+        assert bad(**kw) == -2, kw
+    for n in ("X", "W", "Y", "kp", "vp", "ws"):
+        assert bad(**{n: ctypes.c_void_p(4096 + 8)}) == -2, n
+    assert bad(N=7168, K=5120, ldx=5120, ldw=5120, ldy=7168, wsb=16) == -4          # K split: partials in the workspace
