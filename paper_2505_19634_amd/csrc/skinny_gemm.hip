@@ -7,7 +7,7 @@
 //       in steps of half a chunk (64 k); W and X both go from global memory straight into LDS stages, with no registers
 //       in between; Y^T[n][m] accumulates in registers over the whole K range.  Three forms: 256 weight rows (eight
 //       wavefronts side by side), 128 (four) and 64 (two row wavefronts x two groups that share every stage and take half
-//       of its k each; their accumulators are added up through LDS at the end).
+//       of its k each; their accumulators are added up through LDS at the end).  PARTS: 128 weight rows and half of the tokens.
 //   skinny_gemm_reduce_kernel  only when K is split across workgroups (few weight rows): sums the fp32
 //       partials in a fixed order and converts.
 //   skinny_gemm_direct_kernel<RN, TT, WAVES, UB>  small matrices: a workgroup owns 16 * RN weight rows and 16 * TT tokens for
@@ -34,22 +34,35 @@ constexpr int kGemmTileFloats = 32 * 32;  // one accumulator tile: 32 weight row
 // 162; 28672 x 4096 49.5 / 48.9 / 65.3 -> 37.5 / 37.9 / 62.7; 22016 x 2048 19.3 / 20.4 / 31.4 -> 17.4 / 18.7 / 31.7.  At other strides
 // it gives nothing and X is shared worse (55296 x 5120 87.1 / 128 -> 88.9 / 131 us at 40 / 192 tokens; 33280 x 3072 level).
 constexpr int kStaggerStride = 2048;
+// Bytes of X from which the workgroups of an XCD are given a run of the K splits instead of every eighth block of all of them, so that its
+// 4 MB of L2 see only their share of X.  Staggered blocks walk that share at different places: 8192 x 28672 at 80 / 96 / 128 / 192 tokens
+// 93.6 / 103 / 129 / 166 us, dealt by runs 93.8 / 92 / 95 / 115; below the line 4096 x 14336 at 96 tokens 30.8 / 32.0.  Unstaggered blocks pass
+// X in step: dealt by runs, all of an XCD are at the same lines at once (7168 x 5120 at 192 tokens 28.7 -> 32.1, 5120 x 27648 level), so
+// they stay as they were -- but for two token parts, which have twice the workgroups at X: 1024 x 18944 at 174 tokens 22.7 -> 20.8, 2048 x
+// 28672 at 230 52.7 -> 47.7, while 920 x 10240 at 218 tokens (4.5 MB) 17.3 -> 18.9.
+constexpr long long kXcdTokens = 5 << 20;
+constexpr int kPartsMaxK = 12288;         // two token parts from 129 tokens up to this K, from 161 beyond
 constexpr int kGemmOutRow = 80;           // bytes per token row of a 32 x 32 bf16 tile on its way out through LDS (64 + pad)
 
 struct GemmParams {  // (in the order in which the kernels come to need it)
     const __bf16 *X, *W;
     long long ldx, ldw;
     int M, N, K;
-    int tokens;  // direct: tokens a workgroup owns
+    int tokens;  // direct form, and stream forms with two token parts: tokens a workgroup owns
     int ksplit;
     int rows;     // weight rows a wavefront owns: 32, or fewer (a multiple of 4) when that fills the chip better
     FastDiv d_ksplit;           // by ksplit
+    FastDiv d_nblocks;          // by nblocks
     FastDiv d_steps[2];         // by the half-chunk steps of a K split: all splits have one of two numbers of them, 2 apart
     int stagger;                // stream forms: blocks start their K loop at different steps
-    int nblocks, roww, rt, tt;  // launch geometry, for the reduce kernel: blocks, row wavefronts, row / token tiles per wavefront
+    int nblocks;                // blocks of weight rows
+    short items;                // blocks x K splits
+    bool by_xcd;                // each XCD takes a run of them
+    unsigned char parts;        // token parts (1 or 2)
+    unsigned char roww, rt, tt; // for the reduce kernel: row wavefronts, row / token tiles per wavefront
     __bf16* Y;
     long long ldy;
-    float* part;  // fp32 partials when ksplit > 1: [ksplit][block of weight rows][row wavefront][tile][quad][lane] float4
+    float* part;  // fp32 partials when ksplit > 1: [ksplit][token part][block of weight rows][row wavefront][tile][quad][lane] float4
 };
 
 // Where the K and V columns of a QKV projection go beside Y: token m = b * R + r of branch b to position len[b] - R + r of its caches.
@@ -89,7 +102,7 @@ struct GemmPlan {
     GemmForm form;
     int mt, rt;            // stream forms: token tiles of 32; row tiles per wavefront (2: pairs split the token tiles)
     int rows, roww;        // weight rows per wavefront; wavefronts side by side over the rows
-    int nblocks, ksplit;
+    int nblocks, ksplit, parts;
     int rn, tt, nby;       // direct: 16-row and 16-token tiles per workgroup, workgroups over the tokens
 };
 
@@ -158,6 +171,15 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl, double* fill
 //     against 13.2.  Beyond K = 4096 the wavefronts wait for their loads in batches: 5120 x 5120 at 1 token 19.8 us against 13.8.
 //   256-row stream form: more than 256 blocks of 128 rows; an X chunk in LDS serves the most rows.  55296 x 5120 at 64
 //     tokens 92 us, 128-row form 104.
+//   Two token parts, N <= 4608 and more than 128 tokens: blocks of 128 rows x half of the tokens instead of 64 x all, as many K splits.
+//     A unit takes in W and X at some 50 KB/us together, and 128 + M / 2 rows are fewer than 64 + M; the parts of a block lie on one
+//     XCD, side by side, and W comes from HBM once.  2048 x 11008 at 144 / 192 / 256 tokens 22.2 / 23.7 / 27.4 -> 21.1 / 23.0 / 25.1 us; 4608 x
+//     4480 22.4 / 25.6 / 28.6 -> 20.7 / 22.2 / 24.8; 50 sizes of K > 4096 17 % faster.  With a K beyond 12288 and up to 160 tokens level or
+//     slower (3584 x 18944 at 144 tokens 46.7 -> 48.0), with up to 128 tokens too (3264 x 14336 at 123 31.5 -> 36.7).  The same for more rows, 256 x
+//     half of the tokens without a split, loses (22016 x 2048 at 160 / 192 tokens 27.5 / 29.6 -> 29.9 / 30.6).  Beside it the direct form stays
+//     while 0.03 us per KB are below 4.75 us + 0.1 us per MB of W + 6.5e-6 us per token and (N + K): fitted to 141 sizes, 0.33 % over the better
+//     form (the line above: 1.7 %), with 2560 x 2048 at 192 tokens held in the direct form, 14.5 us against 13.8 (let go, 0.05 %).
+//     2184 x 2304 at 245 tokens 18.4 -> 16.0 us, 1536 x 4096 at 244 18.4 -> 14.5.
 //   128-row form below that, 64-row form when it would have to be split more than sevenfold (N <= 4608): the fewer splits,
 //     the fewer fp32 partials, but the more often a unit reads X.  2048 x 11008 at 40 / 192 tokens in 64-row blocks x 8
 //     splits 14.8 / 24.3 us, 128 x 16 17.1 / 26.5; 5120 x 5120 at 64 / 192 tokens 128 x 6 17.9 / 26.0, 64 x 3 17.4 / 28.6; 6144 x 6144
@@ -168,17 +190,19 @@ static inline GemmPlan plan_gemm(int M, int N, int K, bool may_be_direct = true)
     pl.mt = (M + 31) / 32;
     // An even number of token tiles from 4 on: pairs of wavefronts own two row tiles together and half of the token tiles each.
     pl.rt = pl.mt >= 4 && pl.mt % 2 == 0 ? 2 : 1;
-    pl.ksplit = 1;
+    pl.ksplit = pl.parts = 1;
+    const int nb128 = (N + 127) / 128, ks_parts = plan_ksplit(2 * nb128, chunks);
+    const bool parts = nb128 <= 36 && M > (K <= kPartsMaxK ? 128 : 160) && ks_parts > 1;
     if (may_be_direct && K <= 4096 && N <= 8192) {
         double filled;
         const double kb = plan_direct(M, N, K, &pl, &filled), mb = 2e-6 * N * K, tokens = 1e-6 * M * (N + K);
         auto ahead = [&](double k) { return 3.4 + 0.022 * k + 0.14 * mb < 7.0 + 0.125 * mb + 7.0 * tokens; };
-        if (kb > 0.0 && (ahead(filled) || (ahead(kb) && 0.034 * kb + 0.15 * mb < (pl.rn == 4 ? 6.3 : 6.7) + 10.0 * tokens))) {
+        if (kb > 0.0 && (parts ? 0.03 * kb < 4.75 + 0.1 * mb + 6.5 * tokens
+                               : ahead(filled) || (ahead(kb) && 0.034 * kb + 0.15 * mb < (pl.rn == 4 ? 6.3 : 6.7) + 10.0 * tokens))) {
             pl.form = kDirect;
             return pl;
         }
     }
-    const int nb128 = (N + 127) / 128;
     if (nb128 > kNumCU) {
         pl.form = kStream256;
         pl.roww = 8;
@@ -192,6 +216,14 @@ static inline GemmPlan plan_gemm(int M, int N, int K, bool may_be_direct = true)
         pl.roww = 4;
         pl.ksplit = plan_ksplit(nb128, chunks);
         pl.rows = pl.ksplit == 1 ? plan_rows(N, 4, pl.mt) : kGemmRows;
+    } else if (parts) {
+        pl.form = kStream128;
+        pl.roww = 4;
+        pl.rows = kGemmRows;
+        pl.parts = 2;
+        pl.ksplit = ks_parts;
+        pl.mt = ((M + 1) / 2 + 31) / 32;
+        pl.rt = pl.mt == 4 ? 2 : 1;
     } else {
         pl.form = kStream64;
         pl.roww = 2;
@@ -204,7 +236,7 @@ static inline GemmPlan plan_gemm(int M, int N, int K, bool may_be_direct = true)
 
 // Workspace of a plan: the fp32 partials of its K splits, 256 bytes at least.
 static inline size_t plan_bytes(const GemmPlan& pl) {
-    const size_t bytes = pl.ksplit > 1 ? sizeof(float) * pl.ksplit * pl.nblocks * pl.roww * pl.mt * kGemmTileFloats : 0;
+    const size_t bytes = pl.ksplit > 1 ? sizeof(float) * pl.ksplit * pl.parts * pl.nblocks * pl.roww * pl.mt * kGemmTileFloats : 0;
     return bytes < 256 ? 256 : bytes;
 }
 
@@ -246,7 +278,7 @@ static inline size_t plan_bytes(const GemmPlan& pl) {
 // way; Y tiles turn through LDS into 64-byte row pieces.  With the forms above (before: 128 / 256 rows only), reduce launch
 // included, 40 / 192 tokens: 2048 x 11008 20.2 / 34.5 -> 16.8 / 24.5 us; 7168 x 5120 21.5 / 40 -> 20.0 / 29.7; 22016 x 2048
 // 25.4 / 41.5 -> 21.6 / 31.0 (with what came since 14.8 / 24.3, 19.2 / 29.9, 18.8 / 31.7).
-template <int MT, int RT, int WAVES, int KG, int XS>
+template <int MT, int RT, int WAVES, int KG, int XS, bool PARTS = false>
 __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(const GemmParams p) {
     static_assert(RT == 1 || (RT == 2 && MT % 2 == 0), "a pair of wavefronts splits the token tiles evenly");
     constexpr int WS = XS + 1;        // W stages
@@ -269,18 +301,33 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
     // RT = 1: row wavefront w owns row tile w and all tokens.  RT = 2: row wavefronts 2j and 2j + 1 own row tiles 2j and
     // 2j + 1 together, each half of the token tiles, and share the W stages of their 64 rows.
     const int grp = RT == 1 ? wr : wr >> 1, th = RT == 1 ? 0 : wr & 1;
-    const int n0 = blockIdx.x * (p.rows * ROWW) + grp * (p.rows * RT);  // pairs always own 2 x 32 rows
+    int block = blockIdx.x, split = blockIdx.y, part = 0;
+    if (PARTS || p.by_xcd) {  // workgroups of one XCD, in the order in which they start: both parts of an item, then its next one
+        const int xcd = blockIdx.x % kNumXCD, i = (int)blockIdx.x / (PARTS ? 2 * kNumXCD : kNumXCD);
+        part = PARTS ? (int)(blockIdx.x / kNumXCD) & 1 : 0;
+        int item = i * kNumXCD + xcd, end = p.items;  // of the list [split][block]: every eighth one,
+        if (p.by_xcd) {                               // or a run of it
+            const int each = p.items / kNumXCD, more = p.items % kNumXCD, first = xcd * each + min(xcd, more);
+            item = first + i;
+            end = first + each + (xcd < more);
+        }
+        if (item >= end) return;
+        split = quot(item, p.d_nblocks);
+        block = item - split * p.nblocks;
+    }
+    const int M = PARTS ? p.tokens : p.M, m0 = part ? p.M - p.tokens : 0;  // the second part starts early enough to be as long as the first
+    const int n0 = block * (p.rows * ROWW) + grp * (p.rows * RT);  // pairs always own 2 x 32 rows
     const int chunks = p.K / kGemmChunk;
     // (Through host-made divisors: the run-time divisions here, two of them of 64 bits, stood 0.5 us in front of the first load.)
-    const int c_lo = quot(blockIdx.y * chunks, p.d_ksplit);
-    const int c_hi = quot((blockIdx.y + 1) * chunks, p.d_ksplit);
+    const int c_lo = quot(split * chunks, p.d_ksplit);
+    const int c_hi = quot((split + 1) * chunks, p.d_ksplit);
     const int G = 2 * (c_hi - c_lo);  // half-chunk steps
     // Staggered start: block x begins 5 x steps into its K range and wraps around; the pointers go back once, at that step.  (A
     // select of the offset in every transfer instead cost 2 % of 55296 x 5120.)
     int first = 0;
     if (p.stagger && G > 0) {
         const FastDiv d = G == 2 * quot(chunks, p.d_ksplit) ? p.d_steps[0] : p.d_steps[1];
-        const int turn = (int)blockIdx.x * 5, at = turn + quot(turn, d);
+        const int turn = block * 5, at = turn + quot(turn, d);
         first = at - quot(at, d) * G;
     }
     const int wrap = first > 0 ? G - first : -1;  // the step that is back at the start of the range
@@ -296,8 +343,8 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
 #pragma unroll
     for (int i = 0; i < XI; ++i) {
         const int r = (wave + i * WAVES) * 8 + l_row;
-        const int m = r < p.M ? r : p.M - 1;
-        x_src[i] = p.X + (long long)m * p.ldx + (long long)c_lo * kGemmChunk + first * 64 + (l_slot ^ ((r >> 1) & 7)) * 8;
+        const int m = r < M ? r : M - 1;
+        x_src[i] = p.X + (long long)(m0 + m) * p.ldx + (long long)c_lo * kGemmChunk + first * 64 + (l_slot ^ ((r >> 1) & 7)) * 8;
     }
 #pragma unroll
     for (int i = 0; i < WI; ++i) {
@@ -317,7 +364,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
 #pragma unroll
         for (int i = 0; i < XI; ++i) {
             const int j = wave + i * WAVES;
-            if ((i + 1) * WAVES <= XINSTR - 3 || j * 8 < p.M) {  // (all but the last 3 are rows of tokens that exist)
+            if ((i + 1) * WAVES <= XINSTR - 3 || j * 8 < M) {  // (all but the last 3 are rows of tokens that exist)
                 const unsigned lds_base = __builtin_amdgcn_readfirstlane(
                     (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)(stage + j * 8 * kStageRow));
                 asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
@@ -337,10 +384,16 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
         for (int i = 0; i < WI; ++i) {
             const unsigned lds_base = __builtin_amdgcn_readfirstlane(
                 (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)(stage + (kgrp * WI + i) * 8 * kStageRow));
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
-                         :
-                         : "v"(w_src[i] + (long long)g * 64), "s"(lds_base)
-                         : "m0");
+            if (PARTS)
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                             :
+                             : "v"(w_src[i] + (long long)g * 64), "s"(lds_base)
+                             : "m0");
+            else
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
+                             :
+                             : "v"(w_src[i] + (long long)g * 64), "s"(lds_base)
+                             : "m0");
         }
     };
 #pragma clang diagnostic pop
@@ -445,13 +498,13 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
     }
     // register i of accumulator (r, t) of this lane: output row m = (th * TT + t) * 32 + ln,
     // column n = n0 + r * 32 + (i / 4) * 8 + hh * 4 + i % 4
-    if (p.ksplit > 1) {
+    if (PARTS || p.ksplit > 1) {
         float4* dst = reinterpret_cast<float4*>(p.part) +
-                      ((long long)(blockIdx.y * gridDim.x + blockIdx.x) * ROWW + wr) * (TILES * TILE_Q) + lane;
+                      ((long long)((split * (PARTS ? 2 : 1) + part) * p.nblocks + block) * ROWW + wr) * (TILES * TILE_Q) + lane;
 #pragma unroll
         for (int j = 0; j < TILES; ++j) {
             if (KG > 1 && j % KG != kgrp) continue;
-            if ((th * TT + j % TT) * 32 + ln >= p.M) continue;
+            if ((th * TT + j % TT) * 32 + ln >= M) continue;
             const g_f32x16& a = acc[j / TT][j % TT];
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
@@ -468,7 +521,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
     for (int j = 0; j < TILES; ++j) {
         if (KG > 1 && j % KG != kgrp) continue;
         const int m_base = (th * TT + j % TT) * 32;
-        if (m_base >= p.M) continue;
+        if (m_base >= M) continue;
         const g_f32x16& a = acc[j / TT][j % TT];
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
@@ -482,7 +535,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void skinny_gemm_stream_kernel(co
         for (int i = 0; i < 4; ++i) {
             const int ml = i * 8 + (lane >> 3);
             const g_bf16x4 o = *reinterpret_cast<const g_bf16x4*>(tr + ml * kGemmOutRow + nc * 2);
-            if (m_base + ml < p.M && n < p.N && (RT > 1 || nc < p.rows))  // N a multiple of 8: 4 columns are in or out together
+            if (m_base + ml < M && n < p.N && (RT > 1 || nc < p.rows))  // N a multiple of 8: 4 columns are in or out together
                 *reinterpret_cast<g_bf16x4*>(p.Y + (long long)(m_base + ml) * p.ldy + n) = o;
         }
     }
@@ -495,18 +548,19 @@ __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const P p) {
     __shared__ __attribute__((aligned(16))) unsigned char tr[32 * kGemmOutRow];
     const int tiles = p.rt * p.tt;
     const int j = blockIdx.x % tiles, wb = blockIdx.x / tiles;
-    const int wr = wb % p.roww, block = wb / p.roww;
+    const int wr = wb % p.roww, blocks = wb / p.roww, part = blocks / p.nblocks, block = blocks - part * p.nblocks;
+    const int M = p.parts > 1 ? p.tokens : p.M, m0 = part ? p.M - p.tokens : 0;
     const int grp = p.rt == 1 ? wr : wr >> 1, th = p.rt == 1 ? 0 : wr & 1;
     const int m_base = (th * p.tt + j % p.tt) * 32;
     const int n_base = block * (p.rows * p.roww) + grp * (p.rows * p.rt) + (j / p.tt) * 32;
-    if (m_base >= p.M || n_base >= p.N) return;  // uniform over the workgroup
+    if (m_base >= M || n_base >= p.N) return;  // uniform over the workgroup
     const int q4 = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1), ln = lane & 31, hh = lane >> 5;
-    const bool in = m_base + ln < p.M && (p.rt > 1 || q4 * 8 < p.rows);  // what the stream kernel has stored
-    const int ml = threadIdx.x >> 3, nc = (threadIdx.x & 7) * 4, m = m_base + ml, n = n_base + nc;
+    const bool in = m_base + ln < M && (p.rt > 1 || q4 * 8 < p.rows);  // what the stream kernel has stored
+    const int ml = threadIdx.x >> 3, nc = (threadIdx.x & 7) * 4, m = m0 + m_base + ml, n = n_base + nc;
     int t = -1;
     if constexpr (kAppends<P>)
         if (n_base + 32 > p.a.n_new) t = append_position(p.a, min(m, p.M - 1));
-    const long long stride = (long long)p.nblocks * p.roww * tiles * (kGemmTileFloats / 4);
+    const long long stride = (long long)p.nblocks * p.parts * p.roww * tiles * (kGemmTileFloats / 4);
     const float4* src = reinterpret_cast<const float4*>(p.part) + (long long)blockIdx.x * (kGemmTileFloats / 4) + threadIdx.x;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     if (in) {
@@ -532,7 +586,7 @@ __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const P p) {
     o[3] = (__bf16)s.w;
     *reinterpret_cast<g_bf16x4*>(tr + ln * kGemmOutRow + (q4 * 8 + hh * 4) * 2) = o;
     __syncthreads();
-    if (m < p.M && n < p.N && (p.rt > 1 || nc < p.rows)) {
+    if (m_base + ml < M && n < p.N && (p.rt > 1 || nc < p.rows)) {
         const g_bf16x4 y = *reinterpret_cast<const g_bf16x4*>(tr + ml * kGemmOutRow + nc * 2);
         *reinterpret_cast<g_bf16x4*>(p.Y + (long long)m * p.ldy + n) = y;
         if constexpr (kAppends<P>) append_store(p.a, m, t, n, y);
@@ -657,6 +711,13 @@ static void launch_stream(int mt, dim3 grid, hipStream_t s, const GemmParams& p)
     }
 }
 
+template <int WAVES, int KG, int XS>
+static void launch_parts(int mt, dim3 grid, hipStream_t s, const GemmParams& p) {
+    const dim3 block(WAVES * kWave);
+    if (mt == 3) LOTTS_LAUNCH((skinny_gemm_stream_kernel<3, 1, WAVES, KG, XS, true>), grid, block, s, p);
+    else LOTTS_LAUNCH((skinny_gemm_stream_kernel<4, 2, WAVES, KG, XS, true>), grid, block, s, p);
+}
+
 template <int RN, int TT, int WAVES, int UB, typename P>
 static void launch_direct(dim3 grid, hipStream_t s, const P& p) {
     const dim3 block(WAVES * kWave);
@@ -679,10 +740,13 @@ static int prepare(int M, int N, int K, const void* X, int64_t ldx, const void* 
     p.Y = static_cast<__bf16*>(Y);
     p.part = static_cast<float*>(workspace);
     p.M = M; p.N = N; p.K = K; p.ksplit = pl.ksplit; p.rows = pl.rows;
-    p.nblocks = pl.nblocks; p.roww = pl.roww; p.rt = pl.rt; p.tt = pl.mt / pl.rt;
+    p.nblocks = pl.nblocks; p.roww = pl.roww; p.rt = pl.rt; p.tt = pl.mt / pl.rt; p.parts = pl.parts;
     p.stagger = ldw % kStaggerStride == 0;
-    p.tokens = pl.form == kDirect ? (M + pl.nby - 1) / pl.nby : 0;
+    p.by_xcd = pl.ksplit > 1 && (pl.parts > 1 || p.stagger) && 2LL * M * K > kXcdTokens;
+    p.items = (short)(pl.ksplit > 1 ? pl.nblocks * pl.ksplit : 0);
+    p.tokens = pl.form == kDirect ? (M + pl.nby - 1) / pl.nby : (M + pl.parts - 1) / pl.parts;
     p.d_ksplit = fast_div(pl.ksplit);
+    p.d_nblocks = fast_div(pl.nblocks);
     const int steps = 2 * (K / kGemmChunk / pl.ksplit);  // of the shorter splits
     p.d_steps[0] = fast_div(steps > 0 ? steps : 1);
     p.d_steps[1] = fast_div(steps + 2);
@@ -693,10 +757,15 @@ static int prepare(int M, int N, int K, const void* X, int64_t ldx, const void* 
 // The launches of a plan: the one that writes Y gets p as it is.
 template <typename P>
 static int launch_plan(const GemmPlan& pl, hipStream_t s, const P& p) {
-    const dim3 grid(pl.nblocks, pl.form == kDirect ? pl.nby : pl.ksplit);
+    const dim3 grid = p.by_xcd || pl.parts > 1 ? dim3((p.items + kNumXCD - 1) / kNumXCD * kNumXCD * pl.parts)
+                                               : dim3(pl.nblocks, pl.form == kDirect ? pl.nby : pl.ksplit);
     switch (pl.form) {
-        case kStream256: launch_stream<8, 1, 2, 2>(pl.mt, grid, s, p); break;
-        case kStream128: launch_stream<4, 1, 2, 2>(pl.mt, grid, s, p); break;
+        case kStream256:
+            launch_stream<8, 1, 2, 2>(pl.mt, grid, s, p);
+            break;
+        case kStream128:
+            if (pl.parts > 1) launch_parts<4, 1, 2>(pl.mt, grid, s, p);
+            else launch_stream<4, 1, 2, 2>(pl.mt, grid, s, p); break;
         case kStream64: launch_stream<4, 2, 4, 2>(pl.mt, grid, s, p); break;
         case kDirect:
             switch (pl.rn * 10 + pl.tt) {
@@ -712,7 +781,7 @@ static int launch_plan(const GemmPlan& pl, hipStream_t s, const P& p) {
     }
     const int rc = check_launch();
     if (rc != LOTTS_OK || pl.ksplit == 1) return rc;
-    LOTTS_LAUNCH(skinny_gemm_reduce_kernel<P>, dim3((unsigned)(pl.nblocks * pl.roww * pl.mt)), dim3(256), s, p);
+    LOTTS_LAUNCH(skinny_gemm_reduce_kernel<P>, dim3((unsigned)(pl.parts * pl.nblocks * pl.roww * pl.mt)), dim3(256), s, p);
     return check_launch();
 }
 

@@ -45,3 +45,16 @@ def test_every_form(oracle, M, N, K):
     assert (np.abs(y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-3).all(), np.abs(y - ref).max()
     assert np.linalg.norm(y - ref) / np.linalg.norm(ref) <= 3e-3
     assert bool((out[M:] == 7.0).all()) and bool((out[:, N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K", [
+    # two token parts: tokens of the parts in 3 and 4 tiles, odd tokens (the parts overlap by one), blocks 1 .. 36, ragged rows, short K splits
+    (129, 8, 4224), (130, 136, 4480), (161, 264, 5248), (191, 1288, 4352), (192, 2048, 4224), (193, 2056, 4480), (223, 520, 6144), (255, 4600, 4224),
+    (256, 4608, 4352), (256, 128, 8320), (157, 1032, 2944), (251, 1344, 3072), (129, 3592, 1536), (247, 2304, 2048),
+    # either side of K = 12288 and 160 tokens
+    (160, 264, 12288), (160, 264, 12416), (161, 264, 12416),
+    # more than 5 MB of X, the XCDs with runs of the list: two parts, staggered and not; one part, staggered
+    (256, 72, 10368), (255, 1160, 10368), (250, 264, 12288), (193, 520, 14336), (177, 136, 16384), (128, 264, 22528), (97, 72, 28672), (150, 520, 18432),
+])
+def test_token_parts_and_runs_by_xcd(oracle, M, N, K):
+    test_every_form(oracle, M, N, K)
