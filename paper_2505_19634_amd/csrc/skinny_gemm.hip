@@ -14,6 +14,8 @@
 //       the WHOLE K range, its wavefronts a share of K each; no partials, no second launch.
 // skinny_gemm_append, for the QKV projection, also puts its K and V columns into the branches' caches: the kernel that writes Y (the
 // direct or the reduce kernel) stores them twice.
+#include <algorithm>
+
 #include "lotts_common.h"
 
 namespace lotts {
@@ -42,6 +44,7 @@ constexpr int kStaggerStride = 2048;
 // 28672 at 230 52.7 -> 47.7, while 920 x 10240 at 218 tokens (4.5 MB) 17.3 -> 18.9.
 constexpr long long kXcdTokens = 5 << 20;
 constexpr int kPartsMaxK = 12288;         // two token parts from 129 tokens up to this K, from 161 beyond
+static inline int tokens_in_one_part(int K) { return K <= kPartsMaxK ? 128 : 160; }
 constexpr int kGemmOutRow = 80;           // bytes per token row of a 32 x 32 bf16 tile on its way out through LDS (64 + pad)
 
 struct GemmParams {  // (in the order in which the kernels come to need it)
@@ -192,7 +195,7 @@ static inline GemmPlan plan_gemm(int M, int N, int K, bool may_be_direct = true)
     pl.rt = pl.mt >= 4 && pl.mt % 2 == 0 ? 2 : 1;
     pl.ksplit = pl.parts = 1;
     const int nb128 = (N + 127) / 128, ks_parts = plan_ksplit(2 * nb128, chunks);
-    const bool parts = nb128 <= 36 && M > (K <= kPartsMaxK ? 128 : 160) && ks_parts > 1;
+    const bool parts = nb128 <= 36 && M > tokens_in_one_part(K) && ks_parts > 1;
     if (may_be_direct && K <= 4096 && N <= 8192) {
         double filled;
         const double kb = plan_direct(M, N, K, &pl, &filled), mb = 2e-6 * N * K, tokens = 1e-6 * M * (N + K);
@@ -788,10 +791,14 @@ static int launch_plan(const GemmPlan& pl, hipStream_t s, const P& p) {
 }  // namespace lotts
 
 // The query asks for the K splits of the stream form also where the direct form is taken: which one is faster changes back and forth with
-// the tokens, and a workspace sized for the most of them would be too small for fewer.
+// the tokens, and a workspace sized for the most of them would be too small for fewer.  The same where the tokens come to be in two parts:
+// 161 of them beside 3208 weight rows and K = 12416 have 2 % fewer bytes of partials than 160 in one part.
 extern "C" size_t skinny_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K) {
-    if (!lotts::gemm_sizes_ok(M, N, K)) return 0;
-    return lotts::plan_bytes(lotts::plan_gemm(M, N, K, false));
+    using namespace lotts;
+    if (!gemm_sizes_ok(M, N, K)) return 0;
+    const GemmPlan pl = plan_gemm(M, N, K, false);
+    const size_t bytes = plan_bytes(pl);
+    return pl.parts > 1 ? std::max(bytes, plan_bytes(plan_gemm(tokens_in_one_part(K), N, K, false))) : bytes;
 }
 
 extern "C" int skinny_gemm(int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,

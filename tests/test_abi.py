@@ -227,6 +227,14 @@ def test_gemm_workspace_grows_with_the_tokens(lib):
             assert sizes == sorted(sizes), (N, K)
 
 
+def test_gemm_workspace_grows_where_tokens_come_to_be_in_two_parts(lib):
+    need = lib.skinny_gemm_workspace_bytes
+    for N in list(range(8, 4680, 56)) + [64 * n for n in range(1, 73)] + [3208, 3256, 3264]:
+        for K in (1024, 4224, 12288, 12416, 28672):
+            sizes = [need(M, N, K) for M in (1, 33, 97, 127, 128, 129, 159, 160, 161, 192, 193, 256)]
+            assert sizes == sorted(sizes), (N, K)
+
+
 @pytest.mark.parametrize("built", [(), ("liblotts.so",)])
 def test_an_unbuilt_tree_says_so(tmp_path, built):
     """Without the library, or with the library alone, the import names what to run."""
