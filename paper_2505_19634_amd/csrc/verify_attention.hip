@@ -73,7 +73,7 @@ constexpr int kMaxCounters = 16384;  // 64-bit cells at the start of the workspa
 constexpr int kStartTiles = 8;
 // Flat plan: from this many tiles of each wavefront on (a build of the tests sets 0).
 #ifndef LOTTS_FLAT_STEPS
-#define LOTTS_FLAT_STEPS 17
+#define LOTTS_FLAT_STEPS 18
 #endif
 
 struct AttnPlan {
@@ -267,10 +267,11 @@ static inline AttnPlans plan_attention(const lotts_attn_desc& d) {
     // Branches of different lengths.  Fixed shares leave the longest branches' items behind: the host does not know the lengths, so the
     // number of shares cannot follow them.  In the flat plan the items deal a head's tiles among themselves on the device (see FlatCuts),
     // unless the lengths turn out to be alike, and then the same kernel runs the fixed shares.  Finding that out and being able to do either
-    // costs an item about 0.7 us, so it is for long calls only: from 17 tiles a wavefront on, 26 x 2 heads x 1086 + 2399 .. 9596 tokens 43.2 ->
+    // costs an item about 0.7 us, so it is for long calls only: from 18 tiles a wavefront on, 26 x 2 heads x 1086 + 2399 .. 9596 tokens 43.2 ->
     // 39.0 us, 19 x 4 x 1051 + 2722 .. 10890 67.1 -> 59.8, 64 x 2 x 1003 + 1792 .. 7168 65.9 -> 59.0; equal lengths lose 0 .. 2 % (16 x 8 x 572 +
-    // 5318 63.4 -> 64.0, 56 x 2 x 1030 + 5994 73.2 -> 73.0), at D = 64 up to 4 %.  (Of 14 .. 17 tiles a wavefront the different
-    // lengths gain as much, but calls there are short enough for equal ones to lose 1 %.)  At D = 64 with a third more items of whole rows than
+    // 5318 63.4 -> 64.0, 56 x 2 x 1030 + 5994 73.2 -> 73.0; at D = 64 up to 2.6 %, 13 x 16 x 6686 55.9 -> 57.2).  (Of 14 .. 17 tiles a wavefront the different
+    // lengths gain as much, but calls there are short enough for equal ones to lose 1 % and more: 17.9 tiles, 10 x 8 heads x 111 + 7175 tokens, 47.0
+    // -> 48.2, of different lengths 30.1 -> 31.7.)  At D = 64 with a third more items of whole rows than
     // units the few units with two of them hold up everybody, whatever the lengths: always dealt (17 x 16 heads x 897 + 4635
     // tokens 78.5 -> 64.0, 42 x 8 x 390 + 5137 86.8 -> 83.6; with more items than that fixed shares even out).
     const int units = d.D == 64 && pl.nqt == 1 ? 2 * kNumCU : kNumCU;  // (two items to a unit there)
@@ -283,9 +284,10 @@ static inline AttnPlans plan_attention(const lotts_attn_desc& d) {
         pl.flat = d.D == 64 && pl.nqt == 1 && base * pl.nsplit_priv > kNumCU && base * pl.nsplit_priv * 3 <= 4 * kNumCU ? 2 : 1;
         pl.workers = workers;
         // Where an item has whole branches of its own, the last arriver merges the few that are cut; where branches have several items each,
-        // merge workgroups (44 x 2 x 1310 .. 5243 40.7 -> 35.0 us, with the last arriver 38.7).
+        // merge workgroups (44 x 2 x 1310 .. 5243 40.7 -> 35.0 us, with the last arriver 38.7) unless a branch's partials are few bytes: D = 64,
+        // 13 x 16 x 6686 with one row a head 58.8 us with merge workgroups, 57.0 with the last arriver, 12 x 16 x 122 + 6156 with three 52.1 and 50.7.
         pl.merge = kMergeLast;
-        if (workers > d.B) {
+        if (workers > d.B && part_bytes > 8 * 1024) {
             rows_per_merger(kAttnThreads * pl.nqt);
             if ((long long)d.Hkv * (workers + 2 * d.B) * pl.mpp <= kMaxCounters) pl.merge = kMergeGroups;
         }
@@ -407,14 +409,17 @@ __device__ __forceinline__ FlatCuts flat_cuts(const AttnParams& prm, int fold_ti
     // Steps (a tile for every wavefront of an item) of a branch's fixed shares, and how long they take, in steps of a full chip: all
     // items together are bound by the memory, whose rate they share, until so few are left that each is bound by what a unit takes in,
     // about twice as much.  At whatever length L that happens, sum of min(steps, L) / items + (longest - L) / 2 is no
-    // more than the whole time.
+    // more than the whole time.  Where a unit could hold two items (D = 64, one row tile) but every branch is one item and there are no more of
+    // them than units, that is four times as much: 29 x 8 heads x 7898 tokens, all equal, were dealt, 75 us in place of 68.  (With several
+    // shares a branch, which end together, it is not: 8 x 16 heads x 2399 .. 9596 behind 2225 in two shares 51.6 us, dealt 45.3.)
     const int steps = lane < prm.B ? quot(tiles - 1, prm.d_wpriv) + 1 : 0;
     const int longest = wave_max_u31(steps);
+    const int lone = prm.D == 64 && prm.plan.nqt == 1 && prm.plan.nsplit_priv == 1 && 2 * prm.B <= prm.workers ? prm.workers / 2 : prm.workers;
     auto until = [&](int L) {  // (in half steps of all the head's items)
         const int sum = __builtin_amdgcn_readlane(wave_incl_scan_u32(min(steps, L)), kWave - 1);
-        return 2 * sum * prm.plan.nsplit_priv + (longest - L) * prm.workers;
+        return 2 * sum * prm.plan.nsplit_priv + (longest - L) * lone;
     };
-    const int fixed = max(max(until(longest), until(longest * 3 / 4)), max(until(longest / 2), longest * prm.workers));
+    const int fixed = max(max(until(longest), until(longest * 3 / 4)), max(until(longest / 2), longest * lone));
     c.dealt = prm.flat > 1 || fixed * kAttnWaves > (int)(2 * c.total) + 2 * kAttnWaves * prm.workers;
     return c;
 }

@@ -17,16 +17,18 @@ NAMES = ("Q", "Kpre", "Vpre", "Kpriv", "Vpriv", "priv_len")
 
 CASES = [
     # branches with several items each (merge workgroups): one row tile and two, both head dims, a prefix and none
-    BF.with_(B=20, Hq=32, Hkv=8, k=3, P=30, L=400), BF.with_(B=17, Hq=40, Hkv=8, k=8, P=60, L=500), BF.with_(B=12, Hq=80, Hkv=16, k=6, D=64, P=31, L=333),
+    BF.with_(B=20, Hq=32, Hkv=8, k=5, P=30, L=400), BF.with_(B=17, Hq=40, Hkv=8, k=8, P=60, L=500), BF.with_(B=12, Hq=80, Hkv=16, k=6, D=64, P=31, L=333),
     BF.with_(B=9, Hq=16, Hkv=2, k=1, D=64, P=100, L=900),
     BF.with_(B=2, Hq=2, Hkv=1, k=1, D=64, P=0, L=9000),     # up to 512 items for two branches: partials beyond a wavefront's lanes
     BF.with_(B=33, Hq=9, Hkv=3, k=2, D=64, P=0, L=700),     # heads that do not divide the units
+    # several items each, few bytes of partials (the last arriver): one share a branch, and more
+    BF.with_(B=20, Hq=32, Hkv=8, k=3, P=30, L=400), BF.with_(B=12, Hq=16, Hkv=16, k=2, D=64, P=22, L=700), BF.with_(B=10, Hq=32, Hkv=8, k=0, P=11, L=900),
     # items with several branches each (the last arriver)
     BF.with_(B=40, Hq=8, Hkv=8, k=0, P=0, L=300), BF.with_(B=64, Hq=40, Hkv=8, k=7, P=33, L=260),
     BF.with_(B=35, Hq=16, Hkv=16, k=2, D=64, P=40, L=200), BF.with_(B=34, Hq=80, Hkv=16, k=7, D=64, P=0, L=130),
     BF.with_(B=18, Hq=16, Hkv=16, k=0, D=64, P=20, L=230),  # a few more items of whole rows than units
 ]
-LONG = [BF.with_(B=64, Hq=2, Hkv=2, k=1, P=70, L=4352), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2200)]
+LONG = [BF.with_(B=64, Hq=2, Hkv=2, k=1, P=70, L=4608), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2300)]
 
 
 def lengths(cfg, pattern):
@@ -65,7 +67,7 @@ def test_lengths(flat, oracle, cfg, pattern):
     run_attention(flat, oracle, cfg, priv_len=lengths(cfg, pattern))
 
 
-@pytest.mark.parametrize("cfg", [CASES[0], CASES[1], CASES[6]], ids=["groups", "two_row_tiles", "last_arriver"])
+@pytest.mark.parametrize("cfg", [CASES[0], CASES[1], CASES[6], CASES[9]], ids=["groups", "two_row_tiles", "few_bytes", "last_arriver"])
 def test_replays_with_other_lengths(flat, cfg):
     """What a captured call deals follows the lengths it finds, and every cell is down again when it ends."""
     sets = [attn_to_dev(cfg, S.attention_inputs(cfg, salt=i, priv_len=lengths(cfg, p))) for i, p in enumerate(("equal", "shuffled", "one"))]
