@@ -180,9 +180,10 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl, double* fill
 //     4480 22.4 / 25.6 / 28.6 -> 20.7 / 22.2 / 24.8; 50 sizes of K > 4096 17 % faster.  With a K beyond 12288 and up to 160 tokens level or
 //     slower (3584 x 18944 at 144 tokens 46.7 -> 48.0), with up to 128 tokens too (3264 x 14336 at 123 31.5 -> 36.7).  The same for more rows, 256 x
 //     half of the tokens without a split, loses (22016 x 2048 at 160 / 192 tokens 27.5 / 29.6 -> 29.9 / 30.6).  Beside it the direct form stays
-//     while 0.03 us per KB are below 4.75 us + 0.1 us per MB of W + 6.5e-6 us per token and (N + K): fitted to 141 sizes, 0.33 % over the better
-//     form (the line above: 1.7 %), with 2560 x 2048 at 192 tokens held in the direct form, 14.5 us against 13.8 (let go, 0.05 %).
-//     2184 x 2304 at 245 tokens 18.4 -> 16.0 us, 1536 x 4096 at 244 18.4 -> 14.5.
+//     while 0.03 us per KB are below 6.75 us + 4e-6 us per token and (N + K): fitted to 402 sizes (32 .. 4608 rows, K 1024 .. 4096), 0.16 %
+//     over the better form (always direct 9.4 %, never 24 %; a line of 4.75 us + 0.1 us per MB of W + 6.5e-6 us, from fewer sizes and none
+//     below 600 rows, 1.2 %: 200 x 2176 at 146 tokens 7.4 us direct, streamed 9.9).  2184 x 2304 at 245 tokens 18.4 -> 16.0 us, 1536 x 4096 at
+//     244 18.4 -> 14.5, 2560 x 2048 at 150 / 192 / 240 14.2 / 14.6 / 16.8 -> 12.9 / 14.0 / 15.9.
 //   128-row form below that, 64-row form when it would have to be split more than sevenfold (N <= 4608): the fewer splits,
 //     the fewer fp32 partials, but the more often a unit reads X.  2048 x 11008 at 40 / 192 tokens in 64-row blocks x 8
 //     splits 14.8 / 24.3 us, 128 x 16 17.1 / 26.5; 5120 x 5120 at 64 / 192 tokens 128 x 6 17.9 / 26.0, 64 x 3 17.4 / 28.6; 6144 x 6144
@@ -200,7 +201,7 @@ static inline GemmPlan plan_gemm(int M, int N, int K, bool may_be_direct = true)
         double filled;
         const double kb = plan_direct(M, N, K, &pl, &filled), mb = 2e-6 * N * K, tokens = 1e-6 * M * (N + K);
         auto ahead = [&](double k) { return 3.4 + 0.022 * k + 0.14 * mb < 7.0 + 0.125 * mb + 7.0 * tokens; };
-        if (kb > 0.0 && (parts ? 0.03 * kb < 4.75 + 0.1 * mb + 6.5 * tokens
+        if (kb > 0.0 && (parts ? 0.03 * kb < 6.75 + 4.0 * tokens
                                : ahead(filled) || (ahead(kb) && 0.034 * kb + 0.15 * mb < (pl.rn == 4 ? 6.3 : 6.7) + 10.0 * tokens))) {
             pl.form = kDirect;
             return pl;

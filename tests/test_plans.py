@@ -6,7 +6,17 @@ def test_gemm_forms_on_either_side_of_the_line():
     """Sizes measured in both forms, us.  Counting even shares of the tokens alone, the direct form was taken where it is the slower
     one: 64 weight rows to a workgroup, or X the smaller part of what it takes in."""
     streamed = [(168, 3968, 2176), (36, 8064, 1536), (100, 4352, 1792), (46, 3968, 1920), (184, 3072, 1920), (255, 2688, 2688)]
-    direct = [(1, 2560, 2048), (40, 2560, 2048), (192, 2560, 2048), (192, 2048, 2048), (34, 1408, 1152), (66, 2176, 1408), (108, 1024, 2176), (36, 3328, 1536)]
+    direct = [(1, 2560, 2048), (40, 2560, 2048), (192, 2048, 2048), (34, 1408, 1152), (66, 2176, 1408), (108, 1024, 2176), (36, 3328, 1536)]
+    plans = ask(["gemm %d %d %d" % s for s in streamed + direct])
+    assert [p["form"] == "direct" for p in plans] == [False] * len(streamed) + [True] * len(direct), plans
+
+
+def test_gemm_forms_beside_two_token_parts():
+    """Sizes measured in the direct form and in two token parts, us: 2560 x 2048 streams at every number of tokens (direct 14.2 at 150, 14.5 at
+    160, 14.6 at 192, 16.8 at 240; in two parts 12.9, 13.1, 14.0, 15.9), few weight rows do not (200 x 2176 at 146 tokens 7.4 and 9.9)."""
+    streamed = [(M, 2560, 2048) for M in (150, 160, 170, 176, 184, 188, 190, 191, 192, 193, 194, 196, 200, 208, 216, 224, 240)]
+    streamed += [(192, 2304, 2048), (192, 2432, 2048), (192, 3072, 2048), (192, 2560, 1920), (192, 2560, 2176), (201, 1384, 3200), (252, 1336, 2432)]
+    direct = [(134, 104, 2176), (146, 200, 2176), (182, 208, 2176), (143, 600, 2176), (173, 400, 2176), (148, 520, 2176), (135, 72, 2944)]
     plans = ask(["gemm %d %d %d" % s for s in streamed + direct])
     assert [p["form"] == "direct" for p in plans] == [False] * len(streamed) + [True] * len(direct), plans
 
