@@ -94,6 +94,7 @@ struct AttnPlan {
 struct AttnPlans : AttnPlan {
     int flat;     // 0: shares of fixed number; 1: the items deal the tiles by the branches' lengths where those differ; 2: always
     int workers;  // flat: items per KV head
+    int flat_merge;  // who merges where the tiles are dealt by the lengths: kMergeLast or kMergeGroups
 };
 constexpr int kMergeLast = 0;    // the last-arriving workgroup of a (KV head, branch), inside the attention launch
 constexpr int kMergeGroups = 1;  // merge workgroups at the end of the attention launch's grid
@@ -126,7 +127,7 @@ struct AttnParams {
     float* lse;
     long long o_stride_b, o_stride_r, o_stride_h;
     // flat plans only (behind everything else: a call that is not captured reads its arguments from far away, 0.2 us for every line more)
-    int flat, workers;
+    int flat, workers, flat_merge;
     FastDiv d_workers;  // by workers
 };
 
@@ -266,19 +267,19 @@ static inline AttnPlans plan_attention(const lotts_attn_desc& d) {
     }
     // Branches of different lengths.  Fixed shares leave the longest branches' items behind: the host does not know the lengths, so the
     // number of shares cannot follow them.  In the flat plan the items deal a head's tiles among themselves on the device (see FlatCuts),
-    // unless the lengths turn out to be alike, and then the same kernel runs the fixed shares.  Finding that out and being able to do either
-    // costs an item about 0.7 us, so it is for long calls only: from 18 tiles a wavefront on, 26 x 2 heads x 1086 + 2399 .. 9596 tokens 43.2 ->
-    // 39.0 us, 19 x 4 x 1051 + 2722 .. 10890 67.1 -> 59.8, 64 x 2 x 1003 + 1792 .. 7168 65.9 -> 59.0; equal lengths lose 0 .. 2 % (16 x 8 x 572 +
-    // 5318 63.4 -> 64.0, 56 x 2 x 1030 + 5994 73.2 -> 73.0; at D = 64 up to 2.6 %, 13 x 16 x 6686 55.9 -> 57.2).  (Of 14 .. 17 tiles a wavefront the different
-    // lengths gain as much, but calls there are short enough for equal ones to lose 1 % and more: 17.9 tiles, 10 x 8 heads x 111 + 7175 tokens, 47.0
-    // -> 48.2, of different lengths 30.1 -> 31.7.)  At D = 64 with a third more items of whole rows than
-    // units the few units with two of them hold up everybody, whatever the lengths: always dealt (17 x 16 heads x 897 + 4635
-    // tokens 78.5 -> 64.0, 42 x 8 x 390 + 5137 86.8 -> 83.6; with more items than that fixed shares even out).
+    // unless that would gain too little for these lengths, and then the same kernel runs the fixed shares, with their own merge and the same bits.
+    // An item finds that out before its first tile, 0.5 .. 0.8 us, so it is for long calls only: from 18 tiles a wavefront on, 26 x 2 heads x 1086 +
+    // 2399 .. 9596 tokens 43.2 -> 39.0 us, 19 x 4 x 1051 + 2722 .. 10890 67.1 -> 59.8, 64 x 2 x 1003 + 1792 .. 7168 63.9 -> 58.3.  Equal lengths
+    // are told at once: over 60 sizes 1.6 % slower to 2.6 % faster than without a flat plan, on average 0.1 % slower at D = 128, 0.4 % at D = 64
+    // (dealt all the same, or merged as dealt tiles are, up to 9 % slower: 7 x 16 heads x 15408 tokens, D = 64, 70.6 us against 64.8).  (Of 14 .. 17 tiles a wavefront different lengths gain as much, but those that are not dealt lose a larger part of their time.)  At D = 64
+    // with a third more items of whole rows than units the few units with two of them hold up everybody, whatever the lengths: always dealt
+    // (17 x 16 heads x 897 + 4635 tokens 78.5 -> 64.0, 42 x 8 x 390 + 5137 86.8 -> 83.6; 36 sizes of equal lengths 12 % faster, the worst, 42 x 8 x
+    // 3702, 3 % slower, of different ones 12 .. 43 %; with more items than that fixed shares even out).
     const int units = d.D == 64 && pl.nqt == 1 ? 2 * kNumCU : kNumCU;  // (two items to a unit there)
     const int workers = units / d.Hkv;
     const long long farthest = std::max((d.Lmax + 32LL) * d.kpriv_stride_t, (d.P + 32LL) * d.kpre_stride_t) * 2;  // bytes
     const long long flat_bytes = (long long)d.Hkv * (workers + d.B) * GR * (d.D * 4 + 8) + kMaxCounters * 8 + 512;
-    if (simple && !pl.one && d.B > 1 && d.B <= kWave && workers > 0 && (pl.nsplit_priv == 1 || d.B * pl.nsplit_priv <= workers) &&
+    if (simple && !pl.one && pl.merge != kMergeLaunch && d.B > 1 && d.B <= kWave && workers > 0 && (pl.nsplit_priv == 1 || d.B * pl.nsplit_priv <= workers) &&
         (long long)d.B * tiles_all >= (long long)LOTTS_FLAT_STEPS * kAttnWaves * workers &&
         (long long)d.B * (tiles_all + kStartTiles) * workers < (1LL << 31) && farthest < (1LL << 31) && flat_bytes <= (16 << 20)) {
         pl.flat = d.D == 64 && pl.nqt == 1 && base * pl.nsplit_priv > kNumCU && base * pl.nsplit_priv * 3 <= 4 * kNumCU ? 2 : 1;
@@ -286,13 +287,13 @@ static inline AttnPlans plan_attention(const lotts_attn_desc& d) {
         // Where an item has whole branches of its own, the last arriver merges the few that are cut; where branches have several items each,
         // merge workgroups (44 x 2 x 1310 .. 5243 40.7 -> 35.0 us, with the last arriver 38.7) unless a branch's partials are few bytes: D = 64,
         // 13 x 16 x 6686 with one row a head 58.8 us with merge workgroups, 57.0 with the last arriver, 12 x 16 x 122 + 6156 with three 52.1 and 50.7.
-        pl.merge = kMergeLast;
+        pl.flat_merge = kMergeLast;
         if (workers > d.B && part_bytes > 8 * 1024) {
-            rows_per_merger(kAttnThreads * pl.nqt);
-            if ((long long)d.Hkv * (workers + 2 * d.B) * pl.mpp <= kMaxCounters) pl.merge = kMergeGroups;
+            if (pl.merge != kMergeGroups) rows_per_merger(kAttnThreads * pl.nqt);  // (fixed shares have the same ones)
+            if ((long long)d.Hkv * (workers + 2 * d.B) * pl.mpp <= kMaxCounters) pl.flat_merge = kMergeGroups;
         }
     }
-    pl.n_merge = pl.merge == kMergeGroups ? d.B * d.Hkv * pl.mpp : 0;
+    pl.n_merge = pl.merge == kMergeGroups || (pl.flat && pl.flat_merge == kMergeGroups) ? d.B * d.Hkv * pl.mpp : 0;
     pl.n_pre_items = d.Hkv * pl.n_rg_pre * pl.nsplit_pre;
     pl.n_priv_items = pl.flat ? d.Hkv * std::max(pl.workers, d.B * pl.nsplit_priv) : d.B * d.Hkv * pl.n_rg_priv * pl.nsplit_priv;
     return pl;
@@ -399,9 +400,10 @@ struct FlatCuts {
     bool dealt;      // by the lengths; or the fixed number of shares to every branch
 };
 __device__ __forceinline__ FlatCuts flat_cuts(const AttnParams& prm, int fold_tiles, int lane, int L) {
-    FlatCuts c;
+    FlatCuts c = {};
     L = L < prm.R ? prm.R : (L > prm.Lmax ? prm.Lmax : L);
     c.len = L;
+    if (prm.flat == 1 && __ballot(L != __builtin_amdgcn_readfirstlane(L)) == 0) return c;  // all alike: fixed shares
     const int tiles = fold_tiles + (L - 1) / kTile + 1;
     c.end = wave_incl_scan_u32(lane < prm.B ? kStartTiles + tiles : 0);
     c.total = __builtin_amdgcn_readlane(c.end, kWave - 1);
@@ -434,16 +436,10 @@ __device__ __forceinline__ void flat_branch(const FlatCuts& c, int b, unsigned* 
     *last = __builtin_amdgcn_readlane(c.end, b) - 1;
 }
 __device__ __forceinline__ Partials flat_partials(const AttnParams& prm, const FlatCuts& c, int kvh, int b) {
-    int number = b * prm.plan.nsplit_priv, n = prm.plan.nsplit_priv;
-    if (c.dealt) {
-        unsigned first, last;
-        flat_branch(c, b, &first, &last);
-        const int w0 = flat_worker(c, first);
-        n = flat_worker(c, last) - w0 + 1;
-        number = w0 + b;
-    }
-    number += kvh * (prm.workers + prm.B);
-    return {(unsigned)number * prm.GR, 1u, (unsigned)prm.GR, n, number};
+    unsigned first, last;
+    flat_branch(c, b, &first, &last);
+    const int w0 = flat_worker(c, first), number = w0 + b + kvh * (prm.workers + prm.B);
+    return {(unsigned)number * prm.GR, 1u, (unsigned)prm.GR, flat_worker(c, last) - w0 + 1, number};
 }
 __device__ __forceinline__ Partials fixed_partials(const AttnParams& prm, int kvh, int b) {
     const unsigned n = prm.plan.nslots;
@@ -707,8 +703,10 @@ __device__ __forceinline__ const AttnParams& reread(const AttnParams& prm) {
     }
 }
 
+// (At D = 64 and one row tile, 43 KB of LDS, three workgroups fit a unit if their registers do: 44 x 16 heads x 336 + 2023 tokens with 174
+// registers 63.0 us, with 168 57.7.)
 template <int D, int NQT, int GROUPS, bool ONE, bool FLAT>
-__global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn_kernel(const AttnParams prm_) {
+__global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : D == 64 ? 3 : 2)) void attn_kernel(const AttnParams prm_) {
     const AttnParams& prm = prm_;
     // GROUPS = 2: eight wavefronts, two per SIMD.  The second group of four takes the second row tile; wavefront w of
     // either group streams the same key tiles, so the two share them: each loads half of a tile into a slab both
@@ -754,15 +752,19 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
         id -= pl.n_priv_items + pl.n_pre_items;
         const int rest = quot(id, prm.d_hkv), kvh = id - rest * prm.Hkv;
         const int b = quot(rest, prm.d_mpp), chunk = rest - b * pl.mpp;
-        Partials parts;
+        Partials parts = fixed_partials(prm, kvh, b);
+        bool dealt = false;
         if constexpr (FLAT) {
-            parts = flat_partials(prm, flat_cuts(prm, pl.fold ? prm.tiles_pre : 0, lane, prm.priv_len[min(lane, prm.B - 1)]), kvh, b);
-            if (parts.n == 1) return;  // whole rows of one item
-        } else {
-            parts = fixed_partials(prm, kvh, b);
+            const FlatCuts cuts = flat_cuts(prm, pl.fold ? prm.tiles_pre : 0, lane, prm.priv_len[min(lane, prm.B - 1)]);
+            dealt = cuts.dealt;
+            if (dealt) parts = flat_partials(prm, cuts, kvh, b);
+            if ((dealt ? prm.flat_merge : pl.merge) != kMergeGroups || parts.n == 1) return;  // (whole rows of one item)
         }
-        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b, chunk, parts,
-                                                   [&] { return merger_stays<FLAT>(prm, parts, reinterpret_cast<int*>(sh_l), kvh, b, chunk); });
+        merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b, chunk, parts, [&] {
+            int* const stays = reinterpret_cast<int*>(sh_l);
+            if (FLAT && dealt) return merger_stays<true>(prm, parts, stays, kvh, b, chunk);
+            return merger_stays<false>(prm, parts, stays, kvh, b, chunk);
+        });
         return;
     }
     const bool is_private = FLAT || id < pl.n_priv_items;
@@ -1050,11 +1052,12 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
         float2 own_ml[QPT];
         // Those of the first nrows rows go out: as the output itself, or as this item's partial.
         Partials parts;
-        if constexpr (FLAT) {
+        if (FLAT && cuts.dealt) {
             parts = flat_partials(prm, cuts, kvh, b_item);
-            slot = cuts.dealt ? piece_of + b_item - (parts.cell - kvh * (prm.workers + prm.B)) : split;
+            slot = piece_of + b_item - (parts.cell - kvh * (prm.workers + prm.B));
         } else {
             parts = fixed_partials(prm, kvh, b_item);
+            if (FLAT) slot = split;
         }
         const int b_put = b_item, rho_put = rho0, end_put = rho_end;  // (the next segment's are set before this one's rows go out)
         auto put = [&](int tile, int nrows) {
@@ -1067,8 +1070,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
                     if (row0 + q * RSTEP < nrows) store_merged(prm, kvh, b_put, rho + q * RSTEP - b_put * GR, c4, own_o[q], own_ml[q].x, own_ml[q].y);
                 return;
             }
-            const unsigned pidx = FLAT ? parts.first + slot * parts.step + (rho - b_put * GR) : ((unsigned)kvh * prm.B * GR + rho) * pl.nslots + slot;
-            const unsigned step_q = RSTEP * (FLAT ? 1 : pl.nslots);
+            const unsigned pidx = FLAT ? parts.first + slot * parts.step + (rho - b_put * GR) * parts.row_step : ((unsigned)kvh * prm.B * GR + rho) * pl.nslots + slot;
+            const unsigned step_q = RSTEP * (FLAT ? parts.row_step : pl.nslots);
             unsigned at_o = prm.off_o + (pidx * D + c4 * 4) * 4u, at_ml = prm.off_ml + pidx * 8u;
             if (pl.merge != kMergeLaunch) {
 #pragma unroll
@@ -1405,9 +1408,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             }
         }
 
-        if constexpr (FLAT) {
+        if (FLAT && cuts.dealt) {
             const AttnParams& prm = reread<FLAT>(prm_);
-            const AttnPlan& pl = prm.plan;
             // Only the first and the last segment of an item can be cut; both are counted at the end, so that nothing waits for a
             // partial's way to memory in between.
             if (seg.b < prm.B) {
@@ -1424,15 +1426,16 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             if (!cut_first && !cut_last) return;
             __builtin_amdgcn_s_waitcnt(0);  // the partials are in memory
             __syncthreads();
-            if (pl.merge == kMergeGroups) {
+            if (prm.flat_merge == kMergeGroups) {
+                const AttnPlan& pl = prm.plan;
                 if (tid < kWave) {
                     bool mine = false;
-                    if (cut_last && tid < pl.mpp && atomicExch(merger_flag<FLAT>(prm, parts, kvh, b_put, tid, slot), prm.tag + 1) == prm.tag + 2)
-                        mine = count_partials(prm, parts, merger_count<FLAT>(prm, kvh, b_put, tid), 1);
+                    if (cut_last && tid < pl.mpp && atomicExch(merger_flag<true>(prm, parts, kvh, b_put, tid, slot), prm.tag + 1) == prm.tag + 2)
+                        mine = count_partials(prm, parts, merger_count<true>(prm, kvh, b_put, tid), 1);
                     const unsigned long long found = __ballot(mine);
                     mine = false;
-                    if (cut_first && tid < pl.mpp && atomicExch(merger_flag<FLAT>(prm, parts_first, kvh, b_first_seg, tid, slot_first), prm.tag + 1) == prm.tag + 2)
-                        mine = count_partials(prm, parts_first, merger_count<FLAT>(prm, kvh, b_first_seg, tid), 1);
+                    if (cut_first && tid < pl.mpp && atomicExch(merger_flag<true>(prm, parts_first, kvh, b_first_seg, tid, slot_first), prm.tag + 1) == prm.tag + 2)
+                        mine = count_partials(prm, parts_first, merger_count<true>(prm, kvh, b_first_seg, tid), 1);
                     const unsigned long long found_first = __ballot(mine);
                     if (tid == 0) {
                         sh_flat[0] = found;
@@ -1445,8 +1448,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
                     const int be = e == 0 ? b_put : b_first_seg;
                     for (unsigned long long left = sh_flat[e]; left; left &= left - 1) {  // uniform over the workgroup
                         const int c = __ffsll((long long)left) - 1;
-                        for (int j = tid; j < pe.n; j += kAttnThreads * GROUPS) cell_clear(merger_flag<FLAT>(prm, pe, kvh, be, c, j));
-                        if (tid == 0) cell_clear(merger_count<FLAT>(prm, kvh, be, c));
+                        for (int j = tid; j < pe.n; j += kAttnThreads * GROUPS) cell_clear(merger_flag<true>(prm, pe, kvh, be, c, j));
+                        if (tid == 0) cell_clear(merger_count<true>(prm, kvh, be, c));
                         merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, be, c, pe, [] { return true; });
                         __syncthreads();
                     }
@@ -1537,8 +1540,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             if (tid < kWave) {  // mpp <= rows of an item <= 64
                 bool mine = false;
                 if (tid < pl.mpp) {
-                    if (atomicExch(merger_flag<FLAT>(prm, parts, kvh, b_item, tid, slot), prm.tag + 1) == prm.tag + 2)  // that workgroup has left
-                        mine = count_partials(prm, parts, merger_count<FLAT>(prm, kvh, b_item, tid), 1);
+                    if (atomicExch(merger_flag<false>(prm, parts, kvh, b_item, tid, slot), prm.tag + 1) == prm.tag + 2)  // that workgroup has left
+                        mine = count_partials(prm, parts, merger_count<false>(prm, kvh, b_item, tid), 1);
                 }
                 const unsigned long long all = __ballot(mine);
                 if (tid == 0) *sh_mine = all;
@@ -1546,8 +1549,8 @@ __global__ __launch_bounds__(kAttnThreads * GROUPS, (NQT > 1 ? 1 : 2)) void attn
             __syncthreads();
             for (unsigned long long left = *sh_mine; left; left &= left - 1) {  // uniform over the workgroup
                 const int c = __ffsll((long long)left) - 1;
-                if (tid < pl.nslots) cell_clear(merger_flag<FLAT>(prm, parts, kvh, b_item, c, tid));
-                if (tid == 0) cell_clear(merger_count<FLAT>(prm, kvh, b_item, c));
+                if (tid < pl.nslots) cell_clear(merger_flag<false>(prm, parts, kvh, b_item, c, tid));
+                if (tid == 0) cell_clear(merger_count<false>(prm, kvh, b_item, c));
                 merge_rows<D, true, kAttnThreads * GROUPS>(prm, lds, kvh, b_item, c, parts, [] { return true; });
                 __syncthreads();
             }
@@ -1821,7 +1824,7 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
     const long long tile_span = (1LL << 31) / (2 * kTile);  // elements from key to key
     prm.near_rows = d.kpriv_stride_t < tile_span && d.kpre_stride_t < tile_span;
     prm.tag = (g_call_tag.fetch_add(1, std::memory_order_relaxed) + 1) << kTagShift;
-    prm.flat = pl.flat; prm.workers = pl.workers;
+    prm.flat = pl.flat; prm.workers = pl.workers; prm.flat_merge = pl.flat_merge;
     prm.d_workers = fast_div(pl.workers > 0 ? pl.workers : 1);
     const long long items = (long long)pl.n_pre_items + pl.n_priv_items + pl.n_merge;
     if (items > 0x7fffffffLL) return LOTTS_ERR_SHAPE;

@@ -28,6 +28,9 @@ CASES = [
     BF.with_(B=35, Hq=16, Hkv=16, k=2, D=64, P=40, L=200), BF.with_(B=34, Hq=80, Hkv=16, k=7, D=64, P=0, L=130),
     BF.with_(B=18, Hq=16, Hkv=16, k=0, D=64, P=20, L=230),  # a few more items of whole rows than units
 ]
+# those where equal lengths are not dealt; the last ones have two shares, which the later of two items merges
+SHARED = [c for i, c in enumerate(CASES) if i not in (5, 13)] + [BF.with_(B=14, Hq=32, Hkv=8, k=1, D=64, P=0, L=900),
+                                                                 BF.with_(B=12, Hq=32, Hkv=8, k=5, P=30, L=900)]
 LONG = [BF.with_(B=64, Hq=2, Hkv=2, k=1, P=70, L=4608), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2300)]
 
 
@@ -61,10 +64,35 @@ def flat():
     assert m.load() is usual and binding._workspaces is workspaces
 
 
+def without_dealing(m, d):
+    """(O, lse) of the library itself, whose plan for a short call has fixed shares."""
+    from paper_2505_19634_amd import binding
+    torch.cuda.synchronize()
+    with pytest.MonkeyPatch.context() as mp:
+        mp.setattr(binding, "LIB_PATH", os.path.join(os.path.dirname(binding.LIB_PATH), "liblotts.so"))
+        mp.setattr(binding, "_lib", None)
+        mp.setattr(binding, "_workspaces", {})
+        mp.setattr(binding, "_sized", {})
+        out = m.verify_attention(*(d[n] for n in NAMES), return_lse=True)
+        torch.cuda.synchronize()
+    return out
+
+
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: "B%d_k%d_Hq%d_Hkv%d_D%d_P%d_L%d" % (c.B, c.k, c.Hq, c.Hkv, c.D, c.P, c.L))
 @pytest.mark.parametrize("pattern", ["equal", "ragged", "shuffled", "first", "last", "one"])
 def test_lengths(flat, oracle, cfg, pattern):
     run_attention(flat, oracle, cfg, priv_len=lengths(cfg, pattern))
+
+
+@pytest.mark.parametrize("cfg", SHARED, ids=lambda c: "B%d_k%d_Hq%d_Hkv%d_D%d_P%d_L%d" % (c.B, c.k, c.Hq, c.Hkv, c.D, c.P, c.L))
+@pytest.mark.parametrize("share", [1.0, 0.6])
+def test_equal_lengths_have_the_bits_of_fixed_shares(flat, cfg, share):
+    """Nothing is dealt where all lengths are alike: the shares and the merge of the plan without them, as the library itself takes it for calls
+    this short."""
+    d = attn_to_dev(cfg, S.attention_inputs(cfg, priv_len=np.full(cfg.B, max(cfg.k + 1, int(cfg.L * share)), np.int32)))
+    got = [t.clone() for t in flat.verify_attention(*(d[n] for n in NAMES), return_lse=True)]
+    want = without_dealing(flat, d)
+    assert all(torch.equal(g, w) for g, w in zip(got, want))
 
 
 @pytest.mark.parametrize("cfg", [CASES[0], CASES[1], CASES[6], CASES[9]], ids=["groups", "two_row_tiles", "few_bytes", "last_arriver"])

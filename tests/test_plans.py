@@ -55,12 +55,14 @@ def test_logits_lists_reach_every_size_of_piece():
 
 def test_lengths_lists_reach_the_flat_plan():
     """Small calls in the tests' build, long ones in the library itself: both merges, one row tile and two, with and without a prefix."""
-    from test_gpu_attention_lengths import CASES, LONG
+    from test_gpu_attention_lengths import CASES, LONG, SHARED
     line = lambda c: attention(c).replace("attention", "lengths")
     plans = ask([line(c) for c in CASES], ("-DLOTTS_FLAT_STEPS=0",))
     assert all(p["flat"] for p in plans), list(zip(CASES, plans))
     assert {(c.D, p["nqt"], p["merge"]) for c, p in zip(CASES, plans)} == {(D, nqt, m) for D in (64, 128) for nqt in (1, 2) for m in (0, 1)}
     assert {p["fold"] for p in plans} == {0, 1} and 2 in {p["flat"] for p in plans}
+    assert all(p["flat"] == 1 for p in ask([line(c) for c in SHARED], ("-DLOTTS_FLAT_STEPS=0",)))
+    assert {p["merge"] for p in ask([attention(c) for c in SHARED])} == {0, 1, 3, 4}  # all that fixed shares of long calls have
     assert not any(p["flat"] for p in ask([line(c) for c in CASES]))
     assert all(p["flat"] == 1 for p in ask([line(c) for c in LONG]))
     # one branch more than a wavefront has lanes, rows of several row groups, a prefix in items of its own: not these
