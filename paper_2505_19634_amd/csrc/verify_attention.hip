@@ -410,19 +410,26 @@ __device__ __forceinline__ FlatCuts flat_cuts(const AttnParams& prm, int fold_ti
     c.workers = min(prm.workers, (int)c.total);  // (at least one place each)
     // Steps (a tile for every wavefront of an item) of a branch's fixed shares, and how long they take, in steps of a full chip: all
     // items together are bound by the memory, whose rate they share, until so few are left that each is bound by what a unit takes in,
-    // about twice as much.  At whatever length L that happens, sum of min(steps, L) / items + (longest - L) / 2 is no
-    // more than the whole time.  Where a unit could hold two items (D = 64, one row tile) but every branch is one item and there are no more of
-    // them than units, that is four times as much: 29 x 8 heads x 7898 tokens, all equal, were dealt, 75 us in place of 68.  (With several
-    // shares a branch, which end together, it is not: 8 x 16 heads x 2399 .. 9596 behind 2225 in two shares 51.6 us, dealt 45.3.)
+    // about twice as much, items of which a unit could hold two (D = 64, one row tile) a little more than that (`lone`).  At whatever length L
+    // that happens, sum of min(steps, L) / items + (longest - L) / 2 is no more than the whole time; nor are two items of mean length in
+    // one unit, where there are such.  Dealt, they take what the memory takes, and some more: a 16th where a unit could hold two, otherwise
+    // 8 tiles a branch, 4 at D = 64.  Fitted to 158 sizes x 6 kinds of different lengths, each measured both ways: 19 of the 948 come out behind
+    // their fixed shares by more than 1 %, and they gain 17 % on average.  (With one step of all wavefronts more for every size, and lone
+    // items of D = 64 at two or four times, 29 did: 14 x 8 heads of about 12000 tokens 51.5 us in fixed shares, dealt 54.5.)
     const int steps = lane < prm.B ? quot(tiles - 1, prm.d_wpriv) + 1 : 0;
     const int longest = wave_max_u31(steps);
-    const int lone = prm.D == 64 && prm.plan.nqt == 1 && prm.plan.nsplit_priv == 1 && 2 * prm.B <= prm.workers ? prm.workers / 2 : prm.workers;
-    auto until = [&](int L) {  // (in half steps of all the head's items)
-        const int sum = __builtin_amdgcn_readlane(wave_incl_scan_u32(min(steps, L)), kWave - 1);
-        return 2 * sum * prm.plan.nsplit_priv + (longest - L) * lone;
-    };
-    const int fixed = max(max(until(longest), until(longest * 3 / 4)), max(until(longest / 2), longest * lone));
-    c.dealt = prm.flat > 1 || fixed * kAttnWaves > (int)(2 * c.total) + 2 * kAttnWaves * prm.workers;
+    const bool two_a_unit = prm.D == 64 && prm.plan.nqt == 1;
+    const int lone = two_a_unit ? prm.workers * 7 / 8 : prm.workers;
+    const int total = (int)(2 * c.total), dealt = total + (two_a_unit ? total / 16 : prm.D / 8 * prm.B);
+    c.dealt = prm.flat > 1 || longest * lone * kAttnWaves > dealt;
+    if (c.dealt) return c;
+    auto sum_until = [&](int L) { return (int)__builtin_amdgcn_readlane(wave_incl_scan_u32(min(steps, L)), kWave - 1); };
+    auto until = [&](int L) { return 2 * sum_until(L) * prm.plan.nsplit_priv + (longest - L) * lone; };  // (in half steps of all the head's items)
+    const int sum = sum_until(longest);
+    int fixed = max(max(2 * sum * prm.plan.nsplit_priv, until(longest * 3 / 4)), max(until(longest / 2), until(longest / 4)));
+    if (two_a_unit && 2 * prm.B * prm.plan.nsplit_priv > prm.workers)  // more items than units: some units have two
+        fixed = max(fixed, (int)(1.8f * sum * lone * __builtin_amdgcn_rcpf(prm.B)));
+    c.dealt = fixed * kAttnWaves > dealt;
     return c;
 }
 __device__ __forceinline__ unsigned flat_cut(const AttnParams& prm, const FlatCuts& c, int i) {
