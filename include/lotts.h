@@ -96,7 +96,9 @@ size_t verify_attention_workspace_bytes(const lotts_attn_desc *desc);
  *   O      [B][R][Hq][D] dtype, out
  *   lse    [B][R][Hq] fp32, out, may be NULL: natural-log sum of exp of the scaled scores
  *   workspace: >= verify_attention_workspace_bytes(desc), 16-byte aligned, zero-filled before first use
- *            (see above: arrival cells).  Calls that may overlap in time -- different streams --
+ *            (see above: arrival cells).  Long calls of up to 64 branches ask for more than they cannot do without, to
+ *            share the work out by the branches' lengths; with less, as what a call of more branches asks for, they are served
+ *            without that, down to the partials of equal shares.  Calls that may overlap in time -- different streams --
  *            need workspaces of their own; calls on one stream can share one.
  * bf16 inputs are multiplied on the matrix cores with fp32 accumulation; fp32 inputs are
  * computed in fp32 throughout.

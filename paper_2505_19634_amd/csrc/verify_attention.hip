@@ -136,7 +136,7 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // Launch plan.  Depends on the descriptor only (never on device data), so the workspace query
 // and the launch agree.  The HBM stream runs best with one streaming workgroup per compute
 // unit, so the private caches are cut into just enough key shares to give every CU one item.
-static inline AttnPlans plan_attention(const lotts_attn_desc& d) {
+static inline AttnPlans plan_attention(const lotts_attn_desc& d, bool may_be_flat = true) {
     AttnPlans pl = {};
     const int GR = (d.Hq / d.Hkv) * (d.k + 1);
     pl.nqt = GR > kRowTile ? 2 : 1;
@@ -279,7 +279,7 @@ static inline AttnPlans plan_attention(const lotts_attn_desc& d) {
     const int workers = units / d.Hkv;
     const long long farthest = std::max((d.Lmax + 32LL) * d.kpriv_stride_t, (d.P + 32LL) * d.kpre_stride_t) * 2;  // bytes
     const long long flat_bytes = (long long)d.Hkv * (workers + d.B) * GR * (d.D * 4 + 8) + kMaxCounters * 8 + 512;
-    if (simple && !pl.one && pl.merge != kMergeLaunch && d.B > 1 && d.B <= kWave && workers > 0 && (pl.nsplit_priv == 1 || d.B * pl.nsplit_priv <= workers) &&
+    if (may_be_flat && simple && !pl.one && pl.merge != kMergeLaunch && d.B > 1 && d.B <= kWave && workers > 0 && (pl.nsplit_priv == 1 || d.B * pl.nsplit_priv <= workers) &&
         (long long)d.B * tiles_all >= (long long)LOTTS_FLAT_STEPS * kAttnWaves * workers &&
         (long long)d.B * (tiles_all + kStartTiles) * workers < (1LL << 31) && farthest < (1LL << 31) && flat_bytes <= (16 << 20)) {
         pl.flat = d.D == 64 && pl.nqt == 1 && base * pl.nsplit_priv > kNumCU && base * pl.nsplit_priv * 3 <= 4 * kNumCU ? 2 : 1;
@@ -1774,9 +1774,9 @@ static int fill_desc(const lotts_attn_desc* in, lotts_attn_desc* d) {
 
 // Bytes of workspace for a checked descriptor; 0 when the geometry cannot be served (partials are
 // addressed with 32-bit byte offsets, arrivals per cell are counted in 16 bits).
-static size_t workspace_need(const lotts_attn_desc& d) {
+static size_t workspace_need(const lotts_attn_desc& d, bool may_be_flat = true) {
     if (d.dtype == LOTTS_F32) return 256;  // the fp32 path needs none; keep the pointer non-NULL
-    const AttnPlans pl = plan_attention(d);
+    const AttnPlans pl = plan_attention(d, may_be_flat);
     const long long arrivals = pl.flat ? pl.workers : (long long)pl.n_rg_priv * pl.nsplit_priv + (long long)pl.nsplit_pre * (pl.n_rg_priv + 1);
     if (arrivals >= (1 << kTagShift)) return 0;
     const size_t bytes = workspace_layout(d, pl, nullptr, nullptr);
@@ -1784,10 +1784,10 @@ static size_t workspace_need(const lotts_attn_desc& d) {
 }
 
 // Everything after the argument checks that both entry points share: plan, parameters, launches.
-// `workspace` holds at least workspace_need(d) bytes.
+// `workspace` holds at least workspace_need(d, may_be_flat) bytes.
 static int launch_attention(const lotts_attn_desc& d, const void* Q, const void* Kpre, const void* Vpre,
                             const void* Kpriv, const void* Vpriv, const int32_t* priv_len, void* O, float* lse,
-                            void* workspace, hipStream_t s) {
+                            void* workspace, hipStream_t s, bool may_be_flat) {
     AttnParams prm;
     prm.Q = Q; prm.Kpre = Kpre; prm.Vpre = Vpre; prm.Kpriv = Kpriv; prm.Vpriv = Vpriv;
     prm.priv_len = priv_len;
@@ -1814,7 +1814,7 @@ static int launch_attention(const lotts_attn_desc& d, const void* Q, const void*
         return check_launch();
     }
 
-    const AttnPlans pl = plan_attention(d);
+    const AttnPlans pl = plan_attention(d, may_be_flat);
     prm.plan = pl;
     size_t off_o, off_ml;
     const size_t total = workspace_layout(d, pl, &off_o, &off_ml);
@@ -1919,9 +1919,11 @@ extern "C" int verify_attention(const lotts_attn_desc* desc, const void* Q, cons
     if (!workspace) return LOTTS_ERR_NULL;
     const size_t need = workspace_need(d);
     if (need == 0) return LOTTS_ERR_SHAPE;  // a geometry whose partials the 32-bit offsets cannot address
-    if (workspace_bytes < need) return LOTTS_ERR_WORKSPACE;
+    // Fixed shares have fewer partials than dealt tiles: a buffer sized for more branches, whose plan may not be flat, holds those of fewer.
+    const bool may_be_flat = workspace_bytes >= need;
+    if (!may_be_flat && workspace_bytes < workspace_need(d, false)) return LOTTS_ERR_WORKSPACE;
     if (((uintptr_t)workspace & (d.dtype == LOTTS_BF16 ? 15 : 3)) != 0) return LOTTS_ERR_SHAPE;
-    return launch_attention(d, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, O, lse, workspace, (hipStream_t)stream);
+    return launch_attention(d, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, O, lse, workspace, (hipStream_t)stream, may_be_flat);
 }
 
 extern "C" int verify_attention_noalloc(const lotts_attn_desc* desc, const void* Q, const void* Kpre, const void* Vpre,
@@ -1939,5 +1941,5 @@ extern "C" int verify_attention_noalloc(const lotts_attn_desc* desc, const void*
     void* ptr = nullptr;
     rc = scratch_of_current_device(&ptr);
     if (rc != LOTTS_OK) return rc;
-    return launch_attention(d, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, O, lse, ptr, (hipStream_t)stream);
+    return launch_attention(d, Q, Kpre, Vpre, Kpriv, Vpriv, priv_len, O, lse, ptr, (hipStream_t)stream, true);
 }

@@ -45,7 +45,8 @@ int main() {
             d.dtype = LOTTS_BF16;
             if (scanf("%d %d %d %d %d %d %d", &d.B, &d.k, &d.Hq, &d.Hkv, &d.D, &d.P, &d.Lmax) != 7) return 1;
             const lotts::AttnPlans p = lotts::plan_attention(d);
-            printf("flat %d workers %d merge %d nqt %d fold %d\n", p.flat, p.workers, p.flat ? p.flat_merge : p.merge, p.nqt, p.fold);
+            printf("flat %d workers %d merge %d nqt %d fold %d bytes %zu least %zu\n", p.flat, p.workers, p.flat ? p.flat_merge : p.merge, p.nqt, p.fold,
+                   lotts::workspace_layout(d, p, nullptr, nullptr), lotts::workspace_layout(d, lotts::plan_attention(d, false), nullptr, nullptr));
         } else {
             return 1;
         }

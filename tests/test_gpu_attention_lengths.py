@@ -188,6 +188,28 @@ def test_nearly_equal_lengths_are_not_dealt(flat, cfg, shortest, dealt):
     assert torch.allclose(got[1], want[1], rtol=0, atol=1e-4)
 
 
+def test_a_workspace_for_more_branches_serves_fewer():
+    """128 branches ask for fewer bytes than 64, whose tiles are dealt by their lengths; the 64 then take fixed shares."""
+    import ctypes
+    import paper_2505_19634_amd as lotts
+    cfg = BF.with_(B=64, Hq=16, Hkv=2, k=3, P=70, L=4608)
+    d = long_inputs(cfg)
+    want, lse = (t.clone() for t in lotts.verify_attention(*(d[n] for n in NAMES), return_lse=True))
+    desc = lotts.make_attn_desc(d["Q"], d["Kpre"], d["Kpriv"], want)
+    need = lambda: lotts.load().verify_attention_workspace_bytes(ctypes.byref(desc))
+    most = need()
+    desc.B = 128
+    fewer = need()
+    assert 0 < fewer < most
+    guard = torch.zeros(most, dtype=torch.uint8, device=DEV)
+    guard[fewer:] = 7
+    for _ in range(2):
+        O, got = lotts.verify_attention(*(d[n] for n in NAMES), return_lse=True, workspace=guard[:fewer])
+        torch.cuda.synchronize()
+        assert torch.allclose(got, lse, rtol=0, atol=1e-4) and ((O - want).float().norm() / want.float().norm()).item() <= 8e-3
+        assert bool((guard[fewer:] == 7).all())
+
+
 @pytest.mark.parametrize("cfg", LONG, ids=["groups", "last_arriver"])
 def test_long_calls(cfg):
     """The library itself, against plain fp32 attention of some branches."""

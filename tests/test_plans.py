@@ -68,3 +68,17 @@ def test_lengths_lists_reach_the_flat_plan():
     # one branch more than a wavefront has lanes, rows of several row groups, a prefix in items of its own: not these
     other = [LONG[0].with_(B=65), LONG[0].with_(k=70), LONG[0].with_(P=LONG[0].L)]
     assert not any(p["flat"] for p in ask([line(c) for c in other]))
+
+
+def test_a_buffer_for_more_branches_holds_fewer():
+    """Where dealt tiles have more partials than the fixed shares of more branches, the fixed shares of the fewer fit: 64 branches of two KV heads
+    ask for 4.9 MB, 128 for 3.3."""
+    from synth_inputs import CONFIGS
+    cfg = CONFIGS["C3"].with_(Hq=16, Hkv=2, k=2, P=1003, L=7168)
+    few, many = ask([attention(cfg.with_(B=B)).replace("attention", "lengths") for B in (64, 128)])
+    assert few["flat"] == 1 and not many["flat"]
+    assert few["least"] <= many["bytes"] == many["least"] < few["bytes"]
+    sizes = [cfg.with_(B=B, Hq=Hq, Hkv=Hkv, D=D, k=k, P=P, L=L) for B in (2, 7, 20, 40, 63) for Hq, Hkv, D in ((16, 2, 128), (40, 8, 128), (16, 16, 64))
+             for k in (0, 3, 8) for P in (0, 500) for L in (2000, 16000)]
+    plans = ask([attention(c).replace("attention", "lengths") for c in sizes])
+    assert all(p["least"] <= p["bytes"] for p in plans) and sum(p["flat"] > 0 for p in plans) > 50
