@@ -71,7 +71,8 @@ constexpr int kMaxCounters = 16384;  // 64-bit cells at the start of the workspa
 // out, Q and a first tile come in: about two tiles of each wavefront; 6 is level, without any 44 x 2 heads x 1310 .. 5243 tokens
 // took 2 % more).
 constexpr int kStartTiles = 8;
-// Flat plan: from this many tiles of each wavefront on (a build of the tests sets 0).
+// Flat plan: from this many tiles of each wavefront on.  (A build of the tests sets 0, and deals whatever lengths differ: calls as short as
+// theirs would not gain by it.)
 #ifndef LOTTS_FLAT_STEPS
 #define LOTTS_FLAT_STEPS 18
 #endif
@@ -92,7 +93,7 @@ struct AttnPlan {
     int runs;           // runs of key tiles of an item
 };
 struct AttnPlans : AttnPlan {
-    int flat;     // 0: shares of fixed number; 1: the items deal the tiles by the branches' lengths where those differ; 2: always
+    int flat;     // 0: shares of fixed number; 1: the items deal the tiles by the branches' lengths where that gains; 2: always; 3: where lengths differ
     int workers;  // flat: items per KV head
     int flat_merge;  // who merges where the tiles are dealt by the lengths: kMergeLast or kMergeGroups
 };
@@ -282,7 +283,7 @@ static inline AttnPlans plan_attention(const lotts_attn_desc& d, bool may_be_fla
     if (may_be_flat && simple && !pl.one && pl.merge != kMergeLaunch && d.B > 1 && d.B <= kWave && workers > 0 && (pl.nsplit_priv == 1 || d.B * pl.nsplit_priv <= workers) &&
         (long long)d.B * tiles_all >= (long long)LOTTS_FLAT_STEPS * kAttnWaves * workers &&
         (long long)d.B * (tiles_all + kStartTiles) * workers < (1LL << 31) && farthest < (1LL << 31) && flat_bytes <= (16 << 20)) {
-        pl.flat = d.D == 64 && pl.nqt == 1 && base * pl.nsplit_priv > kNumCU && base * pl.nsplit_priv * 3 <= 4 * kNumCU ? 2 : 1;
+        pl.flat = d.D == 64 && pl.nqt == 1 && base * pl.nsplit_priv > kNumCU && base * pl.nsplit_priv * 3 <= 4 * kNumCU ? 2 : LOTTS_FLAT_STEPS > 0 ? 1 : 3;
         pl.workers = workers;
         // Where an item has whole branches of its own, the last arriver merges the few that are cut; where branches have several items each,
         // merge workgroups (44 x 2 x 1310 .. 5243 40.7 -> 35.0 us, with the last arriver 38.7) unless a branch's partials are few bytes: D = 64,
@@ -403,7 +404,7 @@ __device__ __forceinline__ FlatCuts flat_cuts(const AttnParams& prm, int fold_ti
     FlatCuts c = {};
     L = L < prm.R ? prm.R : (L > prm.Lmax ? prm.Lmax : L);
     c.len = L;
-    if (prm.flat == 1 && __ballot(L != __builtin_amdgcn_readfirstlane(L)) == 0) return c;  // all alike: fixed shares
+    if (prm.flat != 2 && __ballot(L != __builtin_amdgcn_readfirstlane(L)) == 0) return c;  // all alike: fixed shares
     const int tiles = fold_tiles + (L - 1) / kTile + 1;
     c.end = wave_incl_scan_u32(lane < prm.B ? kStartTiles + tiles : 0);
     c.total = __builtin_amdgcn_readlane(c.end, kWave - 1);

@@ -1,6 +1,6 @@
 """verify_attention where the items deal a KV head's tiles by the branches' lengths, on the device.  A build of the library that does so for
-calls of any length (liblotts_flat.so) runs small geometries against the CPU oracle; which plans they reach is checked on the host
-(test_plans.py)."""
+calls of any length, wherever lengths differ (liblotts_flat.so), runs small geometries against the CPU oracle; which plans they reach is
+checked on the host (test_plans.py).  Long calls run in the library itself, which deals where that gains."""
 import os
 
 import numpy as np
@@ -31,7 +31,10 @@ CASES = [
 # those where equal lengths are not dealt; the last ones have two shares, which the later of two items merges
 SHARED = [c for i, c in enumerate(CASES) if i not in (5, 13)] + [BF.with_(B=14, Hq=32, Hkv=8, k=1, D=64, P=0, L=900),
                                                                  BF.with_(B=12, Hq=32, Hkv=8, k=5, P=30, L=900)]
-LONG = [BF.with_(B=64, Hq=2, Hkv=2, k=1, P=70, L=4608), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2300)]
+# merge workgroups and the last arriver, one row tile and two; lengths uneven enough to be dealt
+LONG = [BF.with_(B=64, Hq=16, Hkv=2, k=3, P=70, L=4608), BF.with_(B=40, Hq=16, Hkv=2, k=4, P=0, L=7400),
+        BF.with_(B=64, Hq=2, Hkv=2, k=1, P=70, L=4608), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2300)]
+LONG_IDS = ["groups", "groups_two_row_tiles", "last_arriver", "last_arriver_two_row_tiles"]
 
 
 def lengths(cfg, pattern):
@@ -42,14 +45,16 @@ def lengths(cfg, pattern):
         return np.linspace(lo, cfg.L, B).astype(np.int32)
     if pattern == "shuffled":
         return np.random.default_rng(B).permutation(np.linspace(lo, cfg.L, B)).astype(np.int32)
-    out = np.full(B, lo, np.int32)  # all but one hold the new tokens only
-    out[{"first": 0, "last": B - 1, "one": B // 2}[pattern]] = cfg.L
-    return out if pattern != "none" else np.full(B, lo, np.int32)
+    if pattern == "uneven":
+        return np.random.default_rng(B).permutation(lo + (cfg.L - lo) * np.linspace(0, 1, B) ** 3).astype(np.int32)
+    out = np.full(B, lo, np.int32)  # all but one hold the new tokens only, or all but one token more
+    out[{"first": 0, "last": B - 1, "one": B // 2, "none": B // 3}[pattern]] = cfg.L if pattern != "none" else lo + 1
+    return out
 
 
-@pytest.fixture(scope="module")
+@pytest.fixture
 def flat():
-    """The package on top of that build, with workspaces of its own, for the tests of this file."""
+    """The package on top of that build, with workspaces of its own, for one test: the others are about the library itself."""
     import paper_2505_19634_amd as m
     from paper_2505_19634_amd import binding
     usual, workspaces = m.load(), binding._workspaces
@@ -79,7 +84,7 @@ def without_dealing(m, d):
 
 
 @pytest.mark.parametrize("cfg", CASES, ids=lambda c: "B%d_k%d_Hq%d_Hkv%d_D%d_P%d_L%d" % (c.B, c.k, c.Hq, c.Hkv, c.D, c.P, c.L))
-@pytest.mark.parametrize("pattern", ["equal", "ragged", "shuffled", "first", "last", "one"])
+@pytest.mark.parametrize("pattern", ["equal", "ragged", "shuffled", "first", "last", "one", "none"])
 def test_lengths(flat, oracle, cfg, pattern):
     run_attention(flat, oracle, cfg, priv_len=lengths(cfg, pattern))
 
@@ -163,6 +168,14 @@ def test_calls_side_by_side(flat):
         assert all(torch.equal(o, w) for o, w in zip(round_, want))
 
 
+@pytest.fixture
+def itself():
+    """The package on top of the library itself, whatever other fixtures are alive."""
+    import paper_2505_19634_amd as m
+    assert os.path.basename(m.load()._name) == "liblotts.so"
+    return m
+
+
 def long_inputs(cfg):
     g = torch.Generator(device=DEV)
     g.manual_seed(cfg.B)
@@ -170,33 +183,42 @@ def long_inputs(cfg):
     d = {"Q": t(cfg.B, cfg.k + 1, cfg.Hq, cfg.D), "Kpriv": t(cfg.B, cfg.Hkv, cfg.L, cfg.D), "Vpriv": t(cfg.B, cfg.Hkv, cfg.L, cfg.D)}
     for n in ("Kpre", "Vpre"):
         d[n] = t(cfg.Hkv, cfg.P, cfg.D) if cfg.P else None
-    d["priv_len"] = torch.from_numpy(lengths(cfg, "shuffled")).to(DEV)
+    d["priv_len"] = torch.from_numpy(lengths(cfg, "uneven")).to(DEV)
     return d
 
 
-@pytest.mark.parametrize("cfg", [BF.with_(B=14, Hq=32, Hkv=8, k=1, D=64, P=0, L=4000), BF.with_(B=7, Hq=16, Hkv=16, k=7, D=64, P=0, L=5000)],
+def fixed_shares(m, d):
+    """(O, lse) of a call whose workspace holds the partials of fixed shares and not those of dealt tiles."""
+    import ctypes
+    O, lse = torch.empty_like(d["Q"]), torch.empty(d["Q"].shape[:3], dtype=torch.float32, device=DEV)
+    lib, desc = m.load(), m.make_attn_desc(d["Q"], d["Kpre"], d["Kpriv"], O)
+    ws = torch.zeros(lib.verify_attention_workspace_bytes(ctypes.byref(desc)) - 256, dtype=torch.uint8, device=DEV)
+    m.verify_attention(*(d[n] for n in NAMES), out=O, lse=lse, workspace=ws)
+    torch.cuda.synchronize()
+    return O, lse
+
+
+@pytest.mark.parametrize("cfg", [BF.with_(B=14, Hq=32, Hkv=8, k=1, D=64, P=0, L=12491), BF.with_(B=7, Hq=16, Hkv=16, k=7, D=64, P=0, L=15408)],
                          ids=["14x8", "7x16"])
-@pytest.mark.parametrize("shortest,dealt", [(7 / 8, False), (1 / 2, True), (1 / 16, True)])
-def test_nearly_equal_lengths_are_not_dealt(flat, cfg, shortest, dealt):
+@pytest.mark.parametrize("shortest,dealt", [(1, False), (7 / 8, False), (1 / 2, True), (1 / 16, True)])
+def test_nearly_equal_lengths_are_not_dealt(itself, cfg, shortest, dealt):
     """Two shares a branch and most of the units with one item fill the memory already: 14 x 8 heads x 12491 tokens down to 10930 51.5 us in fixed
     shares, dealt 54.5.  What was dealt shows in the low bits."""
     d = long_inputs(cfg)
     d["priv_len"] = torch.from_numpy(np.linspace(cfg.L * shortest, cfg.L, cfg.B).astype(np.int32)).to(DEV)
-    got = [t.clone() for t in flat.verify_attention(*(d[n] for n in NAMES), return_lse=True)]
-    want = without_dealing(flat, d)
+    got = [t.clone() for t in itself.verify_attention(*(d[n] for n in NAMES), return_lse=True)]
+    want = fixed_shares(itself, d)
     assert all(torch.equal(g, w) for g, w in zip(got, want)) != dealt
     assert torch.allclose(got[1], want[1], rtol=0, atol=1e-4)
 
 
-def test_a_workspace_for_more_branches_serves_fewer():
+def test_a_workspace_for_more_branches_serves_fewer(itself):
     """128 branches ask for fewer bytes than 64, whose tiles are dealt by their lengths; the 64 then take fixed shares."""
     import ctypes
-    import paper_2505_19634_amd as lotts
-    cfg = BF.with_(B=64, Hq=16, Hkv=2, k=3, P=70, L=4608)
-    d = long_inputs(cfg)
-    want, lse = (t.clone() for t in lotts.verify_attention(*(d[n] for n in NAMES), return_lse=True))
-    desc = lotts.make_attn_desc(d["Q"], d["Kpre"], d["Kpriv"], want)
-    need = lambda: lotts.load().verify_attention_workspace_bytes(ctypes.byref(desc))
+    d = long_inputs(LONG[0])
+    want, lse = (t.clone() for t in itself.verify_attention(*(d[n] for n in NAMES), return_lse=True))
+    desc = itself.make_attn_desc(d["Q"], d["Kpre"], d["Kpriv"], want)
+    need = lambda: itself.load().verify_attention_workspace_bytes(ctypes.byref(desc))
     most = need()
     desc.B = 128
     fewer = need()
@@ -204,18 +226,18 @@ def test_a_workspace_for_more_branches_serves_fewer():
     guard = torch.zeros(most, dtype=torch.uint8, device=DEV)
     guard[fewer:] = 7
     for _ in range(2):
-        O, got = lotts.verify_attention(*(d[n] for n in NAMES), return_lse=True, workspace=guard[:fewer])
+        O, got = itself.verify_attention(*(d[n] for n in NAMES), return_lse=True, workspace=guard[:fewer])
         torch.cuda.synchronize()
         assert torch.allclose(got, lse, rtol=0, atol=1e-4) and ((O - want).float().norm() / want.float().norm()).item() <= 8e-3
         assert bool((guard[fewer:] == 7).all())
 
 
-@pytest.mark.parametrize("cfg", LONG, ids=["groups", "last_arriver"])
-def test_long_calls(cfg):
-    """The library itself, against plain fp32 attention of some branches."""
-    import paper_2505_19634_amd as lotts
+@pytest.mark.parametrize("cfg", LONG, ids=LONG_IDS)
+def test_long_calls(itself, cfg):
+    """The library itself, against plain fp32 attention of some branches; the lengths are dealt."""
     d = long_inputs(cfg)
-    O = lotts.verify_attention(*(d[n] for n in NAMES))
+    O, lse = (t.clone() for t in itself.verify_attention(*(d[n] for n in NAMES), return_lse=True))
+    assert not torch.equal(lse, fixed_shares(itself, d)[1])
     G = cfg.Hq // cfg.Hkv
     for b in range(0, cfg.B, 7):
         L = int(d["priv_len"][b])
@@ -229,7 +251,7 @@ def test_long_calls(cfg):
             assert err <= 8e-3, (b, r, err)  # one row of few: twice the band of whole outputs (4e-3)
 
 
-@pytest.mark.parametrize("cfg", LONG, ids=["groups", "last_arriver"])
+@pytest.mark.parametrize("cfg", LONG, ids=LONG_IDS)
 def test_long_calls_without_patience(no_polls, cfg):  # noqa: F811
     """Merge workgroups that leave at once: the items merge in their place, in the same order."""
     from paper_2505_19634_amd import binding

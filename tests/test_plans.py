@@ -61,12 +61,13 @@ def test_lengths_lists_reach_the_flat_plan():
     assert all(p["flat"] for p in plans), list(zip(CASES, plans))
     assert {(c.D, p["nqt"], p["merge"]) for c, p in zip(CASES, plans)} == {(D, nqt, m) for D in (64, 128) for nqt in (1, 2) for m in (0, 1)}
     assert {p["fold"] for p in plans} == {0, 1} and 2 in {p["flat"] for p in plans}
-    assert all(p["flat"] == 1 for p in ask([line(c) for c in SHARED], ("-DLOTTS_FLAT_STEPS=0",)))
+    assert all(p["flat"] == 3 for p in ask([line(c) for c in SHARED], ("-DLOTTS_FLAT_STEPS=0",)))
     assert {p["merge"] for p in ask([attention(c) for c in SHARED])} == {0, 1, 3, 4}  # all that fixed shares of long calls have
     assert not any(p["flat"] for p in ask([line(c) for c in CASES]))
-    assert all(p["flat"] == 1 for p in ask([line(c) for c in LONG]))
+    long = ask([line(c) for c in LONG])
+    assert all(p["flat"] == 1 for p in long) and {(p["nqt"], p["merge"]) for p in long} == {(1, 0), (1, 1), (2, 0), (2, 1)}
     # one branch more than a wavefront has lanes, rows of several row groups, a prefix in items of its own: not these
-    other = [LONG[0].with_(B=65), LONG[0].with_(k=70), LONG[0].with_(P=LONG[0].L)]
+    other = [LONG[0].with_(B=65), LONG[0].with_(k=8), LONG[0].with_(P=LONG[0].L)]
     assert not any(p["flat"] for p in ask([line(c) for c in other]))
 
 
