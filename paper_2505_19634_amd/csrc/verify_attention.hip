@@ -27,8 +27,8 @@
 //       over all of them.  The 4 states
 //       are combined through LDS after one barrier and the item's un-normalised partial goes to
 //       the workspace -- or, if the item holds whole rows (no key shares, no prefix items), straight to O.
-//       Who merges the partials of a row depends on how many there are: of two, or of up to eight with few bytes, the item
-//       that finishes last (arrivals are counted per (KV head, branch) in a cell that carries the call's tag: what an earlier
+//       Who merges the partials of a row depends on how many there are (of dealt tiles, below: on how many there may be): of two, or of
+//       up to eight with few bytes, the item that finishes last (arrivals are counted per (KV head, branch) in a cell that carries the call's tag: what an earlier
 //       call left there, complete or not, counts as zero arrivals); of more, merge workgroups at the end of the grid, which wait for a flag of
 //       every partial they read and share the rows among them; one whose flags stay out for long leaves, and the item that
 //       delivers the last partial merges in its place.  Partials cross workgroups -- and XCDs,
@@ -286,10 +286,12 @@ static inline AttnPlans plan_attention(const lotts_attn_desc& d, bool may_be_fla
         pl.flat = d.D == 64 && pl.nqt == 1 && base * pl.nsplit_priv > kNumCU && base * pl.nsplit_priv * 3 <= 4 * kNumCU ? 2 : LOTTS_FLAT_STEPS > 0 ? 1 : 3;
         pl.workers = workers;
         // Where an item has whole branches of its own, the last arriver merges the few that are cut; where branches have several items each,
-        // merge workgroups (44 x 2 x 1310 .. 5243 40.7 -> 35.0 us, with the last arriver 38.7) unless a branch's partials are few bytes: D = 64,
-        // 13 x 16 x 6686 with one row a head 58.8 us with merge workgroups, 57.0 with the last arriver, 12 x 16 x 122 + 6156 with three 52.1 and 50.7.
+        // merge workgroups, however few bytes their partials would be in fixed shares: a branch that is longer than the others has up to
+        // all items' partials, which one arriver adds up in a chain.  44 sizes with up to 8 KB, one branch longer than the others 30 x 2
+        // heads, 10030 tokens 25.0 -> 12.1 us, on average 19 % (D = 64) and 37 %, a quarter of them longer 4 and 9 %, lengths between
+        // a quarter and all 0.2 and 2 %; the workgroups that are left over cost calls in fixed shares 0.1 %.
         pl.flat_merge = kMergeLast;
-        if (workers > d.B && part_bytes > 8 * 1024) {
+        if (workers > d.B) {
             if (pl.merge != kMergeGroups) rows_per_merger(kAttnThreads * pl.nqt);  // (fixed shares have the same ones)
             if ((long long)d.Hkv * (workers + 2 * d.B) * pl.mpp <= kMaxCounters) pl.flat_merge = kMergeGroups;
         }

@@ -21,7 +21,7 @@ CASES = [
     BF.with_(B=9, Hq=16, Hkv=2, k=1, D=64, P=100, L=900),
     BF.with_(B=2, Hq=2, Hkv=1, k=1, D=64, P=0, L=9000),     # up to 512 items for two branches: partials beyond a wavefront's lanes
     BF.with_(B=33, Hq=9, Hkv=3, k=2, D=64, P=0, L=700),     # heads that do not divide the units
-    # several items each, few bytes of partials (the last arriver): one share a branch, and more
+    # several items each, few bytes of partials in fixed shares: one share a branch, and more
     BF.with_(B=20, Hq=32, Hkv=8, k=3, P=30, L=400), BF.with_(B=12, Hq=16, Hkv=16, k=2, D=64, P=22, L=700), BF.with_(B=10, Hq=32, Hkv=8, k=0, P=11, L=900),
     # items with several branches each (the last arriver)
     BF.with_(B=40, Hq=8, Hkv=8, k=0, P=0, L=300), BF.with_(B=64, Hq=40, Hkv=8, k=7, P=33, L=260),
@@ -33,8 +33,9 @@ SHARED = [c for i, c in enumerate(CASES) if i not in (5, 13)] + [BF.with_(B=14, 
                                                                  BF.with_(B=12, Hq=32, Hkv=8, k=5, P=30, L=900)]
 # merge workgroups and the last arriver, one row tile and two; lengths uneven enough to be dealt
 LONG = [BF.with_(B=64, Hq=16, Hkv=2, k=3, P=70, L=4608), BF.with_(B=40, Hq=16, Hkv=2, k=4, P=0, L=7400),
-        BF.with_(B=64, Hq=2, Hkv=2, k=1, P=70, L=4608), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2300)]
-LONG_IDS = ["groups", "groups_two_row_tiles", "last_arriver", "last_arriver_two_row_tiles"]
+        BF.with_(B=40, Hq=32, Hkv=8, k=3, P=0, L=2000), BF.with_(B=33, Hq=72, Hkv=8, k=3, P=0, L=2300),
+        BF.with_(B=30, Hq=2, Hkv=2, k=1, P=58, L=10030)]
+LONG_IDS = ["groups", "groups_two_row_tiles", "last_arriver", "last_arriver_two_row_tiles", "groups_few_bytes"]
 
 
 def lengths(cfg, pattern):
@@ -46,7 +47,7 @@ def lengths(cfg, pattern):
     if pattern == "shuffled":
         return np.random.default_rng(B).permutation(np.linspace(lo, cfg.L, B)).astype(np.int32)
     if pattern == "uneven":
-        return np.random.default_rng(B).permutation(lo + (cfg.L - lo) * np.linspace(0, 1, B) ** 3).astype(np.int32)
+        return np.random.default_rng(B).permutation(lo + (cfg.L - lo) * np.linspace(0, 1, B) ** 6).astype(np.int32)
     out = np.full(B, lo, np.int32)  # all but one hold the new tokens only, or all but one token more
     out[{"first": 0, "last": B - 1, "one": B // 2, "none": B // 3}[pattern]] = cfg.L if pattern != "none" else lo + 1
     return out
