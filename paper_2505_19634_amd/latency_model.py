@@ -148,8 +148,7 @@ class FullModel:
         z = lambda *sh: torch.zeros(sh, dtype=torch.bfloat16, device=self.dev)
         self.h = bf(M, s.hidden)
         self.qkv, self.attn, self.o, self.gu = z(M, qkv_n), z(B, R, s.Hq, s.D), z(M, s.hidden), z(M, 2 * s.mlp)
-        heads = self.qkv.view(B, R, s.Hq + 2 * s.Hkv, s.D)
-        self.q_view, self.k_view, self.v_view = heads[:, :, :s.Hq], heads[:, :, s.Hq:s.Hq + s.Hkv], heads[:, :, s.Hq + s.Hkv:]
+        self.q_view = self.qkv.view(B, R, s.Hq + 2 * s.Hkv, s.D)[:, :, :s.Hq]
         self.zt = z(B, R, s.V)
         self.zd = bf(B, gamma, s.V) if gamma else None
         self.draft = torch.zeros((B, gamma), dtype=torch.int32, device=self.dev) if gamma else None
