@@ -100,6 +100,9 @@ size_t verify_attention_workspace_bytes(const lotts_attn_desc *desc);
  *            share the work out by the branches' lengths; with less, as what a call of more branches asks for, they are served
  *            without that, down to the partials of equal shares.  Calls that may overlap in time -- different streams --
  *            need workspaces of their own; calls on one stream can share one.
+ * The same descriptor, data, lengths and workspace size give the same bits, whatever runs beside the call.  How the keys of a branch are
+ * cut into partial sums follows from the descriptor, but in long bf16 calls, where the lengths differ, from the lengths of ALL branches: the low
+ * bits of a branch's O and lse may then change when another branch's length changes (or the workspace is smaller than asked for).
  * bf16 inputs are multiplied on the matrix cores with fp32 accumulation; fp32 inputs are
  * computed in fp32 throughout.
  */
@@ -110,7 +113,7 @@ int verify_attention(const lotts_attn_desc *desc, const void *Q, const void *Kpr
 /*
  * verify_attention_noalloc -- verify_attention for callers that cannot allocate device memory or
  * hand over a workspace: code that runs under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc.  Same operation, same kernels, same results bit for bit; the arrival
+ * that forbid hipMalloc.  Same operation, same kernels, same results bit for bit (as with a workspace of the size asked for); the arrival
  * cells and partials live in a 16 MiB scratch array built into the library (static device
  * memory: each GPU the library runs on holds its copy until the process ends) instead of a
  * caller's workspace.  The call allocates and frees nothing and calls no allocating routine.
@@ -269,6 +272,8 @@ int skinny_gemm(int32_t M, int32_t N, int32_t K, const void *X, int64_t ldx, con
  * skinny_gemm_append -- the QKV projection of the B * (k + 1) new tokens with the append of its K and V columns: skinny_gemm into Y
  * and kv_append of Y's last 2 * Hkv * D columns (the K heads, then the V heads) to the tails of the private caches, in
  * skinny_gemm's launches.  Y and the caches get the bits that the two calls give them.
+ * For decoders that put K and V into the cache as the projection leaves them: what works on K in between (a rotary embedding, a norm of the
+ * heads) comes in front of kv_append, in a launch of its own.
  *   X [B * (k + 1)][K], W [N][K], Y [B * (k + 1)][N]: as for skinny_gemm, row b * (k + 1) + r = new token r of branch b;
  *       B * (k + 1) <= 256, 2 * Hkv * D <= N, D a multiple of 8, ldy a multiple of 8, Y 16-byte aligned
  *   Kpriv, Vpriv, their strides, Lmax, priv_len: as for kv_append (bf16); the caches overlap no other operand
