@@ -552,7 +552,8 @@ __global__ __launch_bounds__(256) void skinny_gemm_reduce_kernel(const P p) {
     __shared__ __attribute__((aligned(16))) unsigned char tr[32 * kGemmOutRow];
     const int tiles = p.rt * p.tt;
     const int j = blockIdx.x % tiles, wb = blockIdx.x / tiles;
-    const int wr = wb % p.roww, blocks = wb / p.roww, part = blocks / p.nblocks, block = blocks - part * p.nblocks;
+    const int wr = wb % p.roww, blocks = wb / p.roww;
+    const int part = blocks >= p.nblocks, block = part ? blocks - p.nblocks : blocks;  // (two parts at most; a run-time division is 0.05 .. 0.1 us)
     const int M = p.parts > 1 ? p.tokens : p.M, m0 = part ? p.M - p.tokens : 0;
     const int grp = p.rt == 1 ? wr : wr >> 1, th = p.rt == 1 ? 0 : wr & 1;
     const int m_base = (th * p.tt + j % p.tt) * 32;
