@@ -163,7 +163,7 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl, double* fill
 //   Direct, up to K = 4096 and 8192 rows: 3.4 us + 0.022 us per KB of a workgroup's W and X (whole batches of loads) + 0.14 us per
 //     MB of W, against 7 us + 0.125 us per MB of W + 7e-6 us per token and (N + K) of the split stream forms; both fitted to 1188
 //     sizes (1536 .. 14336 rows, K 512 .. 4096, 1 .. 192 tokens) with tiles full of tokens, where the choice costs 0.4 % over the better
-//     form: 2560 x 2048 at 1 / 40 / 192 tokens 5.1 / 7.6 / 13.4 us against 7.9 / 9.2 / 15.0; 4736 x 1280 at 24 tokens 12.4 against 9.7; 6144
+//     form: 2560 x 2048 at 1 / 40 tokens 5.1 / 7.6 us against 7.9 / 9.2; 4736 x 1280 at 24 tokens 12.4 against 9.7; 6144
 //     x 4096 at 2 tokens 17.7 against 13.2.  Even shares are fewer KB, but not all of what is counted less is time saved: where only they
 //     put the direct form ahead, 0.034 us per KB + 0.15 us per MB of W have to stay below 6.7 us (6.3 with 64 weight rows to a
 //     workgroup) + 10e-6 us per token and (N + K), fitted to 492 such sizes: always direct is 5.3 % over the better form there (3968 x
@@ -176,7 +176,7 @@ static inline double plan_direct(int M, int N, int K, GemmPlan* pl, double* fill
 //     tokens 92 us, 128-row form 104.
 //   Two token parts, N <= 4608 and more than 128 tokens: blocks of 128 rows x half of the tokens instead of 64 x all, as many K splits.
 //     A unit takes in W and X at some 50 KB/us together, and 128 + M / 2 rows are fewer than 64 + M; the parts of a block lie on one
-//     XCD, side by side, and W comes from HBM once.  2048 x 11008 at 144 / 192 / 256 tokens 22.2 / 23.7 / 27.4 -> 21.1 / 23.0 / 25.1 us; 4608 x
+//     XCD, side by side, and W comes from HBM once.  2048 x 11008 at 144 / 192 / 256 tokens 22.8 / 24.0 / 27.4 -> 21.5 / 22.7 / 24.8 us; 4608 x
 //     4480 22.4 / 25.6 / 28.6 -> 20.7 / 22.2 / 24.8; 50 sizes of K > 4096 17 % faster.  With a K beyond 12288 and up to 160 tokens level or
 //     slower (3584 x 18944 at 144 tokens 46.7 -> 48.0), with up to 128 tokens too (3264 x 14336 at 123 31.5 -> 36.7).  The same for more rows, 256 x
 //     half of the tokens without a split, loses (22016 x 2048 at 160 / 192 tokens 27.5 / 29.6 -> 29.9 / 30.6).  Beside it the direct form stays
