@@ -43,13 +43,17 @@ def _whole(t):
     return t._base if t._base is not None else t
 
 
-@pytest.mark.parametrize("B,k,Hq,Hkv,D,K", [
+SIZES = [
     (1, 0, 1, 1, 8, 128), (1, 0, 16, 2, 128, 2048), (5, 2, 3, 2, 24, 1024), (8, 4, 16, 2, 128, 2048), (16, 3, 32, 8, 128, 4096),
     (3, 8, 28, 4, 128, 3584), (13, 2, 0, 4, 64, 640), (64, 3, 16, 16, 64, 1024), (1, 255, 16, 2, 128, 2048), (27, 7, 32, 8, 64, 1152),
     (4, 4, 40, 8, 128, 5120), (16, 3, 40, 8, 128, 5120), (32, 5, 33, 3, 72, 4480), (7, 0, 8, 1, 8, 8320), (85, 2, 64, 8, 128, 8192),
     (43, 2, 20, 4, 128, 8192), (51, 4, 12, 2, 64, 12288),   # K split and the tokens in two parts
     (5, 0, 2299, 3, 8, 256), (32, 7, 2555, 3, 8, 128),   # W streamed with K unsplit
-])
+    (40, 3, 12, 2, 128, 2048), (21, 2, 24, 4, 128, 2048), (47, 3, 8, 2, 128, 1536), (21, 2, 4, 2, 128, 4096),   # direct tiles with several workgroups over the tokens
+]
+
+
+@pytest.mark.parametrize("B,k,Hq,Hkv,D,K", SIZES)
 def test_append_in_the_projection(lotts, B, k, Hq, Hkv, D, K):
     print("projection with append", B, k, Hq, Hkv, D, K, flush=True)
     Lmax = k + 40

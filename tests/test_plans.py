@@ -21,6 +21,14 @@ def test_gemm_forms_beside_two_token_parts():
     assert [p["form"] == "direct" for p in plans] == [False] * len(streamed) + [True] * len(direct), plans
 
 
+def test_append_list_reaches_every_form():
+    """Every tile of the direct form, K split in blocks of 64 and 128 rows, two token parts, and a product that streams W unsplit."""
+    from test_gpu_gemm_append import SIZES
+    plans = ask(["gemm %d %d %d" % (B * (k + 1), (Hq + 2 * Hkv) * D, K) for B, k, Hq, Hkv, D, K in SIZES])
+    assert {(p["rn"], p["tt"]) for p in plans if p["form"] == "direct"} == {(1, 1), (1, 2), (2, 1), (2, 2), (2, 3), (4, 2), (4, 3)}
+    assert {(p["form"], p["ksplit"] > 1) for p in plans if p["form"] != "direct"} == {("stream64", True), ("stream128", True), ("stream128", False)}
+
+
 def test_short_sub_chunks_of_the_acceptance():
     from test_gpu_accept_parts import SHORT
     for (groups, parts, B, V), plan in zip(SHORT, ask(["accept %d %d" % c[2:] for c in SHORT])):
